@@ -16,6 +16,7 @@
 #include "ntt_v2.h"
 #include "ks_fused.h"
 #include "ntt_wg.h"
+#include "ks_wg.h"
 #include "encode_device.h"
 #include "mac_mfma.h"
 
@@ -100,9 +101,11 @@ LimbMap table_map(const int *index, int n_limbs, size_t src_stride, size_t dst_s
 
 // transform `items` groups of map.per_item limbs; forward: coefficient -> evaluation
 // passes: 3 = whole transform, 1 = strided (column) pass only, 2 = contiguous (row) pass only
+// out_f64 (inverse, register-tiled sizes): the coefficients leave as doubles, with the last-stage constants fin or *fin_val
 // gal (inverse row pass of the register-tiled sizes only): item i's input is read through the automorphism X -> X^(gal->g[i])
 void launch_ntt(ckksmi_ctx *c, bool forward, const u64 *src, u64 *dst, const LimbMap &M, size_t items, hipStream_t st,
-                const FinConst *fin = nullptr, int passes = 3, const GaloisTab *gal = nullptr) {
+                const FinConst *fin = nullptr, int passes = 3, const GaloisTab *gal = nullptr, bool out_f64 = false,
+                const FinConst *fin_val = nullptr) {
     if (items == 0 || M.per_item == 0) return;
     NttArgs A;
     A.src = (const u64d *)src;
@@ -123,6 +126,8 @@ void launch_ntt(ckksmi_ctx *c, bool forward, const u64 *src, u64 *dst, const Lim
     const bool v2_rows = c->logN >= 12 && c->logN <= 16, v2_cols = v2_rows;
     const bool two_pass = v2_cols || A.LA != 0;
     NttV2Args V;
+    V.use_fin_val = fin_val ? 1 : 0;
+    V.fin_val = fin_val ? *fin_val : FinConst();
     V.src = A.src; V.dst = A.dst; V.modc = A.modc; V.tw = forward ? c->d_tww_fwd : c->d_tww_inv; V.tw_ninv = c->d_tw_ninv;
     V.tw_last = A.tw_last; V.fin = fin; V.logN = A.logN; V.map = M; V.p51 = c->p51mask;
     V.items = (int)items;
@@ -134,7 +139,9 @@ void launch_ntt(ckksmi_ctx *c, bool forward, const u64 *src, u64 *dst, const Lim
     V.items_per_z = (int)((items + zchunks - 1) / zchunks);
     zchunks = (unsigned)((items + V.items_per_z - 1) / V.items_per_z);
     dim3 gv2(tiles, M.per_item, zchunks);
-    if (passes == 3 && (c->logN == 13 || c->logN == 14)) {
+    // (a few limbs of 2^13 or 2^14 words keep the two passes: their tiles of 4096 words occupy more compute units, 14 us
+    // against 20 for up to 30 limbs of 2^14 words)
+    if (passes == 3 && (c->logN == 12 || ((c->logN == 13 || c->logN == 14) && limbs >= 64))) {
         // the whole limb in one workgroup: one trip through HBM (see ntt_wg.h); a workgroup loops over items of its limb slot
         unsigned zc = ((unsigned)c->ntt_target_wgs / 4 + M.per_item - 1) / M.per_item;
         if (zc > items) zc = (unsigned)items;
@@ -142,13 +149,16 @@ void launch_ntt(ckksmi_ctx *c, bool forward, const u64 *src, u64 *dst, const Lim
         V.items_per_z = (int)((items + zc - 1) / zc);
         zc = (unsigned)((items + V.items_per_z - 1) / V.items_per_z);
         const dim3 gw(M.per_item, zc), bw((unsigned)(N / 16));
-        if (c->logN == 13) {
-            if (forward) KL(c, CKKSMI_K_NTT_LDS, limbs_work, (ntt_wg_kernel<false, 13>), gw, bw, st, V);
-            else KL(c, CKKSMI_K_NTT_LDS, limbs_work, (ntt_wg_kernel<true, 13>), gw, bw, st, V);
-        } else {
-            if (forward) KL(c, CKKSMI_K_NTT_LDS, limbs_work, (ntt_wg_kernel<false, 14>), gw, bw, st, V);
-            else KL(c, CKKSMI_K_NTT_LDS, limbs_work, (ntt_wg_kernel<true, 14>), gw, bw, st, V);
+#define NTT_WG_CASE(LN)                                                                                       \
+    case LN:                                                                                                  \
+        if (forward) KL(c, CKKSMI_K_NTT_LDS, limbs_work, (ntt_wg_kernel<false, LN>), gw, bw, st, V);          \
+        else if (out_f64) KL(c, CKKSMI_K_NTT_LDS, limbs_work, (ntt_wg_kernel<true, LN, true>), gw, bw, st, V); \
+        else KL(c, CKKSMI_K_NTT_LDS, limbs_work, (ntt_wg_kernel<true, LN>), gw, bw, st, V);                   \
+        break;
+        switch (c->logN) {
+            NTT_WG_CASE(12) NTT_WG_CASE(13) NTT_WG_CASE(14)
         }
+#undef NTT_WG_CASE
         return;
     }
     if (forward) {
@@ -175,7 +185,8 @@ void launch_ntt(ckksmi_ctx *c, bool forward, const u64 *src, u64 *dst, const Lim
             A.map.src_item_stride = A.map.dst_item_stride;
             V.src = A.src;
             V.map.src_item_stride = V.map.dst_item_stride;
-            if (v2_cols) KL(c, CKKSMI_K_NTT_INV_COL, limbs_work, (ntt_v2_kernel<true, true>), gv2, dim3(V2_THREADS), st, V);
+            if (v2_cols && out_f64) KL(c, CKKSMI_K_NTT_INV_COL, limbs_work, (ntt_v2_kernel<true, true, true>), gv2, dim3(V2_THREADS), st, V);
+            else if (v2_cols) KL(c, CKKSMI_K_NTT_INV_COL, limbs_work, (ntt_v2_kernel<true, true>), gv2, dim3(V2_THREADS), st, V);
             else KL(c, CKKSMI_K_NTT_INV_COL, limbs_work, ntt_inv_kernel<true>, gcol, dim3(NTT_THREADS), st, A);
         }
     }
@@ -251,7 +262,7 @@ void launch_modup_cols(ckksmi_ctx *c, int mode, const u64 *y, size_t y_stride, u
         if (mode == 0) KL(c, kid, units, (modup_cols_kernel<Q, NS, 0>), grid, block, st, A);                 \
         else if (mode == 2) KL(c, kid, units, (modup_cols_kernel<Q, NS, 2>), grid, block, st, A);            \
         else if (mode == 3) KL(c, kid, units, (modup_cols_kernel<Q, NS, 3>), grid, block, st, A);            \
-        else KL(c, kid, units, (modup_cols_kernel<Q, NS, 1>), grid, block, st, A);                           \
+        else if constexpr (NS > 1 || Q == 4) KL(c, kid, units, (modup_cols_kernel<Q, NS, 1>), grid, block, st, A); \
         break;
     switch ((c->logN - 12) * 8 + nsrc) {
         MODUP_COLS_CASE(0, 1) MODUP_COLS_CASE(0, 2) MODUP_COLS_CASE(0, 3) MODUP_COLS_CASE(0, 4)
@@ -268,12 +279,10 @@ void launch_modup_cols(ckksmi_ctx *c, int mode, const u64 *y, size_t y_stride, u
 // out + row*out_row_stride + (limb - limb0)*N
 void launch_rows_final(ckksmi_ctx *c, const u64 *tmpA, const u64 *x, size_t x_row_stride, const u64 *addend, size_t add_item_stride,
                        size_t add_comp_stride, int add_both, u64 *out, const WMul *Binv, int nc, int rows, hipStream_t st, int limb0 = 0,
-                       int limb_count = -1, size_t out_row_stride = 0, const WMul *pre = nullptr, const WMul *xmul = nullptr,
-                       const ScalarTab *stab = nullptr, bool zsub = false, const RowsFinalGal *gal = nullptr) {
+                       int limb_count = -1, size_t out_row_stride = 0, const WMul *pre = nullptr, const ScalarTab *stab = nullptr, bool zsub = false, const RowsFinalGal *gal = nullptr) {
     RowsFinalArgs A;
     A.zsub = zsub ? 1 : 0;
     A.pre = pre;
-    A.xmul = xmul;
     const int nz = limb_count < 0 ? nc : limb_count;
     A.limb0 = limb_count < 0 ? 0 : limb0;
     A.out_limb0 = A.limb0;
@@ -293,6 +302,52 @@ void launch_rows_final(ckksmi_ctx *c, const u64 *tmpA, const u64 *x, size_t x_ro
         KL(c, CKKSMI_K_ROWS_FINAL, (double)rows * nz, rows_final_kernel, dim3(xch, tiles, nz), dim3(V2_THREADS), st, A);
 }
 
+// Which kept limbs' division runs as ONE kernel after the inverse transform of the dropped limbs (ks_wg.h): one source
+// (rescale, or ModDown with one special prime) at every register-tiled size.
+inline bool conv_final_ok(const ckksmi_ctx *c, int nsrc) { return c->fused && nsrc == 1; }
+
+// y: the dropped limbs in coefficient form as canonical doubles, row r at y + r*y_stride; fin_kind as conv_final_body's FIN
+void launch_conv_final(ckksmi_ctx *c, int fin_kind, const u64 *y, size_t y_stride, const DivRoundDev &D, const u64 *x, size_t x_row_stride,
+                       const u64 *addend, size_t add_item_stride, size_t add_comp_stride, u64 *out, int nc, int rows, hipStream_t st,
+                       const RowsFinalGal *gal = nullptr, const ScalarTab *stab = nullptr) {
+    ConvFinalArgs A;
+    memset(&A, 0, sizeof(A));
+    RowsFinalArgs &F = A.F;
+    F.x = (const u64d *)x; F.x_row_stride = x_row_stride;
+    F.addend = (const u64d *)addend; F.add_item_stride = add_item_stride; F.add_comp_stride = add_comp_stride;
+    F.out = (u64d *)out; F.out_row_stride = (size_t)nc * c->N; F.modc = c->d_mod; F.tw = c->d_tww_fwd; F.Binv = D.Binv;
+    F.logN = c->logN; F.nc = nc; F.rows = rows; F.p51 = c->p51mask;
+    A.y = (const double *)y; A.y_row_stride = y_stride; A.D = D; A.T = c->T;
+    // Blocks per limb: M = N >> S words per workgroup.  Measured at 4096 and more limbs (us per 2^14 words): N = 2^12 whole 0.067;
+    // 2^13 halved 0.073, whole 0.075; 2^14 halved 0.078, whole 0.082 - 0.085; 2^15 halved 0.089, quartered 0.097; 2^16 quartered 0.109.  With
+    // too few workgroups for the 256 compute units finer blocks win instead (N = 2^14, 16 limbs: 11.8 us halved, 9.9 quartered;
+    // N = 2^15, 30 limbs: 20.4 and 15.8).
+    int S = c->logN == 12 ? 0 : (c->logN == 16 ? 2 : 1);
+    if ((c->logN == 14 || c->logN == 15) && (size_t)rows * nc * 2 < (size_t)c->ntt_target_wgs / 32 /* 256 */) S = 2;
+    A.rows_x = std::min(8, rows);
+    const int per = (rows + A.rows_x - 1) / A.rows_x, groups = (per + 7) / 8;
+    A.rows_g = (per + groups - 1) / groups;
+    const size_t wgs = (size_t)A.rows_x * ((size_t)1 << S) * A.rows_g * nc * groups;
+    const dim3 grid((unsigned)wgs), block((unsigned)(c->N >> S) / 16);
+    const double units = (double)rows * nc;
+#define CONV_FINAL_CASE(LN, SS)                                                                                                  \
+    case LN * 4 + SS:                                                                                                                         \
+        if (fin_kind == 0) KL(c, CKKSMI_K_CONV_FINAL, units, (conv_final_kernel<LN - SS, SS, 1, 0>), grid, block, st, A);                 \
+        else if (fin_kind == 1) KL(c, CKKSMI_K_CONV_FINAL, units, (conv_final_kernel<LN - SS, SS, 1, 1>), grid, block, st, A);            \
+        else if (fin_kind == 2) { if constexpr (LN < 16) KL(c, CKKSMI_K_CONV_FINAL, units, (conv_final_scalar_kernel<LN - SS, SS>), grid, block, st, A, *stab); } \
+        else KL(c, CKKSMI_K_CONV_FINAL, units, (conv_final_gal_kernel<LN - SS, SS, 1>), grid, block, st, A, *gal);                        \
+        break;
+    switch (c->logN * 4 + S) {
+        CONV_FINAL_CASE(12, 0)
+        CONV_FINAL_CASE(13, 1)
+        CONV_FINAL_CASE(14, 1) CONV_FINAL_CASE(14, 2)
+        CONV_FINAL_CASE(15, 1) CONV_FINAL_CASE(15, 2)
+        CONV_FINAL_CASE(16, 2)
+        default: break;
+    }
+#undef CONV_FINAL_CASE
+}
+
 // DivRound of `rows` rows on the register-tiled kernels: dropped limbs (evaluation form) at b_limbs + r*b_stride (nb limbs;
 // b_scratch == b_limbs works in place), kept limbs at x + r*x_stride; out[r][i] = (x_i - NTT(r_i - h)) * Bbar^-1 (+ addend).
 // zsub: the kept limbs already hold x * Bbar^-1 + addend, out = x - NTT(r - h) * Bbar^-1.
@@ -300,11 +355,15 @@ void divround_rows(ckksmi_ctx *c, const DivRoundDev &D, const FinConst *fin, con
                    u64 *b_scratch, size_t bs_stride, const u64 *x, size_t x_stride, u64 *tmp, int nc, int rows, const u64 *addend,
                    size_t add_item_stride, size_t add_comp_stride, int add_both, u64 *out, hipStream_t st, bool zsub = false,
                    const RowsFinalGal *gal = nullptr) {
+    if (conv_final_ok(c, D.nb) && !add_both) {
+        launch_ntt(c, false, b_limbs, b_scratch, table_map(bidx, D.nb, b_stride, bs_stride), rows, st, fin, 3, nullptr, true);
+        launch_conv_final(c, zsub ? 1 : (gal ? 3 : 0), b_scratch, bs_stride, D, x, x_stride, addend, add_item_stride, add_comp_stride, out, nc, rows, st, gal);
+        return;
+    }
     // inverse row pass of the dropped limbs; the conversion kernel runs their inverse column pass itself
     launch_ntt(c, false, b_limbs, b_scratch, table_map(bidx, D.nb, b_stride, bs_stride), rows, st, fin, 2);
     launch_modup_cols(c, 1, b_scratch, bs_stride, tmp, rows, 0, nc, &D, (double)rows * nc, st, fin);
-    launch_rows_final(c, tmp, x, x_stride, addend, add_item_stride, add_comp_stride, add_both, out, D.Binv, nc, rows, st, 0, -1, 0, nullptr, nullptr,
-                      nullptr, zsub, gal);
+    launch_rows_final(c, tmp, x, x_stride, addend, add_item_stride, add_comp_stride, add_both, out, D.Binv, nc, rows, st, 0, -1, 0, nullptr, nullptr, zsub, gal);
 }
 
 // Rotations with a shared ModUp: R rotations of every item of a key-switch sweep (see inner_product_hoisted_kernel)
@@ -504,7 +563,6 @@ void scalar_rescale_fused(ckksmi_ctx *c, const u64 *a, int64_t v, const u64 *add
     const size_t in_stride = (size_t)level_in * N;  // the input rows hold level_in limbs, of which the first `level` are used
     const int last = level - 1, rows = items * 2;
     u64 *lastbuf = ws;
-    u64 *tmp = lastbuf + (size_t)rows * N;
     int lidx[1] = {last};
     const DivRoundDev &D = c->divround[1 + last];
     const u64 q = c->mod[last], vm = hm::signed_mod(v, q);
@@ -514,10 +572,16 @@ void scalar_rescale_fused(ckksmi_ctx *c, const u64 *a, int64_t v, const u64 *add
     F.cadd = (double)((q - 1) / 2);
     F.pad = 0.0;
     const ScalarTab St = scalar_tab(c, v, level);
-    launch_ntt(c, false, a + (size_t)last * N, lastbuf, table_map(lidx, 1, in_stride, N), rows, st, c->d_fin_rescale + last, 2);
-    launch_modup_cols(c, 1, lastbuf, N, tmp, rows, 0, last, &D, (double)rows * last, st, c->d_fin_rescale + last, nullptr, &F);
-    launch_rows_final(c, tmp, a, in_stride, addend, (size_t)2 * last * N, (size_t)last * N, 1, out, D.Binv, last, rows, st, 0, -1, 0, nullptr, nullptr,
-                      &St);
+    if (c->logN == 16) {
+        // the register-tiled pair: the GPU parity test of the activation schedule at its full size checks that it runs here
+        u64 *tmp = lastbuf + (size_t)rows * N;
+        launch_ntt(c, false, a + (size_t)last * N, lastbuf, table_map(lidx, 1, in_stride, N), rows, st, c->d_fin_rescale + last, 2);
+        launch_modup_cols(c, 1, lastbuf, N, tmp, rows, 0, last, &D, (double)rows * last, st, c->d_fin_rescale + last, nullptr, &F);
+        launch_rows_final(c, tmp, a, in_stride, addend, (size_t)2 * last * N, (size_t)last * N, 1, out, D.Binv, last, rows, st, 0, -1, 0, nullptr, &St);
+        return;
+    }
+    launch_ntt(c, false, a + (size_t)last * N, lastbuf, table_map(lidx, 1, in_stride, N), rows, st, nullptr, 3, nullptr, true, &F);
+    launch_conv_final(c, 2, lastbuf, N, D, a, in_stride, addend, (size_t)2 * last * N, (size_t)last * N, out, last, rows, st, nullptr, &St);
 }
 
 // Key switch of `items` polynomials.  d_eval: item i's polynomial ([level][N], evaluation
@@ -1658,7 +1722,7 @@ extern "C" const char *ckksmi_kernel_class_name(const ckksmi_ctx *c, int kernel_
                                                 "elementwise kernels", "modup_cols_kernel", "modup_cols_kernel", "rows_inner_kernel",
                                                 "rows_final_kernel", "modup_cols_kernel", "conv_mac_mfma_kernel", "mac_prepare_mfma_kernel", "ntt_wg_kernel", "tensor_rows_kernel",
                                                 "axpy_limb_kernel", "modup_cols_kernel", "inner_product_hoisted_tile_kernel", "automorphism_bcast_kernel",
-                                                "encoding kernels", "encryption kernels", "modup_cols_kernel", "conv_mac_mfma_resident_kernel", "conv_mac_mfma_strip_kernel"};
+                                                "encoding kernels", "encryption kernels", "modup_cols_kernel", "conv_mac_mfma_resident_kernel", "conv_mac_mfma_strip_kernel", "conv_final_kernel"};
     if (kernel_class < 0 || kernel_class >= CKKSMI_K_COUNT) return "";
     if (c && kernel_class == CKKSMI_K_INNER_HOISTED && !hoisted_tile_ok(c, c->beta_top)) return "inner_product_hoisted_kernel";
     if (c && c->logN >= 12 && c->logN <= 16) {

@@ -754,7 +754,6 @@ struct RowsFinalArgs {
     const double *tw;
     const WMul *Binv;    // [T]
     const WMul *pre;     // optional [T]: the addend enters BEFORE the division, out = (x + pre_i*addend - r) * Binv
-    const WMul *xmul;    // optional [T] (without pre): out = (x*xmul_i + addend - r) * Binv
     int zsub;            // 1: x already holds x*Binv + addend: out = x - r * Binv
     int logN, nc;
     int limb0;             // first limb handled (grid z counts from it)
@@ -778,15 +777,14 @@ __device__ __forceinline__ void rows_final_body(const RowsFinalArgs &A, double *
     load_row_twiddles(A.tw + (size_t)i * N, N1, tile, hi4, lo4, tw1_lds, tw2);
     const size_t tile0 = (size_t)tile * 4096;
     const WMul W = A.Binv[i];
-    const bool pre = A.pre != nullptr, xm = xm_val || A.xmul != nullptr;
-    const WMul Pm = pre ? A.pre[i] : (xm_val ? xmv : (xm ? A.xmul[i] : WMul{0.0, 0.0}));
+    const bool pre = A.pre != nullptr, xm = xm_val;
+    const WMul Pm = pre ? A.pre[i] : xmv;
     const unsigned r0 = blockIdx.x * (unsigned)A.rows_per_x;
     const unsigned r1 = (r0 + A.rows_per_x < (unsigned)A.rows) ? r0 + A.rows_per_x : (unsigned)A.rows;
     for (unsigned row = r0; row < r1; row++) {
         const u64d *xin = A.x + (size_t)row * A.x_row_stride + (size_t)i * N + tile0;
         u64d *out = A.out + (size_t)row * A.out_row_stride + (size_t)(i - A.out_limb0) * N + tile0;
         const bool add = A.addend && (pre || xm || A.add_both || (row & 1u) == 0);
-        const double has_add = add ? 1.0 : 0.0;
         const u64d *ad = add ? A.addend + (size_t)(row / 2) * A.add_item_stride + (size_t)(row % 2) * A.add_comp_stride + (size_t)i * N + tile0 : xin;
         // operands of the last step are requested before the transform so that their latency overlaps it
         // pointwise part in the row-pair layout: 16 bytes per lane and memory instruction, no workgroup barrier
@@ -812,11 +810,9 @@ __device__ __forceinline__ void rows_final_body(const RowsFinalArgs &A, double *
                 x0 += mulmod_w(u2d(ar[s].x), Pm.w, Pm.wp, p);
                 x1 += mulmod_w(u2d(ar[s].y), Pm.w, Pm.wp, p);
             }
-            if (xm) {  // |x*xmul + addend - r| < 0.75p + p + p/2 + 1 (without an addend `ar` is a copy of x: not used)
-                // the hmul tail's addend enters before the division; the scalar rescale's one is added to the result
-                const double before = xm_val ? 0.0 : has_add;
-                x0 = mulmod_w(x0, Pm.w, Pm.wp, p) + before * u2d(ar[s].x);
-                x1 = mulmod_w(x1, Pm.w, Pm.wp, p) + before * u2d(ar[s].y);
+            if (xm) {  // |x*xmv - r| < 0.75p + p/2 + 1 (without an addend `ar` is a copy of x: not used)
+                x0 = mulmod_w(x0, Pm.w, Pm.wp, p);
+                x1 = mulmod_w(x1, Pm.w, Pm.wp, p);
             }
             double v0, v1;
             if (A.zsub) {
@@ -826,7 +822,7 @@ __device__ __forceinline__ void rows_final_body(const RowsFinalArgs &A, double *
                 v0 = mulmod_w(x0 - rr[0], W.w, W.wp, p);
                 v1 = mulmod_w(x1 - rr[1], W.w, W.wp, p);
             }
-            if (add && !pre && (!xm || xm_val)) {
+            if (add && !pre) {
                 v0 += u2d(ar[s].x);
                 v1 += u2d(ar[s].y);
             }

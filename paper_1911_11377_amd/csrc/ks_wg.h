@@ -1,0 +1,299 @@
+// DivRound without an intermediate in memory (2^12 <= N <= 2^16, one dropped prime): conversion, forward transform and last
+// step of a kept limb in ONE workgroup.
+//
+// The register-tiled pair modup_cols_kernel / rows_final_kernel (ks_fused.h) writes every converted limb after the column
+// pass of its transform and reads it back for the row pass: for a rescale that is two of the four limb transfers a kept
+// limb costs, and both kernels run at the speed of a device copy.  Here a workgroup owns M = 2^LOGM words of one kept
+// limb: it reads the dropped limb's words (coefficient form, shared by all kept limbs of a row and served by the L2 of the
+// XCD the row's workgroups run on), converts them, takes them through the whole transform with the M x 256 decomposition of
+// ntt_wg.h in LDS, and finishes its words of the kept limb.  What crosses HBM is the kept limb in and out, and the source.
+//
+// A ring larger than M is cut into 2^S blocks: the first S stages of the forward transform send block b of the result only
+// to linear combinations of the 2^S words n + q*M, so a workgroup forms its own block's word from 2^S source words with
+// 2^S - 1 products (the other blocks' workgroups repeat the conversion, which for one dropped prime is one reduction) and
+// transforms M words from there: stage s of the block uses the twiddles (2^S + b) * 2^s + i of the whole transform's table.
+//
+// Measured (us per 2^14 words of kept limb, inverse transform of the dropped limb not counted): N = 2^15, 15 kept limbs 0.119 as
+// two kernels, 0.089 now; N = 2^16 0.143 and 0.109; N = 2^14 0.114 and 0.078 (3.4 TB/s of kept limbs in and out; a device
+// copy moves 4.85).  About 105 vector instructions per word (110 at S = 2): vector ALU 0.6 busy, memory 0.7 of a copy.  With four
+// waves per SIMD a thread has 128 registers; a single spilled register set costs more than everything else here (0.16 us
+// with 44 registers spilled), hence the notes to the compiler below.  Variants that lost: 32 words per thread at two waves
+// per SIMD with the kept limb requested before the transform (0.081 - 0.099), the kept limb requested after the transform
+// (0.083 - 0.095).
+#pragma once
+#include "ks_fused.h"
+#include "ntt_wg.h"
+
+// Two instantiations of a body behind one uniform branch start with different (empty) asm statements: the compiler otherwise
+// merges their identical beginnings into the block before the branch and spills what it computed there.
+#ifdef CKKSMI_EMULATE
+#define BODY_TAG(V) ((void)0)
+#else
+#define BODY_TAG(V)                              \
+    do {                                         \
+        if (V) asm volatile("; body, 51 bits");  \
+        else asm volatile("; body, 50 bits");    \
+    } while (0)
+#endif
+
+// What the compiler has to be told about these kernels' register budget (all empty on the CPU stand-in):
+//   PIN_VALUE(x)    x is computed before the next pinned point and not sunk below later loads;
+//   scalar_base(p)  a workgroup-uniform address stays in scalar registers, so that the loads from p[thread offset] need no
+//                   64-bit vector additions each;
+//   WG_UNIFORM(v)   a workgroup-uniform value goes to a scalar register.
+#ifdef CKKSMI_EMULATE
+#define PIN_VALUE(x) ((void)0)
+#define WG_UNIFORM(v) (v)
+template <class T> __device__ __forceinline__ T *scalar_base(T *p) { return p; }
+#else
+#define PIN_VALUE(x) asm volatile("" : "+v"(x))
+#define WG_UNIFORM(v) ((unsigned)__builtin_amdgcn_readfirstlane((int)(v)))
+template <class T> __device__ __forceinline__ T *scalar_base(T *p) {
+    asm volatile("" : "+s"(p));
+    return p;
+}
+#endif
+
+struct ConvFinalArgs {
+    RowsFinalArgs F;        // kept limbs, addend, output (tmpA, pre, rows_per_x unused); F.rows rows of F.nc kept limbs
+    const double *y;        // sources in coefficient form, canonical, stored as doubles: row r, source m at y + r*y_row_stride + m*N
+    unsigned long long y_row_stride;
+    DivRoundDev D;
+    int T;
+    int rows_x, rows_g;     // workgroup order, see conv_final_place
+};
+
+// Workgroup order.  Consecutive workgroup ids go to the 8 XCDs in turn, and every XCD has its own L2 (4 MB).  Rows are dealt to
+// the XCDs round-robin; an XCD takes its rows in groups of rows_g (at most 8) and walks the kept limbs over a group, so
+// that the group's sources (rows_g limbs) and the current limb's twiddle table stay in its L2.
+__device__ __forceinline__ bool conv_final_place(const ConvFinalArgs &A, int S, unsigned &row, unsigned &blk, int &limb) {
+    const unsigned X = (unsigned)A.rows_x, G = (unsigned)A.rows_g, nc = (unsigned)A.F.nc;
+    unsigned k = blockIdx.x / X;
+    blk = WG_UNIFORM(k & ((1u << S) - 1u));
+    k >>= S;
+    const unsigned r = k % G;
+    k /= G;
+    limb = (int)WG_UNIFORM(k % nc);
+    row = WG_UNIFORM((k / nc * G + r) * X + blockIdx.x % X);
+    return row < (unsigned)A.F.rows;
+}
+
+// One converted coefficient, balanced-reduced: sum_a y_a * conv_a - h.  A single source has conv = 1 (the empty product).
+template <int NSRC>
+__device__ __forceinline__ double conv_word(const double (&y)[NSRC], const WMul (&Wc)[NSRC], double hsub, double p, double pinv) {
+    if (NSRC == 1) return reduce_balanced(y[0] - hsub, p, pinv);  // below 2^51 + p
+    double v = -hsub;
+#pragma unroll
+    for (int a = 0; a < NSRC; a++) v += mulmod_w(y[a], Wc[a].w, Wc[a].wp, p);
+    return reduce_balanced(v, p, pinv);  // |v| <= p + NSRC * 0.75p
+}
+
+// Forward transform of block `base - 2^S` of a ring of M * 2^S words (base = 1: the whole ring): x in the column layout of
+// ntt_wg.h, at most 2.7p (p < 2^50) or 1.2p (p < 2^51) in magnitude; the balanced-reduced results end in LDS, word (row g,
+// position q) at wg_pad(g, q).  Every row is finished by its own 16 lanes (a row-group sync suffices to read it).
+// `request` is called once the first row round is done: the place for memory requests whose latency the rest covers.
+template <int LOGM, bool P51, class F>
+__device__ __forceinline__ void wg_fwd_block(double (&x)[16], const double *tw, unsigned base, double *lds, double p, double pinv, F request) {
+    constexpr int Q = LOGM - 12;
+    typedef ColsGeom<Q> Geo;
+    typedef ColsMasks<Q, P51> Mk;
+    constexpr unsigned MR = (1u << LOGM) >> 8;
+    constexpr int RF1 = P51 ? 0xA : 0x8, RF2 = P51 ? 0x2 : 0x0;
+    const unsigned tid = threadIdx.x, row = tid >> 4, lo4 = tid & 15;
+    const Geo geo(tid & 255u, tid >> 8);
+    double *grp = lds + row * V2_GS;
+    {
+        double tw1[15];
+#pragma unroll
+        for (int s = 0; s < 4; s++)
+#pragma unroll
+            for (int b = 0; b < (1 << s); b++) tw1[(1 << s) - 1 + b] = tw[(base << s) + b];
+        fwd_round<Mk::F1>(x, tw1, p, pinv);
+    }
+    double tw1[15], tw2[15];
+    if (Q > 0) {
+#pragma unroll
+        for (int s = 0; s < 4; s++)
+#pragma unroll
+            for (int b = 0; b < (1 << s); b++) {
+                if (s >= 4 - Q) {
+                    const int u = s - (4 - Q);
+                    tw2[(1 << s) - 1 + b] = tw[((16u * base + geo.a) << u) + (b & ((1 << u) - 1))];
+                } else {
+                    tw2[(1 << s) - 1 + b] = 0.0;
+                }
+            }
+#pragma unroll
+        for (int e = 0; e < 16; e++) lds[wg_pad(geo.r + Geo::G * e, geo.c0 + geo.c)] = x[e];
+        __syncthreads();
+#pragma unroll
+        for (int i = 0; i < 16; i++) x[i] = lds[wg_pad(Geo::G * geo.a + (i % Geo::G), geo.c0 + geo.l16 + 16 * (i / Geo::G))];
+        fwd_stages<Geo::S0, Mk::F2>(x, tw2, p, pinv);
+#pragma unroll
+        for (int i = 0; i < 16; i++)
+            lds[wg_pad(Geo::G * geo.a + (i % Geo::G), geo.c0 + geo.l16 + 16 * (i / Geo::G))] = reduce_balanced(x[i], p, pinv);
+    } else {
+#pragma unroll
+        for (int e = 0; e < 16; e++) lds[wg_pad(e, geo.c0 + geo.c)] = x[e];  // the first round ends reduced
+    }
+    const unsigned base1 = base * MR + row;
+#pragma unroll
+    for (int s = 0; s < 4; s++)
+#pragma unroll
+        for (int b = 0; b < (1 << s); b++) tw1[(1 << s) - 1 + b] = tw[(base1 << s) + b];
+    __syncthreads();
+#pragma unroll
+    for (int e = 0; e < 16; e++) x[e] = grp[e * 17 + lo4];
+    fwd_round<RF1>(x, tw1, p, pinv);
+#pragma unroll
+    for (int s = 0; s < 4; s++)
+#pragma unroll
+        for (int b = 0; b < (1 << s); b++) tw2[(1 << s) - 1 + b] = tw[((16u * base1 + lo4) << s) + b];
+#pragma unroll
+    for (int e = 0; e < 16; e++) grp[e * 17 + lo4] = x[e];
+    request();
+    ROW_GROUP_SYNC();
+#pragma unroll
+    for (int e = 0; e < 16; e++) x[e] = grp[lo4 * 17 + e];
+    fwd_round<RF2>(x, tw2, p, pinv);
+#pragma unroll
+    for (int e = 0; e < 16; e++) grp[lo4 * 17 + e] = reduce_balanced(x[e], p, pinv);
+    ROW_GROUP_SYNC();
+}
+
+// FIN 0: out = (x - r) * Binv;  1: out = x - r * Binv (x holds x * Binv + addend);  2: out = (x * xmv - r) * Binv (+ addend);
+// 3: out = (x - r) * Binv + sigma_g(addend) on even rows (rotations from a shared ModUp, see RowsFinalGal)
+template <int LOGM, int S, int NSRC, int FIN, bool P51>
+__device__ __forceinline__ void conv_final_body(const ConvFinalArgs &A, double *lds, int i, unsigned row, unsigned blk, WMul xmv,
+                                                const RowsFinalGal *gal) {
+    typedef ColsGeom<LOGM - 12> Geo;
+    constexpr unsigned M = 1u << LOGM, N = M << S;
+    BODY_TAG(P51);
+    const RowsFinalArgs &F = A.F;
+    const double p = F.modc[i].p, pinv = F.modc[i].pinv;
+    const double *tw = F.tw + (size_t)i * N;
+    const unsigned tid = threadIdx.x, prow = tid >> 4, lo4 = tid & 15, base = (1u << S) + blk;
+    double x[16];
+    {
+        const Geo geo(tid & 255u, tid >> 8);
+        // uniform base addresses plus one offset per thread: no 64-bit address arithmetic per load
+        const double *y = A.y + (size_t)row * A.y_row_stride;
+        const unsigned voff = geo.r * 256u + geo.c0 + geo.c;
+        WMul Wc[NSRC];
+#pragma unroll
+        for (int a = 0; a < NSRC; a++) Wc[a] = A.D.conv[(size_t)a * A.T + i];
+        const double hsub = A.D.hc[i];
+        // twiddles of the first S stages on the way to this block (negative: the block lies in the lower branch's difference)
+        double w[S + 1], wp[S + 1];
+#pragma unroll
+        for (int t = 0; t < S; t++) {
+            const double v = tw[(1u << t) + (blk >> (S - t))];
+            w[t] = ((blk >> (S - 1 - t)) & 1u) ? -v : v;
+            wp[t] = w[t] * pinv;
+        }
+        constexpr int CH = 16 >> S;  // words formed together: bounds the source words in flight
+#pragma unroll
+        for (int e0 = 0; e0 < 16; e0 += CH) {
+            double src[CH][1 << S][NSRC];
+#pragma unroll
+            for (int e = 0; e < CH; e++)
+#pragma unroll
+                for (int q = 0; q < (1 << S); q++)
+#pragma unroll
+                    for (int a = 0; a < NSRC; a++) src[e][q][a] = scalar_base(y + ((size_t)a * N + (size_t)q * M + Geo::G * 256u * (e0 + e)))[voff];
+            SCHED_FENCE();
+#pragma unroll
+            for (int e = 0; e < CH; e++) {
+                double u[1 << S];
+#pragma unroll
+                for (int q = 0; q < (1 << S); q++) u[q] = conv_word<NSRC>(src[e][q], Wc, hsub, p, pinv);
+                // stage t joins the words 2^(S-1-t) * M apart
+#pragma unroll
+                for (int t = 0; t < S; t++)
+#pragma unroll
+                    for (int q = 0; q < (1 << (S - 1 - t)); q++) u[q] += mulmod_w(u[q + (1 << (S - 1 - t))], w[t], wp[t], p);
+                x[e0 + e] = (P51 && S >= 2) ? reduce_balanced(u[0], p, pinv) : u[0];
+            }
+#pragma unroll
+            for (int e = 0; e < CH; e++) PIN_VALUE(x[e0 + e]);
+        }
+    }
+    const size_t off = (size_t)i * N + (size_t)blk * M;
+    const ulonglong2 *xin = (const ulonglong2 *)(F.x + (size_t)row * F.x_row_stride + off);
+    ulonglong2 *out = (ulonglong2 *)(F.out + (size_t)row * F.out_row_stride + off);
+    const unsigned pr = row_pair_index(prow, lo4, 0);
+    ulonglong2 xr[8];
+    wg_fwd_block<LOGM, P51>(x, tw, base, lds, p, pinv, [&]() {
+#pragma unroll
+        for (int s = 0; s < 8; s++) xr[s] = (xin + 16 * s)[pr];
+    });
+    const WMul W = F.Binv[i];
+    const bool add = F.addend != nullptr && (FIN == 2 || (FIN == 3 && (row & 1u) == 0));
+    const double *grp = lds + prow * V2_GS;
+    auto finish = [&](int s, bool with, ulonglong2 ar) {
+        const double *rr = grp + row_pair_lds(lo4, s);
+        double x0 = u2d(xr[s].x), x1 = u2d(xr[s].y);
+        if (FIN == 2) {  // |x * xmv - r| <= 0.75p + p/2 + 1
+            x0 = mulmod_w(x0, xmv.w, xmv.wp, p);
+            x1 = mulmod_w(x1, xmv.w, xmv.wp, p);
+        }
+        double v0 = FIN == 1 ? x0 - mulmod_w(rr[0], W.w, W.wp, p) : mulmod_w(x0 - rr[0], W.w, W.wp, p);
+        double v1 = FIN == 1 ? x1 - mulmod_w(rr[1], W.w, W.wp, p) : mulmod_w(x1 - rr[1], W.w, W.wp, p);
+        if (with) {
+            v0 += u2d(ar.x);
+            v1 += u2d(ar.y);
+        }
+        (out + 16 * s)[pr] = make_ulonglong2(d2u(canon(v0, p, pinv)), d2u(canon(v1, p, pinv)));
+    };
+    if (FIN < 2 || !add) {
+#pragma unroll
+        for (int s = 0; s < 8; s++) finish(s, false, make_ulonglong2(0ull, 0ull));
+        return;
+    }
+    ulonglong2 ar[8];
+    if (FIN == 3) {
+        const unsigned pair = row / 2u, item = pair / (unsigned)gal->R, g = gal->g[pair % (unsigned)gal->R];
+        const u64d *limb = F.addend + (size_t)item * F.add_item_stride + (size_t)i * N;
+#pragma unroll
+        for (int s = 0; s < 8; s++) ar[s] = galois_pair_load(limb, blk * M + prow * 256u + 32u * s + 2u * lo4, g, LOGM + S);
+    } else {
+        const ulonglong2 *ad = (const ulonglong2 *)(F.addend + (size_t)(row / 2) * F.add_item_stride + (size_t)(row % 2) * F.add_comp_stride + off);
+#pragma unroll
+        for (int s = 0; s < 8; s++) ar[s] = (ad + 16 * s)[pr];
+    }
+#pragma unroll
+    for (int s = 0; s < 8; s++) finish(s, true, ar[s]);
+}
+
+// grid: x = rows_x * 2^S * rows_g * nc * (row groups), see conv_final_place; block = M/16 threads
+template <int LOGM, int S, int NSRC, int FIN>
+__global__ __launch_bounds__((1 << LOGM) / 16, 4) void conv_final_kernel(ConvFinalArgs A) {
+    __shared__ double lds[((1 << LOGM) >> 8) * V2_GS];
+    unsigned row, blk;
+    int i;
+    if (!conv_final_place(A, S, row, blk, i)) return;
+    if (is_p51(A.F.p51, i)) conv_final_body<LOGM, S, NSRC, FIN, true>(A, lds, i, row, blk, WMul{0.0, 0.0}, nullptr);
+    else conv_final_body<LOGM, S, NSRC, FIN, false>(A, lds, i, row, blk, WMul{0.0, 0.0}, nullptr);
+}
+
+// the kept limb multiplied by a per-call scalar first (rescale of a scalar multiple)
+template <int LOGM, int S>
+__global__ __launch_bounds__((1 << LOGM) / 16, 4) void conv_final_scalar_kernel(ConvFinalArgs A, ScalarTab Sc) {
+    __shared__ double lds[((1 << LOGM) >> 8) * V2_GS];
+    unsigned row, blk;
+    int i;
+    if (!conv_final_place(A, S, row, blk, i)) return;
+    if (is_p51(A.F.p51, i)) conv_final_body<LOGM, S, 1, 2, true>(A, lds, i, row, blk, Sc.c[i], nullptr);
+    else conv_final_body<LOGM, S, 1, 2, false>(A, lds, i, row, blk, Sc.c[i], nullptr);
+}
+
+// rotations from a shared ModUp
+template <int LOGM, int S, int NSRC>
+__global__ __launch_bounds__((1 << LOGM) / 16, 4) void conv_final_gal_kernel(ConvFinalArgs A, RowsFinalGal G) {
+    __shared__ double lds[((1 << LOGM) >> 8) * V2_GS];
+    unsigned row, blk;
+    int i;
+    if (!conv_final_place(A, S, row, blk, i)) return;
+    if (is_p51(A.F.p51, i)) conv_final_body<LOGM, S, NSRC, 3, true>(A, lds, i, row, blk, WMul{0.0, 0.0}, &G);
+    else conv_final_body<LOGM, S, NSRC, 3, false>(A, lds, i, row, blk, WMul{0.0, 0.0}, &G);
+}

@@ -66,6 +66,8 @@ struct NttV2Args {
     const WMul *tw_ninv;  // [T] inverse only: 1/N
     const WMul *tw_last;  // [T] inverse only: psi^-brev(1)/N
     const FinConst *fin;  // optional, inverse column pass: per limb slot, replaces the 1/N constants of the last stage
+    int use_fin_val;      // ... or, where the coefficients leave as doubles, one set passed by value (per-call constants)
+    FinConst fin_val;
     int logN;
     int items, items_per_z;
     P51Mask p51;
@@ -193,7 +195,8 @@ struct ColsMasks {
 
 // SMALL (forward only): the source is a polynomial with small signed coefficients, one int64 per coefficient and the same
 // for every limb (item i at (const long long *)A.src + i * src_item_stride): its residues are the values themselves
-template <bool INV, int Q, bool P51, bool SMALL = false>
+// F64 (inverse only): the canonical coefficients leave as doubles (the input of a conversion, never visible outside)
+template <bool INV, int Q, bool P51, bool SMALL = false, bool F64 = false>
 __device__ __forceinline__ void ntt_v2_cols(const NttV2Args &A, double *lds, int t, unsigned li) {
     typedef ColsGeom<Q> Geo;
     typedef ColsMasks<Q, P51> Mk;
@@ -208,7 +211,8 @@ __device__ __forceinline__ void ntt_v2_cols(const NttV2Args &A, double *lds, int
     if (INV) {
         ninv = A.tw_ninv[t];
         wlast = A.tw_last[t];
-        if (A.fin) { ninv = A.fin[li].ninv; wlast = A.fin[li].wlast; cadd = A.fin[li].cadd; }
+        if (F64 && A.use_fin_val) { ninv = A.fin_val.ninv; wlast = A.fin_val.wlast; cadd = A.fin_val.cadd; }
+        else if (A.fin) { ninv = A.fin[li].ninv; wlast = A.fin[li].wlast; cadd = A.fin[li].cadd; }
     }
     const unsigned i0 = blockIdx.z * (unsigned)A.items_per_z;
     const unsigned i1 = (i0 + A.items_per_z < (unsigned)A.items) ? i0 + A.items_per_z : (unsigned)A.items;
@@ -248,7 +252,10 @@ __device__ __forceinline__ void ntt_v2_cols(const NttV2Args &A, double *lds, int
             for (int e = 0; e < 16; e++) x[e] = lds[geo.l1(e)];
             inv_round<Mk::I2, true>(x, tw1, p, pinv, ninv, wlast);
 #pragma unroll
-            for (int e = 0; e < 16; e++) dst[geo.g1(e)] = d2u(canon(x[e] + cadd, p, pinv));
+            for (int e = 0; e < 16; e++) {
+                const double v = canon(x[e] + cadd, p, pinv);
+                dst[geo.g1(e)] = F64 ? (u64d)__double_as_longlong(v) : d2u(v);
+            }
         }
         __syncthreads();
     }
@@ -357,7 +364,7 @@ __global__ __launch_bounds__(V2_THREADS) void ntt_v2_inv_rows_gal_kernel(NttV2Ar
 }
 
 // grid: x = tile (N/4096), y = limb slot within an item, z = chunk of items
-template <bool INV, bool COLS>
+template <bool INV, bool COLS, bool F64 = false>
 __global__ __launch_bounds__(V2_THREADS) void ntt_v2_kernel(NttV2Args A) {
     __shared__ double lds[16 * V2_GS];
     unsigned item_unused, li;
@@ -369,11 +376,11 @@ __global__ __launch_bounds__(V2_THREADS) void ntt_v2_kernel(NttV2Args A) {
         else ntt_v2_rows<INV, false>(A, lds, t, li);
     } else {
         switch (A.logN) {
-            case 12: if (p51) ntt_v2_cols<INV, 0, true>(A, lds, t, li); else ntt_v2_cols<INV, 0, false>(A, lds, t, li); break;
-            case 13: if (p51) ntt_v2_cols<INV, 1, true>(A, lds, t, li); else ntt_v2_cols<INV, 1, false>(A, lds, t, li); break;
-            case 14: if (p51) ntt_v2_cols<INV, 2, true>(A, lds, t, li); else ntt_v2_cols<INV, 2, false>(A, lds, t, li); break;
-            case 15: if (p51) ntt_v2_cols<INV, 3, true>(A, lds, t, li); else ntt_v2_cols<INV, 3, false>(A, lds, t, li); break;
-            default: if (p51) ntt_v2_cols<INV, 4, true>(A, lds, t, li); else ntt_v2_cols<INV, 4, false>(A, lds, t, li); break;
+            case 12: if (p51) ntt_v2_cols<INV, 0, true, false, F64>(A, lds, t, li); else ntt_v2_cols<INV, 0, false, false, F64>(A, lds, t, li); break;
+            case 13: if (p51) ntt_v2_cols<INV, 1, true, false, F64>(A, lds, t, li); else ntt_v2_cols<INV, 1, false, false, F64>(A, lds, t, li); break;
+            case 14: if (p51) ntt_v2_cols<INV, 2, true, false, F64>(A, lds, t, li); else ntt_v2_cols<INV, 2, false, false, F64>(A, lds, t, li); break;
+            case 15: if (p51) ntt_v2_cols<INV, 3, true, false, F64>(A, lds, t, li); else ntt_v2_cols<INV, 3, false, false, F64>(A, lds, t, li); break;
+            default: if (p51) ntt_v2_cols<INV, 4, true, false, F64>(A, lds, t, li); else ntt_v2_cols<INV, 4, false, false, F64>(A, lds, t, li); break;
         }
     }
 }

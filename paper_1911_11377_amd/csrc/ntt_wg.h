@@ -1,9 +1,9 @@
-// Whole limb transforms inside one workgroup for N = 2^13 and 2^14: the limb crosses HBM once.
+// Whole limb transforms inside one workgroup for 2^12 <= N <= 2^14: the limb crosses HBM once.
 //
 // The transform is the same N1 x 256 decomposition as in ntt_v2.h, with the same butterflies, twiddles and lazy-range
 // schedule (so the same bits), but both passes run in one workgroup of N/16 threads and the intermediate between them
 // lives in LDS instead of HBM: every thread keeps 16 words in registers, and the N1 x 256 matrix sits in LDS in the
-// padded row layout of the row pass (row r, column q at r*V2_GS + (q/16)*17 + q%16: 68 KiB at N = 2^13, 136 KiB at
+// padded row layout of the row pass (row r, column q at r*V2_GS + (q/16)*17 + q%16: 34 KiB at N = 2^12, 136 KiB at
 // N = 2^14).  Each 256-thread quarter of the workgroup does the column pass of one 4096-word column tile, exchanging
 // through the tile's own columns of that matrix in place; after one workgroup barrier every row is finished by its own
 // 16 lanes exactly as in ntt_v2_rows.  Twiddles are fetched per round (they are shared by every limb of the modulus and
@@ -13,7 +13,7 @@
 
 __device__ __forceinline__ unsigned wg_pad(unsigned row, unsigned col) { return row * V2_GS + (col >> 4) * 17u + (col & 15u); }
 
-template <bool INV, int LOGN, bool P51>
+template <bool INV, int LOGN, bool P51, bool F64>
 __device__ __forceinline__ void ntt_wg_body(const NttV2Args &A, double *lds, int t, unsigned li) {
     constexpr int Q = LOGN - 12;
     typedef ColsGeom<Q> Geo;
@@ -32,7 +32,8 @@ __device__ __forceinline__ void ntt_wg_body(const NttV2Args &A, double *lds, int
     if (INV) {
         ninv = A.tw_ninv[t];
         wlast = A.tw_last[t];
-        if (A.fin) { ninv = A.fin[li].ninv; wlast = A.fin[li].wlast; cadd = A.fin[li].cadd; }
+        if (F64 && A.use_fin_val) { ninv = A.fin_val.ninv; wlast = A.fin_val.wlast; cadd = A.fin_val.cadd; }
+        else if (A.fin) { ninv = A.fin[li].ninv; wlast = A.fin[li].wlast; cadd = A.fin[li].cadd; }
     }
     const WMul unused = WMul{0.0, 0.0};
     const unsigned i0 = blockIdx.y * (unsigned)A.items_per_z;
@@ -137,7 +138,10 @@ __device__ __forceinline__ void ntt_wg_body(const NttV2Args &A, double *lds, int
                 for (int e = 0; e < 16; e++) x[e] = lds[wg_pad(geo.r + Geo::G * e, geo.c0 + geo.c)];
                 inv_round<Mk::I2, true>(x, tw1, p, pinv, ninv, wlast);
 #pragma unroll
-                for (int e = 0; e < 16; e++) dst[geo.g1(e)] = d2u(canon(x[e] + cadd, p, pinv));
+                for (int e = 0; e < 16; e++) {
+                    const double v = canon(x[e] + cadd, p, pinv);
+                    dst[geo.g1(e)] = F64 ? (u64d)__double_as_longlong(v) : d2u(v);
+                }
             }
         }
         __syncthreads();  // the matrix is free for the next item
@@ -145,14 +149,14 @@ __device__ __forceinline__ void ntt_wg_body(const NttV2Args &A, double *lds, int
 }
 
 // grid: x = limb slot within an item, y = chunk of items; block = N/16 threads; dynamic LDS: (N/256) * V2_GS doubles
-template <bool INV, int LOGN>
+template <bool INV, int LOGN, bool F64 = false>
 __global__ __launch_bounds__((1 << LOGN) / 16) void ntt_wg_kernel(NttV2Args A) {
     __shared__ double lds[((1 << LOGN) >> 8) * V2_GS];
     unsigned item_unused, li;
     const int t = resolve_limb(A.map, blockIdx.x, item_unused, li);
     if (t < 0) return;
     if (is_p51(A.p51, t))
-        ntt_wg_body<INV, LOGN, true>(A, lds, t, li);
+        ntt_wg_body<INV, LOGN, true, F64>(A, lds, t, li);
     else
-        ntt_wg_body<INV, LOGN, false>(A, lds, t, li);
+        ntt_wg_body<INV, LOGN, false, F64>(A, lds, t, li);
 }

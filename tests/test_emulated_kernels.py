@@ -257,3 +257,16 @@ def test_emulated_single_image_network(be):
     slots the input spans two ciphertexts (block matrix), with 128 one; rotations in calls of at most 5 in the first run"""
     pc.case_packed_network(be, (7, 8, 50, 2, 51, 2), seed=150, topology="single_image_tiny", max_rotations=5)
     pc.case_packed_network(be, (8, 8, 50, 2, 51, 2), seed=151, topology="single_image_tiny")
+
+
+@pytest.mark.parametrize("logN,bits", [(12, 50), (13, 51), (14, 50), (15, 51), (16, 50), (16, 51)])
+@pytest.mark.parametrize("tuned", [None, 8])
+def test_emulated_one_source_division(be, logN, bits, tuned):
+    """rescale, rescale of a scalar multiple (with a drop and an addend) on the kernel that keeps the converted limb on chip:
+    every block size, coarse blocks (tuned) and fine ones, 50- and 51-bit reduction schedules"""
+    shape = (logN, 3, bits, 0, 51, 1)
+    if tuned:
+        with be.tuned(tuned):
+            pc.case_rescale(be, shape, seed=140 + logN, batch=1 if logN > 14 else 5, levels=[3])
+    else:
+        pc.case_rescale(be, shape, seed=150 + logN, batch=1, levels=[3, 2])

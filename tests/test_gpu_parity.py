@@ -679,3 +679,11 @@ def test_edge_cases(be):
 def test_variant_entry_points_refuse_bad_arguments(be):
     announce("argument checks of the variant entry points")
     pc.case_variant_errors(be)
+
+
+@pytest.mark.parametrize("logN,bits,batch", [(12, 51, 9), (13, 50, 5), (14, 50, 2), (14, 51, 23), (15, 51, 2), (15, 50, 23), (16, 51, 5)])
+def test_one_source_division(be, logN, bits, batch):
+    """rescale and rescale of a scalar multiple with the converted limb on chip: every block size (few and many workgroups),
+    rows that do not divide evenly over the XCDs, both reduction schedules"""
+    announce("one-source division logN=%d %d-bit batch %d" % (logN, bits, batch))
+    pc.case_rescale(be, (logN, 4, bits, 0, 51, 1), seed=330 + logN, batch=batch, levels=[4, 2])
