@@ -1586,9 +1586,11 @@ extern "C" int ckksmi_conv2d_mac_rows(ckksmi_ctx *c, const uint64_t *in, const i
         unsigned long long *off64 = (unsigned long long *)wp; wp += ms.off_bytes;
         unsigned *tapoff = (unsigned *)wp; wp += ms.tapoff_bytes;
         double *wsum = (double *)wp;
-        const size_t prep = std::max(std::max(ms.afrag_bytes / 16, (size_t)ms.Kb * 64), (size_t)level * ms.Mg * MM_CH);
+        const size_t prep = std::max(ms.afrag_bytes / 16 / MM_DIG, (size_t)ms.Kb * 64);
         KL(c, CKKSMI_K_MACPREP_MFMA, 1, mac_prepare_mfma_kernel, dim3(ew_blocks(prep)), dim3(EW_THREADS), S(stream), (const long long *)w, afrag, taps,
-                      off64, tapoff, ms.SR, ms.SC, wsum, c->d_mod, level, c->logN, O, C, kh, kw, in_rows, W, ms.Kb, ms.Mg, ms.quad);
+           off64, tapoff, ms.SR, ms.SC, c->d_mod, level, c->logN, O, C, kh, kw, in_rows, W, ms.Kb, ms.Mg, ms.quad);
+        KL(c, CKKSMI_K_MACPREP_MFMA, 0, mac_wsum_kernel, dim3((unsigned)(ms.Mg * MM_CH), (unsigned)level), dim3(EW_THREADS), S(stream), (const long long *)w, wsum, c->d_mod,
+           O, C * kh * kw);
         MacMfmaArgs A;
         A.in = (const u64d *)in; A.out = (u64d *)out; A.afrag = afrag; A.taps = taps; A.off64 = off64; A.tapoff = tapoff; A.wsum = wsum; A.modc = c->d_mod;
         A.pow24 = c->d_pow24;

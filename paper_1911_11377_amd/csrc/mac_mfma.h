@@ -112,9 +112,21 @@ __host__ __device__ __forceinline__ int mm_slot_tap(int kb, int g, int t, int Kb
     return (quad && kb == Kb - 1) ? 64 * kb + t : 64 * kb + 16 * g + t;
 }
 
-// One thread per 16-byte A fragment chunk, per tap-table slot and per wsum entry.
+// w mod q in [-(q-1)/2, (q-1)/2] without an integer division (q odd, q < 2^51): the quotient is estimated in double precision
+// and the remainder taken in wrapping 64-bit arithmetic; the second step repairs the estimate where w / q does not fit 53 bits.
+__device__ __forceinline__ long long mm_balanced(long long w, long long q, double qinv) {
+    long long r = (long long)((unsigned long long)w - (unsigned long long)(long long)rint((double)w * qinv) * (unsigned long long)q);
+    r = (long long)((unsigned long long)r - (unsigned long long)(long long)rint((double)r * qinv) * (unsigned long long)q);
+    if (r > q / 2) r -= q;
+    if (r < -(q / 2)) r += q;
+    return r;
+}
+
+// A fragments (one thread per 16 taps of one channel: all seven digit chunks, so that every weight is reduced once per modulus)
+// and tap-table slots.  The weights of a 3136 -> 256 layer at 8 primes take 0.06 ms; one thread per digit chunk, with an
+// integer division per weight and the sums below made by a thread each, took 2.16 ms.
 __global__ __launch_bounds__(EW_THREADS) void mac_prepare_mfma_kernel(const long long *w, v4i *afrag, TapEnt *taps, unsigned long long *off64,
-                                                                      unsigned *tapoff, int SR, int SC, double *wsum, const ModConst *modc, int level, int logN, int O, int C,
+                                                                      unsigned *tapoff, int SR, int SC, const ModConst *modc, int level, int logN, int O, int C,
                                                                       int kh, int kw, int in_rows, int W, int Kb, int Mg, int quad) {
     const size_t idx = (size_t)blockIdx.x * EW_THREADS + threadIdx.x;
     const int K = C * kh * kw;
@@ -132,47 +144,68 @@ __global__ __launch_bounds__(EW_THREADS) void mac_prepare_mfma_kernel(const long
         off64[slot] = ((unsigned long long)rows << logN) * 8ull;
         tapoff[slot] = k < K ? (unsigned)((((k / (kh * kw)) * SR + (k / kw) % kh) * SC + k % kw) * 128) : 0u;
     }
-    if (idx < (size_t)level * Mg * MM_CH) {
-        const int i = (int)(idx / ((size_t)Mg * MM_CH)), m = (int)(idx % ((size_t)Mg * MM_CH));
-        const long long q = (long long)modc[i].p;
-        long long s = 0;  // sum of the balanced weights mod q, in (-q, q)
-        if (m < O)
-            for (int k = 0; k < K; k++) s = (s + w[(size_t)m * K + k] % q) % q;
-        if (s < 0) s += q;
-        // B * s mod q by Horner over the 7 bytes of B (all 0x80): r < q < 2^51, so 256 r + 128 s < 2^60
-        unsigned long long r = 0;
-        for (int j = 0; j < MM_DIG; j++) r = (r * 256ull + 128ull * (unsigned long long)s) % (unsigned long long)q;
-        wsum[idx] = (double)r;
-    }
-    const size_t total = (size_t)level * Kb * Mg * MM_FRAG;
+    const size_t total = (size_t)level * Kb * Mg * MM_MB * 64;
     if (idx >= total) return;
     size_t r = idx;
     const int lane = (int)(r % 64); r /= 64;
-    const int j = (int)(r % MM_DIG); r /= MM_DIG;
     const int mb = (int)(r % MM_MB); r /= MM_MB;
     const int mg = (int)(r % Mg); r /= Mg;
     const int kb = (int)(r % Kb); r /= Kb;
     const int i = (int)r;
     const long long q = (long long)modc[i].p;
+    const double qinv = modc[i].pinv;
     const int m = (mg * MM_MB + mb) * 16 + lane % 16;
     const int g = lane / 16;
     const bool qs = quad && kb == Kb - 1;
-    const int dig = qs ? j - g : j;  // quad step: fragment i0 = j holds digit i0 - g in k-group g
-    unsigned bytes[4] = {0, 0, 0, 0};
+    unsigned long long d7[16];
+#pragma unroll
     for (int t = 0; t < 16; t++) {
         const int k = mm_slot_tap(kb, g, t, Kb, quad);
-        long long bal = 0;
-        if (m < O && k < K && dig >= 0) {
-            bal = w[(size_t)m * K + k] % q;  // (-q, q)
-            if (bal > q / 2) bal -= q;
-            if (bal < -(q / 2)) bal += q;
-        }
-        const unsigned long long d7 = ((unsigned long long)bal + MM_BIAS) ^ MM_BIAS;
-        bytes[t / 4] |= (unsigned)((d7 >> (8 * (dig < 0 ? 0 : dig))) & 0xff) << (8 * (t % 4));
+        const long long bal = (m < O && k < K) ? mm_balanced(w[(size_t)m * K + k], q, qinv) : 0ll;
+        d7[t] = ((unsigned long long)bal + MM_BIAS) ^ MM_BIAS;
     }
-    v4i f;
-    f[0] = (int)bytes[0]; f[1] = (int)bytes[1]; f[2] = (int)bytes[2]; f[3] = (int)bytes[3];
-    afrag[idx] = f;
+    v4i *out = afrag + (((size_t)i * Kb + kb) * Mg + mg) * MM_FRAG + (size_t)mb * MM_DIG * 64 + lane;
+#pragma unroll
+    for (int j = 0; j < MM_DIG; j++) {
+        const int dig = qs ? j - g : j;  // quad step: fragment i0 = j holds digit i0 - g in k-group g
+        const int sh = 8 * (dig < 0 ? 0 : dig);
+        v4i f;
+#pragma unroll
+        for (int c4 = 0; c4 < 4; c4++) {
+            unsigned bytes = 0;
+#pragma unroll
+            for (int t = 0; t < 4; t++) bytes |= (unsigned)((d7[4 * c4 + t] >> sh) & 0xff) << (8 * t);
+            f[c4] = dig < 0 ? 0 : (int)bytes;
+        }
+        out[(size_t)j * 64] = f;
+    }
+}
+
+// wsum[i][m] = B * sum_tap w mod p, canonical; grid: x = channel (padded to whole groups), y = limb
+__global__ __launch_bounds__(EW_THREADS) void mac_wsum_kernel(const long long *w, double *wsum, const ModConst *modc, int O, int K) {
+    __shared__ long long part[EW_THREADS];
+    const int m = (int)blockIdx.x, i = (int)blockIdx.y, tid = (int)threadIdx.x;
+    const long long q = (long long)modc[i].p;
+    const double qinv = modc[i].pinv;
+    long long s = 0;
+    if (m < O)
+        for (int k = tid; k < K; k += EW_THREADS) s += mm_balanced(w[(size_t)m * K + k], q, qinv);  // at most 64 terms below 2^50
+    part[tid] = mm_balanced(s, q, qinv);
+    __syncthreads();
+    for (int h = EW_THREADS / 2; h > 0; h >>= 1) {
+        if (tid < h) part[tid] += part[tid + h];  // at most 256 terms below 2^50
+        __syncthreads();
+    }
+    if (tid) return;
+    s = mm_balanced(part[0], q, qinv);
+    if (s < 0) s += q;
+    // B * s mod q by Horner over the 7 bytes of B (all 0x80): r < q < 2^51, so 256 r + 128 s < 2^60
+    long long r = 0;
+    for (int j = 0; j < MM_DIG; j++) {
+        r = mm_balanced(r * 256 + 128 * s, q, qinv);
+        if (r < 0) r += q;
+    }
+    wsum[(size_t)i * gridDim.x + m] = (double)r;
 }
 
 // 4x4 byte transpose: a[t] holds digits (bytes) j0..j0+3 of tap t; out[j] = those digits of taps 0..3
