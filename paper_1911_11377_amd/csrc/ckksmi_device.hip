@@ -139,9 +139,9 @@ void launch_ntt(ckksmi_ctx *c, bool forward, const u64 *src, u64 *dst, const Lim
     V.items_per_z = (int)((items + zchunks - 1) / zchunks);
     zchunks = (unsigned)((items + V.items_per_z - 1) / V.items_per_z);
     dim3 gv2(tiles, M.per_item, zchunks);
-    // (a few limbs of 2^13 or 2^14 words keep the two passes: their tiles of 4096 words occupy more compute units, 14 us
-    // against 20 for up to 30 limbs of 2^14 words)
-    if (passes == 3 && (c->logN == 12 || ((c->logN == 13 || c->logN == 14) && limbs >= 64))) {
+    // (a few limbs of 2^14 words keep the two passes, whose tiles of 4096 words occupy more compute units: 13.7 us against 16 for
+    // 16 limbs; 8 limbs of 2^13 words: 13.1 us against 9.6)
+    if (passes == 3 && (c->logN == 12 || c->logN == 13 || (c->logN == 14 && limbs >= 64))) {
         // the whole limb in one workgroup: one trip through HBM (see ntt_wg.h); a workgroup loops over items of its limb slot
         unsigned zc = ((unsigned)c->ntt_target_wgs / 4 + M.per_item - 1) / M.per_item;
         if (zc > items) zc = (unsigned)items;

@@ -43,6 +43,7 @@ struct TensorRowsArgs {
 
 template <bool P51>
 __device__ __forceinline__ void tensor_rows_body(const TensorRowsArgs &A, double *lds, unsigned item, int i) {
+    BODY_TAG(P51);
     constexpr int I1 = P51 ? 0x2 : 0x4, I2 = P51 ? 0x1 : 0x4;
     const unsigned N = 1u << A.logN, N1 = N >> 8;
     const ModConst mc = A.modc[i];
@@ -483,6 +484,7 @@ struct RowsInnerArgs {
 template <bool P51, bool GAL = false>
 __device__ __forceinline__ void rows_inner_body(const RowsInnerArgs &A, const KeyTab &K, double *lds, double *tw1_lds, double *tw2_lds, int t,
                                                 unsigned x, const GaloisTab *gal = nullptr) {
+    BODY_TAG(P51);
     constexpr int F1 = P51 ? 0xA : 0x8, F2 = P51 ? 0x2 : 0x0;
     const unsigned N = 1u << A.logN, N1 = N >> 8;
     const double p = A.modc[t].p, pinv = A.modc[t].pinv;

@@ -17,42 +17,12 @@
 // two kernels, 0.089 now; N = 2^16 0.143 and 0.109; N = 2^14 0.114 and 0.078 (3.4 TB/s of kept limbs in and out; a device
 // copy moves 4.85).  About 105 vector instructions per word (110 at S = 2): vector ALU 0.6 busy, memory 0.7 of a copy.  With four
 // waves per SIMD a thread has 128 registers; a single spilled register set costs more than everything else here (0.16 us
-// with 44 registers spilled), hence the notes to the compiler below.  Variants that lost: 32 words per thread at two waves
+// with 44 registers spilled), hence the notes to the compiler (ntt_v2.h).  Variants that lost: 32 words per thread at two waves
 // per SIMD with the kept limb requested before the transform (0.081 - 0.099), the kept limb requested after the transform
 // (0.083 - 0.095).
 #pragma once
 #include "ks_fused.h"
 #include "ntt_wg.h"
-
-// Two instantiations of a body behind one uniform branch start with different (empty) asm statements: the compiler otherwise
-// merges their identical beginnings into the block before the branch and spills what it computed there.
-#ifdef CKKSMI_EMULATE
-#define BODY_TAG(V) ((void)0)
-#else
-#define BODY_TAG(V)                              \
-    do {                                         \
-        if (V) asm volatile("; body, 51 bits");  \
-        else asm volatile("; body, 50 bits");    \
-    } while (0)
-#endif
-
-// What the compiler has to be told about these kernels' register budget (all empty on the CPU stand-in):
-//   PIN_VALUE(x)    x is computed before the next pinned point and not sunk below later loads;
-//   scalar_base(p)  a workgroup-uniform address stays in scalar registers, so that the loads from p[thread offset] need no
-//                   64-bit vector additions each;
-//   WG_UNIFORM(v)   a workgroup-uniform value goes to a scalar register.
-#ifdef CKKSMI_EMULATE
-#define PIN_VALUE(x) ((void)0)
-#define WG_UNIFORM(v) (v)
-template <class T> __device__ __forceinline__ T *scalar_base(T *p) { return p; }
-#else
-#define PIN_VALUE(x) asm volatile("" : "+v"(x))
-#define WG_UNIFORM(v) ((unsigned)__builtin_amdgcn_readfirstlane((int)(v)))
-template <class T> __device__ __forceinline__ T *scalar_base(T *p) {
-    asm volatile("" : "+s"(p));
-    return p;
-}
-#endif
 
 struct ConvFinalArgs {
     RowsFinalArgs F;        // kept limbs, addend, output (tmpA, pre, rows_per_x unused); F.rows rows of F.nc kept limbs
@@ -86,79 +56,6 @@ __device__ __forceinline__ double conv_word(const double (&y)[NSRC], const WMul 
 #pragma unroll
     for (int a = 0; a < NSRC; a++) v += mulmod_w(y[a], Wc[a].w, Wc[a].wp, p);
     return reduce_balanced(v, p, pinv);  // |v| <= p + NSRC * 0.75p
-}
-
-// Forward transform of block `base - 2^S` of a ring of M * 2^S words (base = 1: the whole ring): x in the column layout of
-// ntt_wg.h, at most 2.7p (p < 2^50) or 1.2p (p < 2^51) in magnitude; the balanced-reduced results end in LDS, word (row g,
-// position q) at wg_pad(g, q).  Every row is finished by its own 16 lanes (a row-group sync suffices to read it).
-// `request` is called once the first row round is done: the place for memory requests whose latency the rest covers.
-template <int LOGM, bool P51, class F>
-__device__ __forceinline__ void wg_fwd_block(double (&x)[16], const double *tw, unsigned base, double *lds, double p, double pinv, F request) {
-    constexpr int Q = LOGM - 12;
-    typedef ColsGeom<Q> Geo;
-    typedef ColsMasks<Q, P51> Mk;
-    constexpr unsigned MR = (1u << LOGM) >> 8;
-    constexpr int RF1 = P51 ? 0xA : 0x8, RF2 = P51 ? 0x2 : 0x0;
-    const unsigned tid = threadIdx.x, row = tid >> 4, lo4 = tid & 15;
-    const Geo geo(tid & 255u, tid >> 8);
-    double *grp = lds + row * V2_GS;
-    {
-        double tw1[15];
-#pragma unroll
-        for (int s = 0; s < 4; s++)
-#pragma unroll
-            for (int b = 0; b < (1 << s); b++) tw1[(1 << s) - 1 + b] = tw[(base << s) + b];
-        fwd_round<Mk::F1>(x, tw1, p, pinv);
-    }
-    double tw1[15], tw2[15];
-    if (Q > 0) {
-#pragma unroll
-        for (int s = 0; s < 4; s++)
-#pragma unroll
-            for (int b = 0; b < (1 << s); b++) {
-                if (s >= 4 - Q) {
-                    const int u = s - (4 - Q);
-                    tw2[(1 << s) - 1 + b] = tw[((16u * base + geo.a) << u) + (b & ((1 << u) - 1))];
-                } else {
-                    tw2[(1 << s) - 1 + b] = 0.0;
-                }
-            }
-#pragma unroll
-        for (int e = 0; e < 16; e++) lds[wg_pad(geo.r + Geo::G * e, geo.c0 + geo.c)] = x[e];
-        __syncthreads();
-#pragma unroll
-        for (int i = 0; i < 16; i++) x[i] = lds[wg_pad(Geo::G * geo.a + (i % Geo::G), geo.c0 + geo.l16 + 16 * (i / Geo::G))];
-        fwd_stages<Geo::S0, Mk::F2>(x, tw2, p, pinv);
-#pragma unroll
-        for (int i = 0; i < 16; i++)
-            lds[wg_pad(Geo::G * geo.a + (i % Geo::G), geo.c0 + geo.l16 + 16 * (i / Geo::G))] = reduce_balanced(x[i], p, pinv);
-    } else {
-#pragma unroll
-        for (int e = 0; e < 16; e++) lds[wg_pad(e, geo.c0 + geo.c)] = x[e];  // the first round ends reduced
-    }
-    const unsigned base1 = base * MR + row;
-#pragma unroll
-    for (int s = 0; s < 4; s++)
-#pragma unroll
-        for (int b = 0; b < (1 << s); b++) tw1[(1 << s) - 1 + b] = tw[(base1 << s) + b];
-    __syncthreads();
-#pragma unroll
-    for (int e = 0; e < 16; e++) x[e] = grp[e * 17 + lo4];
-    fwd_round<RF1>(x, tw1, p, pinv);
-#pragma unroll
-    for (int s = 0; s < 4; s++)
-#pragma unroll
-        for (int b = 0; b < (1 << s); b++) tw2[(1 << s) - 1 + b] = tw[((16u * base1 + lo4) << s) + b];
-#pragma unroll
-    for (int e = 0; e < 16; e++) grp[e * 17 + lo4] = x[e];
-    request();
-    ROW_GROUP_SYNC();
-#pragma unroll
-    for (int e = 0; e < 16; e++) x[e] = grp[lo4 * 17 + e];
-    fwd_round<RF2>(x, tw2, p, pinv);
-#pragma unroll
-    for (int e = 0; e < 16; e++) grp[lo4 * 17 + e] = reduce_balanced(x[e], p, pinv);
-    ROW_GROUP_SYNC();
 }
 
 // FIN 0: out = (x - r) * Binv;  1: out = x - r * Binv (x holds x * Binv + addend);  2: out = (x * xmv - r) * Binv (+ addend);

@@ -34,6 +34,36 @@
 #else
 #define NTT_SCHED_FENCE() __builtin_amdgcn_sched_barrier(0)
 #endif
+// Two instantiations of a body behind one uniform branch start with different (empty) asm statements: the compiler otherwise
+// merges their identical beginnings into the block before the branch and spills what it computed there.
+#ifdef CKKSMI_EMULATE
+#define BODY_TAG(V) ((void)0)
+#else
+#define BODY_TAG(V)                              \
+    do {                                         \
+        if (V) asm volatile("; body, 51 bits");  \
+        else asm volatile("; body, 50 bits");    \
+    } while (0)
+#endif
+
+// What the compiler has to be told to stay within a kernel's registers (all empty on the CPU stand-in):
+//   PIN_VALUE(x)    x is computed before the next pinned point and not sunk below later loads;
+//   scalar_base(p)  a workgroup-uniform address stays in scalar registers, so that the loads from p[thread offset] need no
+//                   64-bit vector additions each;
+//   WG_UNIFORM(v)   a workgroup-uniform value goes to a scalar register.
+#ifdef CKKSMI_EMULATE
+#define PIN_VALUE(x) ((void)0)
+#define WG_UNIFORM(v) (v)
+template <class T> __device__ __forceinline__ T *scalar_base(T *p) { return p; }
+#else
+#define PIN_VALUE(x) asm volatile("" : "+v"(x))
+#define WG_UNIFORM(v) ((unsigned)__builtin_amdgcn_readfirstlane((int)(v)))
+template <class T> __device__ __forceinline__ T *scalar_base(T *p) {
+    asm volatile("" : "+s"(p));
+    return p;
+}
+#endif
+
 #define V2_GS 272  // doubles per padded 16x17 group in LDS (row pass)
 
 // Row pass: the 16 lanes that work on one row of 256 words exchange their words through that row's own LDS group and

@@ -7,25 +7,102 @@
 // N = 2^14).  Each 256-thread quarter of the workgroup does the column pass of one 4096-word column tile, exchanging
 // through the tile's own columns of that matrix in place; after one workgroup barrier every row is finished by its own
 // 16 lanes exactly as in ntt_v2_rows.  Twiddles are fetched per round (they are shared by every limb of the modulus and
-// stay in L2) instead of being held across items: a thread's registers hold one round's set at a time.
+// stay in L2) instead of being held across items: a thread's registers hold one round's set at a time, which keeps the
+// 1024-thread size within its 128 registers (with both rounds' twiddles requested early 21 forward and 34 inverse registers
+// spilled).  4096 limbs, forward / inverse: N = 2^12 3.7 / 3.7 TB/s (two passes through HBM: 2.7 / 2.7), 2^13 3.4 / 3.9, 2^14
+// 3.2 / 3.4; a device copy moves 4.85.
 #pragma once
 #include "ntt_v2.h"
 
 __device__ __forceinline__ unsigned wg_pad(unsigned row, unsigned col) { return row * V2_GS + (col >> 4) * 17u + (col & 15u); }
 
+// Forward transform of block `base - 2^S` of a ring of M * 2^S words (base = 1: the whole ring): x in the column layout (word
+// (geo.r + G*e, geo.c0 + geo.c)), at most 2.7p (p < 2^50) or 1.2p (p < 2^51) in magnitude; the balanced-reduced results end in LDS, word (row g,
+// position q) at wg_pad(g, q).  Every row is finished by its own 16 lanes (a row-group sync suffices to read it).
+// `request` is called once the first row round is done: the place for memory requests whose latency the rest covers.
+template <int LOGM, bool P51, class F>
+__device__ __forceinline__ void wg_fwd_block(double (&x)[16], const double *tw, unsigned base, double *lds, double p, double pinv, F request) {
+    constexpr int Q = LOGM - 12;
+    typedef ColsGeom<Q> Geo;
+    typedef ColsMasks<Q, P51> Mk;
+    constexpr unsigned MR = (1u << LOGM) >> 8;
+    constexpr int RF1 = P51 ? 0xA : 0x8, RF2 = P51 ? 0x2 : 0x0;
+    const unsigned tid = threadIdx.x, row = tid >> 4, lo4 = tid & 15;
+    const Geo geo(tid & 255u, tid >> 8);
+    double *grp = lds + row * V2_GS;
+    {
+        double tw1[15];
+#pragma unroll
+        for (int s = 0; s < 4; s++)
+#pragma unroll
+            for (int b = 0; b < (1 << s); b++) tw1[(1 << s) - 1 + b] = tw[(base << s) + b];
+        fwd_round<Mk::F1>(x, tw1, p, pinv);
+    }
+    double tw1[15], tw2[15];
+    if (Q > 0) {
+#pragma unroll
+        for (int s = 0; s < 4; s++)
+#pragma unroll
+            for (int b = 0; b < (1 << s); b++) {
+                if (s >= 4 - Q) {
+                    const int u = s - (4 - Q);
+                    tw2[(1 << s) - 1 + b] = tw[((16u * base + geo.a) << u) + (b & ((1 << u) - 1))];
+                } else {
+                    tw2[(1 << s) - 1 + b] = 0.0;
+                }
+            }
+#pragma unroll
+        for (int e = 0; e < 16; e++) lds[wg_pad(geo.r + Geo::G * e, geo.c0 + geo.c)] = x[e];
+        __syncthreads();
+#pragma unroll
+        for (int i = 0; i < 16; i++) x[i] = lds[wg_pad(Geo::G * geo.a + (i % Geo::G), geo.c0 + geo.l16 + 16 * (i / Geo::G))];
+        fwd_stages<Geo::S0, Mk::F2>(x, tw2, p, pinv);
+#pragma unroll
+        for (int i = 0; i < 16; i++)
+            lds[wg_pad(Geo::G * geo.a + (i % Geo::G), geo.c0 + geo.l16 + 16 * (i / Geo::G))] = reduce_balanced(x[i], p, pinv);
+    } else {
+#pragma unroll
+        for (int e = 0; e < 16; e++) lds[wg_pad(e, geo.c0 + geo.c)] = x[e];  // the first round ends reduced
+    }
+    const unsigned base1 = base * MR + row;
+#pragma unroll
+    for (int s = 0; s < 4; s++)
+#pragma unroll
+        for (int b = 0; b < (1 << s); b++) tw1[(1 << s) - 1 + b] = tw[(base1 << s) + b];
+    __syncthreads();
+#pragma unroll
+    for (int e = 0; e < 16; e++) x[e] = grp[e * 17 + lo4];
+    fwd_round<RF1>(x, tw1, p, pinv);
+#pragma unroll
+    for (int s = 0; s < 4; s++)
+#pragma unroll
+        for (int b = 0; b < (1 << s); b++) tw2[(1 << s) - 1 + b] = tw[((16u * base1 + lo4) << s) + b];
+#pragma unroll
+    for (int e = 0; e < 16; e++) grp[e * 17 + lo4] = x[e];
+    request();
+    ROW_GROUP_SYNC();
+#pragma unroll
+    for (int e = 0; e < 16; e++) x[e] = grp[lo4 * 17 + e];
+    fwd_round<RF2>(x, tw2, p, pinv);
+#pragma unroll
+    for (int e = 0; e < 16; e++) grp[lo4 * 17 + e] = reduce_balanced(x[e], p, pinv);
+    ROW_GROUP_SYNC();
+}
+
 template <bool INV, int LOGN, bool P51, bool F64>
 __device__ __forceinline__ void ntt_wg_body(const NttV2Args &A, double *lds, int t, unsigned li) {
+    BODY_TAG(P51);
     constexpr int Q = LOGN - 12;
     typedef ColsGeom<Q> Geo;
     typedef ColsMasks<Q, P51> Mk;
     constexpr unsigned N = 1u << LOGN, N1 = N >> 8;
-    constexpr int RF1 = P51 ? 0xA : 0x8, RF2 = P51 ? 0x2 : 0x0;   // row pass, forward (as ntt_v2_rows)
-    constexpr int RI1 = P51 ? 0x2 : 0x4, RI2 = P51 ? 0x1 : 0x4;   // row pass, inverse
+    constexpr int RI1 = P51 ? 0x2 : 0x4, RI2 = P51 ? 0x1 : 0x4;   // row pass, inverse (as ntt_v2_rows)
     const double p = A.modc[t].p, pinv = A.modc[t].pinv;
     const double *tw = A.tw + (size_t)t * N;
     const unsigned tid = threadIdx.x;
     const Geo geo(tid & 255u, tid >> 8);          // column pass: this quarter's column tile
     const unsigned row = tid >> 4, lo4 = tid & 15;  // row pass: one row per 16 lanes
+    const unsigned voff = geo.r * 256u + geo.c0 + geo.c, pr = row_pair_index(row, lo4, 0);
     double *grp = lds + row * V2_GS;
     WMul ninv = WMul{0.0, 0.0}, wlast = WMul{0.0, 0.0};
     double cadd = 0.0;
@@ -43,76 +120,50 @@ __device__ __forceinline__ void ntt_wg_body(const NttV2Args &A, double *lds, int
         u64d *dst = A.dst + (size_t)it * A.map.dst_item_stride + (size_t)li * N;
         double x[16];
         if (!INV) {
-            // ---- column pass, from HBM into the LDS matrix
-            {
-                u64d raw[16];
+            u64d raw[16];
 #pragma unroll
-                for (int e = 0; e < 16; e++) raw[e] = src[geo.g1(e)];
-                {
-                    double tw1[15];
+            for (int e = 0; e < 16; e++) raw[e] = scalar_base(src + Geo::G * 256u * e)[voff];
+            NTT_SCHED_FENCE();
 #pragma unroll
-                    for (int i = 0; i < 15; i++) tw1[i] = tw[1 + i];
-                    NTT_SCHED_FENCE();
+            for (int e = 0; e < 16; e++) x[e] = u2d(raw[e]);
+            wg_fwd_block<LOGN, P51>(x, tw, 1u, lds, p, pinv, []() {});
+            // canonical words out in word pairs: 16 bytes per lane, 256 contiguous bytes per row and store
 #pragma unroll
-                    for (int e = 0; e < 16; e++) x[e] = u2d(raw[e]);
-                    fwd_round<Mk::F1>(x, tw1, p, pinv);
-                }
-                // the second round's twiddles are requested here: their latency overlaps the exchange
-                double tw1u[15], tw2u[15];
-                load_cols_twiddles<Q>(tw, geo.a, tw1u, tw2u);
-#pragma unroll
-                for (int e = 0; e < 16; e++) lds[wg_pad(geo.r + Geo::G * e, geo.c0 + geo.c)] = x[e];
-                __syncthreads();
-#pragma unroll
-                for (int i = 0; i < 16; i++) x[i] = lds[wg_pad(Geo::G * geo.a + (i % Geo::G), geo.c0 + geo.l16 + 16 * (i / Geo::G))];
-                fwd_stages<Geo::S0, Mk::F2>(x, tw2u, p, pinv);
-#pragma unroll
-                for (int i = 0; i < 16; i++)
-                    lds[wg_pad(Geo::G * geo.a + (i % Geo::G), geo.c0 + geo.l16 + 16 * (i / Geo::G))] = reduce_balanced(x[i], p, pinv);
-            }
-            __syncthreads();
-            // ---- row pass, from the LDS matrix to HBM
-            {
-                double tw1[15], tw2[15];
-                load_twiddles(tw, N1 + row, lo4, tw1, tw2);
-#pragma unroll
-                for (int e = 0; e < 16; e++) x[e] = grp[e * 17 + lo4];
-                fwd_round<RF1>(x, tw1, p, pinv);
-#pragma unroll
-                for (int e = 0; e < 16; e++) grp[e * 17 + lo4] = x[e];
-                ROW_GROUP_SYNC();
-#pragma unroll
-                for (int e = 0; e < 16; e++) x[e] = grp[lo4 * 17 + e];
-                fwd_round<RF2>(x, tw2, p, pinv);
-#pragma unroll
-                for (int e = 0; e < 16; e++) grp[lo4 * 17 + e] = canon(x[e], p, pinv);
-                ROW_GROUP_SYNC();
-                // canonical words out in word pairs: 16 bytes per lane, 256 contiguous bytes per row and store
-#pragma unroll
-                for (int s = 0; s < 8; s++) {
-                    const double *rr = grp + row_pair_lds(lo4, s);
-                    ((ulonglong2 *)dst)[row_pair_index(row, lo4, s)] = make_ulonglong2(d2u(rr[0]), d2u(rr[1]));
-                }
+            for (int s = 0; s < 8; s++) {
+                const double *rr = grp + row_pair_lds(lo4, s);
+                ((ulonglong2 *)dst + 16 * s)[pr] = make_ulonglong2(d2u(canon_small(rr[0], p)), d2u(canon_small(rr[1], p)));
             }
         } else {
             // ---- row pass, from HBM into the LDS matrix
             {
-                ulonglong2 raw[8];
-#pragma unroll
-                for (int s = 0; s < 8; s++) raw[s] = ((const ulonglong2 *)src)[row_pair_index(row, lo4, s)];
                 double tw1[15], tw2[15];
-                load_twiddles(tw, N1 + row, lo4, tw1, tw2);
-                NTT_SCHED_FENCE();
+                const unsigned base1 = N1 + row;
+                {
+                    ulonglong2 raw[8];
 #pragma unroll
-                for (int s = 0; s < 8; s++) {
-                    double *rr = grp + row_pair_lds(lo4, s);
-                    rr[0] = u2d(raw[s].x);
-                    rr[1] = u2d(raw[s].y);
+                    for (int s = 0; s < 8; s++) raw[s] = ((const ulonglong2 *)src + 16 * s)[pr];
+#pragma unroll
+                    for (int s = 0; s < 4; s++)
+#pragma unroll
+                        for (int b = 0; b < (1 << s); b++) tw2[(1 << s) - 1 + b] = tw[((16u * base1 + lo4) << s) + b];
+                    NTT_SCHED_FENCE();
+#pragma unroll
+                    for (int s = 0; s < 8; s++) {
+                        double *rr = grp + row_pair_lds(lo4, s);
+                        rr[0] = u2d(raw[s].x);
+                        rr[1] = u2d(raw[s].y);
+                    }
                 }
                 ROW_GROUP_SYNC();
 #pragma unroll
                 for (int e = 0; e < 16; e++) x[e] = grp[lo4 * 17 + e];
                 inv_round<RI1, false>(x, tw2, p, pinv, unused, unused);
+#pragma unroll
+                for (int e = 0; e < 16; e++) PIN_VALUE(x[e]);  // the first round is done with its twiddles before the second's arrive
+#pragma unroll
+                for (int s = 0; s < 4; s++)
+#pragma unroll
+                    for (int b = 0; b < (1 << s); b++) tw1[(1 << s) - 1 + b] = tw[(base1 << s) + b];
 #pragma unroll
                 for (int e = 0; e < 16; e++) grp[lo4 * 17 + e] = x[e];
                 ROW_GROUP_SYNC();
@@ -120,27 +171,34 @@ __device__ __forceinline__ void ntt_wg_body(const NttV2Args &A, double *lds, int
                 for (int e = 0; e < 16; e++) x[e] = grp[e * 17 + lo4];
                 inv_round<RI2, false>(x, tw1, p, pinv, unused, unused);
 #pragma unroll
-                for (int e = 0; e < 16; e++) grp[e * 17 + lo4] = reduce_balanced(x[e], p, pinv);
+                for (int e = 0; e < 16; e++) {
+                    x[e] = reduce_balanced(x[e], p, pinv);
+                    PIN_VALUE(x[e]);
+                }
+#pragma unroll
+                for (int e = 0; e < 16; e++) grp[e * 17 + lo4] = x[e];
             }
-            __syncthreads();
             // ---- column pass, from the LDS matrix to HBM
             {
                 double tw1[15], tw2u[15];
                 load_cols_twiddles<Q>(tw, geo.a, tw1, tw2u);
-#pragma unroll
-                for (int i = 0; i < 16; i++) x[i] = lds[wg_pad(Geo::G * geo.a + (i % Geo::G), geo.c0 + geo.l16 + 16 * (i / Geo::G))];
-                inv_stages<Geo::S0, Mk::I1, false>(x, tw2u, p, pinv, ninv, wlast);
-                reduce16(x, p, pinv);
-#pragma unroll
-                for (int i = 0; i < 16; i++) lds[wg_pad(Geo::G * geo.a + (i % Geo::G), geo.c0 + geo.l16 + 16 * (i / Geo::G))] = x[i];
                 __syncthreads();
+                if (Q > 0) {
+#pragma unroll
+                    for (int i = 0; i < 16; i++) x[i] = lds[wg_pad(Geo::G * geo.a + (i % Geo::G), geo.c0 + geo.l16 + 16 * (i / Geo::G))];
+                    inv_stages<Geo::S0, Mk::I1, false>(x, tw2u, p, pinv, ninv, wlast);
+                    reduce16(x, p, pinv);
+#pragma unroll
+                    for (int i = 0; i < 16; i++) lds[wg_pad(Geo::G * geo.a + (i % Geo::G), geo.c0 + geo.l16 + 16 * (i / Geo::G))] = x[i];
+                    __syncthreads();
+                }
 #pragma unroll
                 for (int e = 0; e < 16; e++) x[e] = lds[wg_pad(geo.r + Geo::G * e, geo.c0 + geo.c)];
                 inv_round<Mk::I2, true>(x, tw1, p, pinv, ninv, wlast);
 #pragma unroll
                 for (int e = 0; e < 16; e++) {
                     const double v = canon(x[e] + cadd, p, pinv);
-                    dst[geo.g1(e)] = F64 ? (u64d)__double_as_longlong(v) : d2u(v);
+                    scalar_base(dst + Geo::G * 256u * e)[voff] = F64 ? (u64d)__double_as_longlong(v) : d2u(v);
                 }
             }
         }
