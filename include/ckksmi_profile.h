@@ -52,7 +52,8 @@ extern "C" {
 #define CKKSMI_K_MAC_MFMA_RES 29    /* the same for layers of few taps: weight digits resident in LDS, several positions per workgroup */
 #define CKKSMI_K_MAC_MFMA_STRIP 30  /* ... and a narrow window: four neighbouring positions share a strip of the image staged in LDS */
 #define CKKSMI_K_CONV_FINAL 31    /* conversion, whole forward transform and last step of a DivRound in one workgroup per kept limb (block) */
-#define CKKSMI_K_COUNT 32
+#define CKKSMI_K_INNER_WG 32      /* ModUp's conversion, whole forward transform and inner product in one workgroup per extended limb (block) */
+#define CKKSMI_K_COUNT 33
 int ckksmi_profile_enable(ckksmi_ctx *ctx, int on);
 int ckksmi_profile_read(ckksmi_ctx *ctx, int kernel_class, double *total_ms, long long *launches, double *units);
 /* name of the kernel that class runs as in this context (the transforms have size-specific kernels) */

@@ -17,6 +17,7 @@
 #include "ks_fused.h"
 #include "ntt_wg.h"
 #include "ks_wg.h"
+#include "ks_inner_wg.h"
 #include "encode_device.h"
 #include "mac_mfma.h"
 
@@ -102,10 +103,11 @@ LimbMap table_map(const int *index, int n_limbs, size_t src_stride, size_t dst_s
 // transform `items` groups of map.per_item limbs; forward: coefficient -> evaluation
 // passes: 3 = whole transform, 1 = strided (column) pass only, 2 = contiguous (row) pass only
 // out_f64 (inverse, register-tiled sizes): the coefficients leave as doubles, with the last-stage constants fin or *fin_val
-// gal (inverse row pass of the register-tiled sizes only): item i's input is read through the automorphism X -> X^(gal->g[i])
+// ten (inverse, whole limbs, N <= 2^13): the input is the third tensor component of these operands (src unused)
+// gal (inverse row pass of the register-tiled sizes, or whole limbs with out_f64, N <= 2^13): item i's input is read through the automorphism X -> X^(gal->g[i])
 void launch_ntt(ckksmi_ctx *c, bool forward, const u64 *src, u64 *dst, const LimbMap &M, size_t items, hipStream_t st,
                 const FinConst *fin = nullptr, int passes = 3, const GaloisTab *gal = nullptr, bool out_f64 = false,
-                const FinConst *fin_val = nullptr) {
+                const FinConst *fin_val = nullptr, const TensorSrc *ten = nullptr) {
     if (items == 0 || M.per_item == 0) return;
     NttArgs A;
     A.src = (const u64d *)src;
@@ -149,11 +151,13 @@ void launch_ntt(ckksmi_ctx *c, bool forward, const u64 *src, u64 *dst, const Lim
         V.items_per_z = (int)((items + zc - 1) / zc);
         zc = (unsigned)((items + V.items_per_z - 1) / V.items_per_z);
         const dim3 gw(M.per_item, zc), bw((unsigned)(N / 16));
-#define NTT_WG_CASE(LN)                                                                                       \
-    case LN:                                                                                                  \
-        if (forward) KL(c, CKKSMI_K_NTT_LDS, limbs_work, (ntt_wg_kernel<false, LN>), gw, bw, st, V);          \
+#define NTT_WG_CASE(LN)                                                                                        \
+    case LN:                                                                                                   \
+        if (forward) KL(c, CKKSMI_K_NTT_LDS, limbs_work, (ntt_wg_kernel<false, LN>), gw, bw, st, V);           \
+        else if (LN < 14 && ten) KL(c, CKKSMI_K_TENSOR_ROWS, limbs_work, tensor_wg_kernel<LN < 14 ? LN : 13>, gw, bw, st, V, *ten); \
+        else if (LN < 14 && gal) KL(c, CKKSMI_K_NTT_LDS, limbs_work, ntt_wg_inv_gal_kernel<LN < 14 ? LN : 13>, gw, bw, st, V, *gal); \
         else if (out_f64) KL(c, CKKSMI_K_NTT_LDS, limbs_work, (ntt_wg_kernel<true, LN, true>), gw, bw, st, V); \
-        else KL(c, CKKSMI_K_NTT_LDS, limbs_work, (ntt_wg_kernel<true, LN>), gw, bw, st, V);                   \
+        else KL(c, CKKSMI_K_NTT_LDS, limbs_work, (ntt_wg_kernel<true, LN>), gw, bw, st, V);                    \
         break;
         switch (c->logN) {
             NTT_WG_CASE(12) NTT_WG_CASE(13) NTT_WG_CASE(14)
@@ -462,12 +466,50 @@ void merged_division(ckksmi_ctx *c, u64 *acc, const u64 *addend, size_t add_item
 // limb joins the special limbs as a conversion source, so one more than k sources must fit.
 inline bool one_conversion_tail_ok(const ckksmi_ctx *c) { return c->fused && c->d_fin_tail != nullptr; }
 
+// third tensor component + its inverse row pass into ymid (see tensor_rows_kernel); register-tiled sizes only
+void launch_tensor_rows(ckksmi_ctx *c, const u64 *a, const u64 *b, u64 *ymid, int level, int items, hipStream_t st, int terms = 1) {
+    TensorRowsArgs A;
+    A.terms = terms;
+    A.a = (const u64d *)a; A.b = (const u64d *)b; A.ymid = (u64d *)ymid; A.modc = c->d_mod; A.tw_inv = c->d_tww_inv;
+    A.logN = c->logN; A.level = level; A.p51 = c->p51mask;
+    KL(c, CKKSMI_K_TENSOR_ROWS, (double)items * level, tensor_rows_kernel, dim3((unsigned)(c->N / 4096), level, items), dim3(V2_THREADS), st, A);
+}
+
+// Does a key switch of this shape keep its lifted limbs on chip (ks_inner_wg.h)?  One workgroup walks all digits of a limb
+// (block): below 128 of them (N = 2^12) or 512 the chip is not filled and the two-kernel form, which spreads the digits over
+// workgroups, is faster (8 primes, N = 2^12: 36 workgroups 0.94 x, 144 1.02 - 1.06 x, 576 1.15 x, 2304 1.18 x).  N = 2^13 is cut into two
+// blocks, whose workgroups both convert every source word: with one source per digit that still wins (576 workgroups
+// 1.02 - 1.07 x, 4608 1.10 x), with three it does not (24 primes, 64 items: 0.92 x).  At N = 2^14 (two blocks of 2^13 words at one workgroup per
+// compute unit, or four of 2^12) it takes 1.65 - 1.72 ms for 256 items of 8 limbs, the two kernels 1.70 with a cheaper transform in front.
+inline bool inner_wg_ok(const ckksmi_ctx *c, int level, int items) {
+    const size_t wgs = (size_t)items * (level + c->k), fill = (size_t)c->ntt_target_wgs / 64;  // 128
+    return (c->logN == 12 && wgs >= fill) || (c->logN == 13 && c->alpha == 1 && 2 * wgs >= 4 * fill);
+}
+
+void launch_inner_wg(ckksmi_ctx *c, const RowsInnerArgs &R, const KeyTab &K, const u64 *y, int items, hipStream_t st, const GaloisTab *gal) {
+    InnerWgArgs A;
+    A.R = R; A.y = (const double *)y; A.cc = c->d_modup_c; A.items = items; A.items_x = std::min(8, items);
+    const int S = c->logN - 12;
+    const dim3 grid((unsigned)(((items + A.items_x - 1) / A.items_x * A.items_x) << S), (unsigned)R.E), block(256);
+    const double units = (double)items * R.E;
+#define INNER_WG_CASE(LN, SS, NS)                                                                                      \
+    case LN * 8 + NS:                                                                                                  \
+        if (gal) KL(c, CKKSMI_K_INNER_WG, units, (inner_wg_gal_kernel<LN - SS, SS, NS>), grid, block, st, A, K, *gal); \
+        else KL(c, CKKSMI_K_INNER_WG, units, (inner_wg_kernel<LN - SS, SS, NS>), grid, block, st, A, K);               \
+        break;
+    switch (c->logN * 8 + c->alpha) {
+        INNER_WG_CASE(12, 0, 1) INNER_WG_CASE(12, 0, 2) INNER_WG_CASE(12, 0, 3) INNER_WG_CASE(12, 0, 4)
+        INNER_WG_CASE(13, 1, 1)
+        default: break;
+    }
+#undef INNER_WG_CASE
+}
+
 // Key switch on the register-tiled kernels (2^12 <= N <= 2^16).
 // tail: the key switch is followed by a rescale of (result + addend), both components have an addend, and `out` receives
 // the rescaled ciphertexts [items][2][level-1][N] (needs one_conversion_tail_ok).
 // ta != nullptr (the composite multiply; d_eval and addend unused): the polynomial switched is the third tensor component
-// of the operands ta, tb ([items][terms][2][level][N]), whose inverse row pass the tensor kernel already left at the start of
-// the workspace, and the other two components are the addends; the fused inner product forms all three from the operands.
+// of the operands ta, tb ([items][terms][2][level][N]), formed on the way into its inverse transform, and the other two components are the addends; the fused inner product forms all three from the operands.
 void ks_core_fused(ckksmi_ctx *c, const u64 *d_eval, size_t d_stride, const KeyTab &K, int items, int level, const u64 *addend,
                    size_t add_item_stride, size_t add_comp_stride, int add_both, u64 *out, u64 *ws, hipStream_t st,
                    bool tail = false, bool merged = false, const HoistPlan *hoist = nullptr, const u64 *ta = nullptr, const u64 *tb = nullptr,
@@ -481,11 +523,21 @@ void ks_core_fused(ckksmi_ctx *c, const u64 *d_eval, size_t d_stride, const KeyT
     u64 *tmp = acc + (size_t)items * R * 2 * E * N;
     int idx[CKKSMI_MAX_MODULI];
     for (int i = 0; i < level; i++) idx[i] = i;
-    // y_i = d_i * qhat_i^-1 comes straight out of the inverse transform (row pass here, column pass inside the conversion
-    // kernel); the conversion rides on the column pass of the forward transform of its results
+    // y_i = d_i * qhat_i^-1 comes straight out of the inverse transform
     const FinConst *fin_up = c->d_fin_modup + (size_t)level * c->n_q;
-    if (!ta) launch_ntt(c, false, d_eval, ymid, table_map(idx, level, d_stride, (size_t)level * N), items, st, fin_up, 2, gal);
-    launch_modup_cols(c, 0, ymid, 0, dtA, items, level, 0, nullptr, (double)items * (beta * E - level), st, fin_up);
+    const bool on_chip = !hoist && inner_wg_ok(c, level, items);
+    if (on_chip) {
+        // whole inverse transform; the lifted limbs never leave the inner product's workgroups
+        const TensorSrc T = {(const u64d *)ta, (const u64d *)tb, level, terms};
+        launch_ntt(c, false, ta ? ymid : d_eval, ymid, table_map(idx, level, ta ? (size_t)level * N : d_stride, (size_t)level * N), items, st, fin_up, 3, gal,
+                   true, nullptr, ta ? &T : nullptr);
+    } else {
+        // row pass here (with ta: in the tensor kernel), column pass inside the conversion kernel; the conversion rides on the
+        // column pass of the forward transform of its results
+        if (ta) launch_tensor_rows(c, ta, tb, ymid, level, items, st, terms);
+        else launch_ntt(c, false, d_eval, ymid, table_map(idx, level, d_stride, (size_t)level * N), items, st, fin_up, 2, gal);
+        launch_modup_cols(c, 0, ymid, 0, dtA, items, level, 0, nullptr, (double)items * (beta * E - level), st, fin_up);
+    }
     int sidx[CKKSMI_MAX_SPECIAL];
     for (int m = 0; m < c->k; m++) sidx[m] = c->n_q + m;
     u64 *specials = acc + (size_t)level * N;
@@ -517,7 +569,8 @@ void ks_core_fused(ckksmi_ctx *c, const u64 *d_eval, size_t d_stride, const KeyT
     RI.Pinv = c->divround[0].Binv;
     RI.addend = (const u64d *)addend; RI.add_item_stride = add_item_stride; RI.add_comp_stride = add_comp_stride;
     RI.ta = (const u64d *)ta; RI.tb = (const u64d *)tb; RI.terms = terms; RI.keep_acc = merged ? 1 : 0; RI.Pmod = c->d_pmod;
-    if (gal) KL(c, CKKSMI_K_ROWS_INNER, (double)items * E, rows_inner_gal_kernel, dim3(RI.kt * items, tiles / RI.kt, E), dim3(V2_THREADS), st, RI, K, *gal);
+    if (on_chip) launch_inner_wg(c, RI, K, ymid, items, st, gal);
+    else if (gal) KL(c, CKKSMI_K_ROWS_INNER, (double)items * E, rows_inner_gal_kernel, dim3(RI.kt * items, tiles / RI.kt, E), dim3(V2_THREADS), st, RI, K, *gal);
     else KL(c, CKKSMI_K_ROWS_INNER, (double)items * E, rows_inner_kernel, dim3(RI.kt * items, tiles / RI.kt, E), dim3(V2_THREADS), st, RI, K);
     if (merged) {
         merged_division(c, acc, ta ? nullptr : addend, add_item_stride, add_comp_stride, out, tmp, items, level, st);
@@ -700,15 +753,6 @@ void launch_tensor(ckksmi_ctx *c, const u64 *a, const u64 *b, u64 *d, int level,
     const size_t total = (size_t)items * level * c->N / 2;  // word pairs
     KL(c, CKKSMI_K_TENSOR, (double)items * level * terms, tensor_kernel, dim3(ew_blocks(total)), dim3(EW_THREADS), st, (const u64d *)a, (const u64d *)b, (u64d *)d, c->d_mod,
                   c->logN, level, total, terms);
-}
-
-// third tensor component + its inverse row pass into ymid (see tensor_rows_kernel); register-tiled sizes only
-void launch_tensor_rows(ckksmi_ctx *c, const u64 *a, const u64 *b, u64 *ymid, int level, int items, hipStream_t st, int terms = 1) {
-    TensorRowsArgs A;
-    A.terms = terms;
-    A.a = (const u64d *)a; A.b = (const u64d *)b; A.ymid = (u64d *)ymid; A.modc = c->d_mod; A.tw_inv = c->d_tww_inv;
-    A.logN = c->logN; A.level = level; A.p51 = c->p51mask;
-    KL(c, CKKSMI_K_TENSOR_ROWS, (double)items * level, tensor_rows_kernel, dim3((unsigned)(c->N / 4096), level, items), dim3(V2_THREADS), st, A);
 }
 
 int sweep_items(size_t ws_bytes, size_t words_per_item, int batch) {
@@ -1214,8 +1258,6 @@ static int hmul_relin_rescale_impl(ckksmi_ctx *c, const uint64_t *a, const uint6
         u64 *d = (u64 *)ws;                              // [items][3][level][N]
         u64 *r = d + (size_t)items * 3 * level * N;      // [items][2][level][N]
         u64 *rest = r + (size_t)items * 2 * level * N;
-        // register-tiled sizes: the tensor kernel takes d2 through the inverse row pass on the way (its output lands where
-        // the key switch expects it: the start of its workspace)
         const size_t in0 = (size_t)b0 * terms * 2 * level * N;
         u64 *o = out + (size_t)b0 * 2 * (level - 1) * N;
         if (!c->fused) {
@@ -1232,7 +1274,6 @@ static int hmul_relin_rescale_impl(ckksmi_ctx *c, const uint64_t *a, const uint6
         }
         // the tensor is never written: its third component goes through the inverse row pass on the way, the inner product forms
         // what it needs of all three from the operands
-        launch_tensor_rows(c, a + in0, b + in0, rest, level, items, S(stream), terms);
         if (merged || one_conversion_tail_ok(c)) {
             // one division by P*q_{level-1} of (accumulators + P*(d0, d1)), or ModDown + add + rescale as one conversion
             ks_core_fused(c, nullptr, 0, K, items, level, nullptr, 0, 0, 1, o, rest, S(stream), !merged, merged, nullptr, a + in0, b + in0, terms);
@@ -1724,7 +1765,7 @@ extern "C" const char *ckksmi_kernel_class_name(const ckksmi_ctx *c, int kernel_
                                                 "elementwise kernels", "modup_cols_kernel", "modup_cols_kernel", "rows_inner_kernel",
                                                 "rows_final_kernel", "modup_cols_kernel", "conv_mac_mfma_kernel", "mac_prepare_mfma_kernel", "ntt_wg_kernel", "tensor_rows_kernel",
                                                 "axpy_limb_kernel", "modup_cols_kernel", "inner_product_hoisted_tile_kernel", "automorphism_bcast_kernel",
-                                                "encoding kernels", "encryption kernels", "modup_cols_kernel", "conv_mac_mfma_resident_kernel", "conv_mac_mfma_strip_kernel", "conv_final_kernel"};
+                                                "encoding kernels", "encryption kernels", "modup_cols_kernel", "conv_mac_mfma_resident_kernel", "conv_mac_mfma_strip_kernel", "conv_final_kernel", "inner_wg_kernel"};
     if (kernel_class < 0 || kernel_class >= CKKSMI_K_COUNT) return "";
     if (c && kernel_class == CKKSMI_K_INNER_HOISTED && !hoisted_tile_ok(c, c->beta_top)) return "inner_product_hoisted_kernel";
     if (c && c->logN >= 12 && c->logN <= 16) {

@@ -479,42 +479,14 @@ struct RowsInnerArgs {
     const WMul *Pmod;    // [T] P mod q_i
 };
 
-// GAL (a rotation): the source polynomial d_eval and the addend are read through the automorphism X -> X^g of their item
-// (gal->g[item]), so that no rotated copy of the ciphertext is ever written
-template <bool P51, bool GAL = false>
-__device__ __forceinline__ void rows_inner_body(const RowsInnerArgs &A, const KeyTab &K, double *lds, double *tw1_lds, double *tw2_lds, int t,
-                                                unsigned x, const GaloisTab *gal = nullptr) {
-    BODY_TAG(P51);
-    constexpr int F1 = P51 ? 0xA : 0x8, F2 = P51 ? 0x2 : 0x0;
-    const unsigned N = 1u << A.logN, N1 = N >> 8;
-    const double p = A.modc[t].p, pinv = A.modc[t].pinv;
-    const unsigned tid = threadIdx.x, hi4 = tid >> 4, lo4 = tid & 15;
-    // Workgroups are handed to the 8 XCDs round-robin by linear id, and every XCD has its own L2.  blockIdx.x packs
-    // (row tile mod KT, item) with KT = min(tiles, 8) in the low position, so that all items' workgroups for one key
-    // tile (same extended limb, same row tile) land on the same XCD and the key tile is fetched from HBM once.
-    const unsigned KT = A.kt;
-    const unsigned item = blockIdx.x / KT, tile = blockIdx.x % KT + KT * blockIdx.y;
-    {
-        // both rounds' twiddles live in LDS here (round 2: [15][256], conflict-free): the registers are needed for the
-        // accumulators and the operands in flight
-        double tw2[15];
-        load_row_twiddles(A.tw + (size_t)t * N, N1, tile, hi4, lo4, tw1_lds, tw2);
-#pragma unroll
-        for (int i = 0; i < 15; i++) tw2_lds[i * 256 + tid] = tw2[i];
-    }
-    const u64d *key = K.key[K.slot[item]];
-    const size_t tile0 = (size_t)tile * 4096;
-    double *grp = lds + hi4 * V2_GS;
-    double a0[16], a1[16];
-#pragma unroll
-    for (int i = 0; i < 16; i++) a0[i] = a1[i] = 0.0;
-    // Multiply-accumulate layout (row_pair_index): a thread owns 8 word pairs of the row its 16 lanes transform, so that key
-    // words, the own digit's words and the results move 16 bytes per lane and the whole digit loop needs no workgroup barrier;
-    // accumulator 2*s + b belongs to the word at column 32*s + 2*lo4 + b of row hi4.
-    // The digit that contains this limb needs no transform: its operand is the source polynomial itself.
-    const int j_own = (int)x < A.level ? (int)x / A.alpha : -1;
-    const bool tensor_mode = !GAL && A.ta != nullptr && j_own >= 0;
-    int pending = 1;  // terms in the accumulators since their last reduction (the own digit's term counts)
+// The term of the digit that contains limb x (its operand is the source polynomial itself, no transform) of a thread's 16
+// words: pairs row_pair_index(hi4, lo4, s) from word tile0 of the limb; accumulator 2*s + b belongs to word b of pair s.
+// In tensor mode also P * (d0, d1).  pending: terms in the accumulators since their last reduction.
+template <bool GAL>
+__device__ __forceinline__ void inner_own_digit(const RowsInnerArgs &A, const u64d *key, unsigned item, int t, unsigned x, int j_own, bool tensor_mode,
+                                                size_t tile0, unsigned hi4, unsigned lo4, double p, double pinv, double (&a0)[16], double (&a1)[16],
+                                                int &pending, const GaloisTab *gal) {
+    const unsigned N = 1u << A.logN;
     if (tensor_mode) {
         // d0, d1, d2 of the thread's 16 words from the operands (summed over the terms, balanced-reduced)
         const size_t st = (size_t)A.level * N / 2;  // pairs between the two components of a ciphertext
@@ -591,6 +563,99 @@ __device__ __forceinline__ void rows_inner_body(const RowsInnerArgs &A, const Ke
             a1[2 * s + 1] = mulmod_w(u2d(kr1[s].y), v1, vp1, p);
         }
     }
+}
+
+// The accumulators leave as z (folded tail), as acc + P*d, or as they are
+template <bool GAL>
+__device__ __forceinline__ void inner_store(const RowsInnerArgs &A, unsigned item, int t, unsigned x, bool tensor_mode, size_t tile0, unsigned hi4,
+                                            unsigned lo4, double p, double pinv, const double (&a0)[16], const double (&a1)[16], const GaloisTab *gal) {
+    const unsigned N = 1u << A.logN;
+    u64d *o0 = A.acc + (((size_t)item * 2 + 0) * A.E + x) * N + tile0;
+    u64d *o1 = A.acc + (((size_t)item * 2 + 1) * A.E + x) * N + tile0;
+    if (tensor_mode && !A.keep_acc) {
+        // z = (acc + P*d) * P^-1; accumulators are below 2^53: the prepared product is exact for them as they are
+        const WMul Pi = A.Pinv[t];
+#pragma unroll
+        for (int s = 0; s < 8; s++) {
+            const double z00 = mulmod_w(a0[2 * s], Pi.w, Pi.wp, p), z01 = mulmod_w(a0[2 * s + 1], Pi.w, Pi.wp, p);
+            const double z10 = mulmod_w(a1[2 * s], Pi.w, Pi.wp, p), z11 = mulmod_w(a1[2 * s + 1], Pi.w, Pi.wp, p);
+            ((ulonglong2 *)o0)[row_pair_index(hi4, lo4, s)] = make_ulonglong2(d2u(canon(z00, p, pinv)), d2u(canon(z01, p, pinv)));
+            ((ulonglong2 *)o1)[row_pair_index(hi4, lo4, s)] = make_ulonglong2(d2u(canon(z10, p, pinv)), d2u(canon(z11, p, pinv)));
+        }
+        return;
+    }
+    if (!tensor_mode && A.fold_tail && (int)x < A.level) {
+        const WMul Pi = A.Pinv[t];
+        const u64d *l0 = A.addend + (size_t)item * A.add_item_stride + (size_t)x * N, *d0 = l0 + tile0;
+        const bool both = A.fold_tail == 1;  // 2: only the first component has an addend (rotation)
+        const u64d *l1 = both ? l0 + A.add_comp_stride : l0, *d1 = l1 + tile0;
+        const double has1 = both ? 1.0 : 0.0;
+        ulonglong2 dw0[8], dw1[8];
+#pragma unroll
+        for (int s = 0; s < 8; s++) {
+            if (GAL) {
+                const unsigned j = (unsigned)tile0 + hi4 * 256u + 32u * s + 2u * lo4;
+                dw0[s] = galois_pair_load(l0, j, gal->g[item], A.logN);
+                dw1[s] = both ? galois_pair_load(l1, j, gal->g[item], A.logN) : dw0[s];
+            } else {
+                dw0[s] = ((const ulonglong2 *)d0)[row_pair_index(hi4, lo4, s)];
+                dw1[s] = ((const ulonglong2 *)d1)[row_pair_index(hi4, lo4, s)];
+            }
+        }
+#pragma unroll
+        for (int s = 0; s < 8; s++) {
+            // accumulators are below 2^53: the prepared product is exact for them as they are
+            const double z00 = mulmod_w(a0[2 * s], Pi.w, Pi.wp, p) + u2d(dw0[s].x), z01 = mulmod_w(a0[2 * s + 1], Pi.w, Pi.wp, p) + u2d(dw0[s].y);
+            const double z10 = mulmod_w(a1[2 * s], Pi.w, Pi.wp, p) + has1 * u2d(dw1[s].x), z11 = mulmod_w(a1[2 * s + 1], Pi.w, Pi.wp, p) + has1 * u2d(dw1[s].y);
+            ((ulonglong2 *)o0)[row_pair_index(hi4, lo4, s)] = make_ulonglong2(d2u(canon(z00, p, pinv)), d2u(canon(z01, p, pinv)));
+            ((ulonglong2 *)o1)[row_pair_index(hi4, lo4, s)] = make_ulonglong2(d2u(canon(z10, p, pinv)), d2u(canon(z11, p, pinv)));
+        }
+        return;
+    }
+#pragma unroll
+    for (int s = 0; s < 8; s++) {
+        ((ulonglong2 *)o0)[row_pair_index(hi4, lo4, s)] = make_ulonglong2(d2u(canon(a0[2 * s], p, pinv)), d2u(canon(a0[2 * s + 1], p, pinv)));
+        ((ulonglong2 *)o1)[row_pair_index(hi4, lo4, s)] = make_ulonglong2(d2u(canon(a1[2 * s], p, pinv)), d2u(canon(a1[2 * s + 1], p, pinv)));
+    }
+}
+
+// GAL (a rotation): the source polynomial d_eval and the addend are read through the automorphism X -> X^g of their item
+// (gal->g[item]), so that no rotated copy of the ciphertext is ever written
+template <bool P51, bool GAL = false>
+__device__ __forceinline__ void rows_inner_body(const RowsInnerArgs &A, const KeyTab &K, double *lds, double *tw1_lds, double *tw2_lds, int t,
+                                                unsigned x, const GaloisTab *gal = nullptr) {
+    BODY_TAG(P51);
+    constexpr int F1 = P51 ? 0xA : 0x8, F2 = P51 ? 0x2 : 0x0;
+    const unsigned N = 1u << A.logN, N1 = N >> 8;
+    const double p = A.modc[t].p, pinv = A.modc[t].pinv;
+    const unsigned tid = threadIdx.x, hi4 = tid >> 4, lo4 = tid & 15;
+    // Workgroups are handed to the 8 XCDs round-robin by linear id, and every XCD has its own L2.  blockIdx.x packs
+    // (row tile mod KT, item) with KT = min(tiles, 8) in the low position, so that all items' workgroups for one key
+    // tile (same extended limb, same row tile) land on the same XCD and the key tile is fetched from HBM once.
+    const unsigned KT = A.kt;
+    const unsigned item = blockIdx.x / KT, tile = blockIdx.x % KT + KT * blockIdx.y;
+    {
+        // both rounds' twiddles live in LDS here (round 2: [15][256], conflict-free): the registers are needed for the
+        // accumulators and the operands in flight
+        double tw2[15];
+        load_row_twiddles(A.tw + (size_t)t * N, N1, tile, hi4, lo4, tw1_lds, tw2);
+#pragma unroll
+        for (int i = 0; i < 15; i++) tw2_lds[i * 256 + tid] = tw2[i];
+    }
+    const u64d *key = K.key[K.slot[item]];
+    const size_t tile0 = (size_t)tile * 4096;
+    double *grp = lds + hi4 * V2_GS;
+    double a0[16], a1[16];
+#pragma unroll
+    for (int i = 0; i < 16; i++) a0[i] = a1[i] = 0.0;
+    // Multiply-accumulate layout (row_pair_index): a thread owns 8 word pairs of the row its 16 lanes transform, so that key
+    // words, the own digit's words and the results move 16 bytes per lane and the whole digit loop needs no workgroup barrier;
+    // accumulator 2*s + b belongs to the word at column 32*s + 2*lo4 + b of row hi4.
+    // The digit that contains this limb needs no transform: its operand is the source polynomial itself.
+    const int j_own = (int)x < A.level ? (int)x / A.alpha : -1;
+    const bool tensor_mode = !GAL && A.ta != nullptr && j_own >= 0;
+    int pending = 1;  // terms in the accumulators since their last reduction (the own digit's term counts)
+    inner_own_digit<GAL>(A, key, item, t, x, j_own, tensor_mode, tile0, hi4, lo4, p, pinv, a0, a1, pending, gal);
     // The other digits, software-pipelined so that no memory latency sits in front of arithmetic: the limb words of a
     // digit are requested while the previous digit is multiplied, its key words while the limb goes through the row
     // pass.  xr holds the column-pass output of the converted limb in the register layout of the row pass.
@@ -666,53 +731,7 @@ __device__ __forceinline__ void rows_inner_body(const RowsInnerArgs &A, const Ke
         ROW_GROUP_SYNC();  // the row's lanes have read its words before the next digit overwrites them
         j = jn;
     }
-    u64d *o0 = A.acc + (((size_t)item * 2 + 0) * A.E + x) * N + tile0;
-    u64d *o1 = A.acc + (((size_t)item * 2 + 1) * A.E + x) * N + tile0;
-    if (tensor_mode && !A.keep_acc) {
-        // z = (acc + P*d) * P^-1; accumulators are below 2^53: the prepared product is exact for them as they are
-        const WMul Pi = A.Pinv[t];
-#pragma unroll
-        for (int s = 0; s < 8; s++) {
-            const double z00 = mulmod_w(a0[2 * s], Pi.w, Pi.wp, p), z01 = mulmod_w(a0[2 * s + 1], Pi.w, Pi.wp, p);
-            const double z10 = mulmod_w(a1[2 * s], Pi.w, Pi.wp, p), z11 = mulmod_w(a1[2 * s + 1], Pi.w, Pi.wp, p);
-            ((ulonglong2 *)o0)[row_pair_index(hi4, lo4, s)] = make_ulonglong2(d2u(canon(z00, p, pinv)), d2u(canon(z01, p, pinv)));
-            ((ulonglong2 *)o1)[row_pair_index(hi4, lo4, s)] = make_ulonglong2(d2u(canon(z10, p, pinv)), d2u(canon(z11, p, pinv)));
-        }
-        return;
-    }
-    if (!tensor_mode && A.fold_tail && (int)x < A.level) {
-        const WMul Pi = A.Pinv[t];
-        const u64d *l0 = A.addend + (size_t)item * A.add_item_stride + (size_t)x * N, *d0 = l0 + tile0;
-        const bool both = A.fold_tail == 1;  // 2: only the first component has an addend (rotation)
-        const u64d *l1 = both ? l0 + A.add_comp_stride : l0, *d1 = l1 + tile0;
-        const double has1 = both ? 1.0 : 0.0;
-        ulonglong2 dw0[8], dw1[8];
-#pragma unroll
-        for (int s = 0; s < 8; s++) {
-            if (GAL) {
-                const unsigned j = (unsigned)tile0 + hi4 * 256u + 32u * s + 2u * lo4;
-                dw0[s] = galois_pair_load(l0, j, gal->g[item], A.logN);
-                dw1[s] = both ? galois_pair_load(l1, j, gal->g[item], A.logN) : dw0[s];
-            } else {
-                dw0[s] = ((const ulonglong2 *)d0)[row_pair_index(hi4, lo4, s)];
-                dw1[s] = ((const ulonglong2 *)d1)[row_pair_index(hi4, lo4, s)];
-            }
-        }
-#pragma unroll
-        for (int s = 0; s < 8; s++) {
-            // accumulators are below 2^53: the prepared product is exact for them as they are
-            const double z00 = mulmod_w(a0[2 * s], Pi.w, Pi.wp, p) + u2d(dw0[s].x), z01 = mulmod_w(a0[2 * s + 1], Pi.w, Pi.wp, p) + u2d(dw0[s].y);
-            const double z10 = mulmod_w(a1[2 * s], Pi.w, Pi.wp, p) + has1 * u2d(dw1[s].x), z11 = mulmod_w(a1[2 * s + 1], Pi.w, Pi.wp, p) + has1 * u2d(dw1[s].y);
-            ((ulonglong2 *)o0)[row_pair_index(hi4, lo4, s)] = make_ulonglong2(d2u(canon(z00, p, pinv)), d2u(canon(z01, p, pinv)));
-            ((ulonglong2 *)o1)[row_pair_index(hi4, lo4, s)] = make_ulonglong2(d2u(canon(z10, p, pinv)), d2u(canon(z11, p, pinv)));
-        }
-        return;
-    }
-#pragma unroll
-    for (int s = 0; s < 8; s++) {
-        ((ulonglong2 *)o0)[row_pair_index(hi4, lo4, s)] = make_ulonglong2(d2u(canon(a0[2 * s], p, pinv)), d2u(canon(a0[2 * s + 1], p, pinv)));
-        ((ulonglong2 *)o1)[row_pair_index(hi4, lo4, s)] = make_ulonglong2(d2u(canon(a1[2 * s], p, pinv)), d2u(canon(a1[2 * s + 1], p, pinv)));
-    }
+    inner_store<GAL>(A, item, t, x, tensor_mode, tile0, hi4, lo4, p, pinv, a0, a1, gal);
 }
 
 // grid: x = (row tile mod kt) + kt * item, y = row tile / kt, z = extended limb

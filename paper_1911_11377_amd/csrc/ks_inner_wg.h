@@ -1,0 +1,243 @@
+// Key switching at N = 2^12 and 2^13 without the lifted limbs in memory: ModUp's conversion, the whole forward transform of a
+// lifted limb and the inner product with the switching key in ONE workgroup.
+//
+// modup_cols_kernel + rows_inner_kernel (ks_fused.h) carry beta * E limbs per polynomial through memory between the column
+// and the row pass of their transform, the largest traffic of a product.  A block of 2^12 words does not need to: a workgroup
+// owns (extended limb x, block, item), walks the digits, converts the digit's words (coefficient form, read by all extended
+// limbs of the item), transforms them in LDS and adds their products with the key words to the accumulators in its
+// registers.  N = 2^13 is cut into two blocks as in ks_wg.h.  Two workgroups of four waves per compute unit (256 registers:
+// accumulators, key words and the words in transform); what bounds it is the vector ALU (about 95 instructions per word and
+// digit) and two barriers per digit.  Products at 8 primes, 256 items: N = 2^12 621 -> 527 us, 2^13 1177 -> 1061 us.
+#pragma once
+#include "ks_wg.h"
+
+struct InnerWgArgs {
+    RowsInnerArgs R;   // dtA, kt unused
+    const double *y;   // [items][level][N] conversion inputs, coefficient form, canonical, as doubles
+    const WMul *cc;    // ModUp constants [beta_top][alpha][alpha][T]
+    int items, items_x;
+};
+
+// A uniform entry of the (read-only) twiddle table through the scalar cache: held in scalar registers over the digits
+#ifdef CKKSMI_EMULATE
+static inline double table_load(const double *t, unsigned i) { return t[i]; }
+#else
+typedef const __attribute__((address_space(4))) double *ConstTable;
+__device__ __forceinline__ double table_load(const double *t, unsigned i) { return ((ConstTable)(unsigned long long)t)[i]; }
+#endif
+
+// LDS of a workgroup: the matrix of wg_fwd_block, the first row round's twiddles [M/256][16] and the second's [15][M/16].  All
+// digits of a workgroup use the same twiddles, and fetching them per digit exposes their latency three times.
+template <int LOGM>
+struct InnerWgLds {
+    static constexpr unsigned T = (1u << LOGM) / 16, MAT = ((1u << LOGM) >> 8) * V2_GS, TW1 = MAT, TW2 = TW1 + T, TOTAL = TW2 + 15 * T;
+};
+
+// wg_fwd_block with the twiddles at hand: twc the first column round's, twu the second's, the row rounds' in LDS.  One barrier
+// (two with a second column round) inside; the caller puts one between a digit's last use of the matrix and the next digit.
+template <int LOGM, bool P51, class F>
+__device__ __forceinline__ void inner_fwd_block(double (&x)[16], const double (&twc)[15], const double (&twu)[15], double *lds, double p, double pinv,
+                                                F request) {
+    constexpr int Q = LOGM - 12;
+    typedef ColsGeom<Q> Geo;
+    typedef ColsMasks<Q, P51> Mk;
+    typedef InnerWgLds<LOGM> Lay;
+    constexpr int RF1 = P51 ? 0xA : 0x8, RF2 = P51 ? 0x2 : 0x0;
+    const unsigned tid = threadIdx.x, row = tid >> 4, lo4 = tid & 15;
+    const Geo geo(tid & 255u, tid >> 8);
+    double *grp = lds + row * V2_GS;
+    fwd_round<Mk::F1>(x, twc, p, pinv);
+    if (Q > 0) {
+#pragma unroll
+        for (int e = 0; e < 16; e++) lds[wg_pad(geo.r + Geo::G * e, geo.c0 + geo.c)] = x[e];
+        __syncthreads();
+#pragma unroll
+        for (int i = 0; i < 16; i++) x[i] = lds[wg_pad(Geo::G * geo.a + (i % Geo::G), geo.c0 + geo.l16 + 16 * (i / Geo::G))];
+        fwd_stages<Geo::S0, Mk::F2>(x, twu, p, pinv);
+#pragma unroll
+        for (int i = 0; i < 16; i++)
+            lds[wg_pad(Geo::G * geo.a + (i % Geo::G), geo.c0 + geo.l16 + 16 * (i / Geo::G))] = reduce_balanced(x[i], p, pinv);
+    } else {
+#pragma unroll
+        for (int e = 0; e < 16; e++) lds[wg_pad(e, geo.c0 + geo.c)] = x[e];  // the first round ends reduced
+    }
+    __syncthreads();
+    request();
+#pragma unroll
+    for (int e = 0; e < 16; e++) x[e] = grp[e * 17 + lo4];
+    {
+        double t1[15];
+#pragma unroll
+        for (int i = 0; i < 15; i++) t1[i] = lds[Lay::TW1 + row * 16 + i];
+        fwd_round<RF1>(x, t1, p, pinv);
+    }
+#pragma unroll
+    for (int e = 0; e < 16; e++) grp[e * 17 + lo4] = x[e];
+    ROW_GROUP_SYNC();
+#pragma unroll
+    for (int e = 0; e < 16; e++) x[e] = grp[lo4 * 17 + e];
+    {
+        double t2[15];
+#pragma unroll
+        for (int i = 0; i < 15; i++) t2[i] = lds[Lay::TW2 + i * Lay::T + tid];
+        fwd_round<RF2>(x, t2, p, pinv);
+    }
+#pragma unroll
+    for (int e = 0; e < 16; e++) grp[lo4 * 17 + e] = reduce_balanced(x[e], p, pinv);
+    ROW_GROUP_SYNC();
+}
+
+template <int LOGM, int S, int NSRC, bool P51, bool GAL>
+__device__ __forceinline__ void inner_wg_body(const InnerWgArgs &A, const KeyTab &K, double *lds, int t, unsigned x, unsigned item, unsigned blk,
+                                              const GaloisTab *gal) {
+    BODY_TAG(P51);
+    typedef ColsGeom<LOGM - 12> Geo;
+    constexpr unsigned M = 1u << LOGM, N = M << S;
+    typedef InnerWgLds<LOGM> Lay;
+    const RowsInnerArgs &R = A.R;
+    const double p = R.modc[t].p, pinv = R.modc[t].pinv;
+    const double *tw = R.tw + (size_t)t * N;
+    const unsigned tid = threadIdx.x, prow = tid >> 4, lo4 = tid & 15, base = (1u << S) + blk;
+    const u64d *key = K.key[K.slot[item]];
+    const size_t tile0 = (size_t)blk * M;
+    double a0[16], a1[16];
+#pragma unroll
+    for (int i = 0; i < 16; i++) a0[i] = a1[i] = 0.0;
+    const int j_own = (int)x < R.level ? (int)x / R.alpha : -1;
+    const bool tensor_mode = !GAL && R.ta != nullptr && j_own >= 0;
+    int pending = 1;
+    inner_own_digit<GAL>(R, key, item, t, x, j_own, tensor_mode, tile0, prow, lo4, p, pinv, a0, a1, pending, gal);
+    // twiddles of the first S stages on the way to this block, see conv_final_body
+    double w[S + 1], wp[S + 1];
+#pragma unroll
+    for (int q = 0; q < S; q++) {
+        const double v = tw[(1u << q) + (blk >> (S - q))];
+        w[q] = ((blk >> (S - 1 - q)) & 1u) ? -v : v;
+        wp[q] = w[q] * pinv;
+    }
+    const Geo geo(tid & 255u, tid >> 8);
+    const unsigned voff = geo.r * 256u + geo.c0 + geo.c, pr = row_pair_index(prow, lo4, 0);
+    double twc[15], twu[15];
+#pragma unroll
+    for (int s = 0; s < 4; s++)
+#pragma unroll
+        for (int b = 0; b < (1 << s); b++) {
+            twc[(1 << s) - 1 + b] = table_load(tw, (base << s) + b);
+            const int u = s - (4 - (LOGM - 12));
+            twu[(1 << s) - 1 + b] = u >= 0 ? tw[((16u * base + geo.a) << u) + (b & ((1 << u) - 1))] : 0.0;
+        }
+    {
+        const unsigned base1 = base * (M >> 8) + prow;
+#pragma unroll
+        for (int s = 0; s < 4; s++)
+#pragma unroll
+            for (int b = 0; b < (1 << s); b++) lds[Lay::TW2 + ((1 << s) - 1 + b) * Lay::T + tid] = tw[((16u * base1 + lo4) << s) + b];
+        if (lo4 < 15) {
+            // entry i = (1 << s) - 1 + b of the row's first round
+            const unsigned s = (lo4 >= 7) ? 3 : (lo4 >= 3) ? 2 : (lo4 >= 1) ? 1 : 0, b = lo4 - ((1u << s) - 1);
+            lds[Lay::TW1 + prow * 16 + lo4] = tw[(base1 << s) + b];
+        }
+    }
+    for (int j = 0; j < R.beta; j++) {
+        if (j == j_own) continue;
+        const int lo = j * R.alpha, nd = R.level - lo < R.alpha ? R.level - lo : R.alpha;
+        double xx[16];
+        {
+            const double *y = A.y + ((size_t)item * R.level + lo) * N;
+            WMul Wc[NSRC];
+            const size_t crow = ((size_t)lo + (nd - 1)) * R.alpha;
+#pragma unroll
+            for (int a = 0; a < NSRC; a++) Wc[a] = a < nd ? A.cc[(crow + a) * R.T + t] : WMul{0.0, 0.0};
+            constexpr int CH = NSRC > 1 ? (8 >> S) : (16 >> S);  // words formed together: bounds the source words in flight
+#pragma unroll
+            for (int e0 = 0; e0 < 16; e0 += CH) {
+                double src[CH][1 << S][NSRC];
+#pragma unroll
+                for (int e = 0; e < CH; e++)
+#pragma unroll
+                    for (int q = 0; q < (1 << S); q++)
+#pragma unroll
+                        for (int a = 0; a < NSRC; a++)  // a missing source (digit cut short by the level) re-reads the first one: its constant is zero
+                            src[e][q][a] = scalar_base(y + ((size_t)(a < nd ? a : 0) * N + (size_t)q * M + Geo::G * 256u * (e0 + e)))[voff];
+                SCHED_FENCE();
+#pragma unroll
+                for (int e = 0; e < CH; e++) {
+                    double u[1 << S];
+#pragma unroll
+                    for (int q = 0; q < (1 << S); q++) u[q] = conv_word<NSRC>(src[e][q], Wc, 0.0, p, pinv);
+#pragma unroll
+                    for (int q1 = 0; q1 < S; q1++)
+#pragma unroll
+                        for (int q = 0; q < (1 << (S - 1 - q1)); q++) u[q] += mulmod_w(u[q + (1 << (S - 1 - q1))], w[q1], wp[q1], p);
+                    xx[e0 + e] = (P51 && S >= 2) ? reduce_balanced(u[0], p, pinv) : u[0];
+                }
+#pragma unroll
+                for (int e = 0; e < CH; e++) PIN_VALUE(xx[e0 + e]);
+            }
+        }
+        const ulonglong2 *k0 = (const ulonglong2 *)(key + (((size_t)j * 2 + 0) * R.T + t) * N + tile0);
+        const ulonglong2 *k1 = (const ulonglong2 *)(key + (((size_t)j * 2 + 1) * R.T + t) * N + tile0);
+        ulonglong2 kr0[8], kr1[8];
+        __syncthreads();  // everybody is done with the matrix (before the first digit: the twiddles are in place)
+        inner_fwd_block<LOGM, P51>(xx, twc, twu, lds, p, pinv, [&]() {
+#pragma unroll
+            for (int s = 0; s < 8; s++) {
+                kr0[s] = (k0 + 16 * s)[pr];
+                kr1[s] = (k1 + 16 * s)[pr];
+            }
+        });
+        const double *grp = lds + prow * V2_GS;
+#pragma unroll
+        for (int s = 0; s < 8; s++) {
+            // the transformed word is the prepared factor, each term is below 0.875p (as in rows_inner_body)
+            const double *vrow = grp + row_pair_lds(lo4, s);
+            const double v0 = vrow[0], vp0 = v0 * pinv, v1 = vrow[1], vp1 = v1 * pinv;
+            a0[2 * s] += mulmod_w(u2d(kr0[s].x), v0, vp0, p);
+            a1[2 * s] += mulmod_w(u2d(kr1[s].x), v0, vp0, p);
+            a0[2 * s + 1] += mulmod_w(u2d(kr0[s].y), v1, vp1, p);
+            a1[2 * s + 1] += mulmod_w(u2d(kr1[s].y), v1, vp1, p);
+        }
+        if (++pending == (P51 ? 4 : 8)) {
+#pragma unroll
+            for (int i = 0; i < 16; i++) {
+                a0[i] = reduce_balanced(a0[i], p, pinv);
+                a1[i] = reduce_balanced(a1[i], p, pinv);
+            }
+            pending = 0;
+        }
+    }
+    inner_store<GAL>(R, item, t, x, tensor_mode, tile0, prow, lo4, p, pinv, a0, a1, gal);
+}
+
+// Consecutive workgroups go to the 8 XCDs in turn: an item's blocks sit on one XCD (they read the same sources), the items of an
+// extended limb are dealt over the XCDs (each keeps the limb's key words, 2 * beta * N of them, in its L2).
+__device__ __forceinline__ bool inner_wg_place(const InnerWgArgs &A, int S, unsigned &item, unsigned &blk) {
+    const unsigned X = (unsigned)A.items_x, g = blockIdx.x / (X << S), r = blockIdx.x % (X << S);
+    blk = WG_UNIFORM(r / X);
+    item = WG_UNIFORM(g * X + r % X);
+    return item < (unsigned)A.items;
+}
+
+// grid: x = see inner_wg_place, y = extended limb; block = M/16 threads
+template <int LOGM, int S, int NSRC>
+__global__ __launch_bounds__((1 << LOGM) / 16, 2) void inner_wg_kernel(InnerWgArgs A, KeyTab K) {
+    __shared__ double lds[InnerWgLds<LOGM>::TOTAL];
+    unsigned item, blk;
+    if (!inner_wg_place(A, S, item, blk)) return;
+    const unsigned x = blockIdx.y;
+    const int t = (int)x < A.R.level ? (int)x : A.R.n_q + (int)x - A.R.level;
+    if (is_p51(A.R.p51, t)) inner_wg_body<LOGM, S, NSRC, true, false>(A, K, lds, t, x, item, blk, nullptr);
+    else inner_wg_body<LOGM, S, NSRC, false, false>(A, K, lds, t, x, item, blk, nullptr);
+}
+
+// the same for rotations: source polynomial and addend read through the items' automorphisms
+template <int LOGM, int S, int NSRC>
+__global__ __launch_bounds__((1 << LOGM) / 16, 2) void inner_wg_gal_kernel(InnerWgArgs A, KeyTab K, GaloisTab G) {
+    __shared__ double lds[InnerWgLds<LOGM>::TOTAL];
+    unsigned item, blk;
+    if (!inner_wg_place(A, S, item, blk)) return;
+    const unsigned x = blockIdx.y;
+    const int t = (int)x < A.R.level ? (int)x : A.R.n_q + (int)x - A.R.level;
+    if (is_p51(A.R.p51, t)) inner_wg_body<LOGM, S, NSRC, true, true>(A, K, lds, t, x, item, blk, &G);
+    else inner_wg_body<LOGM, S, NSRC, false, true>(A, K, lds, t, x, item, blk, &G);
+}

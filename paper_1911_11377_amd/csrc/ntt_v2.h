@@ -50,13 +50,16 @@
 //   PIN_VALUE(x)    x is computed before the next pinned point and not sunk below later loads;
 //   scalar_base(p)  a workgroup-uniform address stays in scalar registers, so that the loads from p[thread offset] need no
 //                   64-bit vector additions each;
-//   WG_UNIFORM(v)   a workgroup-uniform value goes to a scalar register.
+//   WG_UNIFORM(v)   a workgroup-uniform value goes to a scalar register;
+//   LOAD_FENCE()    memory accesses stay on their side.
 #ifdef CKKSMI_EMULATE
 #define PIN_VALUE(x) ((void)0)
+#define LOAD_FENCE() ((void)0)
 #define WG_UNIFORM(v) (v)
 template <class T> __device__ __forceinline__ T *scalar_base(T *p) { return p; }
 #else
 #define PIN_VALUE(x) asm volatile("" : "+v"(x))
+#define LOAD_FENCE() asm volatile("" ::: "memory")
 #define WG_UNIFORM(v) ((unsigned)__builtin_amdgcn_readfirstlane((int)(v)))
 template <class T> __device__ __forceinline__ T *scalar_base(T *p) {
     asm volatile("" : "+s"(p));

@@ -89,8 +89,17 @@ __device__ __forceinline__ void wg_fwd_block(double (&x)[16], const double *tw, 
     ROW_GROUP_SYNC();
 }
 
-template <bool INV, int LOGN, bool P51, bool F64>
-__device__ __forceinline__ void ntt_wg_body(const NttV2Args &A, double *lds, int t, unsigned li) {
+// Operands of a product whose third tensor component enters its key switch through the inverse transform
+struct TensorSrc {
+    const u64d *a, *b;  // [items][terms][2][level][N]
+    int level, terms;
+};
+
+// SRC (inverse only): 0 the words of src; 1 read through the automorphism X -> X^g of the item (a rotation's polynomial);
+// 2 the third tensor component sum_t a1_t * b1_t of the item, formed on the way (never written)
+template <bool INV, int LOGN, bool P51, bool F64, int SRC = 0>
+__device__ __forceinline__ void ntt_wg_body(const NttV2Args &A, double *lds, int t, unsigned li, const GaloisTab *gal = nullptr,
+                                            const TensorSrc *ten = nullptr) {
     BODY_TAG(P51);
     constexpr int Q = LOGN - 12;
     typedef ColsGeom<Q> Geo;
@@ -138,14 +147,50 @@ __device__ __forceinline__ void ntt_wg_body(const NttV2Args &A, double *lds, int
             {
                 double tw1[15], tw2[15];
                 const unsigned base1 = N1 + row;
-                {
+                if (SRC == 2) {
+                    const size_t st = (size_t)ten->level * N / 2, it0 = (size_t)it * ten->terms * 2 * st;  // pairs between components
+                    const ulonglong2 *pa = (const ulonglong2 *)ten->a + it0 + st + (size_t)li * (N / 2);
+                    const ulonglong2 *pb = (const ulonglong2 *)ten->b + it0 + st + (size_t)li * (N / 2);
+#pragma unroll
+                    for (int h = 0; h < 2; h++) {  // four pairs at a time: bounds the registers in flight
+                        double d2[8];
+                        for (int tm = 0; tm < ten->terms; tm++) {
+                            ulonglong2 a1[4], b1[4];
+#pragma unroll
+                            for (int s = 0; s < 4; s++) {
+                                a1[s] = (pa + 2 * st * tm + 16 * (4 * h + s))[pr];
+                                b1[s] = (pb + 2 * st * tm + 16 * (4 * h + s))[pr];
+                            }
+                            NTT_SCHED_FENCE();
+#pragma unroll
+                            for (int s = 0; s < 4; s++) {  // |sum| <= p/2 + 1 + 1.25p
+                                const double v0 = mulmod(u2d(a1[s].x), u2d(b1[s].x), p, pinv), v1 = mulmod(u2d(a1[s].y), u2d(b1[s].y), p, pinv);
+                                d2[2 * s] = tm ? reduce_balanced(d2[2 * s] + v0, p, pinv) : v0;
+                                d2[2 * s + 1] = tm ? reduce_balanced(d2[2 * s + 1] + v1, p, pinv) : v1;
+                            }
+                        }
+#pragma unroll
+                        for (int s = 0; s < 4; s++) {
+                            // from the canonical representative, as when d2 comes from memory
+                            double *rr = grp + row_pair_lds(lo4, 4 * h + s);
+                            rr[0] = canon(d2[2 * s], p, pinv);
+                            rr[1] = canon(d2[2 * s + 1], p, pinv);
+                        }
+                    }
+                    LOAD_FENCE();
+                } else {
                     ulonglong2 raw[8];
 #pragma unroll
-                    for (int s = 0; s < 8; s++) raw[s] = ((const ulonglong2 *)src + 16 * s)[pr];
+                    for (int s = 0; s < 8; s++) {
+                        if (SRC == 1) raw[s] = galois_pair_load(src, row * 256u + 32u * s + 2u * lo4, gal->g[it], LOGN);
+                        else raw[s] = ((const ulonglong2 *)src + 16 * s)[pr];
+                    }
+                    if (SRC == 0) {
 #pragma unroll
-                    for (int s = 0; s < 4; s++)
+                        for (int s = 0; s < 4; s++)
 #pragma unroll
-                        for (int b = 0; b < (1 << s); b++) tw2[(1 << s) - 1 + b] = tw[((16u * base1 + lo4) << s) + b];
+                            for (int b = 0; b < (1 << s); b++) tw2[(1 << s) - 1 + b] = tw[((16u * base1 + lo4) << s) + b];
+                    }
                     NTT_SCHED_FENCE();
 #pragma unroll
                     for (int s = 0; s < 8; s++) {
@@ -153,6 +198,13 @@ __device__ __forceinline__ void ntt_wg_body(const NttV2Args &A, double *lds, int
                         rr[0] = u2d(raw[s].x);
                         rr[1] = u2d(raw[s].y);
                     }
+                    if (SRC != 0) LOAD_FENCE();
+                }
+                if (SRC != 0) {  // the source needs the registers: the first round's twiddles come after it
+#pragma unroll
+                    for (int s = 0; s < 4; s++)
+#pragma unroll
+                        for (int b = 0; b < (1 << s); b++) tw2[(1 << s) - 1 + b] = tw[((16u * base1 + lo4) << s) + b];
                 }
                 ROW_GROUP_SYNC();
 #pragma unroll
@@ -217,4 +269,24 @@ __global__ __launch_bounds__((1 << LOGN) / 16) void ntt_wg_kernel(NttV2Args A) {
         ntt_wg_body<INV, LOGN, true, F64>(A, lds, t, li);
     else
         ntt_wg_body<INV, LOGN, false, F64>(A, lds, t, li);
+}
+
+// conversion inputs of a key switch (doubles), same grid: a rotation's polynomial, a product's third tensor component
+template <int LOGN>
+__global__ __launch_bounds__((1 << LOGN) / 16) void ntt_wg_inv_gal_kernel(NttV2Args A, GaloisTab G) {
+    __shared__ double lds[((1 << LOGN) >> 8) * V2_GS];
+    unsigned item_unused, li;
+    const int t = resolve_limb(A.map, blockIdx.x, item_unused, li);
+    if (t < 0) return;
+    if (is_p51(A.p51, t)) ntt_wg_body<true, LOGN, true, true, 1>(A, lds, t, li, &G);
+    else ntt_wg_body<true, LOGN, false, true, 1>(A, lds, t, li, &G);
+}
+template <int LOGN>
+__global__ __launch_bounds__((1 << LOGN) / 16) void tensor_wg_kernel(NttV2Args A, TensorSrc T) {
+    __shared__ double lds[((1 << LOGN) >> 8) * V2_GS];
+    unsigned item_unused, li;
+    const int t = resolve_limb(A.map, blockIdx.x, item_unused, li);
+    if (t < 0) return;
+    if (is_p51(A.p51, t)) ntt_wg_body<true, LOGN, true, true, 2>(A, lds, t, li, nullptr, &T);
+    else ntt_wg_body<true, LOGN, false, true, 2>(A, lds, t, li, nullptr, &T);
 }

@@ -270,3 +270,14 @@ def test_emulated_one_source_division(be, logN, bits, tuned):
             pc.case_rescale(be, shape, seed=140 + logN, batch=1 if logN > 14 else 5, levels=[3])
     else:
         pc.case_rescale(be, shape, seed=150 + logN, batch=1, levels=[3, 2])
+
+
+@pytest.mark.parametrize("shape,batch", [((12, 5, 51, 2, 51, 2), 2), ((12, 4, 50, 1, 51, 1), 9), ((12, 7, 50, 3, 51, 3), 1), ((13, 3, 50, 1, 51, 1), 3)])
+def test_emulated_key_switch_on_chip(be, shape, batch):
+    """lifted limbs that never leave their workgroup: digits cut short by the level, one to three sources, halves of a 2^13 ring, items
+    that do not divide evenly over the XCDs; products, sums of products, relinearisation and rotations"""
+    with be.tuned(64):
+        level = shape[1]
+        pc.case_relin_and_composite(be, shape, seed=170, batch=batch, levels=[level, level - 1])
+        pc.case_rotate(be, shape, seed=171, rotations=[1, 1000], batch=batch, level=level - 1)
+        pc.case_sum_of_products(be, shape, seed=172, terms=3, batch=1, levels=[level])

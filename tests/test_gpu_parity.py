@@ -687,3 +687,23 @@ def test_one_source_division(be, logN, bits, batch):
     rows that do not divide evenly over the XCDs, both reduction schedules"""
     announce("one-source division logN=%d %d-bit batch %d" % (logN, bits, batch))
     pc.case_rescale(be, (logN, 4, bits, 0, 51, 1), seed=330 + logN, batch=batch, levels=[4, 2])
+
+
+@pytest.mark.parametrize("shape,batch,level", [((12, 8, 50, 1, 51, 1), 40, 8), ((12, 11, 50, 3, 51, 3), 13, 10), ((12, 5, 51, 2, 51, 2), 21, 5),
+                                               ((13, 8, 50, 1, 51, 1), 33, 7)])
+def test_key_switch_on_chip(be, shape, batch, level):
+    """batches large enough for the kernel that keeps the lifted limbs on chip: products, relinearisation and rotations"""
+    announce("key switch on chip %r batch %d" % (shape, batch))
+    pc.case_relin_and_composite(be, shape, seed=340, batch=batch, levels=[level])
+    pc.case_rotate(be, shape, seed=341, rotations=[1, 777, 2000], batch=batch, level=level)
+    ctx = be.context(*shape)
+    ctx.profile_enable(True)
+    a = be.empty(batch, 2, level, 1 << shape[0])
+    a.zero_()
+    key = be.empty(ctx.beta_top, 2, ctx.T, 1 << shape[0])
+    key.zero_()
+    ws = be.ws(ctx.workspace_bytes(ckksmi.OP_HMUL_RELIN_RESCALE, level, batch))
+    ctx.hmul_relin_rescale(a, a, key, be.empty(batch, 2, level - 1, 1 << shape[0]), level, batch, ws)
+    be.torch.cuda.synchronize()
+    assert "inner_wg_kernel" in ctx.profile_read()
+    ctx.close()
