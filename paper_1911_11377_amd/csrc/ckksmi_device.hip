@@ -313,13 +313,14 @@ inline bool conv_final_ok(const ckksmi_ctx *c, int nsrc) { return c->fused && ns
 // y: the dropped limbs in coefficient form as canonical doubles, row r at y + r*y_stride; fin_kind as conv_final_body's FIN
 void launch_conv_final(ckksmi_ctx *c, int fin_kind, const u64 *y, size_t y_stride, const DivRoundDev &D, const u64 *x, size_t x_row_stride,
                        const u64 *addend, size_t add_item_stride, size_t add_comp_stride, u64 *out, int nc, int rows, hipStream_t st,
-                       const RowsFinalGal *gal = nullptr, const ScalarTab *stab = nullptr) {
+                       const RowsFinalGal *gal = nullptr, const ScalarTab *stab = nullptr, const DivRoundDev *D2 = nullptr) {
     ConvFinalArgs A;
     memset(&A, 0, sizeof(A));
+    if (D2) A.hc2 = D2->hc;
     RowsFinalArgs &F = A.F;
     F.x = (const u64d *)x; F.x_row_stride = x_row_stride;
     F.addend = (const u64d *)addend; F.add_item_stride = add_item_stride; F.add_comp_stride = add_comp_stride;
-    F.out = (u64d *)out; F.out_row_stride = (size_t)nc * c->N; F.modc = c->d_mod; F.tw = c->d_tww_fwd; F.Binv = D.Binv;
+    F.out = (u64d *)out; F.out_row_stride = (size_t)nc * c->N; F.modc = c->d_mod; F.tw = c->d_tww_fwd; F.Binv = D2 ? D2->Binv : D.Binv;
     F.logN = c->logN; F.nc = nc; F.rows = rows; F.p51 = c->p51mask;
     A.y = (const double *)y; A.y_row_stride = y_stride; A.D = D; A.T = c->T;
     // Blocks per limb: M = N >> S words per workgroup.  Measured at 4096 and more limbs (us per 2^14 words): N = 2^12 whole 0.067;
@@ -341,6 +342,17 @@ void launch_conv_final(ckksmi_ctx *c, int fin_kind, const u64 *y, size_t y_strid
         else if (fin_kind == 2) { if constexpr (LN < 16) KL(c, CKKSMI_K_CONV_FINAL, units, (conv_final_scalar_kernel<LN - SS, SS>), grid, block, st, A, *stab); } \
         else KL(c, CKKSMI_K_CONV_FINAL, units, (conv_final_gal_kernel<LN - SS, SS, 1>), grid, block, st, A, *gal);                        \
         break;
+    if (fin_kind == 4) {  // sizes of tail_wg_ok
+#define CONV_TAIL_CASE(LN, SS, NS) case (LN * 4 + SS) * 8 + NS: KL(c, CKKSMI_K_CONV_FINAL, units, (conv_final_kernel<LN - SS, SS, NS, 4>), grid, block, st, A); break;
+        switch ((c->logN * 4 + S) * 8 + c->k + 1) {
+            CONV_TAIL_CASE(12, 0, 2) CONV_TAIL_CASE(12, 0, 3) CONV_TAIL_CASE(12, 0, 4)
+            CONV_TAIL_CASE(13, 1, 2)
+            CONV_TAIL_CASE(14, 1, 2) CONV_TAIL_CASE(14, 2, 2)
+            default: break;
+        }
+#undef CONV_TAIL_CASE
+        return;
+    }
     switch (c->logN * 4 + S) {
         CONV_FINAL_CASE(12, 0)
         CONV_FINAL_CASE(13, 1)
@@ -505,6 +517,26 @@ void launch_inner_wg(ckksmi_ctx *c, const RowsInnerArgs &R, const KeyTab &K, con
 #undef INNER_WG_CASE
 }
 
+// ModDown followed by rescale with the converted limbs on chip (tail_sources_kernel, conv_final_kernel): one workgroup per row makes
+// the k + 1 sources one after the other, then one per kept limb (block) the rest.  Products at 8 primes, against three kernels:
+// N = 2^12 1.05 - 1.16 x from one item on (with k = 3 from 32 rows on: 4 rows 0.93 x, 128 rows 1.15 x); N = 2^13 and 2^14 from 64 rows on
+// 1.07 and 1.03 - 1.07 x (2 rows 0.95 and 0.68 x: few compute units, each with a long chain).  More special primes at N > 2^12
+// would convert every source word twice (two blocks).
+inline bool tail_wg_ok(const ckksmi_ctx *c, int rows) {
+    const int fill = c->ntt_target_wgs / 128;  // 64
+    return (c->logN == 12 && (c->k == 1 || rows >= fill / 2)) || ((c->logN == 13 || c->logN == 14) && c->k == 1 && rows >= fill);
+}
+void launch_tail_sources(ckksmi_ctx *c, u64 *bl, size_t row_stride, int level, int rows, const FinConst *fin, const DivRoundDev &DB, hipStream_t st) {
+    TailSourcesArgs A;
+    memset(&A, 0, sizeof(A));
+    A.bl = (u64d *)bl; A.row_stride = row_stride; A.modc = c->d_mod; A.tw_inv = c->d_tww_inv; A.fin = fin; A.D = c->divround[0]; A.hb2 = DB.hb[0];
+    A.T = c->T; A.last = level - 1; A.n_q = c->n_q; A.k = c->k; A.p51 = c->p51mask;
+    const double units = (double)rows * (c->k + 1);
+    if (c->logN == 12) KL(c, CKKSMI_K_NTT_LDS, units, tail_sources_kernel<12>, dim3(rows), dim3(256), st, A);
+    else if (c->logN == 13) KL(c, CKKSMI_K_NTT_LDS, units, tail_sources_kernel<13>, dim3(rows), dim3(512), st, A);
+    else KL(c, CKKSMI_K_NTT_LDS, units, tail_sources_kernel<14>, dim3(rows), dim3(1024), st, A);
+}
+
 // Key switch on the register-tiled kernels (2^12 <= N <= 2^16).
 // tail: the key switch is followed by a rescale of (result + addend), both components have an addend, and `out` receives
 // the rescaled ciphertexts [items][2][level-1][N] (needs one_conversion_tail_ok).
@@ -589,6 +621,11 @@ void ks_core_fused(ckksmi_ctx *c, const u64 *d_eval, size_t d_stride, const KeyT
         D3.b_idx[0] = last;
         for (int m = 0; m < c->k; m++) D3.b_idx[1 + m] = c->n_q + m;
         const FinConst *ft = c->d_fin_tail + (size_t)level * CKKSMI_MAX_SPECIAL;
+        if (tail_wg_ok(c, rows)) {
+            launch_tail_sources(c, bl, (size_t)E * N, level, rows, ft, DB, st);
+            launch_conv_final(c, 4, bl, (size_t)E * N, c->divround[0], acc, (size_t)E * N, nullptr, 0, 0, out, last, rows, st, nullptr, nullptr, &DB);
+            return;
+        }
         launch_ntt(c, false, bl, bl, table_map(D3.b_idx, D3.nb, (size_t)E * N, (size_t)E * N), rows, st, ft, 2);
         launch_modup_cols(c, 3, bl, (size_t)E * N, tmp, rows, 0, last, &D3, (double)rows * last, st, ft, &DB);
         launch_rows_final(c, tmp, acc, (size_t)E * N, nullptr, 0, 0, 0, out, DB.Binv, last, rows, st);

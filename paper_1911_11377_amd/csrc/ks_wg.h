@@ -29,6 +29,7 @@ struct ConvFinalArgs {
     const double *y;        // sources in coefficient form, canonical, stored as doubles: row r, source m at y + r*y_row_stride + m*N
     unsigned long long y_row_stride;
     DivRoundDev D;
+    const double *hc2;      // FIN 4: the rescale's h mod c
     int T;
     int rows_x, rows_g;     // workgroup order, see conv_final_place
 };
@@ -58,8 +59,23 @@ __device__ __forceinline__ double conv_word(const double (&y)[NSRC], const WMul 
     return reduce_balanced(v, p, pinv);  // |v| <= p + NSRC * 0.75p
 }
 
+// The same for ModDown followed by rescale as one conversion (see modup_cols_kernel MODE 3): y[0] is the rescale's conversion
+// input y_B, y[1 ..] ModDown's; the value is (sum_a y_a * conv_a - hA) * P^-1 + y_B - hB.
+template <int NSRC>
+__device__ __forceinline__ double tail_word(const double (&y)[NSRC], const WMul (&Wc)[NSRC], double hA, WMul Pinv, double hB, double p, double pinv) {
+    double v = -hA;
+    if (NSRC == 2) {
+        v += y[1];  // one special prime: its constant is 1; below 2^51 + p
+    } else {
+#pragma unroll
+        for (int a = 1; a < NSRC; a++) v += mulmod_w(y[a], Wc[a].w, Wc[a].wp, p);
+    }
+    return reduce_balanced(mulmod_w(reduce_balanced(v, p, pinv), Pinv.w, Pinv.wp, p) + y[0] - hB, p, pinv);
+}
+
 // FIN 0: out = (x - r) * Binv;  1: out = x - r * Binv (x holds x * Binv + addend);  2: out = (x * xmv - r) * Binv (+ addend);
-// 3: out = (x - r) * Binv + sigma_g(addend) on even rows (rotations from a shared ModUp, see RowsFinalGal)
+// 3: out = (x - r) * Binv + sigma_g(addend) on even rows (rotations from a shared ModUp, see RowsFinalGal);  4: FIN 0 for ModDown
+// followed by rescale in one conversion (sources from tail_sources_kernel; D describes the ModDown, F.Binv the rescale)
 template <int LOGM, int S, int NSRC, int FIN, bool P51>
 __device__ __forceinline__ void conv_final_body(const ConvFinalArgs &A, double *lds, int i, unsigned row, unsigned blk, WMul xmv,
                                                 const RowsFinalGal *gal) {
@@ -78,8 +94,10 @@ __device__ __forceinline__ void conv_final_body(const ConvFinalArgs &A, double *
         const unsigned voff = geo.r * 256u + geo.c0 + geo.c;
         WMul Wc[NSRC];
 #pragma unroll
-        for (int a = 0; a < NSRC; a++) Wc[a] = A.D.conv[(size_t)a * A.T + i];
+        for (int a = 0; a < NSRC; a++) Wc[a] = A.D.conv[(size_t)(FIN == 4 ? (a ? a - 1 : 0) : a) * A.T + i];
         const double hsub = A.D.hc[i];
+        const WMul Pinv = FIN == 4 ? A.D.Binv[i] : WMul{0.0, 0.0};
+        const double hB = FIN == 4 ? A.hc2[i] : 0.0;
         // twiddles of the first S stages on the way to this block (negative: the block lies in the lower branch's difference)
         double w[S + 1], wp[S + 1];
 #pragma unroll
@@ -88,7 +106,7 @@ __device__ __forceinline__ void conv_final_body(const ConvFinalArgs &A, double *
             w[t] = ((blk >> (S - 1 - t)) & 1u) ? -v : v;
             wp[t] = w[t] * pinv;
         }
-        constexpr int CH = 16 >> S;  // words formed together: bounds the source words in flight
+        constexpr int CH = (NSRC > 1 ? 8 : 16) >> S;  // words formed together: bounds the source words in flight
 #pragma unroll
         for (int e0 = 0; e0 < 16; e0 += CH) {
             double src[CH][1 << S][NSRC];
@@ -103,7 +121,8 @@ __device__ __forceinline__ void conv_final_body(const ConvFinalArgs &A, double *
             for (int e = 0; e < CH; e++) {
                 double u[1 << S];
 #pragma unroll
-                for (int q = 0; q < (1 << S); q++) u[q] = conv_word<NSRC>(src[e][q], Wc, hsub, p, pinv);
+                for (int q = 0; q < (1 << S); q++)
+                    u[q] = FIN == 4 ? tail_word<NSRC>(src[e][q], Wc, hsub, Pinv, hB, p, pinv) : conv_word<NSRC>(src[e][q], Wc, hsub, p, pinv);
                 // stage t joins the words 2^(S-1-t) * M apart
 #pragma unroll
                 for (int t = 0; t < S; t++)
@@ -142,7 +161,7 @@ __device__ __forceinline__ void conv_final_body(const ConvFinalArgs &A, double *
         }
         (out + 16 * s)[pr] = make_ulonglong2(d2u(canon(v0, p, pinv)), d2u(canon(v1, p, pinv)));
     };
-    if (FIN < 2 || !add) {
+    if (FIN < 2 || FIN == 4 || !add) {
 #pragma unroll
         for (int s = 0; s < 8; s++) finish(s, false, make_ulonglong2(0ull, 0ull));
         return;
@@ -193,4 +212,65 @@ __global__ __launch_bounds__((1 << LOGM) / 16, 4) void conv_final_gal_kernel(Con
     if (!conv_final_place(A, S, row, blk, i)) return;
     if (is_p51(A.F.p51, i)) conv_final_body<LOGM, S, NSRC, 3, true>(A, lds, i, row, blk, WMul{0.0, 0.0}, &G);
     else conv_final_body<LOGM, S, NSRC, 3, false>(A, lds, i, row, blk, WMul{0.0, 0.0}, &G);
+}
+
+// ------------------------------------------------------------------ sources of ModDown followed by rescale
+// The limb a product's rescale drops and the special limbs of one row (neighbours in the extended layout), taken through their
+// inverse transforms by one workgroup, in place: ModDown's conversion inputs y_m, and in place of the dropped limb the
+// rescale's y_B = (s + h_B) mod q_last, s = u - (sum_m y_m * conv_m - h_A) * P^-1 the ModDown result of that limb, whose
+// evaluation form u comes in with P^-1 and the addend already applied (z of the inner product).  512 rows of two limbs at N = 2^14: 0.11 ms
+// for this kernel and 0.39 for the kept limbs, against 0.07 (inverse row pass) + 0.21 (conversion) + 0.30 (last pass).
+struct TailSourcesArgs {
+    u64d *bl;                          // row r, limb m at bl + r*row_stride + m*N; results as doubles
+    unsigned long long row_stride;
+    const ModConst *modc;
+    const double *tw_inv;
+    const FinConst *fin;               // [k + 1] last-stage constants
+    DivRoundDev D;                     // the ModDown; its kept limb b_idx0 is the dropped one
+    double hb2;
+    int T, last, n_q, k;
+    P51Mask p51;
+};
+
+template <int LOGN>
+__global__ __launch_bounds__((1 << LOGN) / 16) void tail_sources_kernel(TailSourcesArgs A) {
+    __shared__ double lds[((1 << LOGN) >> 8) * V2_GS];
+    typedef ColsGeom<LOGN - 12> Geo;
+    constexpr unsigned N = 1u << LOGN;
+    const unsigned tid = threadIdx.x;
+    const Geo geo(tid & 255u, tid >> 8);
+    const unsigned voff = geo.r * 256u + geo.c0 + geo.c;
+    u64d *bl = A.bl + (size_t)blockIdx.x * A.row_stride;
+    for (int mm = 1; mm <= A.k + 1; mm++) {
+        const int m = mm <= A.k ? mm : 0;  // the dropped limb comes last
+        const int t = m ? A.n_q + m - 1 : A.last;
+        const double p = A.modc[t].p, pinv = A.modc[t].pinv;
+        const FinConst F = A.fin[m];
+        u64d *limb = bl + (size_t)m * N;
+        double x[16];
+        if (is_p51(A.p51, t)) wg_inv_limb<LOGN, true, 0>(x, limb, A.tw_inv + (size_t)t * N, lds, p, pinv, F.ninv, F.wlast, 0, 0, nullptr, nullptr);
+        else wg_inv_limb<LOGN, false, 0>(x, limb, A.tw_inv + (size_t)t * N, lds, p, pinv, F.ninv, F.wlast, 0, 0, nullptr, nullptr);
+        if (m) {
+#pragma unroll
+            for (int e = 0; e < 16; e++) ((double *)scalar_base(limb + Geo::G * 256u * e))[voff] = canon(x[e] + F.cadd, p, pinv);
+        } else {
+            const double hA = A.D.hc[t];
+            const WMul Pinv = A.D.Binv[t];
+            double v[16];
+#pragma unroll
+            for (int e = 0; e < 16; e++) v[e] = -hA;
+            for (int a = 0; a < A.k; a++) {  // this thread wrote these words itself
+                const WMul W = A.D.conv[(size_t)a * A.T + t];
+                const u64d *y = bl + (size_t)(a + 1) * N;
+#pragma unroll
+                for (int e = 0; e < 16; e++) v[e] += mulmod_w(((const double *)scalar_base(y + Geo::G * 256u * e))[voff], W.w, W.wp, p);  // <= p + 3 * 0.75p
+            }
+#pragma unroll
+            for (int e = 0; e < 16; e++) {
+                const double s = canon(x[e] + F.cadd, p, pinv) - mulmod_w(reduce_balanced(v[e], p, pinv), Pinv.w, Pinv.wp, p);  // (-0.75p, 1.75p)
+                ((double *)scalar_base(limb + Geo::G * 256u * e))[voff] = canon(s + A.hb2, p, pinv);
+            }
+        }
+        __syncthreads();  // the matrix is free for the next limb
+    }
 }

@@ -95,17 +95,138 @@ struct TensorSrc {
     int level, terms;
 };
 
-// SRC (inverse only): 0 the words of src; 1 read through the automorphism X -> X^g of the item (a rotation's polynomial);
-// 2 the third tensor component sum_t a1_t * b1_t of the item, formed on the way (never written)
-template <bool INV, int LOGN, bool P51, bool F64, int SRC = 0>
-__device__ __forceinline__ void ntt_wg_body(const NttV2Args &A, double *lds, int t, unsigned li, const GaloisTab *gal = nullptr,
-                                            const TensorSrc *ten = nullptr) {
+// Inverse transform of one limb: word (geo.r + G*e, geo.c0 + geo.c) of the result in x[e], before the final addend and the
+// canonical form.  SRC 0: the words of src; 1: read through the automorphism X -> X^g of item `it` (a rotation's polynomial);
+// 2: the third tensor component sum_t a1_t * b1_t of limb li of item `it`, formed on the way (never written).
+// Ends without a barrier: the caller puts one before the matrix is used again.
+template <int LOGN, bool P51, int SRC>
+__device__ __forceinline__ void wg_inv_limb(double (&x)[16], const u64d *src, const double *tw, double *lds, double p, double pinv, WMul ninv, WMul wlast,
+                                            unsigned li, unsigned it, const GaloisTab *gal, const TensorSrc *ten) {
     BODY_TAG(P51);
     constexpr int Q = LOGN - 12;
     typedef ColsGeom<Q> Geo;
     typedef ColsMasks<Q, P51> Mk;
     constexpr unsigned N = 1u << LOGN, N1 = N >> 8;
     constexpr int RI1 = P51 ? 0x2 : 0x4, RI2 = P51 ? 0x1 : 0x4;   // row pass, inverse (as ntt_v2_rows)
+    const unsigned tid = threadIdx.x, row = tid >> 4, lo4 = tid & 15, pr = row_pair_index(row, lo4, 0);
+    const Geo geo(tid & 255u, tid >> 8);
+    double *grp = lds + row * V2_GS;
+    const WMul unused = WMul{0.0, 0.0};
+    // ---- row pass, from HBM into the LDS matrix
+    {
+        double tw1[15], tw2[15];
+        const unsigned base1 = N1 + row;
+        if (SRC == 2) {
+            const size_t st = (size_t)ten->level * N / 2, it0 = (size_t)it * ten->terms * 2 * st;  // pairs between components
+            const ulonglong2 *pa = (const ulonglong2 *)ten->a + it0 + st + (size_t)li * (N / 2);
+            const ulonglong2 *pb = (const ulonglong2 *)ten->b + it0 + st + (size_t)li * (N / 2);
+#pragma unroll
+            for (int h = 0; h < 2; h++) {  // four pairs at a time: bounds the registers in flight
+                double d2[8];
+                for (int tm = 0; tm < ten->terms; tm++) {
+                    ulonglong2 a1[4], b1[4];
+#pragma unroll
+                    for (int s = 0; s < 4; s++) {
+                        a1[s] = (pa + 2 * st * tm + 16 * (4 * h + s))[pr];
+                        b1[s] = (pb + 2 * st * tm + 16 * (4 * h + s))[pr];
+                    }
+                    NTT_SCHED_FENCE();
+#pragma unroll
+                    for (int s = 0; s < 4; s++) {  // |sum| <= p/2 + 1 + 1.25p
+                        const double v0 = mulmod(u2d(a1[s].x), u2d(b1[s].x), p, pinv), v1 = mulmod(u2d(a1[s].y), u2d(b1[s].y), p, pinv);
+                        d2[2 * s] = tm ? reduce_balanced(d2[2 * s] + v0, p, pinv) : v0;
+                        d2[2 * s + 1] = tm ? reduce_balanced(d2[2 * s + 1] + v1, p, pinv) : v1;
+                    }
+                }
+#pragma unroll
+                for (int s = 0; s < 4; s++) {
+                    // from the canonical representative, as when d2 comes from memory
+                    double *rr = grp + row_pair_lds(lo4, 4 * h + s);
+                    rr[0] = canon(d2[2 * s], p, pinv);
+                    rr[1] = canon(d2[2 * s + 1], p, pinv);
+                }
+            }
+            LOAD_FENCE();
+        } else {
+            ulonglong2 raw[8];
+#pragma unroll
+            for (int s = 0; s < 8; s++) {
+                if (SRC == 1) raw[s] = galois_pair_load(src, row * 256u + 32u * s + 2u * lo4, gal->g[it], LOGN);
+                else raw[s] = ((const ulonglong2 *)src + 16 * s)[pr];
+            }
+            if (SRC == 0) {
+#pragma unroll
+                for (int s = 0; s < 4; s++)
+#pragma unroll
+                    for (int b = 0; b < (1 << s); b++) tw2[(1 << s) - 1 + b] = tw[((16u * base1 + lo4) << s) + b];
+            }
+            NTT_SCHED_FENCE();
+#pragma unroll
+            for (int s = 0; s < 8; s++) {
+                double *rr = grp + row_pair_lds(lo4, s);
+                rr[0] = u2d(raw[s].x);
+                rr[1] = u2d(raw[s].y);
+            }
+            if (SRC != 0) LOAD_FENCE();
+        }
+        if (SRC != 0) {  // the source needs the registers: the first round's twiddles come after it
+#pragma unroll
+            for (int s = 0; s < 4; s++)
+#pragma unroll
+                for (int b = 0; b < (1 << s); b++) tw2[(1 << s) - 1 + b] = tw[((16u * base1 + lo4) << s) + b];
+        }
+        ROW_GROUP_SYNC();
+#pragma unroll
+        for (int e = 0; e < 16; e++) x[e] = grp[lo4 * 17 + e];
+        inv_round<RI1, false>(x, tw2, p, pinv, unused, unused);
+#pragma unroll
+        for (int e = 0; e < 16; e++) PIN_VALUE(x[e]);  // the first round is done with its twiddles before the second's arrive
+#pragma unroll
+        for (int s = 0; s < 4; s++)
+#pragma unroll
+            for (int b = 0; b < (1 << s); b++) tw1[(1 << s) - 1 + b] = tw[(base1 << s) + b];
+#pragma unroll
+        for (int e = 0; e < 16; e++) grp[lo4 * 17 + e] = x[e];
+        ROW_GROUP_SYNC();
+#pragma unroll
+        for (int e = 0; e < 16; e++) x[e] = grp[e * 17 + lo4];
+        inv_round<RI2, false>(x, tw1, p, pinv, unused, unused);
+#pragma unroll
+        for (int e = 0; e < 16; e++) {
+            x[e] = reduce_balanced(x[e], p, pinv);
+            PIN_VALUE(x[e]);
+        }
+#pragma unroll
+        for (int e = 0; e < 16; e++) grp[e * 17 + lo4] = x[e];
+    }
+    // ---- column pass, from the LDS matrix to HBM
+    {
+        double tw1[15], tw2u[15];
+        load_cols_twiddles<Q>(tw, geo.a, tw1, tw2u);
+        __syncthreads();
+        if (Q > 0) {
+#pragma unroll
+            for (int i = 0; i < 16; i++) x[i] = lds[wg_pad(Geo::G * geo.a + (i % Geo::G), geo.c0 + geo.l16 + 16 * (i / Geo::G))];
+            inv_stages<Geo::S0, Mk::I1, false>(x, tw2u, p, pinv, ninv, wlast);
+            reduce16(x, p, pinv);
+#pragma unroll
+            for (int i = 0; i < 16; i++) lds[wg_pad(Geo::G * geo.a + (i % Geo::G), geo.c0 + geo.l16 + 16 * (i / Geo::G))] = x[i];
+            __syncthreads();
+        }
+#pragma unroll
+        for (int e = 0; e < 16; e++) x[e] = lds[wg_pad(geo.r + Geo::G * e, geo.c0 + geo.c)];
+        inv_round<Mk::I2, true>(x, tw1, p, pinv, ninv, wlast);
+    }
+}
+
+// SRC (inverse only): see wg_inv_limb
+template <bool INV, int LOGN, bool P51, bool F64, int SRC = 0>
+__device__ __forceinline__ void ntt_wg_body(const NttV2Args &A, double *lds, int t, unsigned li, const GaloisTab *gal = nullptr,
+                                            const TensorSrc *ten = nullptr) {
+    BODY_TAG(P51);
+    constexpr int Q = LOGN - 12;
+    typedef ColsGeom<Q> Geo;
+    constexpr unsigned N = 1u << LOGN;
     const double p = A.modc[t].p, pinv = A.modc[t].pinv;
     const double *tw = A.tw + (size_t)t * N;
     const unsigned tid = threadIdx.x;
@@ -121,7 +242,6 @@ __device__ __forceinline__ void ntt_wg_body(const NttV2Args &A, double *lds, int
         if (F64 && A.use_fin_val) { ninv = A.fin_val.ninv; wlast = A.fin_val.wlast; cadd = A.fin_val.cadd; }
         else if (A.fin) { ninv = A.fin[li].ninv; wlast = A.fin[li].wlast; cadd = A.fin[li].cadd; }
     }
-    const WMul unused = WMul{0.0, 0.0};
     const unsigned i0 = blockIdx.y * (unsigned)A.items_per_z;
     const unsigned i1 = (i0 + A.items_per_z < (unsigned)A.items) ? i0 + A.items_per_z : (unsigned)A.items;
     for (unsigned it = i0; it < i1; it++) {
@@ -143,115 +263,11 @@ __device__ __forceinline__ void ntt_wg_body(const NttV2Args &A, double *lds, int
                 ((ulonglong2 *)dst + 16 * s)[pr] = make_ulonglong2(d2u(canon_small(rr[0], p)), d2u(canon_small(rr[1], p)));
             }
         } else {
-            // ---- row pass, from HBM into the LDS matrix
-            {
-                double tw1[15], tw2[15];
-                const unsigned base1 = N1 + row;
-                if (SRC == 2) {
-                    const size_t st = (size_t)ten->level * N / 2, it0 = (size_t)it * ten->terms * 2 * st;  // pairs between components
-                    const ulonglong2 *pa = (const ulonglong2 *)ten->a + it0 + st + (size_t)li * (N / 2);
-                    const ulonglong2 *pb = (const ulonglong2 *)ten->b + it0 + st + (size_t)li * (N / 2);
+            wg_inv_limb<LOGN, P51, SRC>(x, src, tw, lds, p, pinv, ninv, wlast, li, it, gal, ten);
 #pragma unroll
-                    for (int h = 0; h < 2; h++) {  // four pairs at a time: bounds the registers in flight
-                        double d2[8];
-                        for (int tm = 0; tm < ten->terms; tm++) {
-                            ulonglong2 a1[4], b1[4];
-#pragma unroll
-                            for (int s = 0; s < 4; s++) {
-                                a1[s] = (pa + 2 * st * tm + 16 * (4 * h + s))[pr];
-                                b1[s] = (pb + 2 * st * tm + 16 * (4 * h + s))[pr];
-                            }
-                            NTT_SCHED_FENCE();
-#pragma unroll
-                            for (int s = 0; s < 4; s++) {  // |sum| <= p/2 + 1 + 1.25p
-                                const double v0 = mulmod(u2d(a1[s].x), u2d(b1[s].x), p, pinv), v1 = mulmod(u2d(a1[s].y), u2d(b1[s].y), p, pinv);
-                                d2[2 * s] = tm ? reduce_balanced(d2[2 * s] + v0, p, pinv) : v0;
-                                d2[2 * s + 1] = tm ? reduce_balanced(d2[2 * s + 1] + v1, p, pinv) : v1;
-                            }
-                        }
-#pragma unroll
-                        for (int s = 0; s < 4; s++) {
-                            // from the canonical representative, as when d2 comes from memory
-                            double *rr = grp + row_pair_lds(lo4, 4 * h + s);
-                            rr[0] = canon(d2[2 * s], p, pinv);
-                            rr[1] = canon(d2[2 * s + 1], p, pinv);
-                        }
-                    }
-                    LOAD_FENCE();
-                } else {
-                    ulonglong2 raw[8];
-#pragma unroll
-                    for (int s = 0; s < 8; s++) {
-                        if (SRC == 1) raw[s] = galois_pair_load(src, row * 256u + 32u * s + 2u * lo4, gal->g[it], LOGN);
-                        else raw[s] = ((const ulonglong2 *)src + 16 * s)[pr];
-                    }
-                    if (SRC == 0) {
-#pragma unroll
-                        for (int s = 0; s < 4; s++)
-#pragma unroll
-                            for (int b = 0; b < (1 << s); b++) tw2[(1 << s) - 1 + b] = tw[((16u * base1 + lo4) << s) + b];
-                    }
-                    NTT_SCHED_FENCE();
-#pragma unroll
-                    for (int s = 0; s < 8; s++) {
-                        double *rr = grp + row_pair_lds(lo4, s);
-                        rr[0] = u2d(raw[s].x);
-                        rr[1] = u2d(raw[s].y);
-                    }
-                    if (SRC != 0) LOAD_FENCE();
-                }
-                if (SRC != 0) {  // the source needs the registers: the first round's twiddles come after it
-#pragma unroll
-                    for (int s = 0; s < 4; s++)
-#pragma unroll
-                        for (int b = 0; b < (1 << s); b++) tw2[(1 << s) - 1 + b] = tw[((16u * base1 + lo4) << s) + b];
-                }
-                ROW_GROUP_SYNC();
-#pragma unroll
-                for (int e = 0; e < 16; e++) x[e] = grp[lo4 * 17 + e];
-                inv_round<RI1, false>(x, tw2, p, pinv, unused, unused);
-#pragma unroll
-                for (int e = 0; e < 16; e++) PIN_VALUE(x[e]);  // the first round is done with its twiddles before the second's arrive
-#pragma unroll
-                for (int s = 0; s < 4; s++)
-#pragma unroll
-                    for (int b = 0; b < (1 << s); b++) tw1[(1 << s) - 1 + b] = tw[(base1 << s) + b];
-#pragma unroll
-                for (int e = 0; e < 16; e++) grp[lo4 * 17 + e] = x[e];
-                ROW_GROUP_SYNC();
-#pragma unroll
-                for (int e = 0; e < 16; e++) x[e] = grp[e * 17 + lo4];
-                inv_round<RI2, false>(x, tw1, p, pinv, unused, unused);
-#pragma unroll
-                for (int e = 0; e < 16; e++) {
-                    x[e] = reduce_balanced(x[e], p, pinv);
-                    PIN_VALUE(x[e]);
-                }
-#pragma unroll
-                for (int e = 0; e < 16; e++) grp[e * 17 + lo4] = x[e];
-            }
-            // ---- column pass, from the LDS matrix to HBM
-            {
-                double tw1[15], tw2u[15];
-                load_cols_twiddles<Q>(tw, geo.a, tw1, tw2u);
-                __syncthreads();
-                if (Q > 0) {
-#pragma unroll
-                    for (int i = 0; i < 16; i++) x[i] = lds[wg_pad(Geo::G * geo.a + (i % Geo::G), geo.c0 + geo.l16 + 16 * (i / Geo::G))];
-                    inv_stages<Geo::S0, Mk::I1, false>(x, tw2u, p, pinv, ninv, wlast);
-                    reduce16(x, p, pinv);
-#pragma unroll
-                    for (int i = 0; i < 16; i++) lds[wg_pad(Geo::G * geo.a + (i % Geo::G), geo.c0 + geo.l16 + 16 * (i / Geo::G))] = x[i];
-                    __syncthreads();
-                }
-#pragma unroll
-                for (int e = 0; e < 16; e++) x[e] = lds[wg_pad(geo.r + Geo::G * e, geo.c0 + geo.c)];
-                inv_round<Mk::I2, true>(x, tw1, p, pinv, ninv, wlast);
-#pragma unroll
-                for (int e = 0; e < 16; e++) {
-                    const double v = canon(x[e] + cadd, p, pinv);
-                    scalar_base(dst + Geo::G * 256u * e)[voff] = F64 ? (u64d)__double_as_longlong(v) : d2u(v);
-                }
+            for (int e = 0; e < 16; e++) {
+                const double v = canon(x[e] + cadd, p, pinv);
+                scalar_base(dst + Geo::G * 256u * e)[voff] = F64 ? (u64d)__double_as_longlong(v) : d2u(v);
             }
         }
         __syncthreads();  // the matrix is free for the next item

@@ -281,3 +281,10 @@ def test_emulated_key_switch_on_chip(be, shape, batch):
         pc.case_relin_and_composite(be, shape, seed=170, batch=batch, levels=[level, level - 1])
         pc.case_rotate(be, shape, seed=171, rotations=[1, 1000], batch=batch, level=level - 1)
         pc.case_sum_of_products(be, shape, seed=172, terms=3, batch=1, levels=[level])
+
+
+@pytest.mark.parametrize("shape,batch", [((12, 4, 51, 3, 51, 3), 2), ((12, 3, 50, 1, 51, 1), 1), ((13, 3, 51, 1, 51, 1), 2), ((14, 3, 50, 1, 51, 1), 1)])
+def test_emulated_tail_on_chip(be, shape, batch):
+    """ModDown followed by rescale without an intermediate: one to three special primes, whole rings and halves"""
+    with be.tuned(64):
+        pc.case_relin_and_composite(be, shape, seed=180, batch=batch, levels=[shape[1], 2])

@@ -707,3 +707,11 @@ def test_key_switch_on_chip(be, shape, batch, level):
     be.torch.cuda.synchronize()
     assert "inner_wg_kernel" in ctx.profile_read()
     ctx.close()
+
+
+@pytest.mark.parametrize("shape,batch,level", [((12, 7, 50, 3, 51, 3), 16, 6), ((12, 4, 51, 2, 51, 2), 17, 4), ((13, 5, 51, 1, 51, 1), 32, 5),
+                                               ((14, 4, 50, 1, 51, 1), 33, 4), ((14, 3, 51, 1, 51, 1), 32, 2)])
+def test_tail_on_chip(be, shape, batch, level):
+    """ModDown followed by rescale without an intermediate, at the smallest batches that take it"""
+    announce("tail on chip %r batch %d" % (shape, batch))
+    pc.case_relin_and_composite(be, shape, seed=350, batch=batch, levels=[level])
