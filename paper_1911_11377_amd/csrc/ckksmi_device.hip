@@ -266,7 +266,7 @@ void launch_modup_cols(ckksmi_ctx *c, int mode, const u64 *y, size_t y_stride, u
         if (mode == 0) KL(c, kid, units, (modup_cols_kernel<Q, NS, 0>), grid, block, st, A);                 \
         else if (mode == 2) KL(c, kid, units, (modup_cols_kernel<Q, NS, 2>), grid, block, st, A);            \
         else if (mode == 3) KL(c, kid, units, (modup_cols_kernel<Q, NS, 3>), grid, block, st, A);            \
-        else if constexpr (NS > 1 || Q == 4) KL(c, kid, units, (modup_cols_kernel<Q, NS, 1>), grid, block, st, A); \
+        else if constexpr (NS > 1 || Q >= 2) KL(c, kid, units, (modup_cols_kernel<Q, NS, 1>), grid, block, st, A); \
         break;
     switch ((c->logN - 12) * 8 + nsrc) {
         MODUP_COLS_CASE(0, 1) MODUP_COLS_CASE(0, 2) MODUP_COLS_CASE(0, 3) MODUP_COLS_CASE(0, 4)
@@ -306,9 +306,14 @@ void launch_rows_final(ckksmi_ctx *c, const u64 *tmpA, const u64 *x, size_t x_ro
         KL(c, CKKSMI_K_ROWS_FINAL, (double)rows * nz, rows_final_kernel, dim3(xch, tiles, nz), dim3(V2_THREADS), st, A);
 }
 
-// Which kept limbs' division runs as ONE kernel after the inverse transform of the dropped limbs (ks_wg.h): one source
-// (rescale, or ModDown with one special prime) at every register-tiled size.
-inline bool conv_final_ok(const ckksmi_ctx *c, int nsrc) { return c->fused && nsrc == 1; }
+// Which divisions run as ONE kernel after the inverse transform of the dropped limb (ks_wg.h): one source (rescale, or ModDown with
+// one special prime), and from N = 2^14 on enough kept limbs.  Few limbs of a large ring are faster on the register-tiled kernels, whose
+// workgroups have shorter chains: rotations of one ciphertext at N = 2^15 with 16 limbs 52.0 against 54.0 us, at N = 2^16 with 16
+// limbs 62.8 against 67.4 and with 42 limbs even; 70 limbs at N = 2^15 already 1.02 x the other way.
+inline bool conv_final_ok(const ckksmi_ctx *c, int nsrc, int rows, int nc) {
+    const size_t limbs = (size_t)rows * nc, fill = (size_t)c->ntt_target_wgs / 128;  // 64
+    return c->fused && nsrc == 1 && (c->logN <= 13 || limbs >= (c->logN == 14 ? fill / 2 : fill));
+}
 
 // y: the dropped limbs in coefficient form as canonical doubles, row r at y + r*y_stride; fin_kind as conv_final_body's FIN
 void launch_conv_final(ckksmi_ctx *c, int fin_kind, const u64 *y, size_t y_stride, const DivRoundDev &D, const u64 *x, size_t x_row_stride,
@@ -371,7 +376,7 @@ void divround_rows(ckksmi_ctx *c, const DivRoundDev &D, const FinConst *fin, con
                    u64 *b_scratch, size_t bs_stride, const u64 *x, size_t x_stride, u64 *tmp, int nc, int rows, const u64 *addend,
                    size_t add_item_stride, size_t add_comp_stride, int add_both, u64 *out, hipStream_t st, bool zsub = false,
                    const RowsFinalGal *gal = nullptr) {
-    if (conv_final_ok(c, D.nb) && !add_both) {
+    if (conv_final_ok(c, D.nb, rows, nc) && !add_both) {
         launch_ntt(c, false, b_limbs, b_scratch, table_map(bidx, D.nb, b_stride, bs_stride), rows, st, fin, 3, nullptr, true);
         launch_conv_final(c, zsub ? 1 : (gal ? 3 : 0), b_scratch, bs_stride, D, x, x_stride, addend, add_item_stride, add_comp_stride, out, nc, rows, st, gal);
         return;
@@ -662,8 +667,8 @@ void scalar_rescale_fused(ckksmi_ctx *c, const u64 *a, int64_t v, const u64 *add
     F.cadd = (double)((q - 1) / 2);
     F.pad = 0.0;
     const ScalarTab St = scalar_tab(c, v, level);
-    if (c->logN == 16) {
-        // the register-tiled pair: the GPU parity test of the activation schedule at its full size checks that it runs here
+    if (c->logN == 16 || !conv_final_ok(c, 1, rows, last)) {
+        // (at N = 2^16 always: the GPU parity test of the activation schedule at its full size checks that this pair runs)
         u64 *tmp = lastbuf + (size_t)rows * N;
         launch_ntt(c, false, a + (size_t)last * N, lastbuf, table_map(lidx, 1, in_stride, N), rows, st, c->d_fin_rescale + last, 2);
         launch_modup_cols(c, 1, lastbuf, N, tmp, rows, 0, last, &D, (double)rows * last, st, c->d_fin_rescale + last, nullptr, &F);

@@ -260,16 +260,13 @@ def test_emulated_single_image_network(be):
 
 
 @pytest.mark.parametrize("logN,bits", [(12, 50), (13, 51), (14, 50), (15, 51), (16, 50), (16, 51)])
-@pytest.mark.parametrize("tuned", [None, 8])
+@pytest.mark.parametrize("tuned", [512, 8])
 def test_emulated_one_source_division(be, logN, bits, tuned):
     """rescale, rescale of a scalar multiple (with a drop and an addend) on the kernel that keeps the converted limb on chip:
-    every block size, coarse blocks (tuned) and fine ones, 50- and 51-bit reduction schedules"""
+    every block size, coarse blocks (8 workgroups are enough) and fine ones (512), 50- and 51-bit reduction schedules"""
     shape = (logN, 3, bits, 0, 51, 1)
-    if tuned:
-        with be.tuned(tuned):
-            pc.case_rescale(be, shape, seed=140 + logN, batch=1 if logN > 14 else 5, levels=[3])
-    else:
-        pc.case_rescale(be, shape, seed=150 + logN, batch=1, levels=[3, 2])
+    with be.tuned(tuned):
+        pc.case_rescale(be, shape, seed=140 + logN, batch=1 if logN > 14 or tuned > 8 else 5, levels=[3, 2])
 
 
 @pytest.mark.parametrize("shape,batch", [((12, 5, 51, 2, 51, 2), 2), ((12, 4, 50, 1, 51, 1), 9), ((12, 7, 50, 3, 51, 3), 1), ((13, 3, 50, 1, 51, 1), 3)])

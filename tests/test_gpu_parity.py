@@ -681,7 +681,7 @@ def test_variant_entry_points_refuse_bad_arguments(be):
     pc.case_variant_errors(be)
 
 
-@pytest.mark.parametrize("logN,bits,batch", [(12, 51, 9), (13, 50, 5), (14, 50, 2), (14, 51, 23), (15, 51, 2), (15, 50, 23), (16, 51, 5)])
+@pytest.mark.parametrize("logN,bits,batch", [(12, 51, 9), (13, 50, 5), (14, 50, 2), (14, 50, 6), (14, 51, 23), (15, 51, 2), (15, 51, 11), (15, 50, 23), (16, 51, 11)])
 def test_one_source_division(be, logN, bits, batch):
     """rescale and rescale of a scalar multiple with the converted limb on chip: every block size (few and many workgroups),
     rows that do not divide evenly over the XCDs, both reduction schedules"""
