@@ -40,8 +40,8 @@ extern "C" {
 #define CKKSMI_K_CONV_COLS_RESCALE 17 /* the same with a single dropped prime (rescale) */
 #define CKKSMI_K_MAC_MFMA 18      /* conv / FC multiply-accumulate on the matrix cores */
 #define CKKSMI_K_MACPREP_MFMA 19  /* its weight digits and tap table */
-#define CKKSMI_K_NTT_LDS 20       /* whole limb transform inside one workgroup's LDS */
-#define CKKSMI_K_TENSOR_ROWS 21   /* tensor product fused with the inverse contiguous pass of its third component */
+#define CKKSMI_K_NTT_LDS 20       /* whole limb transform inside one workgroup's LDS (also the sources of a product's tail) */
+#define CKKSMI_K_TENSOR_ROWS 21   /* tensor product fused with the inverse contiguous pass (small rings: whole inverse transform) of its third component */
 #define CKKSMI_K_AXPY_LIMB 22     /* one limb of every row += constant * another limb (merged division: P*d on the dropped q) */
 #define CKKSMI_K_CONV_COLS_MERGED 23 /* the conversion kernel in the exact form of DivRound, sources {q_last, special primes} */
 #define CKKSMI_K_INNER_HOISTED 24 /* inner product of hoisted rotations (gathers the lifted digits through each automorphism) */

@@ -1,4 +1,4 @@
-// DivRound without an intermediate in memory (2^12 <= N <= 2^16, one dropped prime): conversion, forward transform and last
+// DivRound without an intermediate in memory (2^12 <= N <= 2^16, one dropped prime, and a product's tail): conversion, forward transform, last
 // step of a kept limb in ONE workgroup.
 //
 // The register-tiled pair modup_cols_kernel / rows_final_kernel (ks_fused.h) writes every converted limb after the column
