@@ -252,7 +252,7 @@ __global__ __launch_bounds__((1 << LOGN) / 16) void tail_sources_kernel(TailSour
         else wg_inv_limb<LOGN, false, 0>(x, limb, A.tw_inv + (size_t)t * N, lds, p, pinv, F.ninv, F.wlast, 0, 0, nullptr, nullptr);
         if (m) {
 #pragma unroll
-            for (int e = 0; e < 16; e++) ((double *)scalar_base(limb + Geo::G * 256u * e))[voff] = canon(x[e] + F.cadd, p, pinv);
+            for (int e = 0; e < 16; e++) scalar_base((double *)limb + Geo::G * 256u * e)[voff] = canon(x[e] + F.cadd, p, pinv);
         } else {
             const double hA = A.D.hc[t];
             const WMul Pinv = A.D.Binv[t];
@@ -263,12 +263,12 @@ __global__ __launch_bounds__((1 << LOGN) / 16) void tail_sources_kernel(TailSour
                 const WMul W = A.D.conv[(size_t)a * A.T + t];
                 const u64d *y = bl + (size_t)(a + 1) * N;
 #pragma unroll
-                for (int e = 0; e < 16; e++) v[e] += mulmod_w(((const double *)scalar_base(y + Geo::G * 256u * e))[voff], W.w, W.wp, p);  // <= p + 3 * 0.75p
+                for (int e = 0; e < 16; e++) v[e] += mulmod_w(scalar_base((const double *)y + Geo::G * 256u * e)[voff], W.w, W.wp, p);  // <= p + 3 * 0.75p
             }
 #pragma unroll
             for (int e = 0; e < 16; e++) {
                 const double s = canon(x[e] + F.cadd, p, pinv) - mulmod_w(reduce_balanced(v[e], p, pinv), Pinv.w, Pinv.wp, p);  // (-0.75p, 1.75p)
-                ((double *)scalar_base(limb + Geo::G * 256u * e))[voff] = canon(s + A.hb2, p, pinv);
+                scalar_base((double *)limb + Geo::G * 256u * e)[voff] = canon(s + A.hb2, p, pinv);
             }
         }
         __syncthreads();  // the matrix is free for the next limb

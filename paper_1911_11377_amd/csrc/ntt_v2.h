@@ -48,8 +48,13 @@
 
 // What the compiler has to be told to stay within a kernel's registers (all empty on the CPU stand-in):
 //   PIN_VALUE(x)    x is computed before the next pinned point and not sunk below later loads;
-//   scalar_base(p)  a workgroup-uniform address stays in scalar registers, so that the loads from p[thread offset] need no
-//                   64-bit vector additions each;
+//   scalar_base(p)  a workgroup-uniform address of global memory stays in scalar registers: the accesses p[thread offset] are
+//                   global ones with a scalar base and one 32-bit offset per thread.  The global address space is part of
+//                   what is returned: a generic pointer that comes out of an asm statement makes flat accesses, which take
+//                   no scalar base (one 64-bit vector addition each) and are counted as LDS accesses too, so that all of them
+//                   arrive before the first is used.  8 limbs of 2^13 words forward 9.5 us with flat, 9.1 with global
+//                   accesses; rescale of 256 ciphertexts at N = 2^14, 8 primes 335 and 321 us, N = 2^15, 16 primes, 448
+//                   ciphertexts 2503 and 2469 us;
 //   WG_UNIFORM(v)   a workgroup-uniform value goes to a scalar register;
 //   LOAD_FENCE()    memory accesses stay on their side.
 #ifdef CKKSMI_EMULATE
@@ -61,9 +66,10 @@ template <class T> __device__ __forceinline__ T *scalar_base(T *p) { return p; }
 #define PIN_VALUE(x) asm volatile("" : "+v"(x))
 #define LOAD_FENCE() asm volatile("" ::: "memory")
 #define WG_UNIFORM(v) ((unsigned)__builtin_amdgcn_readfirstlane((int)(v)))
-template <class T> __device__ __forceinline__ T *scalar_base(T *p) {
-    asm volatile("" : "+s"(p));
-    return p;
+template <class T> __device__ __forceinline__ __attribute__((address_space(1))) T *scalar_base(T *p) {
+    auto g = (__attribute__((address_space(1))) T *)p;
+    asm volatile("" : "+s"(g));
+    return g;
 }
 #endif
 
