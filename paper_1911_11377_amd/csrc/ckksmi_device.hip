@@ -334,7 +334,13 @@ void launch_conv_final(ckksmi_ctx *c, int fin_kind, const u64 *y, size_t y_strid
     // N = 2^15, 30 limbs: 20.4 and 15.8).
     int S = c->logN == 12 ? 0 : (c->logN == 16 ? 2 : 1);
     if ((c->logN == 14 || c->logN == 15) && (size_t)rows * nc * 2 < (size_t)c->ntt_target_wgs / 32 /* 256 */) S = 2;
+    // Rows dealt to the eight XCDs leave some of them one row more than the others.  Where that costs a workgroup per compute unit (256
+    // of them, 32 on an XCD) and the rows are few, consecutive workgroups take all rows in turn instead: evenly shared, every XCD
+    // reads every source.  Rescale at N = 2^16, 10 rows of 23 kept limbs: 156 us dealt, 111 in turn (136 as two kernels); 20 of 11: 132 and 107;
+    // N = 2^15, 10 of 11: 47 and 37.  Many rows no longer fit the L2s together: N = 2^16, 42 rows of 7: 186 dealt, 193 in turn.
     A.rows_x = std::min(8, rows);
+    const size_t per_row = (size_t)nc << S;
+    if (rows < 32 && (rows * per_row + 255) / 256 < ((rows + 7) / 8 * per_row + 31) / 32) A.rows_x = rows;
     const int per = (rows + A.rows_x - 1) / A.rows_x, groups = (per + 7) / 8;
     A.rows_g = (per + groups - 1) / groups;
     const size_t wgs = (size_t)A.rows_x * ((size_t)1 << S) * A.rows_g * nc * groups;

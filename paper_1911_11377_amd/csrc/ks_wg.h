@@ -36,7 +36,8 @@ struct ConvFinalArgs {
 
 // Workgroup order.  Consecutive workgroup ids go to the 8 XCDs in turn, and every XCD has its own L2 (4 MB).  Rows are dealt to
 // the XCDs round-robin; an XCD takes its rows in groups of rows_g (at most 8) and walks the kept limbs over a group, so
-// that the group's sources (rows_g limbs) and the current limb's twiddle table stay in its L2.
+// that the group's sources (rows_g limbs) and the current limb's twiddle table stay in its L2.  A few rows that do not divide
+// evenly over the XCDs form one group of rows_x = rows instead (rows_g = 1): consecutive workgroups take them in turn.
 __device__ __forceinline__ bool conv_final_place(const ConvFinalArgs &A, int S, unsigned &row, unsigned &blk, int &limb) {
     const unsigned X = (unsigned)A.rows_x, G = (unsigned)A.rows_g, nc = (unsigned)A.F.nc;
     unsigned k = blockIdx.x / X;

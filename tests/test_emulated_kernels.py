@@ -285,3 +285,10 @@ def test_emulated_tail_on_chip(be, shape, batch):
     """ModDown followed by rescale without an intermediate: one to three special primes, whole rings and halves"""
     with be.tuned(64):
         pc.case_relin_and_composite(be, shape, seed=180, batch=batch, levels=[shape[1], 2])
+
+
+@pytest.mark.parametrize("shape,batch", [((12, 12, 50, 0, 51, 1), 9), ((13, 8, 51, 0, 52, 1), 9), ((12, 3, 50, 0, 51, 1), 17)])
+def test_emulated_one_source_division_uneven_rows(be, shape, batch):
+    """rows that do not divide evenly over the XCDs: few with many kept limbs (all taken in turn), few with few limbs and more of
+    them (dealt to the XCDs, the last row of some missing)"""
+    pc.case_rescale(be, shape, seed=150, batch=batch, levels=[shape[1]])

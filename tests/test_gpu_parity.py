@@ -715,3 +715,11 @@ def test_tail_on_chip(be, shape, batch, level):
     """ModDown followed by rescale without an intermediate, at the smallest batches that take it"""
     announce("tail on chip %r batch %d" % (shape, batch))
     pc.case_relin_and_composite(be, shape, seed=350, batch=batch, levels=[level])
+
+
+@pytest.mark.parametrize("shape,batch,level", [((12, 12, 50, 0, 51, 1), 9, 12), ((13, 8, 51, 0, 52, 1), 9, 8), ((14, 6, 50, 0, 51, 1), 5, 6),
+                                               ((15, 12, 51, 0, 52, 1), 5, 12), ((16, 8, 50, 0, 51, 1), 9, 8)])
+def test_one_source_division_uneven_rows(be, shape, batch, level):
+    """a few rows that do not divide evenly over the XCDs: workgroups take all rows in turn"""
+    announce("one-source division, uneven rows %r batch %d" % (shape, batch))
+    pc.case_rescale(be, shape, seed=360, batch=batch, levels=[level])
