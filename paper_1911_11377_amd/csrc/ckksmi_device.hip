@@ -350,7 +350,7 @@ void launch_conv_final(ckksmi_ctx *c, int fin_kind, const u64 *y, size_t y_strid
     case LN * 4 + SS:                                                                                                                         \
         if (fin_kind == 0) KL(c, CKKSMI_K_CONV_FINAL, units, (conv_final_kernel<LN - SS, SS, 1, 0>), grid, block, st, A);                 \
         else if (fin_kind == 1) KL(c, CKKSMI_K_CONV_FINAL, units, (conv_final_kernel<LN - SS, SS, 1, 1>), grid, block, st, A);            \
-        else if (fin_kind == 2) { if constexpr (LN < 16) KL(c, CKKSMI_K_CONV_FINAL, units, (conv_final_scalar_kernel<LN - SS, SS>), grid, block, st, A, *stab); } \
+        else if (fin_kind == 2) KL(c, CKKSMI_K_CONV_FINAL, units, (conv_final_scalar_kernel<LN - SS, SS>), grid, block, st, A, *stab);    \
         else KL(c, CKKSMI_K_CONV_FINAL, units, (conv_final_gal_kernel<LN - SS, SS, 1>), grid, block, st, A, *gal);                        \
         break;
     if (fin_kind == 4) {  // sizes of tail_wg_ok
@@ -673,8 +673,7 @@ void scalar_rescale_fused(ckksmi_ctx *c, const u64 *a, int64_t v, const u64 *add
     F.cadd = (double)((q - 1) / 2);
     F.pad = 0.0;
     const ScalarTab St = scalar_tab(c, v, level);
-    if (c->logN == 16 || !conv_final_ok(c, 1, rows, last)) {
-        // (at N = 2^16 always: the GPU parity test of the activation schedule at its full size checks that this pair runs)
+    if (!conv_final_ok(c, 1, rows, last)) {
         u64 *tmp = lastbuf + (size_t)rows * N;
         launch_ntt(c, false, a + (size_t)last * N, lastbuf, table_map(lidx, 1, in_stride, N), rows, st, c->d_fin_rescale + last, 2);
         launch_modup_cols(c, 1, lastbuf, N, tmp, rows, 0, last, &D, (double)rows * last, st, c->d_fin_rescale + last, nullptr, &F);

@@ -269,6 +269,33 @@ def case_rescale(be, shape, seed, batch=2, levels=None):
     ctx.close()
 
 
+def case_division_route(be, shape, seed, batch, level, one_kernel, sample=None, fresh_scalar=-99991):
+    """rescale and rescale of a scalar multiple, word for word for the items in `sample`, each by one kernel per kept limb
+    (conv_final_kernel) or by the pair of register-tiled kernels, as the caller expects"""
+    M = make_material(shape, seed)
+    O = M.O
+    ctx = be.context(*shape)
+    a = random_cts(M, level, batch, seed, ("route", level))
+    da = be.to_dev(a)
+    pair = "modup_cols_kernel<%d, 1, 1>" % (shape[0] - 12)
+    for name, op in (("rescale", ckksmi.OP_RESCALE), ("scalar rescale", ckksmi.OP_MUL_SCALAR_RESCALE)):
+        out = be.empty(batch, 2, level - 1, O.N)
+        ws = be.ws(ctx.workspace_bytes(op, level, batch))
+        ctx.profile_enable(True)
+        if op == ckksmi.OP_RESCALE:
+            ctx.rescale(da, out, level, batch, ws, stream=be.stream)
+        else:
+            ctx.mul_scalar_rescale(da, fresh_scalar, out, level, batch, ws, stream=be.stream)
+        got = be.to_host(out).reshape(batch, 2, level - 1, O.N)
+        ran = ctx.profile_read()
+        ctx.profile_enable(False)
+        assert ("conv_final_kernel" in ran, pair in ran) == (one_kernel, not one_kernel), (name, shape, batch, level, sorted(ran))
+        for i in sample or range(batch):
+            x = a[i] if op == ckksmi.OP_RESCALE else O.mul_scalar(a[i], fresh_scalar, level)
+            assert np.array_equal(got[i], O.rescale(x, level)), "%s of item %d differs" % (name, i)
+    ctx.close()
+
+
 def case_relin_and_composite(be, shape, seed, batch=2, levels=None, small_ws=False):
     M = make_material(shape, seed)
     O = M.O

@@ -292,3 +292,11 @@ def test_emulated_one_source_division_uneven_rows(be, shape, batch):
     """rows that do not divide evenly over the XCDs: few with many kept limbs (all taken in turn), few with few limbs and more of
     them (dealt to the XCDs, the last row of some missing)"""
     pc.case_rescale(be, shape, seed=150, batch=batch, levels=[shape[1]])
+
+
+def test_emulated_division_route(be):
+    """rescale and rescale of a scalar multiple at one size take the same kernels, also at N = 2^16"""
+    with be.tuned(512):  # four kept limbs are enough
+        pc.case_division_route(be, (16, 3, 50, 0, 51, 1), seed=155, batch=1, level=3, one_kernel=True)
+        pc.case_division_route(be, (15, 3, 51, 0, 52, 1), seed=156, batch=1, level=3, one_kernel=True)
+        pc.case_division_route(be, (15, 3, 51, 0, 52, 1), seed=157, batch=1, level=2, one_kernel=False)

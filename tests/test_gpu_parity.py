@@ -616,7 +616,7 @@ def test_activation_schedule_full_size_sampled(be):
     and decrypt to the float polynomial within 1e-3"""
     announce("activation schedule N=2^16 level 24 batch 64, sampled parity")
     pc.case_activation(be, C4, seed=7, level=24, batch=64, sample=[0, 33, 63], workers=3,
-                       expect_kernels=("modup_cols_kernel<4, 4, 3>", "modup_cols_kernel<4, 1, 1>", "tensor_rows_kernel"))
+                       expect_kernels=("modup_cols_kernel<4, 4, 3>", "conv_final_kernel", "tensor_rows_kernel"))
 
 
 def test_step_replays_from_a_captured_graph(be):
@@ -723,3 +723,12 @@ def test_one_source_division_uneven_rows(be, shape, batch, level):
     """a few rows that do not divide evenly over the XCDs: workgroups take all rows in turn"""
     announce("one-source division, uneven rows %r batch %d" % (shape, batch))
     pc.case_rescale(be, shape, seed=360, batch=batch, levels=[level])
+
+
+@pytest.mark.parametrize("shape,batch,level,one_kernel", [((14, 6, 50, 0, 51, 1), 2, 6, False), ((14, 6, 50, 0, 51, 1), 4, 6, True),
+                                                          ((15, 12, 50, 0, 51, 1), 2, 12, False), ((15, 12, 50, 0, 51, 1), 3, 12, True),
+                                                          ((16, 12, 51, 0, 52, 1), 2, 12, False), ((16, 12, 51, 0, 52, 1), 4, 12, True)])
+def test_division_route(be, shape, batch, level, one_kernel):
+    """rescale and rescale of a scalar multiple on either side of the number of kept limbs that the one kernel needs"""
+    announce("division route %r batch %d" % (shape, batch))
+    pc.case_division_route(be, shape, seed=365, batch=batch, level=level, one_kernel=one_kernel, sample=[0, batch - 1])
