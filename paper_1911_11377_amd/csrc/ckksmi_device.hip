@@ -310,9 +310,18 @@ void launch_rows_final(ckksmi_ctx *c, const u64 *tmpA, const u64 *x, size_t x_ro
 // one special prime), and from N = 2^14 on enough kept limbs.  Few limbs of a large ring are faster on the register-tiled kernels, whose
 // workgroups have shorter chains: rotations of one ciphertext at N = 2^15 with 16 limbs 52.0 against 54.0 us, at N = 2^16 with 16
 // limbs 62.8 against 67.4 and with 42 limbs even; 70 limbs at N = 2^15 already 1.02 x the other way.
+// At N = 2^16 a workgroup of 1024 threads has a compute unit to itself and 64 limbs are one workgroup on each, about 30 us, where the
+// register-tiled pair takes 22 us and 0.52 us a limb: a last round of workgroups that is nearly empty loses (kept limbs, pair against
+// one kernel: 66 59.7 and 61.2 us, 78 60.6 and 63.4, 84 68.0 and 60.6, 130 81 and 85, 150 92 and 88, 264 even).  With a single kept limb a row the dropped limb
+// is half of the work, and one kernel wins in a few full rounds only (72 rows 67 and 80 us, 128 113 and 107, 160 137 and 142, 400 342 and 366).
 inline bool conv_final_ok(const ckksmi_ctx *c, int nsrc, int rows, int nc) {
     const size_t limbs = (size_t)rows * nc, fill = (size_t)c->ntt_target_wgs / 128;  // 64
-    return c->fused && nsrc == 1 && (c->logN <= 13 || limbs >= (c->logN == 14 ? fill / 2 : fill));
+    if (!c->fused || nsrc != 1) return false;
+    if (c->logN <= 13) return true;
+    if (c->logN < 16) return limbs >= (c->logN == 14 ? fill / 2 : fill);
+    const size_t rounds = fill ? (limbs + fill - 1) / fill : 0;
+    if (limbs < fill) return false;
+    return nc > 1 ? 32 * limbs + 18 * fill >= 29 * fill * rounds : rounds <= 4 && 8 * limbs >= 7 * fill * rounds;
 }
 
 // y: the dropped limbs in coefficient form as canonical doubles, row r at y + r*y_stride; fin_kind as conv_final_body's FIN

@@ -300,3 +300,13 @@ def test_emulated_division_route(be):
         pc.case_division_route(be, (16, 3, 50, 0, 51, 1), seed=155, batch=1, level=3, one_kernel=True)
         pc.case_division_route(be, (15, 3, 51, 0, 52, 1), seed=156, batch=1, level=3, one_kernel=True)
         pc.case_division_route(be, (15, 3, 51, 0, 52, 1), seed=157, batch=1, level=2, one_kernel=False)
+
+
+def test_emulated_division_route_last_round(be):
+    """N = 2^16: a last round of workgroups that is nearly empty keeps the pair of kernels; with a single kept limb a row also one
+    that is half full"""
+    with be.tuned(2048):  # sixteen kept limbs are a round
+        pc.case_division_route(be, (16, 4, 50, 0, 51, 1), seed=158, batch=3, level=4, one_kernel=False, sample=[2])  # 18
+    with be.tuned(512):  # four
+        pc.case_division_route(be, (16, 2, 50, 0, 51, 1), seed=159, batch=3, level=2, one_kernel=False, sample=[2])  # 6
+        pc.case_division_route(be, (16, 2, 50, 0, 51, 1), seed=160, batch=4, level=2, one_kernel=True, sample=[3])   # 8

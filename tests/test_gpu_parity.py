@@ -727,8 +727,10 @@ def test_one_source_division_uneven_rows(be, shape, batch, level):
 
 @pytest.mark.parametrize("shape,batch,level,one_kernel", [((14, 6, 50, 0, 51, 1), 2, 6, False), ((14, 6, 50, 0, 51, 1), 4, 6, True),
                                                           ((15, 12, 50, 0, 51, 1), 2, 12, False), ((15, 12, 50, 0, 51, 1), 3, 12, True),
-                                                          ((16, 12, 51, 0, 52, 1), 2, 12, False), ((16, 12, 51, 0, 52, 1), 4, 12, True)])
+                                                          ((16, 12, 51, 0, 52, 1), 2, 12, False), ((16, 12, 51, 0, 52, 1), 4, 12, True),
+                                                          ((16, 12, 51, 0, 52, 1), 3, 12, False), ((16, 2, 50, 0, 51, 1), 40, 2, False), ((16, 2, 50, 0, 51, 1), 64, 2, True)])
 def test_division_route(be, shape, batch, level, one_kernel):
-    """rescale and rescale of a scalar multiple on either side of the number of kept limbs that the one kernel needs"""
+    """rescale and rescale of a scalar multiple on either side of the number of kept limbs that the one kernel needs; at
+    N = 2^16 also 66 limbs (a second round of workgroups with next to nothing in it) and a single kept limb a row"""
     announce("division route %r batch %d" % (shape, batch))
     pc.case_division_route(be, shape, seed=365, batch=batch, level=level, one_kernel=one_kernel, sample=[0, batch - 1])
