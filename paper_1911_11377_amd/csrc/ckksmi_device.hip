@@ -540,11 +540,13 @@ void launch_inner_wg(ckksmi_ctx *c, const RowsInnerArgs &R, const KeyTab &K, con
 // ModDown followed by rescale with the converted limbs on chip (tail_sources_kernel, conv_final_kernel): one workgroup per row makes
 // the k + 1 sources one after the other, then one per kept limb (block) the rest.  Products at 8 primes, against three kernels:
 // N = 2^12 1.05 - 1.16 x from one item on (with k = 3 from 32 rows on: 4 rows 0.93 x, 128 rows 1.15 x); N = 2^13 and 2^14 from 64 rows on
-// 1.07 and 1.03 - 1.07 x (2 rows 0.95 and 0.68 x: few compute units, each with a long chain).  More special primes at N > 2^12
-// would convert every source word twice (two blocks).
-inline bool tail_wg_ok(const ckksmi_ctx *c, int rows) {
+// 1.07 and 1.03 - 1.07 x (2 rows 0.95 and 0.68 x: few compute units, each with a long chain).  At N = 2^14 the row's chain also has to be
+// made up for by its kept limbs: from 160 of them on (64 rows of 1 77 against 91 us, of 2 104 and 114, of 3 145 and 146, of 7 368 and 346; 88 rows of
+// 2 142 and 139, 128 rows of 1 115 and 121).  More special primes at N > 2^12 would convert every source word twice (two blocks).
+inline bool tail_wg_ok(const ckksmi_ctx *c, int rows, int nc) {
     const int fill = c->ntt_target_wgs / 128;  // 64
-    return (c->logN == 12 && (c->k == 1 || rows >= fill / 2)) || ((c->logN == 13 || c->logN == 14) && c->k == 1 && rows >= fill);
+    if (c->logN == 12) return c->k == 1 || rows >= fill / 2;
+    return c->k == 1 && rows >= fill && (c->logN == 13 || (c->logN == 14 && 2 * (size_t)rows * nc >= 5 * (size_t)fill));
 }
 void launch_tail_sources(ckksmi_ctx *c, u64 *bl, size_t row_stride, int level, int rows, const FinConst *fin, const DivRoundDev &DB, hipStream_t st) {
     TailSourcesArgs A;
@@ -641,7 +643,7 @@ void ks_core_fused(ckksmi_ctx *c, const u64 *d_eval, size_t d_stride, const KeyT
         D3.b_idx[0] = last;
         for (int m = 0; m < c->k; m++) D3.b_idx[1 + m] = c->n_q + m;
         const FinConst *ft = c->d_fin_tail + (size_t)level * CKKSMI_MAX_SPECIAL;
-        if (tail_wg_ok(c, rows)) {
+        if (tail_wg_ok(c, rows, last)) {
             launch_tail_sources(c, bl, (size_t)E * N, level, rows, ft, DB, st);
             launch_conv_final(c, 4, bl, (size_t)E * N, c->divround[0], acc, (size_t)E * N, nullptr, 0, 0, out, last, rows, st, nullptr, nullptr, &DB);
             return;

@@ -296,6 +296,27 @@ def case_division_route(be, shape, seed, batch, level, one_kernel, sample=None, 
     ctx.close()
 
 
+def case_product_route(be, shape, seed, batch, level, expect=(), absent=(), sample=None, merged=False):
+    """the composite product, word for word for the items in `sample`, by kernels among which are those in `expect` and none in `absent`"""
+    M = make_material(shape, seed)
+    O = M.O
+    ctx = be.context(*shape)
+    a, b = random_cts(M, level, batch, seed, ("pa", level)), random_cts(M, level, batch, seed, ("pb", level))
+    out = be.empty(batch, 2, level - 1, O.N)
+    ws = be.ws(ctx.workspace_bytes(ckksmi.OP_HMUL_RELIN_RESCALE, level, batch))
+    ctx.profile_enable(True)
+    call = ctx.hmul_relin_rescale_merged if merged else ctx.hmul_relin_rescale
+    call(be.to_dev(a), be.to_dev(b), be.to_dev(M.rlk), out, level, batch, ws, stream=be.stream)
+    got = be.to_host(out).reshape(batch, 2, level - 1, O.N)
+    ran = ctx.profile_read()
+    ctx.profile_enable(False)
+    assert all(k in ran for k in expect) and not any(k in ran for k in absent), (shape, batch, level, sorted(ran))
+    for i in sample or range(batch):
+        want = (O.hmul_relin_rescale_merged if merged else O.hmul_relin_rescale)(a[i], b[i], M.rlk, level)
+        assert np.array_equal(got[i], want), "product of item %d differs" % i
+    ctx.close()
+
+
 def case_relin_and_composite(be, shape, seed, batch=2, levels=None, small_ws=False):
     M = make_material(shape, seed)
     O = M.O

@@ -310,3 +310,10 @@ def test_emulated_division_route_last_round(be):
     with be.tuned(512):  # four
         pc.case_division_route(be, (16, 2, 50, 0, 51, 1), seed=159, batch=3, level=2, one_kernel=False, sample=[2])  # 6
         pc.case_division_route(be, (16, 2, 50, 0, 51, 1), seed=160, batch=4, level=2, one_kernel=True, sample=[3])   # 8
+
+
+def test_emulated_tail_route(be):
+    """N = 2^14: ModDown followed by rescale goes on chip only with enough kept limbs a row"""
+    with be.tuned(128):  # one row, three kept limbs
+        pc.case_product_route(be, (14, 3, 50, 1, 51, 1), seed=185, batch=1, level=3, expect=["conv_final_kernel"], absent=["modup_cols_kernel<2, 2, 3>"])
+        pc.case_product_route(be, (14, 3, 50, 1, 51, 1), seed=186, batch=1, level=2, expect=["modup_cols_kernel<2, 2, 3>"], absent=["conv_final_kernel"])

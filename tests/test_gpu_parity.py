@@ -710,7 +710,7 @@ def test_key_switch_on_chip(be, shape, batch, level):
 
 
 @pytest.mark.parametrize("shape,batch,level", [((12, 7, 50, 3, 51, 3), 16, 6), ((12, 4, 51, 2, 51, 2), 17, 4), ((13, 5, 51, 1, 51, 1), 32, 5),
-                                               ((14, 4, 50, 1, 51, 1), 33, 4), ((14, 3, 51, 1, 51, 1), 32, 2)])
+                                               ((14, 4, 50, 1, 51, 1), 33, 4), ((14, 3, 51, 1, 51, 1), 40, 3)])
 def test_tail_on_chip(be, shape, batch, level):
     """ModDown followed by rescale without an intermediate, at the smallest batches that take it"""
     announce("tail on chip %r batch %d" % (shape, batch))
@@ -734,3 +734,11 @@ def test_division_route(be, shape, batch, level, one_kernel):
     N = 2^16 also 66 limbs (a second round of workgroups with next to nothing in it) and a single kept limb a row"""
     announce("division route %r batch %d" % (shape, batch))
     pc.case_division_route(be, shape, seed=365, batch=batch, level=level, one_kernel=one_kernel, sample=[0, batch - 1])
+
+
+@pytest.mark.parametrize("batch,level,on_chip", [(32, 2, False), (63, 2, False), (32, 3, False), (40, 3, True), (32, 4, True), (31, 5, False)])
+def test_tail_route(be, batch, level, on_chip):
+    """N = 2^14, one special prime: ModDown followed by rescale on either side of the rows and kept limbs that the on-chip form needs"""
+    announce("tail route batch %d level %d" % (batch, level))
+    names = ["conv_final_kernel"], ["modup_cols_kernel<2, 2, 3>"]
+    pc.case_product_route(be, (14, 5, 50, 1, 51, 1), seed=366, batch=batch, level=level, expect=names[not on_chip], absent=names[on_chip], sample=[0, batch - 1])
