@@ -70,6 +70,7 @@ struct Guard {  // records the first HIP error of a call
     }
     int rc() {
         check(hipGetLastError());
+        if (c->no_kernel.exchange(false)) return CKKSMI_EUNSUPPORTED;
         return ok ? CKKSMI_OK : CKKSMI_EDEVICE;
     }
 };
@@ -101,7 +102,7 @@ LimbMap table_map(const int *index, int n_limbs, size_t src_stride, size_t dst_s
 }
 
 // transform `items` groups of map.per_item limbs; forward: coefficient -> evaluation
-// passes: 3 = whole transform, 1 = strided (column) pass only, 2 = contiguous (row) pass only
+// passes: 3 = whole transform, 2 = contiguous (row) pass only (register-tiled sizes)
 // out_f64 (inverse, register-tiled sizes): the coefficients leave as doubles, with the last-stage constants fin or *fin_val
 // ten (inverse, whole limbs, N <= 2^13): the input is the third tensor component of these operands (src unused)
 // gal (inverse row pass of the register-tiled sizes, or whole limbs with out_f64, N <= 2^13): item i's input is read through the automorphism X -> X^(gal->g[i])
@@ -124,7 +125,8 @@ void launch_ntt(ckksmi_ctx *c, bool forward, const u64 *src, u64 *dst, const Lim
     // limbs actually transformed (the key-switch map skips the limbs of each digit itself)
     const double limbs_work = M.mode == 1 ? (double)items * ((double)M.per_item - M.level) : (double)limbs;
     dim3 grow(limbs, (N1 + R - 1) / R), gcol(limbs, N2 / NTT_TC);
-    // register-tiled kernels for 2^12 <= N <= 2^16 (always two passes; the generic kernels take one up to N = 2^12)
+    // register-tiled kernels for 2^12 <= N <= 2^16 (whole transforms up to N = 2^14 in one pass, see below; the generic kernels take
+    // one up to N = 2^12)
     const bool v2_rows = c->logN >= 12 && c->logN <= 16, v2_cols = v2_rows;
     const bool two_pass = v2_cols || A.LA != 0;
     NttV2Args V;
@@ -267,6 +269,7 @@ void launch_modup_cols(ckksmi_ctx *c, int mode, const u64 *y, size_t y_stride, u
         else if (mode == 2) KL(c, kid, units, (modup_cols_kernel<Q, NS, 2>), grid, block, st, A);            \
         else if (mode == 3) KL(c, kid, units, (modup_cols_kernel<Q, NS, 3>), grid, block, st, A);            \
         else if constexpr (NS > 1 || Q >= 2) KL(c, kid, units, (modup_cols_kernel<Q, NS, 1>), grid, block, st, A); \
+        else c->no_kernel = true; /* one source at N <= 2^13: launch_conv_final */                            \
         break;
     switch ((c->logN - 12) * 8 + nsrc) {
         MODUP_COLS_CASE(0, 1) MODUP_COLS_CASE(0, 2) MODUP_COLS_CASE(0, 3) MODUP_COLS_CASE(0, 4)
@@ -274,7 +277,7 @@ void launch_modup_cols(ckksmi_ctx *c, int mode, const u64 *y, size_t y_stride, u
         MODUP_COLS_CASE(2, 1) MODUP_COLS_CASE(2, 2) MODUP_COLS_CASE(2, 3) MODUP_COLS_CASE(2, 4)
         MODUP_COLS_CASE(3, 1) MODUP_COLS_CASE(3, 2) MODUP_COLS_CASE(3, 3) MODUP_COLS_CASE(3, 4)
         MODUP_COLS_CASE(4, 1) MODUP_COLS_CASE(4, 2) MODUP_COLS_CASE(4, 3) MODUP_COLS_CASE(4, 4)
-        default: break;
+        default: c->no_kernel = true;
     }
 #undef MODUP_COLS_CASE
 }
@@ -282,7 +285,7 @@ void launch_modup_cols(ckksmi_ctx *c, int mode, const u64 *y, size_t y_stride, u
 // limb_count < 0: every limb, out laid out [rows][nc][N]; otherwise only limbs limb0 .. limb0+limb_count-1, written to
 // out + row*out_row_stride + (limb - limb0)*N
 void launch_rows_final(ckksmi_ctx *c, const u64 *tmpA, const u64 *x, size_t x_row_stride, const u64 *addend, size_t add_item_stride,
-                       size_t add_comp_stride, int add_both, u64 *out, const WMul *Binv, int nc, int rows, hipStream_t st, int limb0 = 0,
+                       size_t add_comp_stride, u64 *out, const WMul *Binv, int nc, int rows, hipStream_t st, int limb0 = 0,
                        int limb_count = -1, size_t out_row_stride = 0, const WMul *pre = nullptr, const ScalarTab *stab = nullptr, bool zsub = false, const RowsFinalGal *gal = nullptr) {
     RowsFinalArgs A;
     A.zsub = zsub ? 1 : 0;
@@ -292,7 +295,7 @@ void launch_rows_final(ckksmi_ctx *c, const u64 *tmpA, const u64 *x, size_t x_ro
     A.out_limb0 = A.limb0;
     A.out_row_stride = limb_count < 0 ? (size_t)nc * c->N : out_row_stride;
     A.tmpA = (const u64d *)tmpA; A.x = (const u64d *)x; A.x_row_stride = x_row_stride;
-    A.addend = (const u64d *)addend; A.add_item_stride = add_item_stride; A.add_comp_stride = add_comp_stride; A.add_both = add_both;
+    A.addend = (const u64d *)addend; A.add_item_stride = add_item_stride; A.add_comp_stride = add_comp_stride;
     A.out = (u64d *)out; A.modc = c->d_mod; A.tw = c->d_tww_fwd; A.Binv = Binv; A.logN = c->logN; A.nc = nc;
     A.rows = rows;
     A.p51 = c->p51mask;
@@ -324,10 +327,12 @@ inline bool conv_final_ok(const ckksmi_ctx *c, int nsrc, int rows, int nc) {
     return nc > 1 ? 32 * limbs + 18 * fill >= 29 * fill * rounds : rounds <= 4 && 8 * limbs >= 7 * fill * rounds;
 }
 
-// y: the dropped limbs in coefficient form as canonical doubles, row r at y + r*y_stride; fin_kind as conv_final_body's FIN
+// y: the dropped limbs in coefficient form as canonical doubles, row r at y + r*y_stride; fin_kind as conv_final_body's FIN (2 and
+// 3 take an addend)
 void launch_conv_final(ckksmi_ctx *c, int fin_kind, const u64 *y, size_t y_stride, const DivRoundDev &D, const u64 *x, size_t x_row_stride,
                        const u64 *addend, size_t add_item_stride, size_t add_comp_stride, u64 *out, int nc, int rows, hipStream_t st,
                        const RowsFinalGal *gal = nullptr, const ScalarTab *stab = nullptr, const DivRoundDev *D2 = nullptr) {
+    if (addend && fin_kind != 2 && fin_kind != 3) { c->no_kernel = true; return; }
     ConvFinalArgs A;
     memset(&A, 0, sizeof(A));
     if (D2) A.hc2 = D2->hc;
@@ -368,7 +373,7 @@ void launch_conv_final(ckksmi_ctx *c, int fin_kind, const u64 *y, size_t y_strid
             CONV_TAIL_CASE(12, 0, 2) CONV_TAIL_CASE(12, 0, 3) CONV_TAIL_CASE(12, 0, 4)
             CONV_TAIL_CASE(13, 1, 2)
             CONV_TAIL_CASE(14, 1, 2) CONV_TAIL_CASE(14, 2, 2)
-            default: break;
+            default: c->no_kernel = true;
         }
 #undef CONV_TAIL_CASE
         return;
@@ -379,27 +384,27 @@ void launch_conv_final(ckksmi_ctx *c, int fin_kind, const u64 *y, size_t y_strid
         CONV_FINAL_CASE(14, 1) CONV_FINAL_CASE(14, 2)
         CONV_FINAL_CASE(15, 1) CONV_FINAL_CASE(15, 2)
         CONV_FINAL_CASE(16, 2)
-        default: break;
+        default: c->no_kernel = true;
     }
 #undef CONV_FINAL_CASE
 }
 
 // DivRound of `rows` rows on the register-tiled kernels: dropped limbs (evaluation form) at b_limbs + r*b_stride (nb limbs;
-// b_scratch == b_limbs works in place), kept limbs at x + r*x_stride; out[r][i] = (x_i - NTT(r_i - h)) * Bbar^-1 (+ addend).
+// b_scratch == b_limbs works in place), kept limbs at x + r*x_stride; out[r][i] = (x_i - NTT(r_i - h)) * Bbar^-1.
+// gal (rotations from a shared ModUp): c0 of the input items, read through the automorphisms, joins every even row.
 // zsub: the kept limbs already hold x * Bbar^-1 + addend, out = x - NTT(r - h) * Bbar^-1.
 void divround_rows(ckksmi_ctx *c, const DivRoundDev &D, const FinConst *fin, const int *bidx, const u64 *b_limbs, size_t b_stride,
-                   u64 *b_scratch, size_t bs_stride, const u64 *x, size_t x_stride, u64 *tmp, int nc, int rows, const u64 *addend,
-                   size_t add_item_stride, size_t add_comp_stride, int add_both, u64 *out, hipStream_t st, bool zsub = false,
-                   const RowsFinalGal *gal = nullptr) {
-    if (conv_final_ok(c, D.nb, rows, nc) && !add_both) {
+                   u64 *b_scratch, size_t bs_stride, const u64 *x, size_t x_stride, u64 *tmp, int nc, int rows, u64 *out, hipStream_t st,
+                   bool zsub = false, const RowsFinalGal *gal = nullptr, const u64 *c0 = nullptr, size_t c0_stride = 0) {
+    if (conv_final_ok(c, D.nb, rows, nc)) {
         launch_ntt(c, false, b_limbs, b_scratch, table_map(bidx, D.nb, b_stride, bs_stride), rows, st, fin, 3, nullptr, true);
-        launch_conv_final(c, zsub ? 1 : (gal ? 3 : 0), b_scratch, bs_stride, D, x, x_stride, addend, add_item_stride, add_comp_stride, out, nc, rows, st, gal);
+        launch_conv_final(c, zsub ? 1 : (gal ? 3 : 0), b_scratch, bs_stride, D, x, x_stride, c0, c0_stride, 0, out, nc, rows, st, gal);
         return;
     }
     // inverse row pass of the dropped limbs; the conversion kernel runs their inverse column pass itself
     launch_ntt(c, false, b_limbs, b_scratch, table_map(bidx, D.nb, b_stride, bs_stride), rows, st, fin, 2);
     launch_modup_cols(c, 1, b_scratch, bs_stride, tmp, rows, 0, nc, &D, (double)rows * nc, st, fin);
-    launch_rows_final(c, tmp, x, x_stride, addend, add_item_stride, add_comp_stride, add_both, out, D.Binv, nc, rows, st, 0, -1, 0, nullptr, nullptr, zsub, gal);
+    launch_rows_final(c, tmp, x, x_stride, c0, c0_stride, 0, out, D.Binv, nc, rows, st, 0, -1, 0, nullptr, nullptr, zsub, gal);
 }
 
 // Rotations with a shared ModUp: R rotations of every item of a key-switch sweep (see inner_product_hoisted_kernel)
@@ -475,7 +480,7 @@ void merged_division(ckksmi_ctx *c, u64 *acc, const u64 *addend, size_t add_item
         const FinConst *fin = c->d_fin_merged + (size_t)level * CKKSMI_MAX_SPECIAL;
         launch_ntt(c, false, bl, bl, table_map(D.b_idx, D.nb, (size_t)E * N, (size_t)E * N), rows, st, fin, 2);
         launch_modup_cols(c, 2, bl, (size_t)E * N, tmp, rows, 0, nc, &D, (double)rows * nc, st, fin);
-        launch_rows_final(c, tmp, acc, (size_t)E * N, addend, add_item_stride, add_comp_stride, 1, out, D.Binv, nc, rows, st, 0, -1, 0,
+        launch_rows_final(c, tmp, acc, (size_t)E * N, addend, add_item_stride, add_comp_stride, out, D.Binv, nc, rows, st, 0, -1, 0,
                           addend ? c->d_pmod : nullptr);
         return;
     }
@@ -532,7 +537,7 @@ void launch_inner_wg(ckksmi_ctx *c, const RowsInnerArgs &R, const KeyTab &K, con
     switch (c->logN * 8 + c->alpha) {
         INNER_WG_CASE(12, 0, 1) INNER_WG_CASE(12, 0, 2) INNER_WG_CASE(12, 0, 3) INNER_WG_CASE(12, 0, 4)
         INNER_WG_CASE(13, 1, 1)
-        default: break;
+        default: c->no_kernel = true;
     }
 #undef INNER_WG_CASE
 }
@@ -607,7 +612,7 @@ void ks_core_fused(ckksmi_ctx *c, const u64 *d_eval, size_t d_stride, const KeyT
         FG.R = R;
         for (int r = 0; r < CKKSMI_MAX_KEYS; r++) FG.g[r] = r < R ? hoist->g[r] : 1u;
         divround_rows(c, c->divround[0], c->d_fin_moddown, sidx, specials, (size_t)E * N, specials, (size_t)E * N, acc, (size_t)E * N, tmp, level,
-                      items * R * 2, hoist->c0, hoist->c0_stride, 0, 0, out, st, false, &FG);
+                      items * R * 2, out, st, false, &FG, hoist->c0, hoist->c0_stride);
         return;
     }
     RowsInnerArgs RI;
@@ -650,12 +655,12 @@ void ks_core_fused(ckksmi_ctx *c, const u64 *d_eval, size_t d_stride, const KeyT
         }
         launch_ntt(c, false, bl, bl, table_map(D3.b_idx, D3.nb, (size_t)E * N, (size_t)E * N), rows, st, ft, 2);
         launch_modup_cols(c, 3, bl, (size_t)E * N, tmp, rows, 0, last, &D3, (double)rows * last, st, ft, &DB);
-        launch_rows_final(c, tmp, acc, (size_t)E * N, nullptr, 0, 0, 0, out, DB.Binv, last, rows, st);
+        launch_rows_final(c, tmp, acc, (size_t)E * N, nullptr, 0, 0, out, DB.Binv, last, rows, st);
         return;
     }
     // plain ModDown; with an addend the kept limbs already hold x * P^-1 + addend
     divround_rows(c, c->divround[0], c->d_fin_moddown, sidx, specials, (size_t)E * N, specials, (size_t)E * N, acc, (size_t)E * N, tmp, level, rows,
-                  nullptr, 0, 0, 0, out, st, addend != nullptr || ta != nullptr);
+                  out, st, addend != nullptr || ta != nullptr);
 }
 
 void rescale_core_fused(ckksmi_ctx *c, const u64 *a, u64 *out, int items, int level, u64 *ws, hipStream_t st) {
@@ -664,7 +669,7 @@ void rescale_core_fused(ckksmi_ctx *c, const u64 *a, u64 *out, int items, int le
     u64 *tmp = last + (size_t)items * 2 * N;
     int lidx[1] = {level - 1};
     divround_rows(c, c->divround[1 + (level - 1)], c->d_fin_rescale + (level - 1), lidx, a + (size_t)(level - 1) * N, (size_t)level * N, last,
-                  N, a, (size_t)level * N, tmp, level - 1, items * 2, nullptr, 0, 0, 0, out, st);
+                  N, a, (size_t)level * N, tmp, level - 1, items * 2, out, st);
 }
 
 // out = DivRound_{q_{level-1}}(v * a) without materialising v*a: the dropped limb's inverse transform multiplies by v in its
@@ -688,7 +693,7 @@ void scalar_rescale_fused(ckksmi_ctx *c, const u64 *a, int64_t v, const u64 *add
         u64 *tmp = lastbuf + (size_t)rows * N;
         launch_ntt(c, false, a + (size_t)last * N, lastbuf, table_map(lidx, 1, in_stride, N), rows, st, c->d_fin_rescale + last, 2);
         launch_modup_cols(c, 1, lastbuf, N, tmp, rows, 0, last, &D, (double)rows * last, st, c->d_fin_rescale + last, nullptr, &F);
-        launch_rows_final(c, tmp, a, in_stride, addend, (size_t)2 * last * N, (size_t)last * N, 1, out, D.Binv, last, rows, st, 0, -1, 0, nullptr, &St);
+        launch_rows_final(c, tmp, a, in_stride, addend, (size_t)2 * last * N, (size_t)last * N, out, D.Binv, last, rows, st, 0, -1, 0, nullptr, &St);
         return;
     }
     launch_ntt(c, false, a + (size_t)last * N, lastbuf, table_map(lidx, 1, in_stride, N), rows, st, nullptr, 3, nullptr, true, &F);
@@ -1330,8 +1335,8 @@ static int hmul_relin_rescale_impl(ckksmi_ctx *c, const uint64_t *a, const uint6
             }
             continue;
         }
-        // the tensor is never written: its third component goes through the inverse row pass on the way, the inner product forms
-        // what it needs of all three from the operands
+        // the tensor is never written: its third component is formed on the way into its inverse transform, the inner product
+        // forms what it needs of all three from the operands
         if (merged || one_conversion_tail_ok(c)) {
             // one division by P*q_{level-1} of (accumulators + P*(d0, d1)), or ModDown + add + rescale as one conversion
             ks_core_fused(c, nullptr, 0, K, items, level, nullptr, 0, 0, 1, o, rest, S(stream), !merged, merged, nullptr, a + in0, b + in0, terms);

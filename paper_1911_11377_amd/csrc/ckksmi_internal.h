@@ -124,6 +124,7 @@ struct ckksmi_ctx {
     bool merged_ok = false;             // merged division available: k > 0 and k + 1 <= CKKSMI_MAX_SPECIAL
     P51Mask p51mask = {{0, 0}};
     bool fused = false;  // 2^12 <= N <= 2^16: register-tiled passes with the limb-wise steps fused into them
+    std::atomic<bool> no_kernel{false};  // a launch sequence asked for a kernel that was not built: the call returns an error
 
     // registered Galois keys
     std::vector<std::pair<int, const u64 *>> galois;

@@ -765,9 +765,8 @@ struct RowsFinalArgs {
     const u64d *tmpA;    // [rows][nc][N] column-pass output of (r_i - h)
     const u64d *x;       // kept limbs, evaluation form: row r, limb i at x + r*x_row_stride + i*N
     unsigned long long x_row_stride;
-    const u64d *addend;  // optional: row r limb i at addend + (r/2)*add_item_stride + (r%2)*add_comp_stride + i*N
+    const u64d *addend;  // optional: row r limb i at addend + (r/2)*add_item_stride + (r%2)*add_comp_stride + i*N (odd rows: with pre or a scalar)
     unsigned long long add_item_stride, add_comp_stride;
-    int add_both;
     u64d *out;           // row r, limb i at out + r*out_row_stride + (i - out_limb0)*N
     unsigned long long out_row_stride;
     int out_limb0;
@@ -805,7 +804,7 @@ __device__ __forceinline__ void rows_final_body(const RowsFinalArgs &A, double *
     for (unsigned row = r0; row < r1; row++) {
         const u64d *xin = A.x + (size_t)row * A.x_row_stride + (size_t)i * N + tile0;
         u64d *out = A.out + (size_t)row * A.out_row_stride + (size_t)(i - A.out_limb0) * N + tile0;
-        const bool add = A.addend && (pre || xm || A.add_both || (row & 1u) == 0);
+        const bool add = A.addend && (pre || xm || (row & 1u) == 0);
         const u64d *ad = add ? A.addend + (size_t)(row / 2) * A.add_item_stride + (size_t)(row % 2) * A.add_comp_stride + (size_t)i * N + tile0 : xin;
         // operands of the last step are requested before the transform so that their latency overlaps it
         // pointwise part in the row-pair layout: 16 bytes per lane and memory instruction, no workgroup barrier

@@ -33,34 +33,21 @@ struct InnerWgLds {
     static constexpr unsigned T = (1u << LOGM) / 16, MAT = ((1u << LOGM) >> 8) * V2_GS, TW1 = MAT, TW2 = TW1 + T, TOTAL = TW2 + 15 * T;
 };
 
-// wg_fwd_block with the twiddles at hand: twc the first column round's, twu the second's, the row rounds' in LDS.  One barrier
-// (two with a second column round) inside; the caller puts one between a digit's last use of the matrix and the next digit.
+// wg_fwd_block with the twiddles at hand: twc the column round's (a block of 2^12 words has one), the row rounds' in LDS.  One
+// barrier inside; the caller puts one between a digit's last use of the matrix and the next digit.
 template <int LOGM, bool P51, class F>
-__device__ __forceinline__ void inner_fwd_block(double (&x)[16], const double (&twc)[15], const double (&twu)[15], double *lds, double p, double pinv,
-                                                F request) {
-    constexpr int Q = LOGM - 12;
-    typedef ColsGeom<Q> Geo;
-    typedef ColsMasks<Q, P51> Mk;
+__device__ __forceinline__ void inner_fwd_block(double (&x)[16], const double (&twc)[15], double *lds, double p, double pinv, F request) {
+    static_assert(LOGM == 12, "one column round");
+    typedef ColsGeom<0> Geo;
+    typedef ColsMasks<0, P51> Mk;
     typedef InnerWgLds<LOGM> Lay;
     constexpr int RF1 = P51 ? 0xA : 0x8, RF2 = P51 ? 0x2 : 0x0;
     const unsigned tid = threadIdx.x, row = tid >> 4, lo4 = tid & 15;
     const Geo geo(tid & 255u, tid >> 8);
     double *grp = lds + row * V2_GS;
     fwd_round<Mk::F1>(x, twc, p, pinv);
-    if (Q > 0) {
 #pragma unroll
-        for (int e = 0; e < 16; e++) lds[wg_pad(geo.r + Geo::G * e, geo.c0 + geo.c)] = x[e];
-        __syncthreads();
-#pragma unroll
-        for (int i = 0; i < 16; i++) x[i] = lds[wg_pad(Geo::G * geo.a + (i % Geo::G), geo.c0 + geo.l16 + 16 * (i / Geo::G))];
-        fwd_stages<Geo::S0, Mk::F2>(x, twu, p, pinv);
-#pragma unroll
-        for (int i = 0; i < 16; i++)
-            lds[wg_pad(Geo::G * geo.a + (i % Geo::G), geo.c0 + geo.l16 + 16 * (i / Geo::G))] = reduce_balanced(x[i], p, pinv);
-    } else {
-#pragma unroll
-        for (int e = 0; e < 16; e++) lds[wg_pad(e, geo.c0 + geo.c)] = x[e];  // the first round ends reduced
-    }
+    for (int e = 0; e < 16; e++) lds[wg_pad(e, geo.c0 + geo.c)] = x[e];  // the column round ends reduced
     __syncthreads();
     request();
 #pragma unroll
@@ -117,15 +104,11 @@ __device__ __forceinline__ void inner_wg_body(const InnerWgArgs &A, const KeyTab
     }
     const Geo geo(tid & 255u, tid >> 8);
     const unsigned voff = geo.r * 256u + geo.c0 + geo.c, pr = row_pair_index(prow, lo4, 0);
-    double twc[15], twu[15];
+    double twc[15];
 #pragma unroll
     for (int s = 0; s < 4; s++)
 #pragma unroll
-        for (int b = 0; b < (1 << s); b++) {
-            twc[(1 << s) - 1 + b] = table_load(tw, (base << s) + b);
-            const int u = s - (4 - (LOGM - 12));
-            twu[(1 << s) - 1 + b] = u >= 0 ? tw[((16u * base + geo.a) << u) + (b & ((1 << u) - 1))] : 0.0;
-        }
+        for (int b = 0; b < (1 << s); b++) twc[(1 << s) - 1 + b] = table_load(tw, (base << s) + b);
     {
         const unsigned base1 = base * (M >> 8) + prow;
 #pragma unroll
@@ -179,7 +162,7 @@ __device__ __forceinline__ void inner_wg_body(const InnerWgArgs &A, const KeyTab
         const ulonglong2 *k1 = (const ulonglong2 *)(key + (((size_t)j * 2 + 1) * R.T + t) * N + tile0);
         ulonglong2 kr0[8], kr1[8];
         __syncthreads();  // everybody is done with the matrix (before the first digit: the twiddles are in place)
-        inner_fwd_block<LOGM, P51>(xx, twc, twu, lds, p, pinv, [&]() {
+        inner_fwd_block<LOGM, P51>(xx, twc, lds, p, pinv, [&]() {
 #pragma unroll
             for (int s = 0; s < 8; s++) {
                 kr0[s] = (k0 + 16 * s)[pr];

@@ -402,7 +402,7 @@ __global__ __launch_bounds__(V2_THREADS) void ntt_v2_inv_rows_gal_kernel(NttV2Ar
     else ntt_v2_rows<true, false, true>(A, lds, t, li, &G);
 }
 
-// grid: x = tile (N/4096), y = limb slot within an item, z = chunk of items
+// grid: x = tile (N/4096), y = limb slot within an item, z = chunk of items (column pass: N >= 2^14, smaller rings go through ntt_wg_kernel)
 template <bool INV, bool COLS, bool F64 = false>
 __global__ __launch_bounds__(V2_THREADS) void ntt_v2_kernel(NttV2Args A) {
     __shared__ double lds[16 * V2_GS];
@@ -415,11 +415,9 @@ __global__ __launch_bounds__(V2_THREADS) void ntt_v2_kernel(NttV2Args A) {
         else ntt_v2_rows<INV, false>(A, lds, t, li);
     } else {
         switch (A.logN) {
-            case 12: if (p51) ntt_v2_cols<INV, 0, true, false, F64>(A, lds, t, li); else ntt_v2_cols<INV, 0, false, false, F64>(A, lds, t, li); break;
-            case 13: if (p51) ntt_v2_cols<INV, 1, true, false, F64>(A, lds, t, li); else ntt_v2_cols<INV, 1, false, false, F64>(A, lds, t, li); break;
             case 14: if (p51) ntt_v2_cols<INV, 2, true, false, F64>(A, lds, t, li); else ntt_v2_cols<INV, 2, false, false, F64>(A, lds, t, li); break;
             case 15: if (p51) ntt_v2_cols<INV, 3, true, false, F64>(A, lds, t, li); else ntt_v2_cols<INV, 3, false, false, F64>(A, lds, t, li); break;
-            default: if (p51) ntt_v2_cols<INV, 4, true, false, F64>(A, lds, t, li); else ntt_v2_cols<INV, 4, false, false, F64>(A, lds, t, li); break;
+            case 16: if (p51) ntt_v2_cols<INV, 4, true, false, F64>(A, lds, t, li); else ntt_v2_cols<INV, 4, false, false, F64>(A, lds, t, li); break;
         }
     }
 }

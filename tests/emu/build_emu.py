@@ -11,8 +11,8 @@ LIB = os.path.join(HERE, "libckksmi_emu.so")
 
 
 def build(force=False):
-    srcs = [os.path.join(CSRC, s) for s in ("ckksmi_device.hip", "host_math.cpp", "host_crypto.cpp")] + [os.path.join(HERE, "hip_emu.cpp")]
-    deps = srcs + [os.path.join(CSRC, f) for f in os.listdir(CSRC) if f.endswith(".h")] + [os.path.join(HERE, "hip_emu.h")]
+    srcs = [os.path.join(HERE, "emu_probe.cpp")] + [os.path.join(CSRC, s) for s in ("host_math.cpp", "host_crypto.cpp")] + [os.path.join(HERE, "hip_emu.cpp")]
+    deps = srcs + [os.path.join(CSRC, "ckksmi_device.hip")] + [os.path.join(CSRC, f) for f in os.listdir(CSRC) if f.endswith(".h")] + [os.path.join(HERE, "hip_emu.h")]
     if not force and os.path.exists(LIB) and all(os.path.getmtime(LIB) >= os.path.getmtime(d) for d in deps):
         return LIB
     tmp = LIB + ".tmp.%d" % os.getpid()

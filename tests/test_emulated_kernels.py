@@ -5,6 +5,7 @@ runs them; the parity claims themselves come from the GPU tests."""
 import pytest
 
 import parity_cases as pc
+from paper_1911_11377_amd import ckksmi
 
 # (logN, n_q, q_bits, k, special_bits, alpha)
 TINY = (6, 3, 30, 1, 31, 1)
@@ -198,7 +199,6 @@ def test_emulated_variant_entry_points_refuse_bad_arguments(be):
 
 def test_emulated_misaligned_device_pointer_is_rejected(be):
     """device buffers must be 16-byte aligned (vector accesses of two words): an odd word offset is refused on the host"""
-    from paper_1911_11377_amd import ckksmi
     shape = TINY
     ctx = be.context(*shape)
     N, level = 1 << shape[0], shape[1]
@@ -317,3 +317,12 @@ def test_emulated_tail_route(be):
     with be.tuned(128):  # one row, three kept limbs
         pc.case_product_route(be, (14, 3, 50, 1, 51, 1), seed=185, batch=1, level=3, expect=["conv_final_kernel"], absent=["modup_cols_kernel<2, 2, 3>"])
         pc.case_product_route(be, (14, 3, 50, 1, 51, 1), seed=186, batch=1, level=2, expect=["modup_cols_kernel<2, 2, 3>"], absent=["conv_final_kernel"])
+
+
+@pytest.mark.parametrize("shape,which", [((12, 3, 50, 1, 51, 1), 0), ((13, 3, 50, 1, 51, 1), 1), ((14, 3, 50, 1, 51, 1), 2)])
+def test_emulated_missing_kernel_is_an_error(be, shape, which):
+    """a launch sequence that asks for a kernel which was not built makes the call fail; the next call of the context runs"""
+    ctx = be.context(*shape)
+    assert be.lib.emu_probe_missing_kernel(ctx._h, which) == ckksmi.EUNSUPPORTED
+    assert be.lib.emu_probe_missing_kernel(ctx._h, -1) == 0
+    ctx.close()
