@@ -40,8 +40,8 @@ extern "C" {
 #define CKKSMI_K_CONV_COLS_RESCALE 17 /* the same with a single dropped prime (rescale) */
 #define CKKSMI_K_MAC_MFMA 18      /* conv / FC multiply-accumulate on the matrix cores */
 #define CKKSMI_K_MACPREP_MFMA 19  /* its weight digits and tap table */
-#define CKKSMI_K_NTT_LDS 20       /* whole limb transform inside one workgroup's LDS (also the sources of a product's tail) */
-#define CKKSMI_K_TENSOR_ROWS 21   /* tensor product fused with the inverse contiguous pass (small rings: whole inverse transform) of its third component */
+#define CKKSMI_K_NTT_LDS 20       /* whole limb transform inside one workgroup's LDS */
+#define CKKSMI_K_TENSOR_ROWS 21   /* tensor product fused with the inverse contiguous pass of its third component */
 #define CKKSMI_K_AXPY_LIMB 22     /* one limb of every row += constant * another limb (merged division: P*d on the dropped q) */
 #define CKKSMI_K_CONV_COLS_MERGED 23 /* the conversion kernel in the exact form of DivRound, sources {q_last, special primes} */
 #define CKKSMI_K_INNER_HOISTED 24 /* inner product of hoisted rotations (gathers the lifted digits through each automorphism) */
@@ -53,17 +53,24 @@ extern "C" {
 #define CKKSMI_K_MAC_MFMA_STRIP 30  /* ... and a narrow window: four neighbouring positions share a strip of the image staged in LDS */
 #define CKKSMI_K_CONV_FINAL 31    /* conversion, whole forward transform and last step of a DivRound in one workgroup per kept limb (block) */
 #define CKKSMI_K_INNER_WG 32      /* ModUp's conversion, whole forward transform and inner product in one workgroup per extended limb (block) */
-#define CKKSMI_K_COUNT 33
+#define CKKSMI_K_TENSOR_WG 33     /* third component of the tensor product formed on the way into its whole inverse transform */
+#define CKKSMI_K_NTT_LDS_GAL 34   /* whole inverse transform of a rotation's polynomial, read through the automorphism */
+#define CKKSMI_K_TAIL_SOURCES 35  /* sources of ModDown followed by rescale: inverse transforms of k + 1 limbs a row (units: limbs) */
+#define CKKSMI_K_MACWSUM_MFMA 36  /* weight sums of the matrix-core multiply-accumulate (units: channels x limbs) */
+#define CKKSMI_K_COUNT 37
 int ckksmi_profile_enable(ckksmi_ctx *ctx, int on);
 int ckksmi_profile_read(ckksmi_ctx *ctx, int kernel_class, double *total_ms, long long *launches, double *units);
-/* name of the kernel that class runs as in this context (the transforms have size-specific kernels) */
+/* name of the kernel that class runs as in this context (the transforms have size-specific kernels; a fused kernel's variants for
+ * rotations, _gal, and scalar multiples, _scalar, count under its own name) */
 const char *ckksmi_kernel_class_name(const ckksmi_ctx *ctx, int kernel_class);
 
 
 /* Launch-shape knobs (benchmarks and tests; the defaults suit a full GPU).
  * CKKSMI_TUNE_TARGET_WGS: number of workgroups a transform launch aims for before its workgroups start looping over
  * the items of the batch (default 8192; a small value makes even a small batch exercise the item loops).  The
- * matrix-core multiply-accumulate aims for half of it before a workgroup walks several output positions. */
+ * matrix-core multiply-accumulate aims for half of it before a workgroup walks several output positions.  The numbers of limbs
+ * and rows from which a sequence keeps its converted limbs on chip scale with it: a small value takes these kernels at small
+ * batches.  Results never depend on it. */
 #define CKKSMI_TUNE_TARGET_WGS 0
 int ckksmi_tune(ckksmi_ctx *ctx, int knob, int value);
 

@@ -156,8 +156,8 @@ void launch_ntt(ckksmi_ctx *c, bool forward, const u64 *src, u64 *dst, const Lim
 #define NTT_WG_CASE(LN)                                                                                        \
     case LN:                                                                                                   \
         if (forward) KL(c, CKKSMI_K_NTT_LDS, limbs_work, (ntt_wg_kernel<false, LN>), gw, bw, st, V);           \
-        else if (LN < 14 && ten) KL(c, CKKSMI_K_TENSOR_ROWS, limbs_work, tensor_wg_kernel<LN < 14 ? LN : 13>, gw, bw, st, V, *ten); \
-        else if (LN < 14 && gal) KL(c, CKKSMI_K_NTT_LDS, limbs_work, ntt_wg_inv_gal_kernel<LN < 14 ? LN : 13>, gw, bw, st, V, *gal); \
+        else if (LN < 14 && ten) KL(c, CKKSMI_K_TENSOR_WG, limbs_work, tensor_wg_kernel<LN < 14 ? LN : 13>, gw, bw, st, V, *ten); \
+        else if (LN < 14 && gal) KL(c, CKKSMI_K_NTT_LDS_GAL, limbs_work, ntt_wg_inv_gal_kernel<LN < 14 ? LN : 13>, gw, bw, st, V, *gal); \
         else if (out_f64) KL(c, CKKSMI_K_NTT_LDS, limbs_work, (ntt_wg_kernel<true, LN, true>), gw, bw, st, V); \
         else KL(c, CKKSMI_K_NTT_LDS, limbs_work, (ntt_wg_kernel<true, LN>), gw, bw, st, V);                    \
         break;
@@ -559,9 +559,9 @@ void launch_tail_sources(ckksmi_ctx *c, u64 *bl, size_t row_stride, int level, i
     A.bl = (u64d *)bl; A.row_stride = row_stride; A.modc = c->d_mod; A.tw_inv = c->d_tww_inv; A.fin = fin; A.D = c->divround[0]; A.hb2 = DB.hb[0];
     A.T = c->T; A.last = level - 1; A.n_q = c->n_q; A.k = c->k; A.p51 = c->p51mask;
     const double units = (double)rows * (c->k + 1);
-    if (c->logN == 12) KL(c, CKKSMI_K_NTT_LDS, units, tail_sources_kernel<12>, dim3(rows), dim3(256), st, A);
-    else if (c->logN == 13) KL(c, CKKSMI_K_NTT_LDS, units, tail_sources_kernel<13>, dim3(rows), dim3(512), st, A);
-    else KL(c, CKKSMI_K_NTT_LDS, units, tail_sources_kernel<14>, dim3(rows), dim3(1024), st, A);
+    if (c->logN == 12) KL(c, CKKSMI_K_TAIL_SOURCES, units, tail_sources_kernel<12>, dim3(rows), dim3(256), st, A);
+    else if (c->logN == 13) KL(c, CKKSMI_K_TAIL_SOURCES, units, tail_sources_kernel<13>, dim3(rows), dim3(512), st, A);
+    else KL(c, CKKSMI_K_TAIL_SOURCES, units, tail_sources_kernel<14>, dim3(rows), dim3(1024), st, A);
 }
 
 // Key switch on the register-tiled kernels (2^12 <= N <= 2^16).
@@ -1693,7 +1693,7 @@ extern "C" int ckksmi_conv2d_mac_rows(ckksmi_ctx *c, const uint64_t *in, const i
         const size_t prep = std::max(ms.afrag_bytes / 16 / MM_DIG, (size_t)ms.Kb * 64);
         KL(c, CKKSMI_K_MACPREP_MFMA, 1, mac_prepare_mfma_kernel, dim3(ew_blocks(prep)), dim3(EW_THREADS), S(stream), (const long long *)w, afrag, taps,
            off64, tapoff, ms.SR, ms.SC, c->d_mod, level, c->logN, O, C, kh, kw, in_rows, W, ms.Kb, ms.Mg, ms.quad);
-        KL(c, CKKSMI_K_MACPREP_MFMA, 0, mac_wsum_kernel, dim3((unsigned)(ms.Mg * MM_CH), (unsigned)level), dim3(EW_THREADS), S(stream), (const long long *)w, wsum, c->d_mod,
+        KL(c, CKKSMI_K_MACWSUM_MFMA, (double)ms.Mg * MM_CH * level, mac_wsum_kernel, dim3((unsigned)(ms.Mg * MM_CH), (unsigned)level), dim3(EW_THREADS), S(stream), (const long long *)w, wsum, c->d_mod,
            O, C * kh * kw);
         MacMfmaArgs A;
         A.in = (const u64d *)in; A.out = (u64d *)out; A.afrag = afrag; A.taps = taps; A.off64 = off64; A.tapoff = tapoff; A.wsum = wsum; A.modc = c->d_mod;
@@ -1828,7 +1828,8 @@ extern "C" const char *ckksmi_kernel_class_name(const ckksmi_ctx *c, int kernel_
                                                 "elementwise kernels", "modup_cols_kernel", "modup_cols_kernel", "rows_inner_kernel",
                                                 "rows_final_kernel", "modup_cols_kernel", "conv_mac_mfma_kernel", "mac_prepare_mfma_kernel", "ntt_wg_kernel", "tensor_rows_kernel",
                                                 "axpy_limb_kernel", "modup_cols_kernel", "inner_product_hoisted_tile_kernel", "automorphism_bcast_kernel",
-                                                "encoding kernels", "encryption kernels", "modup_cols_kernel", "conv_mac_mfma_resident_kernel", "conv_mac_mfma_strip_kernel", "conv_final_kernel", "inner_wg_kernel"};
+                                                "encoding kernels", "encryption kernels", "modup_cols_kernel", "conv_mac_mfma_resident_kernel", "conv_mac_mfma_strip_kernel", "conv_final_kernel", "inner_wg_kernel",
+                                                "tensor_wg_kernel", "ntt_wg_inv_gal_kernel", "tail_sources_kernel", "mac_wsum_kernel"};
     if (kernel_class < 0 || kernel_class >= CKKSMI_K_COUNT) return "";
     if (c && kernel_class == CKKSMI_K_INNER_HOISTED && !hoisted_tile_ok(c, c->beta_top)) return "inner_product_hoisted_kernel";
     if (c && c->logN >= 12 && c->logN <= 16) {

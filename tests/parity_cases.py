@@ -269,7 +269,19 @@ def case_rescale(be, shape, seed, batch=2, levels=None):
     ctx.close()
 
 
-def case_division_route(be, shape, seed, batch, level, one_kernel, sample=None, fresh_scalar=-99991):
+@contextlib.contextmanager
+def _kernels(ctx, expect, absent=()):
+    """the calls inside run all kernels of `expect` and none of `absent` (nothing is recorded where both are empty)"""
+    if expect or absent:
+        ctx.profile_enable(True)
+    yield
+    if expect or absent:
+        ran = ctx.profile_read()
+        ctx.profile_enable(False)
+        assert all(k in ran for k in expect) and not any(k in ran for k in absent), (expect, absent, sorted(ran))
+
+
+def case_division_route(be, shape, seed, batch, level, one_kernel, sample=None, scalar=-99991):
     """rescale and rescale of a scalar multiple, word for word for the items in `sample`, each by one kernel per kept limb
     (conv_final_kernel) or by the pair of register-tiled kernels, as the caller expects"""
     M = make_material(shape, seed)
@@ -281,17 +293,14 @@ def case_division_route(be, shape, seed, batch, level, one_kernel, sample=None, 
     for name, op in (("rescale", ckksmi.OP_RESCALE), ("scalar rescale", ckksmi.OP_MUL_SCALAR_RESCALE)):
         out = be.empty(batch, 2, level - 1, O.N)
         ws = be.ws(ctx.workspace_bytes(op, level, batch))
-        ctx.profile_enable(True)
-        if op == ckksmi.OP_RESCALE:
-            ctx.rescale(da, out, level, batch, ws, stream=be.stream)
-        else:
-            ctx.mul_scalar_rescale(da, fresh_scalar, out, level, batch, ws, stream=be.stream)
+        with _kernels(ctx, *((["conv_final_kernel"], [pair]) if one_kernel else ([pair], ["conv_final_kernel"]))):
+            if op == ckksmi.OP_RESCALE:
+                ctx.rescale(da, out, level, batch, ws, stream=be.stream)
+            else:
+                ctx.mul_scalar_rescale(da, scalar, out, level, batch, ws, stream=be.stream)
         got = be.to_host(out).reshape(batch, 2, level - 1, O.N)
-        ran = ctx.profile_read()
-        ctx.profile_enable(False)
-        assert ("conv_final_kernel" in ran, pair in ran) == (one_kernel, not one_kernel), (name, shape, batch, level, sorted(ran))
         for i in sample or range(batch):
-            x = a[i] if op == ckksmi.OP_RESCALE else O.mul_scalar(a[i], fresh_scalar, level)
+            x = a[i] if op == ckksmi.OP_RESCALE else O.mul_scalar(a[i], scalar, level)
             assert np.array_equal(got[i], O.rescale(x, level)), "%s of item %d differs" % (name, i)
     ctx.close()
 
@@ -304,13 +313,11 @@ def case_product_route(be, shape, seed, batch, level, expect=(), absent=(), samp
     a, b = random_cts(M, level, batch, seed, ("pa", level)), random_cts(M, level, batch, seed, ("pb", level))
     out = be.empty(batch, 2, level - 1, O.N)
     ws = be.ws(ctx.workspace_bytes(ckksmi.OP_HMUL_RELIN_RESCALE, level, batch))
-    ctx.profile_enable(True)
     call = ctx.hmul_relin_rescale_merged if merged else ctx.hmul_relin_rescale
-    call(be.to_dev(a), be.to_dev(b), be.to_dev(M.rlk), out, level, batch, ws, stream=be.stream)
+    da, db, evk = be.to_dev(a), be.to_dev(b), be.to_dev(M.rlk)
+    with _kernels(ctx, expect, absent):
+        call(da, db, evk, out, level, batch, ws, stream=be.stream)
     got = be.to_host(out).reshape(batch, 2, level - 1, O.N)
-    ran = ctx.profile_read()
-    ctx.profile_enable(False)
-    assert all(k in ran for k in expect) and not any(k in ran for k in absent), (shape, batch, level, sorted(ran))
     for i in sample or range(batch):
         want = (O.hmul_relin_rescale_merged if merged else O.hmul_relin_rescale)(a[i], b[i], M.rlk, level)
         assert np.array_equal(got[i], want), "product of item %d differs" % i
@@ -381,7 +388,7 @@ def case_merged_product(be, shape, seed, batch=2, levels=None, small_ws=False, e
     ctx.close()
 
 
-def case_rotate(be, shape, seed, rotations, batch=4, level=None):
+def case_rotate(be, shape, seed, rotations, batch=4, level=None, expect=(), absent=()):
     M = make_material(shape, seed, rotations=rotations)
     O = M.O
     ctx = be.context(*shape)
@@ -394,7 +401,8 @@ def case_rotate(be, shape, seed, rotations, batch=4, level=None):
     rots = [rotations[i % len(rotations)] for i in range(batch)]
     out = be.empty(batch, 2, level, O.N)
     ws = be.ws(ctx.workspace_bytes(ckksmi.OP_ROTATE, level, batch))
-    ctx.rotate(da, rots, out, level, batch, ws, stream=be.stream)
+    with _kernels(ctx, expect, absent):
+        ctx.rotate(da, rots, out, level, batch, ws, stream=be.stream)
     got = be.to_host(out).reshape(batch, 2, level, O.N)
     for i in range(batch):
         assert np.array_equal(got[i], O.rotate(a[i], rots[i], M.gk[rots[i]], level)), "rotate item %d by %d differs" % (i, rots[i])
@@ -425,7 +433,7 @@ def case_sum_of_products(be, shape, seed, terms, batch=2, levels=None):
     ctx.close()
 
 
-def case_rotate_hoisted(be, shape, seed, rotations, batch=3, level=None, small_ws=False):
+def case_rotate_hoisted(be, shape, seed, rotations, batch=3, level=None, small_ws=False, expect=(), absent=()):
     """every item through every rotation with one shared ModUp, word for word against the oracle's definition of it"""
     M = make_material(shape, seed, rotations=rotations)
     O = M.O
@@ -442,7 +450,8 @@ def case_rotate_hoisted(be, shape, seed, rotations, batch=3, level=None, small_w
     if small_ws and batch > 1:
         nbytes = nbytes // batch + 8  # one item per sweep
     ws = be.ws(nbytes)
-    ctx.rotate_hoisted(da, list(rotations), out, level, batch, ws, stream=be.stream)
+    with _kernels(ctx, expect, absent):
+        ctx.rotate_hoisted(da, list(rotations), out, level, batch, ws, stream=be.stream)
     got = be.to_host(out).reshape(batch, R, 2, level, O.N)
     for i in range(batch):
         want = O.rotate_hoisted(a[i], rotations, [M.gk[r] for r in rotations], level)

@@ -326,3 +326,16 @@ def test_emulated_missing_kernel_is_an_error(be, shape, which):
     assert be.lib.emu_probe_missing_kernel(ctx._h, which) == ckksmi.EUNSUPPORTED
     assert be.lib.emu_probe_missing_kernel(ctx._h, -1) == 0
     ctx.close()
+
+
+def test_emulated_profile_names_the_kernels_that_run(be):
+    """N = 2^12: the on-chip key switch and tail report their own kernels, the two-kernel forms theirs"""
+    chip = ["inner_wg_kernel", "conv_final_kernel"]
+    with be.tuned(64):
+        pc.case_product_route(be, (12, 3, 50, 1, 51, 1), seed=190, batch=1, level=3, expect=chip + ["tensor_wg_kernel", "tail_sources_kernel"],
+                              absent=["tensor_rows_kernel", "ntt_wg_kernel"])
+        pc.case_rotate(be, (12, 3, 50, 1, 51, 1), seed=191, rotations=[1], batch=1, level=3, expect=chip + ["ntt_wg_inv_gal_kernel", "ntt_wg_kernel"],
+                       absent=["ntt_v2_kernel<true, false>"])
+    pc.case_product_route(be, (12, 3, 50, 3, 51, 3), seed=192, batch=1, level=3,
+                          expect=["tensor_rows_kernel", "modup_cols_kernel<0, 3, 0>", "rows_inner_kernel", "modup_cols_kernel<0, 4, 3>", "rows_final_kernel"],
+                          absent=chip + ["tensor_wg_kernel", "tail_sources_kernel"])
