@@ -105,6 +105,18 @@ def check_moduli(ctx, M):
     assert ctx.moduli == M.O.moduli and ctx.psis == M.O.psis
 
 
+@contextlib.contextmanager
+def _kernels(ctx, expect, absent=()):
+    """the calls inside run all kernels of `expect` and none of `absent` (nothing is recorded where both are empty)"""
+    if expect or absent:
+        ctx.profile_enable(True)
+    yield
+    if expect or absent:
+        ran = ctx.profile_read()
+        ctx.profile_enable(False)
+        assert all(k in ran for k in expect) and not any(k in ran for k in absent), (expect, absent, sorted(ran))
+
+
 def case_ntt(be, shape, seed, batch=2):
     logN, n_q, q_bits, k, special_bits, alpha = shape
     O = orc.Oracle(logN, n_q, q_bits, k, special_bits, alpha)
@@ -223,7 +235,7 @@ def _rc(fn, *args, **kw):
     return 0
 
 
-def case_rescale(be, shape, seed, batch=2, levels=None):
+def case_rescale(be, shape, seed, batch=2, levels=None, expect=(), absent=()):
     M = make_material(shape, seed)
     O = M.O
     ctx = be.context(*shape)
@@ -234,7 +246,8 @@ def case_rescale(be, shape, seed, batch=2, levels=None):
         da = be.to_dev(a)
         out = be.empty(batch, 2, level - 1, O.N)
         ws = be.ws(ctx.workspace_bytes(ckksmi.OP_RESCALE, level, batch))
-        ctx.rescale(da, out, level, batch, ws, stream=be.stream)
+        with _kernels(ctx, expect, absent):
+            ctx.rescale(da, out, level, batch, ws, stream=be.stream)
         got = be.to_host(out).reshape(batch, 2, level - 1, O.N)
         for i in range(batch):
             assert np.array_equal(got[i], O.rescale(a[i], level)), "rescale differs at level %d" % level
@@ -243,8 +256,10 @@ def case_rescale(be, shape, seed, batch=2, levels=None):
         for cst in (-(1 << 38) + 12345, 7, (1 << 52) + 3):
             out2 = be.empty(batch, 2, level - 1, O.N)
             nb = ctx.workspace_bytes(ckksmi.OP_MUL_SCALAR_RESCALE, level, batch)
-            ws2 = be.ws(nb // batch + 8 if (batch > 1 and cst == 7) else nb)  # once with room for one item only
-            ctx.mul_scalar_rescale(da, cst, out2, level, batch, ws2, stream=be.stream)
+            small = batch > 1 and cst == 7  # once with room for one item only
+            ws2 = be.ws(nb // batch + 8 if small else nb)
+            with _kernels(ctx, () if small else expect, () if small else absent):
+                ctx.mul_scalar_rescale(da, cst, out2, level, batch, ws2, stream=be.stream)
             got2 = be.to_host(out2).reshape(batch, 2, level - 1, O.N)
             for i in range(batch):
                 assert np.array_equal(got2[i], O.rescale(O.mul_scalar(a[i], cst, level), level)), "scalar rescale differs at level %d" % level
@@ -260,25 +275,14 @@ def case_rescale(be, shape, seed, batch=2, levels=None):
             # ... and added onto a ciphertext already in the output buffer
             base = random_cts(M, level - 2, batch, seed, ("rs.add", level))
             out4 = be.to_dev(base)
-            ctx.mul_scalar_rescale(da, -99991, out4, level - 1, batch, be.ws(ctx.workspace_bytes(ckksmi.OP_MUL_SCALAR_RESCALE, level - 1, batch)),
-                                   stream=be.stream, level_in=level, addend=out4)
+            with _kernels(ctx, expect, absent):
+                ctx.mul_scalar_rescale(da, -99991, out4, level - 1, batch, be.ws(ctx.workspace_bytes(ckksmi.OP_MUL_SCALAR_RESCALE, level - 1, batch)),
+                                       stream=be.stream, level_in=level, addend=out4)
             got4 = be.to_host(out4).reshape(batch, 2, level - 2, O.N)
             for i in range(batch):
                 want = O.add(O.rescale(O.mul_scalar(a[i][:, : level - 1], -99991, level - 1), level - 1), base[i], level - 2)
                 assert np.array_equal(got4[i], want), "scalar rescale with an addend differs at level %d" % level
     ctx.close()
-
-
-@contextlib.contextmanager
-def _kernels(ctx, expect, absent=()):
-    """the calls inside run all kernels of `expect` and none of `absent` (nothing is recorded where both are empty)"""
-    if expect or absent:
-        ctx.profile_enable(True)
-    yield
-    if expect or absent:
-        ran = ctx.profile_read()
-        ctx.profile_enable(False)
-        assert all(k in ran for k in expect) and not any(k in ran for k in absent), (expect, absent, sorted(ran))
 
 
 def case_division_route(be, shape, seed, batch, level, one_kernel, sample=None, scalar=-99991):
@@ -324,7 +328,7 @@ def case_product_route(be, shape, seed, batch, level, expect=(), absent=(), samp
     ctx.close()
 
 
-def case_relin_and_composite(be, shape, seed, batch=2, levels=None, small_ws=False):
+def case_relin_and_composite(be, shape, seed, batch=2, levels=None, small_ws=False, expect=(), absent=()):
     M = make_material(shape, seed)
     O = M.O
     ctx = be.context(*shape)
@@ -348,7 +352,8 @@ def case_relin_and_composite(be, shape, seed, batch=2, levels=None, small_ws=Fal
         if level >= 2:
             out = be.empty(batch, 2, level - 1, O.N)
             ws2 = be.ws(ctx.workspace_bytes(ckksmi.OP_HMUL_RELIN_RESCALE, level, batch))
-            ctx.hmul_relin_rescale(da, db, evk, out, level, batch, ws2, stream=be.stream)
+            with _kernels(ctx, expect, absent):
+                ctx.hmul_relin_rescale(da, db, evk, out, level, batch, ws2, stream=be.stream)
             got = be.to_host(out).reshape(batch, 2, level - 1, O.N)
             for i in range(batch):
                 assert np.array_equal(got[i], O.hmul_relin_rescale(a[i], b[i], M.rlk, level)), "composite differs"
@@ -726,7 +731,7 @@ def edge_ct(M, level, pattern, comps=2):
     return np.stack([edge_limbs(M.O.q[:level], M.N, pattern) for _ in range(comps)])
 
 
-def case_edge_values(be, shape, seed, level=None, rotation=5, extreme_key=True, seeded_key=True, conv=True, pairs=EDGE_PAIRS):
+def case_edge_values(be, shape, seed, level=None, rotation=5, extreme_key=True, seeded_key=True, conv=True, pairs=EDGE_PAIRS, expect=()):
     """residues at the ends and the middle of [0, q) (all 0, all q-1, (q-1)/2, (q+1)/2, alternating, one-hot) through the
     transforms, the tensor, relinearisation, the composite product, rescale, the scalar rescale, rotation and the
     multiply-accumulate, with the seeded switching key and with a key whose every word is q-1: word for word against the
@@ -791,7 +796,9 @@ def case_edge_values(be, shape, seed, level=None, rotation=5, extreme_key=True, 
                 assert np.array_equal(got[i], O.relin(hd[i], rlk, level)), "relin of %r, key %s" % (EDGE_PAIRS[i], name)
             if level >= 2:
                 out = be.empty(batch, 2, level - 1, N)
-                ctx.hmul_relin_rescale(da, db, evk, out, level, batch, be.ws(ctx.workspace_bytes(ckksmi.OP_HMUL_RELIN_RESCALE, level, batch)), stream=be.stream)
+                with _kernels(ctx, expect):
+                    ctx.hmul_relin_rescale(da, db, evk, out, level, batch, be.ws(ctx.workspace_bytes(ckksmi.OP_HMUL_RELIN_RESCALE, level, batch)),
+                                           stream=be.stream)
                 got = be.to_host(out).reshape(batch, 2, level - 1, N)
                 for i in range(batch):
                     assert np.array_equal(got[i], O.hmul_relin_rescale(a[i], b[i], rlk, level)), "product of %r, key %s" % (EDGE_PAIRS[i], name)

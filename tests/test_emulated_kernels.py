@@ -266,17 +266,19 @@ def test_emulated_one_source_division(be, logN, bits, tuned):
     every block size, coarse blocks (8 workgroups are enough) and fine ones (512), 50- and 51-bit reduction schedules"""
     shape = (logN, 3, bits, 0, 51, 1)
     with be.tuned(tuned):
-        pc.case_rescale(be, shape, seed=140 + logN, batch=1 if logN > 14 or tuned > 8 else 5, levels=[3, 2])
+        # (512: four limbs are a round at N = 2^16, two enough at 2^14; a level of 2 with one item has two)
+        pc.case_rescale(be, shape, seed=140 + logN, batch=1 if logN > 14 or tuned > 8 else 5, levels=[3, 2],
+                        **({"expect": ["conv_final_kernel"], "absent": ["modup_cols_kernel<%d, 1, 1>" % (logN - 12)]} if logN <= 14 or tuned == 8 else {}))
 
 
-@pytest.mark.parametrize("shape,batch", [((12, 5, 51, 2, 51, 2), 2), ((12, 4, 50, 1, 51, 1), 9), ((12, 7, 50, 3, 51, 3), 1), ((13, 3, 50, 1, 51, 1), 3)])
+@pytest.mark.parametrize("shape,batch", [((12, 5, 51, 2, 51, 2), 2), ((12, 4, 50, 1, 51, 1), 9), ((12, 7, 50, 3, 51, 3), 1), ((13, 3, 50, 1, 51, 1), 3), ((12, 6, 50, 4, 51, 4), 1)])
 def test_emulated_key_switch_on_chip(be, shape, batch):
-    """lifted limbs that never leave their workgroup: digits cut short by the level, one to three sources, halves of a 2^13 ring, items
+    """lifted limbs that never leave their workgroup: digits cut short by the level, one to four sources, halves of a 2^13 ring, items
     that do not divide evenly over the XCDs; products, sums of products, relinearisation and rotations"""
     with be.tuned(64):
         level = shape[1]
-        pc.case_relin_and_composite(be, shape, seed=170, batch=batch, levels=[level, level - 1])
-        pc.case_rotate(be, shape, seed=171, rotations=[1, 1000], batch=batch, level=level - 1)
+        pc.case_relin_and_composite(be, shape, seed=170, batch=batch, levels=[level, level - 1], expect=["inner_wg_kernel"], absent=["rows_inner_kernel"])
+        pc.case_rotate(be, shape, seed=171, rotations=[1, 1000], batch=batch, level=level - 1, expect=["inner_wg_kernel"], absent=["rows_inner_kernel"])
         pc.case_sum_of_products(be, shape, seed=172, terms=3, batch=1, levels=[level])
 
 
@@ -284,7 +286,7 @@ def test_emulated_key_switch_on_chip(be, shape, batch):
 def test_emulated_tail_on_chip(be, shape, batch):
     """ModDown followed by rescale without an intermediate: one to three special primes, whole rings and halves"""
     with be.tuned(64):
-        pc.case_relin_and_composite(be, shape, seed=180, batch=batch, levels=[shape[1], 2])
+        pc.case_relin_and_composite(be, shape, seed=180, batch=batch, levels=[shape[1], 2], expect=["tail_sources_kernel", "conv_final_kernel"])
 
 
 @pytest.mark.parametrize("shape,batch", [((12, 12, 50, 0, 51, 1), 9), ((13, 8, 51, 0, 52, 1), 9), ((12, 3, 50, 0, 51, 1), 17)])
@@ -339,3 +341,26 @@ def test_emulated_profile_names_the_kernels_that_run(be):
     pc.case_product_route(be, (12, 3, 50, 3, 51, 3), seed=192, batch=1, level=3,
                           expect=["tensor_rows_kernel", "modup_cols_kernel<0, 3, 0>", "rows_inner_kernel", "modup_cols_kernel<0, 4, 3>", "rows_final_kernel"],
                           absent=chip + ["tensor_wg_kernel", "tail_sources_kernel"])
+
+
+def test_emulated_merged_product_on_chip(be):
+    """the accumulators of the on-chip key switch left as they are for the merged division"""
+    with be.tuned(64):
+        pc.case_product_route(be, (12, 3, 50, 1, 51, 1), seed=193, batch=2, level=3, merged=True, expect=["inner_wg_kernel", "modup_cols_kernel<0, 2, 2>"])
+
+
+@pytest.mark.parametrize("logN,bits,tuned", [(14, 50, 1024), (15, 51, 512), (15, 50, 1024), (16, 51, 512)])
+def test_emulated_rotation_division_on_chip(be, logN, bits, tuned):
+    """ModDown with one special prime at the large rings, halves (512) and quarters (1024, N = 2^16) of a limb: a rotation, and two
+    from a shared ModUp whose last step reads sigma(c0) through the automorphism"""
+    names = {"expect": ["conv_final_kernel"], "absent": ["modup_cols_kernel<%d, 1, 1>" % (logN - 12)]}
+    with be.tuned(tuned):
+        pc.case_rotate(be, (logN, 2, bits, 1, 51, 1), seed=194, rotations=[5, 1000], batch=2, level=2, **names)
+        pc.case_rotate_hoisted(be, (logN, 2, bits, 1, 51, 1), seed=195, rotations=(3, 700), batch=1, level=2, **names)
+
+
+@pytest.mark.parametrize("shape", [(12, 9, 51, 1, 51, 1), (13, 9, 50, 1, 51, 1)])
+def test_emulated_edge_values_on_chip(be, shape):
+    """the on-chip key switch and tail on residues at the ends of [0, q), key of all q-1"""
+    with be.tuned(64):
+        pc.case_edge_values(be, shape, seed=196, conv=False, pairs=FEW_PAIRS[:2], seeded_key=False, expect=["inner_wg_kernel", "tail_sources_kernel"])

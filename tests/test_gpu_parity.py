@@ -681,12 +681,20 @@ def test_variant_entry_points_refuse_bad_arguments(be):
     pc.case_variant_errors(be)
 
 
-@pytest.mark.parametrize("logN,bits,batch", [(12, 51, 9), (13, 50, 5), (14, 50, 2), (14, 50, 6), (14, 51, 23), (15, 51, 2), (15, 51, 11), (15, 50, 23), (16, 51, 11)])
-def test_one_source_division(be, logN, bits, batch):
-    """rescale and rescale of a scalar multiple with the converted limb on chip: every block size (few and many workgroups),
-    rows that do not divide evenly over the XCDs, both reduction schedules"""
+ONE_KERNEL = ["conv_final_kernel"]      # the division by one dropped prime with the converted limb on chip ...
+
+
+def pair(logN):                         # ... and the conversion kernel of the pair that takes few limbs
+    return ["modup_cols_kernel<%d, 1, 1>" % (logN - 12)]
+
+
+@pytest.mark.parametrize("logN,bits,batch,levels", [(12, 51, 9, [4, 2]), (13, 50, 5, [4, 2]), (14, 50, 16, [4, 2]), (14, 51, 23, [4, 2]),
+                                                    (15, 51, 32, [4, 2]), (15, 50, 32, [4])])
+def test_one_source_division(be, logN, bits, batch, levels):
+    """rescale and rescale of a scalar multiple with the converted limb on chip: halves and quarters of a ring (few and many
+    workgroups), rows that do not divide evenly over the XCDs, both reduction schedules"""
     announce("one-source division logN=%d %d-bit batch %d" % (logN, bits, batch))
-    pc.case_rescale(be, (logN, 4, bits, 0, 51, 1), seed=330 + logN, batch=batch, levels=[4, 2])
+    pc.case_rescale(be, (logN, 4, bits, 0, 51, 1), seed=330 + logN, batch=batch, levels=levels, expect=ONE_KERNEL, absent=pair(logN))
 
 
 @pytest.mark.parametrize("shape,batch,level", [((12, 8, 50, 1, 51, 1), 40, 8), ((12, 11, 50, 3, 51, 3), 13, 10), ((12, 5, 51, 2, 51, 2), 21, 5),
@@ -694,19 +702,44 @@ def test_one_source_division(be, logN, bits, batch):
 def test_key_switch_on_chip(be, shape, batch, level):
     """batches large enough for the kernel that keeps the lifted limbs on chip: products, relinearisation and rotations"""
     announce("key switch on chip %r batch %d" % (shape, batch))
-    pc.case_relin_and_composite(be, shape, seed=340, batch=batch, levels=[level])
-    pc.case_rotate(be, shape, seed=341, rotations=[1, 777, 2000], batch=batch, level=level)
-    ctx = be.context(*shape)
-    ctx.profile_enable(True)
-    a = be.empty(batch, 2, level, 1 << shape[0])
-    a.zero_()
-    key = be.empty(ctx.beta_top, 2, ctx.T, 1 << shape[0])
-    key.zero_()
-    ws = be.ws(ctx.workspace_bytes(ckksmi.OP_HMUL_RELIN_RESCALE, level, batch))
-    ctx.hmul_relin_rescale(a, a, key, be.empty(batch, 2, level - 1, 1 << shape[0]), level, batch, ws)
-    be.torch.cuda.synchronize()
-    assert "inner_wg_kernel" in ctx.profile_read()
-    ctx.close()
+    pc.case_relin_and_composite(be, shape, seed=340, batch=batch, levels=[level], expect=["tensor_wg_kernel", "inner_wg_kernel"], absent=["rows_inner_kernel"])
+    pc.case_rotate(be, shape, seed=341, rotations=[1, 777, 2000], batch=batch, level=level, expect=["ntt_wg_inv_gal_kernel", "inner_wg_kernel"],
+                   absent=["rows_inner_kernel"])
+
+
+def test_key_switch_on_chip_other_forms(be):
+    """the merged division behind the on-chip key switch (accumulators left as they are), a sum of products, digits of four primes"""
+    announce("merged product and sum of products, key switch on chip")
+    pc.case_product_route(be, (12, 8, 50, 1, 51, 1), seed=342, batch=40, level=8, merged=True, expect=["inner_wg_kernel", "modup_cols_kernel<0, 2, 2>"],
+                          absent=["rows_inner_kernel"], sample=[0, 7, 39])
+    pc.case_sum_of_products(be, (12, 4, 51, 1, 51, 1), seed=343, terms=3, batch=27, levels=[4])
+    announce("digits of four primes")
+    pc.case_relin_and_composite(be, (12, 9, 50, 4, 51, 4), seed=344, batch=12, levels=[9, 7], expect=["inner_wg_kernel"], absent=["rows_inner_kernel"])
+    pc.case_rotate(be, (12, 9, 50, 4, 51, 4), seed=345, rotations=[3, 500], batch=11, level=8, expect=["inner_wg_kernel"], absent=["rows_inner_kernel"])
+
+
+@pytest.mark.parametrize("shape", [(12, 9, 51, 1, 51, 1), (12, 9, 50, 1, 51, 1), (12, 7, 51, 3, 51, 3), (13, 9, 51, 1, 51, 1), (13, 9, 50, 1, 51, 1)])
+def test_edge_values_on_chip(be, shape):
+    """residues at the ends and the middle of [0, q) and a key of all q-1 through the on-chip key switch and tail: accumulators reduced
+    every four (51-bit) or eight (50-bit) terms"""
+    announce("edge values on chip %r" % (shape,))
+    with be.tuned(64):
+        pc.case_edge_values(be, shape, seed=371, conv=False, pairs=FEW_PAIRS, expect=["inner_wg_kernel", "tail_sources_kernel"])
+
+
+@pytest.mark.parametrize("shape,batch", [((14, 3, 50, 1, 51, 1), 16), ((15, 2, 50, 1, 51, 1), 16), ((15, 2, 51, 1, 51, 1), 32), ((16, 2, 51, 1, 51, 1), 16)])
+def test_rotation_division_on_chip(be, shape, batch):
+    """ModDown with one special prime at the large rings: halves and quarters"""
+    announce("rotation, division on chip %r batch %d" % (shape, batch))
+    pc.case_rotate(be, shape, seed=346, rotations=[5, 1000], batch=batch, expect=ONE_KERNEL, absent=pair(shape[0]))
+
+
+@pytest.mark.parametrize("shape,batch,rotations", [((14, 3, 50, 1, 51, 1), 1, (1, 2, 5, 70, 4000, 8191)), ((15, 2, 50, 1, 51, 1), 2, (1, 2, 4, 8, 16, 32, 64, 16383)),
+                                                   ((15, 2, 51, 1, 51, 1), 4, (1, 2, 4, 8, 16, 32, 64, 128)), ((16, 2, 51, 1, 51, 1), 2, (1, 3, 9, 27, 81, 243, 729, 30000))])
+def test_shared_rotation_division_on_chip(be, shape, batch, rotations):
+    """the same for rotations from a shared ModUp, whose last step reads sigma(c0) through the automorphism"""
+    announce("shared rotations, division on chip %r" % (shape,))
+    pc.case_rotate_hoisted(be, shape, seed=347, rotations=rotations, batch=batch, expect=ONE_KERNEL, absent=pair(shape[0]))
 
 
 @pytest.mark.parametrize("shape,batch,level", [((12, 7, 50, 3, 51, 3), 16, 6), ((12, 4, 51, 2, 51, 2), 17, 4), ((13, 5, 51, 1, 51, 1), 32, 5),
@@ -714,7 +747,8 @@ def test_key_switch_on_chip(be, shape, batch, level):
 def test_tail_on_chip(be, shape, batch, level):
     """ModDown followed by rescale without an intermediate, at the smallest batches that take it"""
     announce("tail on chip %r batch %d" % (shape, batch))
-    pc.case_relin_and_composite(be, shape, seed=350, batch=batch, levels=[level])
+    pc.case_relin_and_composite(be, shape, seed=350, batch=batch, levels=[level], expect=["tail_sources_kernel", "conv_final_kernel"],
+                                absent=["modup_cols_kernel<%d, %d, 3>" % (shape[0] - 12, shape[3] + 1)])
 
 
 @pytest.mark.parametrize("shape,batch,level", [((12, 12, 50, 0, 51, 1), 9, 12), ((13, 8, 51, 0, 52, 1), 9, 8), ((14, 6, 50, 0, 51, 1), 5, 6),
@@ -722,13 +756,13 @@ def test_tail_on_chip(be, shape, batch, level):
 def test_one_source_division_uneven_rows(be, shape, batch, level):
     """a few rows that do not divide evenly over the XCDs: workgroups take all rows in turn"""
     announce("one-source division, uneven rows %r batch %d" % (shape, batch))
-    pc.case_rescale(be, shape, seed=360, batch=batch, levels=[level])
+    pc.case_division_route(be, shape, seed=360, batch=batch, level=level, one_kernel=True)
 
 
 @pytest.mark.parametrize("shape,batch,level,one_kernel", [((14, 6, 50, 0, 51, 1), 2, 6, False), ((14, 6, 50, 0, 51, 1), 4, 6, True),
                                                           ((15, 12, 50, 0, 51, 1), 2, 12, False), ((15, 12, 50, 0, 51, 1), 3, 12, True),
                                                           ((16, 12, 51, 0, 52, 1), 2, 12, False), ((16, 12, 51, 0, 52, 1), 4, 12, True),
-                                                          ((16, 12, 51, 0, 52, 1), 3, 12, False), ((16, 2, 50, 0, 51, 1), 40, 2, False), ((16, 2, 50, 0, 51, 1), 64, 2, True)])
+                                                          ((16, 12, 51, 0, 52, 1), 3, 12, False), ((16, 2, 50, 0, 51, 1), 40, 2, False), ((16, 2, 50, 0, 51, 1), 64, 2, True), ((16, 4, 50, 0, 51, 1), 32, 4, True)])
 def test_division_route(be, shape, batch, level, one_kernel):
     """rescale and rescale of a scalar multiple on either side of the number of kept limbs that the one kernel needs; at
     N = 2^16 also 66 limbs (a second round of workgroups with next to nothing in it) and a single kept limb a row"""
