@@ -143,8 +143,8 @@ void launch_ntt(ckksmi_ctx *c, bool forward, const u64 *src, u64 *dst, const Lim
     V.items_per_z = (int)((items + zchunks - 1) / zchunks);
     zchunks = (unsigned)((items + V.items_per_z - 1) / V.items_per_z);
     dim3 gv2(tiles, M.per_item, zchunks);
-    // (a few limbs of 2^14 words keep the two passes, whose tiles of 4096 words occupy more compute units: 13.7 us against 16 for
-    // 16 limbs; 8 limbs of 2^13 words: 13.1 us against 9.6)
+    // (a few limbs of 2^14 words keep the two passes, whose tiles of 4096 words occupy more compute units: 11.2 us against 15.6 for
+    // 16 limbs; 8 limbs of 2^13 words: 13.1 us against 9.1)
     if (passes == 3 && (c->logN == 12 || c->logN == 13 || (c->logN == 14 && limbs >= 64))) {
         // the whole limb in one workgroup: one trip through HBM (see ntt_wg.h); a workgroup loops over items of its limb slot
         unsigned zc = ((unsigned)c->ntt_target_wgs / 4 + M.per_item - 1) / M.per_item;
@@ -342,10 +342,11 @@ void launch_conv_final(ckksmi_ctx *c, int fin_kind, const u64 *y, size_t y_strid
     F.out = (u64d *)out; F.out_row_stride = (size_t)nc * c->N; F.modc = c->d_mod; F.tw = c->d_tww_fwd; F.Binv = D2 ? D2->Binv : D.Binv;
     F.logN = c->logN; F.nc = nc; F.rows = rows; F.p51 = c->p51mask;
     A.y = (const double *)y; A.y_row_stride = y_stride; A.D = D; A.T = c->T;
-    // Blocks per limb: M = N >> S words per workgroup.  Measured at 4096 and more limbs (us per 2^14 words): N = 2^12 whole 0.067;
-    // 2^13 halved 0.073, whole 0.075; 2^14 halved 0.078, whole 0.082 - 0.085; 2^15 halved 0.089, quartered 0.097; 2^16 quartered 0.109.  With
-    // too few workgroups for the 256 compute units finer blocks win instead (N = 2^14, 16 limbs: 11.8 us halved, 9.9 quartered;
-    // N = 2^15, 30 limbs: 20.4 and 15.8).
+    // Blocks per limb: M = N >> S words per workgroup.  Kernel time of rescales of 256 ciphertexts of 8 (N <= 2^14), 200 of 16 (2^15) or 64 of
+    // 24 primes (2^16), us per 2^14 words: N = 2^12 whole 0.070; 2^13 halved 0.081; 2^14 halved 0.094, quartered 0.101; 2^15 halved 0.094,
+    // quartered 0.106; 2^16 quartered 0.115 (whole limbs took 1.03 x the halves at 2^13 and 1.05 - 1.09 x at 2^14 when the accesses were
+    // flat).  With too few workgroups for the 256 compute units finer blocks win instead (N = 2^14, 16 limbs: 11.8 us halved, 9.9
+    // quartered; N = 2^15, 30 limbs: 20.4 and 15.8).
     int S = c->logN == 12 ? 0 : (c->logN == 16 ? 2 : 1);
     if ((c->logN == 14 || c->logN == 15) && (size_t)rows * nc * 2 < (size_t)c->ntt_target_wgs / 32 /* 256 */) S = 2;
     // Rows dealt to the eight XCDs leave some of them one row more than the others.  Where that costs a workgroup per compute unit (256
@@ -517,7 +518,8 @@ void launch_tensor_rows(ckksmi_ctx *c, const u64 *a, const u64 *b, u64 *ymid, in
 // workgroups, is faster (8 primes, N = 2^12: 36 workgroups 0.94 x, 144 1.02 - 1.06 x, 576 1.15 x, 2304 1.18 x).  N = 2^13 is cut into two
 // blocks, whose workgroups both convert every source word: with one source per digit that still wins (576 workgroups
 // 1.02 - 1.07 x, 4608 1.10 x), with three it does not (24 primes, 64 items: 0.92 x).  At N = 2^14 (two blocks of 2^13 words at one workgroup per
-// compute unit, or four of 2^12) it takes 1.65 - 1.72 ms for 256 items of 8 limbs, the two kernels 1.70 with a cheaper transform in front.
+// compute unit, or four of 2^12) it took 1.65 - 1.72 ms for 256 items of 8 limbs (with flat accesses), the two kernels 1.70 with a cheaper
+// transform in front.
 inline bool inner_wg_ok(const ckksmi_ctx *c, int level, int items) {
     const size_t wgs = (size_t)items * (level + c->k), fill = (size_t)c->ntt_target_wgs / 64;  // 128
     return (c->logN == 12 && wgs >= fill) || (c->logN == 13 && c->alpha == 1 && 2 * wgs >= 4 * fill);

@@ -6,8 +6,9 @@
 // owns (extended limb x, block, item), walks the digits, converts the digit's words (coefficient form, read by all extended
 // limbs of the item), transforms them in LDS and adds their products with the key words to the accumulators in its
 // registers.  N = 2^13 is cut into two blocks as in ks_wg.h.  Two workgroups of four waves per compute unit (256 registers:
-// accumulators, key words and the words in transform); what bounds it is the vector ALU (about 95 instructions per word and
-// digit) and two barriers per digit.  Products at 8 primes, 256 items: N = 2^12 621 -> 527 us, 2^13 1177 -> 1061 us.
+// accumulators, key words and the words in transform; the product form spills 20 around its own digit's operands); what bounds it is
+// the vector ALU (about 95 instructions per word and digit) and two barriers per digit.  Products at 8 primes, 256 items, with the on-chip
+// tail of ks_wg.h: N = 2^12 621 -> 427 us, 2^13 1160 -> 920 us (this kernel 354 and 734).
 #pragma once
 #include "ks_wg.h"
 

@@ -13,13 +13,14 @@
 // 2^S - 1 products (the other blocks' workgroups repeat the conversion, which for one dropped prime is one reduction) and
 // transforms M words from there: stage s of the block uses the twiddles (2^S + b) * 2^s + i of the whole transform's table.
 //
-// Measured (us per 2^14 words of kept limb, inverse transform of the dropped limb not counted): N = 2^15, 15 kept limbs 0.119 as
-// two kernels, 0.089 now; N = 2^16 0.143 and 0.109; N = 2^14 0.114 and 0.078 (3.4 TB/s of kept limbs in and out; a device
-// copy moves 4.85).  About 105 vector instructions per word (110 at S = 2): vector ALU 0.6 busy, memory 0.7 of a copy.  With four
-// waves per SIMD a thread has 128 registers; a single spilled register set costs more than everything else here (0.16 us
-// with 44 registers spilled), hence the notes to the compiler (ntt_v2.h).  Variants that lost: 32 words per thread at two waves
-// per SIMD with the kept limb requested before the transform (0.081 - 0.099), the kept limb requested after the transform
-// (0.083 - 0.095).
+// Measured, whole rescales as two kernels after the inverse row pass and as this one: N = 2^14, 256 ciphertexts of 8 primes 476 and 323 us;
+// 2^15, 448 of 16 primes 3333 and 2460; 2^16, 64 of 24 primes 1433 and 1261; 2^13, 512 of 8 primes 499 and 303.  At N = 2^15 the kernel
+// executes 110 vector instructions per word (vector ALU 0.64 busy) and moves 4.7 TB/s, where a device copy moves 4.85: the kept
+// limbs in and out, and every dropped limb about 12 times of the 30 that its kept limbs and blocks read it.
+// With four waves per SIMD a thread has 128 registers; a single spilled register set costs more than everything else here (0.16 us per
+// 2^14 words with 44 registers spilled, 0.08 without), hence the notes to the compiler (ntt_v2.h).  Variants that lost (both sides with
+// flat accesses, 0.078): 32 words per thread at two waves per SIMD with the kept limb requested before the transform (0.081 - 0.099), the
+// kept limb requested after the transform (0.083 - 0.095).
 #pragma once
 #include "ks_fused.h"
 #include "ntt_wg.h"
@@ -220,7 +221,7 @@ __global__ __launch_bounds__((1 << LOGM) / 16, 4) void conv_final_gal_kernel(Con
 // inverse transforms by one workgroup, in place: ModDown's conversion inputs y_m, and in place of the dropped limb the
 // rescale's y_B = (s + h_B) mod q_last, s = u - (sum_m y_m * conv_m - h_A) * P^-1 the ModDown result of that limb, whose
 // evaluation form u comes in with P^-1 and the addend already applied (z of the inner product).  512 rows of two limbs at N = 2^14: 0.11 ms
-// for this kernel and 0.39 for the kept limbs, against 0.07 (inverse row pass) + 0.21 (conversion) + 0.30 (last pass).
+// for this kernel and 0.36 for the kept limbs, against 0.07 (inverse row pass) + 0.21 (conversion) + 0.30 (last pass).
 struct TailSourcesArgs {
     u64d *bl;                          // row r, limb m at bl + r*row_stride + m*N; results as doubles
     unsigned long long row_stride;

@@ -9,8 +9,10 @@
 // 16 lanes exactly as in ntt_v2_rows.  Twiddles are fetched per round (they are shared by every limb of the modulus and
 // stay in L2) instead of being held across items: a thread's registers hold one round's set at a time, which keeps the
 // 1024-thread size within its 128 registers (with both rounds' twiddles requested early 21 forward and 34 inverse registers
-// spilled).  4096 limbs, forward / inverse: N = 2^12 3.7 / 3.7 TB/s (two passes through HBM: 2.7 / 2.7), 2^13 3.4 / 3.9, 2^14
-// 3.2 / 3.4; a device copy moves 4.85.
+// spilled).  Passes over 4096 limbs one after the other, forward / inverse: N = 2^12 56 / 59 us (two passes through HBM: 87 / 91), 2^13 139 /
+// 126 us (both rounds' twiddles early: 147 / 144), 2^14 300 / 297 us (324 / 308), which is 4.8 / 4.5, 3.9 / 4.3 and 3.6 / 3.6 TB/s (a device copy
+// moves 4.85); 4608 limbs of 2^14 words in bench.py's sweep 2.9 / 3.2 TB/s.  A few limbs of 2^13 words take as long as with early
+// twiddles forward (8 limbs 9.1 us) and 0.2 us longer inverse (9.1 and 9.3 us).
 #pragma once
 #include "ntt_v2.h"
 
@@ -274,7 +276,7 @@ __device__ __forceinline__ void ntt_wg_body(const NttV2Args &A, double *lds, int
     }
 }
 
-// grid: x = limb slot within an item, y = chunk of items; block = N/16 threads; dynamic LDS: (N/256) * V2_GS doubles
+// grid: x = limb slot within an item, y = chunk of items; block = N/16 threads
 template <bool INV, int LOGN, bool F64 = false>
 __global__ __launch_bounds__((1 << LOGN) / 16) void ntt_wg_kernel(NttV2Args A) {
     __shared__ double lds[((1 << LOGN) >> 8) * V2_GS];
