@@ -12,7 +12,7 @@
 // Ranges (p < 2^51, so 4p <= 2^53):
 //   mulmod_w(y, w)  : |y| <= 2^53, |w| <= p/2 prepared as (w, RN(w/p))
 //                     result r = y*w - q*p with |r| <= (1/2 + |y|*2^-53) p  (< 1.5 p)
-//   mulmod(a, b)    : |a|,|b| <= p, result |r| <= 1.25 p
+//   mulmod(a, b)    : |a|,|b| <= p, result |r| <= 1.25 p; in general |a| <= 2^53, |b| <= p/2: |r| <= (1/2 + 1.5 |a|*2^-53) p
 //   reduce_balanced : |x| <= 2^53 -> |r| <= p/2 + 1
 //   canon           : |x| <= 2^53 -> [0, p)
 #pragma once
@@ -56,9 +56,8 @@ __device__ __forceinline__ double canon_small(double r, double p) { return r < 0
 
 __device__ __forceinline__ bool is_p51(const P51Mask &m, int t) { return (m.w[t >> 6] >> (t & 63)) & 1ull; }
 
-// Intermediate between the two passes of a transform (never visible outside the library): the balanced-reduced
-// value stored as the bits of the double itself.  Saves the canonical form and both integer conversions.
-__device__ __forceinline__ unsigned long long mid_store(double x, double p, double pinv) {
-    return (unsigned long long)__double_as_longlong(reduce_balanced(x, p, pinv));
-}
+// Intermediate between the two passes of a transform (never visible outside the library): the value as the pass leaves it
+// (within the bounds of LazyRange, ntt_v2.h), stored as the bits of the double itself.  Saves the canonical form, both integer
+// conversions and the reduction.
+__device__ __forceinline__ unsigned long long mid_store(double x) { return (unsigned long long)__double_as_longlong(x); }
 __device__ __forceinline__ double mid_load(unsigned long long bits) { return __longlong_as_double((long long)bits); }

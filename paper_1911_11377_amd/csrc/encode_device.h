@@ -193,7 +193,7 @@ __device__ __forceinline__ void encrypt_rows_body(const EncryptRowsArgs &A, doub
         ulonglong2 mm[8];
 #pragma unroll
         for (int s = 0; s < 8; s++) mm[s] = ((const ulonglong2 *)(A.pt + ((size_t)it * A.level + i) * N + tile0))[row_pair_index(hi4, lo4, s)];
-        rows_fwd_to_lds<P51>(mid, lds, tw1_lds, tw2, p, pinv, hi4, lo4);
+        rows_fwd_to_lds<P51, false>(mid, lds, tw1_lds, tw2, p, pinv, hi4, lo4);
         double r[16];
 #pragma unroll
         for (int s = 0; s < 8; s++) {
@@ -202,18 +202,18 @@ __device__ __forceinline__ void encrypt_rows_body(const EncryptRowsArgs &A, doub
             r[2 * s + 1] = rr[1];
         }
         ROW_GROUP_SYNC();
-        rows_fwd_to_lds<P51>(mid + st, lds, tw1_lds, tw2, p, pinv, hi4, lo4);
+        rows_fwd_to_lds<P51, true>(mid + st, lds, tw1_lds, tw2, p, pinv, hi4, lo4);
         u64d *c0 = A.ct + ((size_t)it * 2 * A.level + i) * N + tile0, *c1 = c0 + st;
 #pragma unroll
         for (int s = 0; s < 8; s++) {
-            // a product (1.25p), a balanced-reduced word and a canonical one: below 4p
+            // a product of a balanced-reduced word (0.875p), a word of at most ROWX and a canonical one: below 2^53
             const double *ee = lds + hi4 * V2_GS + row_pair_lds(lo4, s);
             const double v0 = mulmod(r[2 * s], u2d(kb[s].x), p, pinv) + ee[0] + u2d(mm[s].x);
             const double v1 = mulmod(r[2 * s + 1], u2d(kb[s].y), p, pinv) + ee[1] + u2d(mm[s].y);
             ((ulonglong2 *)c0)[row_pair_index(hi4, lo4, s)] = make_ulonglong2(d2u(canon(v0, p, pinv)), d2u(canon(v1, p, pinv)));
         }
         ROW_GROUP_SYNC();
-        rows_fwd_to_lds<P51>(mid + 2 * st, lds, tw1_lds, tw2, p, pinv, hi4, lo4);
+        rows_fwd_to_lds<P51, true>(mid + 2 * st, lds, tw1_lds, tw2, p, pinv, hi4, lo4);
 #pragma unroll
         for (int s = 0; s < 8; s++) {
             const double *ee = lds + hi4 * V2_GS + row_pair_lds(lo4, s);

@@ -44,7 +44,6 @@ struct TensorRowsArgs {
 template <bool P51>
 __device__ __forceinline__ void tensor_rows_body(const TensorRowsArgs &A, double *lds, unsigned item, int i) {
     BODY_TAG(P51);
-    constexpr int I1 = P51 ? 0x2 : 0x4, I2 = P51 ? 0x1 : 0x4;
     const unsigned N = 1u << A.logN, N1 = N >> 8;
     const ModConst mc = A.modc[i];
     const double p = mc.p, pinv = mc.pinv;
@@ -79,17 +78,16 @@ __device__ __forceinline__ void tensor_rows_body(const TensorRowsArgs &A, double
         }
         SCHED_FENCE();
 #pragma unroll
-        for (int s = 0; s < 8; s++) {  // |sum| <= p/2 + 1 + 1.25p
+        for (int s = 0; s < 8; s++) {  // one product 1.25p, a sum is reduced
             d2[2 * s] = reduce_balanced(d2[2 * s] + mulmod(u2d(A1[s].x), u2d(B1[s].x), p, pinv), p, pinv);
             d2[2 * s + 1] = reduce_balanced(d2[2 * s + 1] + mulmod(u2d(A1[s].y), u2d(B1[s].y), p, pinv), p, pinv);
         }
     }
 #pragma unroll
     for (int s = 0; s < 8; s++) {
-        // the inverse row pass starts from the canonical representative, as it does when d2 comes from memory
         double *rr = grp + row_pair_lds(lo4, s);
-        rr[0] = canon(d2[2 * s], p, pinv);
-        rr[1] = canon(d2[2 * s + 1], p, pinv);
+        rr[0] = d2[2 * s];
+        rr[1] = d2[2 * s + 1];
     }
     ROW_GROUP_SYNC();
     // inverse row pass of d2 exactly as in ntt_v2_rows
@@ -97,16 +95,16 @@ __device__ __forceinline__ void tensor_rows_body(const TensorRowsArgs &A, double
     double x[16];
 #pragma unroll
     for (int e = 0; e < 16; e++) x[e] = grp[lo4 * 17 + e];
-    inv_round<I1, false>(x, tw2, p, pinv, unused, unused);
+    inv_stages<0, INV_ROW1, P51>(x, tw2, p, pinv, unused, unused);
 #pragma unroll
     for (int e = 0; e < 16; e++) grp[lo4 * 17 + e] = x[e];
     ROW_GROUP_SYNC();
 #pragma unroll
     for (int e = 0; e < 16; e++) x[e] = grp[e * 17 + lo4];
-    inv_round<I2, false>(x, tw1, p, pinv, unused, unused);
+    inv_stages<0, INV_ROW2, P51>(x, tw1, p, pinv, unused, unused);
     u64d *ym = A.ymid + ((size_t)item * A.level + i) * N + tile0;
 #pragma unroll
-    for (int e = 0; e < 16; e++) ym[hi4 * 256 + lo4 + 16 * e] = mid_store(x[e], p, pinv);
+    for (int e = 0; e < 16; e++) ym[hi4 * 256 + lo4 + 16 * e] = mid_store(x[e]);
 }
 
 // grid: x = tile (N/4096), y = limb, z = item
@@ -165,7 +163,6 @@ template <bool P51, int Q>
 __device__ __forceinline__ void inv_cols_in_regs(double (&x)[16], const double *twl, double *lds, const ColsGeom<Q> &geo, double p, double pinv,
                                                  const FinConst &F) {
     typedef ColsGeom<Q> Geo;
-    typedef ColsMasks<Q, P51> Mk;
     const WMul unused = WMul{0.0, 0.0};
     {
         double tw2[15];
@@ -180,9 +177,8 @@ __device__ __forceinline__ void inv_cols_in_regs(double (&x)[16], const double *
                     tw2[(1 << s) - 1 + b] = 0.0;
                 }
             }
-        inv_stages<Geo::S0, Mk::I1, false>(x, tw2, p, pinv, unused, unused);
+        inv_stages<Geo::S0, INV_COL2, P51>(x, tw2, p, pinv, unused, unused);
     }
-    reduce16(x, p, pinv);
 #pragma unroll
     for (int i = 0; i < 16; i++) lds[geo.l2(i)] = x[i];
     __syncthreads();
@@ -192,7 +188,7 @@ __device__ __forceinline__ void inv_cols_in_regs(double (&x)[16], const double *
         double tw1[15];
 #pragma unroll
         for (int i = 0; i < 15; i++) tw1[i] = twl[1 + i];
-        inv_round<Mk::I2, true>(x, tw1, p, pinv, F.ninv, F.wlast);
+        inv_stages<0, INV_COL1, P51>(x, tw1, p, pinv, F.ninv, F.wlast);
     }
 #pragma unroll
     for (int e = 0; e < 16; e++) x[e] = canon(x[e] + F.cadd, p, pinv);
@@ -204,11 +200,19 @@ __device__ __forceinline__ void inv_cols_in_regs(double (&x)[16], const double *
 //     value = (sum_a y_a*conv_a - hA) * P^-1 + y_B - hB     (the two conversion results the last pass would subtract,
 //                                                            brought to one: the transforms are linear)
 template <bool P51, int NSRC, int Q, int VARIANT>
-__device__ __forceinline__ void modup_cols_target(const double (&yd)[NSRC][16], const WMul (&Wc)[NSRC], const double *twl, double *lds, u64d *dst,
+__device__ __forceinline__ void modup_cols_target(const double (&yd)[NSRC][16], WMul (&Wc)[NSRC], const double *twl, double *lds, u64d *dst,
                                                   const ColsGeom<Q> &geo, double p, double pinv, double *twl_next, double tw_store, double hsub,
                                                   unsigned long long vpack, double Bm, const double *ybl = nullptr) {
     typedef ColsGeom<Q> Geo;
-    typedef ColsMasks<Q, P51> Mk;
+    // what enters the first stage, in 1/256 p: p + NSRC * 0.75p, an overshoot's reduced term + NSRC * 0.75p, or (one conversion
+    // for two divisions) a product of at most 0.91p + y_B below 2p + p
+    constexpr int ENTRY = VARIANT == 0 ? 256 + 192 * NSRC : VARIANT == 1 ? 131 + 192 * NSRC : 1001;
+    typedef ColsMasks<Q, P51, ENTRY> Mk;
+    BODY_TAG(P51);
+    if (VARIANT == 2) {  // the products by these constants would be moved above the branch all the same: 350 registers spilled
+#pragma unroll
+        for (int a = 0; a < NSRC; a++) PIN_UNIFORM(Wc[a].w);
+    }
     double x[16];
 #pragma unroll
     for (int e = 0; e < 16; e++) {
@@ -219,9 +223,10 @@ __device__ __forceinline__ void modup_cols_target(const double (&yd)[NSRC][16], 
             const double ya = (VARIANT == 0 && NSRC == 3 && a == 0 && ybl) ? ybl[e * 256 + threadIdx.x] : yd[a][e];
             v += mulmod_w(ya, Wc[a].w, Wc[a].wp, p);
         }
-        x[e] = reduce_balanced(v, p, pinv);  // |v| <= p + NSRC * 0.75p
-        if (VARIANT == 2)  // 0.75p + (y_B < 2^51) + p: below 2^53
-            x[e] = reduce_balanced(mulmod_w(x[e], Wc[0].w, Wc[0].wp, p) + ybl[e * 256 + threadIdx.x] - Bm, p, pinv);
+        x[e] = v;  // |v| <= p + NSRC * 0.75p
+        if (VARIANT == 2) {  // y_B is below the dropped prime, which has as many bits as p: below 2p
+            x[e] = mulmod_w(P51 ? reduce_balanced(v, p, pinv) : v, Wc[0].w, Wc[0].wp, p) + ybl[e * 256 + threadIdx.x] - Bm;
+        }
     }
     {
         double tw1[15];
@@ -251,7 +256,7 @@ __device__ __forceinline__ void modup_cols_target(const double (&yd)[NSRC][16], 
         fwd_stages<Geo::S0, Mk::F2>(x, tw2, p, pinv);
     }
 #pragma unroll
-    for (int i = 0; i < 16; i++) dst[geo.g2(i)] = mid_store(x[i], p, pinv);
+    for (int i = 0; i < 16; i++) dst[geo.g2(i)] = mid_store(x[i]);
 }
 
 // grid: x = column tile (N/4096), y = item * beta + digit, z = chunk of targets_per_wg target limbs
@@ -376,23 +381,23 @@ __global__ __launch_bounds__(V2_THREADS, (NSRC >= 4 && MODE == 2) ? 1 : 2) void 
         double *tnext = twl[(k - k0 + 1) % 3];
         const double tw_store = tw_next;  // twiddle of target k+1, written before this target's barrier
         if (k + 2 < k1) tw_next = A.tw[(size_t)mod_of(ext_of(k + 2)) * N + threadIdx.x];
-        const double p = A.modc[t].p, pinv = A.modc[t].pinv;
+        const double p = table_load(&A.modc[t].p, 0), pinv = table_load(&A.modc[t].pinv, 0);
         WMul Wc[NSRC];
         double hsub = 0.0, Bm = 0.0;
         u64d *dst;
         if (MODE == 0) {
 #pragma unroll
-            for (int a = 0; a < NSRC; a++) Wc[a] = a < nsrc ? A.cc[(crow + a) * A.T + t] : WMul{0.0, 0.0};
+            for (int a = 0; a < NSRC; a++) Wc[a] = a < nsrc ? table_load(&A.cc[(crow + a) * A.T + t]) : WMul{0.0, 0.0};
             dst = A.dst + (((size_t)item * A.beta + j) * A.E + x) * N;
         } else {
 #pragma unroll
             for (int a = 0; a < NSRC; a++)
-                Wc[a] = a < nsrc ? A.D.conv[(size_t)(MODE == 3 ? (a ? a - 1 : 0) : a) * A.T + t] : WMul{0.0, 0.0};
-            hsub = A.D.hc[t];
-            if (MODE == 2) Bm = A.D.Bmod[t];
+                Wc[a] = a < nsrc ? table_load(&A.D.conv[(size_t)(MODE == 3 ? (a ? a - 1 : 0) : a) * A.T + t]) : WMul{0.0, 0.0};
+            hsub = table_load(A.D.hc, t);
+            if (MODE == 2) Bm = table_load(A.D.Bmod, t);
             if (MODE == 3) {
-                Wc[0] = A.D.Binv[t];
-                Bm = A.hc2[t];
+                Wc[0] = table_load(&A.D.Binv[t]);
+                Bm = table_load(A.hc2, t);
             }
             dst = A.dst + ((size_t)blockIdx.y * A.nc + t) * N;
         }
@@ -423,13 +428,13 @@ __device__ __forceinline__ void load_row_twiddles(const double *tw, unsigned N1,
     __syncthreads();
 }
 
-// Finish the forward transform of one 16-row tile (column pass already done) and leave the
-// balanced-reduced results in LDS in the padded layout: word (row g, position q) at g*V2_GS + (q/16)*17 + q%16.
+// Finish the forward transform of one 16-row tile (column pass already done) and leave the results, balanced-reduced or (LAZY)
+// at most LazyRange::ROWX, in LDS in the padded layout: word (row g, position q) at g*V2_GS + (q/16)*17 + q%16.
 // Every row is handled by its own 16 lanes: ends with a row-group sync, and the caller puts one before the next call.
-template <bool P51>
+template <bool P51, bool LAZY>
 __device__ __forceinline__ void rows_fwd_to_lds(const u64d *tile, double *lds, const double *tw1_lds, const double (&tw2)[15], double p,
                                                 double pinv, unsigned hi4, unsigned lo4) {
-    constexpr int F1 = P51 ? 0xA : 0x8, F2 = P51 ? 0x2 : 0x0;
+    typedef RowMasks<P51, LAZY> Mk;
     double *grp = lds + hi4 * V2_GS;
     double x[16];
 #pragma unroll
@@ -439,16 +444,16 @@ __device__ __forceinline__ void rows_fwd_to_lds(const u64d *tile, double *lds, c
         double tw1[15];
 #pragma unroll
         for (int i = 0; i < 15; i++) tw1[i] = tw1_lds[hi4 * 16 + i];
-        fwd_round<F1>(x, tw1, p, pinv);
+        fwd_round<Mk::F1>(x, tw1, p, pinv);
     }
 #pragma unroll
     for (int e = 0; e < 16; e++) grp[e * 17 + lo4] = x[e];
     ROW_GROUP_SYNC();
 #pragma unroll
     for (int e = 0; e < 16; e++) x[e] = grp[lo4 * 17 + e];
-    fwd_round<F2>(x, tw2, p, pinv);
+    fwd_round<Mk::F2>(x, tw2, p, pinv);
 #pragma unroll
-    for (int e = 0; e < 16; e++) grp[lo4 * 17 + e] = reduce_balanced(x[e], p, pinv);
+    for (int e = 0; e < 16; e++) grp[lo4 * 17 + e] = LAZY ? x[e] : reduce_balanced(x[e], p, pinv);
     ROW_GROUP_SYNC();
 }
 
@@ -625,7 +630,7 @@ template <bool P51, bool GAL = false>
 __device__ __forceinline__ void rows_inner_body(const RowsInnerArgs &A, const KeyTab &K, double *lds, double *tw1_lds, double *tw2_lds, int t,
                                                 unsigned x, const GaloisTab *gal = nullptr) {
     BODY_TAG(P51);
-    constexpr int F1 = P51 ? 0xA : 0x8, F2 = P51 ? 0x2 : 0x0;
+    typedef RowMasks<P51, false> Mk;
     const unsigned N = 1u << A.logN, N1 = N >> 8;
     const double p = A.modc[t].p, pinv = A.modc[t].pinv;
     const unsigned tid = threadIdx.x, hi4 = tid >> 4, lo4 = tid & 15;
@@ -684,7 +689,7 @@ __device__ __forceinline__ void rows_inner_body(const RowsInnerArgs &A, const Ke
                 double tw1[15];
 #pragma unroll
                 for (int i = 0; i < 15; i++) tw1[i] = tw1_lds[hi4 * 16 + i];
-                fwd_round<F1>(xx, tw1, p, pinv);
+                fwd_round<Mk::F1>(xx, tw1, p, pinv);
             }
 #pragma unroll
             for (int e = 0; e < 16; e++) grp[e * 17 + lo4] = xx[e];
@@ -695,7 +700,7 @@ __device__ __forceinline__ void rows_inner_body(const RowsInnerArgs &A, const Ke
                 double tw2[15];
 #pragma unroll
                 for (int i = 0; i < 15; i++) tw2[i] = tw2_lds[i * 256 + tid];
-                fwd_round<F2>(xx, tw2, p, pinv);
+                fwd_round<Mk::F2>(xx, tw2, p, pinv);
             }
 #pragma unroll
             for (int e = 0; e < 16; e++) grp[lo4 * 17 + e] = reduce_balanced(xx[e], p, pinv);
@@ -821,16 +826,16 @@ __device__ __forceinline__ void rows_final_body(const RowsFinalArgs &A, double *
             }
         }
         SCHED_FENCE();
-        rows_fwd_to_lds<P51>(A.tmpA + ((size_t)row * A.nc + i) * N + tile0, lds, tw1_lds, tw2, p, pinv, hi4, lo4);
+        rows_fwd_to_lds<P51, true>(A.tmpA + ((size_t)row * A.nc + i) * N + tile0, lds, tw1_lds, tw2, p, pinv, hi4, lo4);
 #pragma unroll
         for (int s = 0; s < 8; s++) {
             const double *rr = lds + hi4 * V2_GS + row_pair_lds(lo4, s);
             double x0 = u2d(xr[s].x), x1 = u2d(xr[s].y);
-            if (pre) {  // |x + pre*addend - r| < p + 1.5p + p/2 + 1
+            if (pre) {  // |x + pre*addend - r| < p + 0.75p + ROWX: below 2^53
                 x0 += mulmod_w(u2d(ar[s].x), Pm.w, Pm.wp, p);
                 x1 += mulmod_w(u2d(ar[s].y), Pm.w, Pm.wp, p);
             }
-            if (xm) {  // |x*xmv - r| < 0.75p + p/2 + 1 (without an addend `ar` is a copy of x: not used)
+            if (xm) {  // |x*xmv - r| < 0.75p + ROWX (without an addend `ar` is a copy of x: not used)
                 x0 = mulmod_w(x0, Pm.w, Pm.wp, p);
                 x1 = mulmod_w(x1, Pm.w, Pm.wp, p);
             }

@@ -19,14 +19,6 @@ struct InnerWgArgs {
     int items, items_x;
 };
 
-// A uniform entry of the (read-only) twiddle table through the scalar cache: held in scalar registers over the digits
-#ifdef CKKSMI_EMULATE
-static inline double table_load(const double *t, unsigned i) { return t[i]; }
-#else
-typedef const __attribute__((address_space(4))) double *ConstTable;
-__device__ __forceinline__ double table_load(const double *t, unsigned i) { return ((ConstTable)(unsigned long long)t)[i]; }
-#endif
-
 // LDS of a workgroup: the matrix of wg_fwd_block, the first row round's twiddles [M/256][16] and the second's [15][M/16].  All
 // digits of a workgroup use the same twiddles, and fetching them per digit exposes their latency three times.
 template <int LOGM>
@@ -40,15 +32,15 @@ template <int LOGM, bool P51, class F>
 __device__ __forceinline__ void inner_fwd_block(double (&x)[16], const double (&twc)[15], double *lds, double p, double pinv, F request) {
     static_assert(LOGM == 12, "one column round");
     typedef ColsGeom<0> Geo;
-    typedef ColsMasks<0, P51> Mk;
+    typedef ColsMasks<0, P51, 308> Mk;
+    typedef RowMasks<P51, false> Rm;
     typedef InnerWgLds<LOGM> Lay;
-    constexpr int RF1 = P51 ? 0xA : 0x8, RF2 = P51 ? 0x2 : 0x0;
     const unsigned tid = threadIdx.x, row = tid >> 4, lo4 = tid & 15;
     const Geo geo(tid & 255u, tid >> 8);
     double *grp = lds + row * V2_GS;
     fwd_round<Mk::F1>(x, twc, p, pinv);
 #pragma unroll
-    for (int e = 0; e < 16; e++) lds[wg_pad(e, geo.c0 + geo.c)] = x[e];  // the column round ends reduced
+    for (int e = 0; e < 16; e++) lds[wg_pad(e, geo.c0 + geo.c)] = x[e];
     __syncthreads();
     request();
 #pragma unroll
@@ -57,7 +49,7 @@ __device__ __forceinline__ void inner_fwd_block(double (&x)[16], const double (&
         double t1[15];
 #pragma unroll
         for (int i = 0; i < 15; i++) t1[i] = lds[Lay::TW1 + row * 16 + i];
-        fwd_round<RF1>(x, t1, p, pinv);
+        fwd_round<Rm::F1>(x, t1, p, pinv);
     }
 #pragma unroll
     for (int e = 0; e < 16; e++) grp[e * 17 + lo4] = x[e];
@@ -68,7 +60,7 @@ __device__ __forceinline__ void inner_fwd_block(double (&x)[16], const double (&
         double t2[15];
 #pragma unroll
         for (int i = 0; i < 15; i++) t2[i] = lds[Lay::TW2 + i * Lay::T + tid];
-        fwd_round<RF2>(x, t2, p, pinv);
+        fwd_round<Rm::F2>(x, t2, p, pinv);
     }
 #pragma unroll
     for (int e = 0; e < 16; e++) grp[lo4 * 17 + e] = reduce_balanced(x[e], p, pinv);

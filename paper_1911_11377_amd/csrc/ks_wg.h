@@ -141,7 +141,7 @@ __device__ __forceinline__ void conv_final_body(const ConvFinalArgs &A, double *
     ulonglong2 *out = (ulonglong2 *)(F.out + (size_t)row * F.out_row_stride + off);
     const unsigned pr = row_pair_index(prow, lo4, 0);
     ulonglong2 xr[8];
-    wg_fwd_block<LOGM, P51>(x, tw, base, lds, p, pinv, [&]() {
+    wg_fwd_block<LOGM, P51, true>(x, tw, base, lds, p, pinv, [&]() {
 #pragma unroll
         for (int s = 0; s < 8; s++) xr[s] = (xin + 16 * s)[pr];
     });
@@ -151,7 +151,7 @@ __device__ __forceinline__ void conv_final_body(const ConvFinalArgs &A, double *
     auto finish = [&](int s, bool with, ulonglong2 ar) {
         const double *rr = grp + row_pair_lds(lo4, s);
         double x0 = u2d(xr[s].x), x1 = u2d(xr[s].y);
-        if (FIN == 2) {  // |x * xmv - r| <= 0.75p + p/2 + 1
+        if (FIN == 2) {  // |x * xmv| <= 0.75p; r is below ROWX, x - r within the range of a product
             x0 = mulmod_w(x0, xmv.w, xmv.wp, p);
             x1 = mulmod_w(x1, xmv.w, xmv.wp, p);
         }

@@ -18,13 +18,19 @@
 // so they are loaded into registers once per workgroup and reused for every item the workgroup
 // loops over (same modulus, same tile): twiddle traffic is amortised over the batch.
 //
-// Between the two passes the words are stored as balanced-reduced doubles (mid_store / mid_load), not as canonical
+// Between the two passes the words are stored as lazily reduced doubles (mid_store / mid_load), not as canonical
 // integers: that intermediate never leaves the library.
 //
-// Lazy ranges (units of p, see device_arith.h): with the quotient w/p recomputed in registers a twiddle
-// product of y is bounded by (1/2 + 1.5*|y|/2^53) p, so a butterfly stage maps a bound B to
-// B + 1/2 + 1.5*B*p/2^53 forward and to 2B inverse; values must stay below 2^53, i.e. 8p for
-// p < 2^50 and 4p for p < 2^51, so the reduction points differ (template parameter P51).
+// Lazy ranges (units of p, see device_arith.h): a twiddle product of y is bounded by (1/2 + 1.5*|y|/2^53) p, so a butterfly
+// stage maps a bound B to B + 1/2 + 1.5*B*p/2^53 forward and to 2B (the sum) or 1/2 + 3*B*p/2^53 (the product) inverse; values
+// must stay below 2^53, i.e. 8p for p < 2^50 and 4p for p < 2^51 (template parameter P51).  A reduction costs three
+// instructions of the eight of a butterfly, so the words that are reduced, and where, are found at compile time (fwd_plan,
+// inv_plan below): forward only the addends u of u +- w*v at one or two of eight stages, inverse only the registers whose
+// sum would pass the limit.  That is 3 (forward) and 6 (inverse) instructions per word of a 16-stage transform at p < 2^50,
+// against 9 and 15 with all words reduced at the end of every round.  With the quotient taken from the product itself (mulmod)
+// a twiddle costs no register and no instruction beside its word.  Together, against reductions of whole rounds and w/p
+// recomputed per block: 64 products at N = 2^16, 24 primes 7569 -> 7216 us, 256 at 2^14, 8 primes 2213 -> 2103, 64 fresh
+// ciphertexts 3474 -> 2790 (their row pass at two waves per SIMD instead of one).
 #pragma once
 #include "device_arith.h"
 
@@ -56,14 +62,17 @@
 //                   accesses; rescale of 256 ciphertexts at N = 2^14, 8 primes 335 and 321 us, N = 2^15, 16 primes, 448
 //                   ciphertexts 2503 and 2469 us;
 //   WG_UNIFORM(v)   a workgroup-uniform value goes to a scalar register;
+//   PIN_UNIFORM(x)  the same as PIN_VALUE for a workgroup-uniform value in scalar registers;
 //   LOAD_FENCE()    memory accesses stay on their side.
 #ifdef CKKSMI_EMULATE
 #define PIN_VALUE(x) ((void)0)
+#define PIN_UNIFORM(x) ((void)0)
 #define LOAD_FENCE() ((void)0)
 #define WG_UNIFORM(v) (v)
 template <class T> __device__ __forceinline__ T *scalar_base(T *p) { return p; }
 #else
 #define PIN_VALUE(x) asm volatile("" : "+v"(x))
+#define PIN_UNIFORM(x) asm volatile("" : "+s"(x))
 #define LOAD_FENCE() asm volatile("" ::: "memory")
 #define WG_UNIFORM(v) ((unsigned)__builtin_amdgcn_readfirstlane((int)(v)))
 template <class T> __device__ __forceinline__ __attribute__((address_space(1))) T *scalar_base(T *p) {
@@ -72,6 +81,16 @@ template <class T> __device__ __forceinline__ __attribute__((address_space(1))) 
     return g;
 }
 #endif
+
+// A workgroup-uniform entry of a read-only table through the scalar cache: it arrives in scalar registers.  (A kernel that also
+// stores gets its uniform loads in vector registers otherwise.)
+#ifdef CKKSMI_EMULATE
+static inline double table_load(const double *t, unsigned i) { return t[i]; }
+#else
+typedef const __attribute__((address_space(4))) double *ConstTable;
+__device__ __forceinline__ double table_load(const double *t, unsigned i) { return ((ConstTable)(unsigned long long)t)[i]; }
+#endif
+__device__ __forceinline__ WMul table_load(const WMul *t) { return WMul{table_load((const double *)t, 0), table_load((const double *)t, 1)}; }
 
 #define V2_GS 272  // doubles per padded 16x17 group in LDS (row pass)
 
@@ -113,13 +132,72 @@ struct NttV2Args {
     LimbMap map;
 };
 
-__device__ __forceinline__ void reduce16(double (&x)[16], double p, double pinv) {
-#pragma unroll
-    for (int e = 0; e < 16; e++) x[e] = reduce_balanced(x[e], p, pinv);
+// Bounds (units of p) where a value changes hands
+template <bool P51>
+struct LazyRange {
+    static constexpr double LIM = P51 ? 4.0 : 8.0;    // 2^53 / p
+    static constexpr double MIDF = P51 ? 2.5 : 3.5;   // forward, between column and row pass
+    static constexpr double ROWX = P51 ? 2.0 : 6.2;   // forward, results that a pointwise step takes as they are
+    static constexpr double INV0 = 1.25, INV1 = 2.0, MIDI = P51 ? 2.0 : 4.0;  // inverse: entry, between rounds, between row and column pass
+};
+#define LAZY_REDUCED 0.51  // |x| <= p/2 + 1
+
+// bound after n forward stages from `entry` when the addends are reduced at the stages of `mask`; above the limit: -1
+constexpr double fwd_bound(bool p51, double entry, int n, int mask) {
+    const double lim = p51 ? 4.0 : 8.0;
+    double b = entry;
+    for (int s = 0; s < n; s++) {
+        if (b > lim) return -1.0;
+        b = ((mask >> s) & 1 ? LAZY_REDUCED : b) + 0.5 + 1.5 * b / lim;
+    }
+    return b > lim ? -1.0 : b;
+}
+// fewest reductions that end at or below `exit`
+constexpr int fwd_plan(bool p51, double entry, int n, double exit) {
+    int best = -1, best_count = n + 1;
+    for (int m = 0; m < (1 << n); m++) {
+        int count = 0;
+        for (int s = 0; s < n; s++) count += (m >> s) & 1;
+        const double b = fwd_bound(p51, entry, n, m);
+        if (b >= 0.0 && b <= exit && count < best_count) {
+            best = m;
+            best_count = count;
+        }
+    }
+    return best;
+}
+
+// Inverse stages 3 .. S0 of a 16-point round: registers reduced before the k-th executed stage (bit = register), and at the end
+struct InvPlan {
+    unsigned before[4], after;
+};
+constexpr InvPlan inv_plan(bool p51, double entry, int S0, double exit, bool final) {
+    const double lim = p51 ? 4.0 : 8.0;
+    InvPlan P{{0, 0, 0, 0}, 0};
+    double b[16] = {};
+    for (int i = 0; i < 16; i++) b[i] = entry;
+    for (int k = 0; k < 4 - S0; k++) {
+        const int s = 3 - k, span = 8 >> s;
+        for (int lo = 0; lo < 16; lo++) {
+            if (lo & span) continue;
+            const int hi = lo + span;
+            for (int r = 0; r < 2 && b[lo] + b[hi] > lim; r++) {  // the larger one first
+                const int i = b[lo] >= b[hi] ? lo : hi;
+                b[i] = LAZY_REDUCED;
+                P.before[k] |= 1u << i;
+            }
+            const double sum = b[lo] + b[hi], prod = 0.5 + 1.5 * sum / lim;
+            b[lo] = final && s == 0 ? prod : sum;
+            b[hi] = prod;
+        }
+    }
+    for (int i = 0; i < 16; i++)
+        if (b[i] > exit) P.after |= 1u << i;
+    return P;
 }
 
 // decimation-in-time stages S0..3 of a 16-point round (spans 8 >> s over the register index);
-// MASK bit s: reduce all words after stage s
+// MASK bit s: the addends of stage s are reduced first
 template <int S0, int MASK>
 __device__ __forceinline__ void fwd_stages(double (&x)[16], const double (&tw)[15], double p, double pinv) {
 #pragma unroll
@@ -127,18 +205,16 @@ __device__ __forceinline__ void fwd_stages(double (&x)[16], const double (&tw)[1
         const int span = 8 >> s;
 #pragma unroll
         for (int b = 0; b < (1 << s); b++) {
-            // registers hold w only; w/p is recomputed per block (one multiply, within 3 ulp of w/p)
-            const double Ww = tw[(1 << s) - 1 + b], Wp = Ww * pinv;
 #pragma unroll
             for (int j = 0; j < span; j++) {
                 const int lo = b * 2 * span + j, hi = lo + span;
-                const double v = mulmod_w(x[hi], Ww, Wp, p);
-                const double u = x[lo];
+                // the quotient from the product itself: no w/p to keep or to compute
+                const double v = mulmod(x[hi], tw[(1 << s) - 1 + b], p, pinv);
+                const double u = (MASK & (1 << s)) ? reduce_balanced(x[lo], p, pinv) : x[lo];
                 x[lo] = u + v;
                 x[hi] = u - v;
             }
         }
-        if (MASK & (1 << s)) reduce16(x, p, pinv);
     }
 }
 template <int MASK>
@@ -146,35 +222,39 @@ __device__ __forceinline__ void fwd_round(double (&x)[16], const double (&tw)[15
     fwd_stages<0, MASK>(x, tw, p, pinv);
 }
 
-// the same stages undone, 3 down to S0 (spans 1,2,..); MASK bit k: reduce after the k-th executed
-// stage; FINAL folds 1/N into the very last stage (s = 0) of the whole transform
-template <int S0, int MASK, bool FINAL>
+// the same stages undone, 3 down to S0 (spans 1,2,..), with the reductions of inv_plan; B: where the round stands (the bounds
+// of its words, InvRound); FINAL folds 1/N into the very last stage (s = 0) of the whole transform
+enum InvRound { INV_ROW1, INV_ROW2, INV_COL2, INV_COL1 };
+template <int S0, InvRound B, bool P51>
 __device__ __forceinline__ void inv_stages(double (&x)[16], const double (&tw)[15], double p, double pinv, WMul ninv, WMul wlast) {
+    typedef LazyRange<P51> R;
+    constexpr bool FINAL = B == INV_COL1;
+    constexpr double ENTRY = B == INV_ROW1 ? R::INV0 : B == INV_COL2 ? R::MIDI : R::INV1;
+    constexpr double EXIT = B == INV_ROW2 ? R::MIDI : FINAL ? R::LIM : R::INV1;
+    constexpr InvPlan PL = inv_plan(P51, ENTRY, S0, EXIT, FINAL);
 #pragma unroll
     for (int k = 0; k < 4 - S0; k++) {
         const int s = 3 - k, span = 8 >> s;
 #pragma unroll
         for (int b = 0; b < (1 << s); b++) {
-            const double Ww = tw[(1 << s) - 1 + b], Wp = Ww * pinv;
 #pragma unroll
             for (int j = 0; j < span; j++) {
                 const int lo = b * 2 * span + j, hi = lo + span;
-                const double u = x[lo], v = x[hi];
+                const double u = (PL.before[k] >> lo) & 1u ? reduce_balanced(x[lo], p, pinv) : x[lo];
+                const double v = (PL.before[k] >> hi) & 1u ? reduce_balanced(x[hi], p, pinv) : x[hi];
                 if (FINAL && s == 0) {
                     x[lo] = mulmod_w(u + v, ninv.w, ninv.wp, p);
                     x[hi] = mulmod_w(u - v, wlast.w, wlast.wp, p);
                 } else {
                     x[lo] = u + v;
-                    x[hi] = mulmod_w(u - v, Ww, Wp, p);
+                    x[hi] = mulmod(u - v, tw[(1 << s) - 1 + b], p, pinv);
                 }
             }
         }
-        if (MASK & (1 << k)) reduce16(x, p, pinv);
     }
-}
-template <int MASK, bool FINAL>
-__device__ __forceinline__ void inv_round(double (&x)[16], const double (&tw)[15], double p, double pinv, WMul ninv, WMul wlast) {
-    inv_stages<0, MASK, FINAL>(x, tw, p, pinv, ninv, wlast);
+#pragma unroll
+    for (int i = 0; i < 16; i++)
+        if ((PL.after >> i) & 1u) x[i] = reduce_balanced(x[i], p, pinv);
 }
 
 // ------------------------------------------------------------------ row pass twiddles
@@ -222,14 +302,20 @@ __device__ __forceinline__ void load_cols_twiddles(const double *tw, unsigned a,
         }
 }
 
-// lazy-range reduction points of the column pass (see header comment)
-template <int Q, bool P51>
+// forward reduction masks of the column pass: round 1, and round 2 (Q stages, register stages from 4 - Q on).  ENTRY256: bound of
+// the input in 1/256 p
+template <int Q, bool P51, int ENTRY256>
 struct ColsMasks {
-    static constexpr int F1 = P51 ? 0xA : 0x8;            // forward round 1 from canonical input, ends reduced
-    static constexpr int F2 = (P51 && Q == 4) ? 0x2 : 0;  // forward round 2 (Q stages) from a reduced value
-    // inverse round 2 (Q stages, executed first, canonical input); always followed by a reduction
-    static constexpr int I1 = P51 ? (Q >= 3 ? 0x2 : 0) : (Q == 4 ? 0x4 : 0);
-    static constexpr int I2 = P51 ? 0x2 : 0;              // inverse round 1 from a reduced value, last stage multiplies
+    static constexpr int PLAN = fwd_plan(P51, ENTRY256 / 256.0, 4 + Q, LazyRange<P51>::MIDF);
+    static_assert(PLAN >= 0, "no reduction schedule");
+    static constexpr int F1 = PLAN & 15, F2 = (PLAN >> 4) << (4 - Q);
+};
+// ... and of the row pass, from MIDF.  LAZY: the results serve a pointwise step as they are, else they are reduced or made canonical
+template <bool P51, bool LAZY>
+struct RowMasks {
+    static constexpr int PLAN = fwd_plan(P51, LazyRange<P51>::MIDF, 8, LAZY ? LazyRange<P51>::ROWX : LazyRange<P51>::LIM);
+    static_assert(PLAN >= 0, "no reduction schedule");
+    static constexpr int F1 = PLAN & 15, F2 = PLAN >> 4;
 };
 
 // SMALL (forward only): the source is a polynomial with small signed coefficients, one int64 per coefficient and the same
@@ -238,7 +324,7 @@ struct ColsMasks {
 template <bool INV, int Q, bool P51, bool SMALL = false, bool F64 = false>
 __device__ __forceinline__ void ntt_v2_cols(const NttV2Args &A, double *lds, int t, unsigned li) {
     typedef ColsGeom<Q> Geo;
-    typedef ColsMasks<Q, P51> Mk;
+    typedef ColsMasks<Q, P51, 256> Mk;
     const unsigned N = 1u << A.logN;
     const double p = A.modc[t].p, pinv = A.modc[t].pinv;
     const double *tw = A.tw + (size_t)t * N;
@@ -278,18 +364,17 @@ __device__ __forceinline__ void ntt_v2_cols(const NttV2Args &A, double *lds, int
             for (int i = 0; i < 16; i++) x[i] = lds[geo.l2(i)];
             fwd_stages<Geo::S0, Mk::F2>(x, tw2, p, pinv);
 #pragma unroll
-            for (int i = 0; i < 16; i++) dst[geo.g2(i)] = mid_store(x[i], p, pinv);
+            for (int i = 0; i < 16; i++) dst[geo.g2(i)] = mid_store(x[i]);
         } else {
 #pragma unroll
             for (int i = 0; i < 16; i++) x[i] = mid_load(src[geo.g2(i)]);
-            inv_stages<Geo::S0, Mk::I1, false>(x, tw2, p, pinv, ninv, wlast);
-            reduce16(x, p, pinv);
+            inv_stages<Geo::S0, INV_COL2, P51>(x, tw2, p, pinv, ninv, wlast);
 #pragma unroll
             for (int i = 0; i < 16; i++) lds[geo.l2(i)] = x[i];
             __syncthreads();
 #pragma unroll
             for (int e = 0; e < 16; e++) x[e] = lds[geo.l1(e)];
-            inv_round<Mk::I2, true>(x, tw1, p, pinv, ninv, wlast);
+            inv_stages<0, INV_COL1, P51>(x, tw1, p, pinv, ninv, wlast);
 #pragma unroll
             for (int e = 0; e < 16; e++) {
                 const double v = canon(x[e] + cadd, p, pinv);
@@ -313,8 +398,7 @@ __device__ __forceinline__ void ntt_v2_rows(const NttV2Args &A, double *lds, int
     load_twiddles(tw, N1 + blockIdx.x * 16 + hi4, lo4, tw1, tw2);
     const unsigned i0 = blockIdx.z * (unsigned)A.items_per_z;
     const unsigned i1 = (i0 + A.items_per_z < (unsigned)A.items) ? i0 + A.items_per_z : (unsigned)A.items;
-    constexpr int F1 = P51 ? 0xA : 0x8, F2 = P51 ? 0x2 : 0x0;
-    constexpr int I1 = P51 ? 0x2 : 0x4, I2 = P51 ? 0x1 : 0x4;
+    typedef RowMasks<P51, false> Mk;
     const size_t tile0 = (size_t)blockIdx.x * 4096;
     double *grp = lds + hi4 * V2_GS;
     for (unsigned it = i0; it < i1; it++) {
@@ -324,13 +408,13 @@ __device__ __forceinline__ void ntt_v2_rows(const NttV2Args &A, double *lds, int
         if (!INV) {
 #pragma unroll
             for (int e = 0; e < 16; e++) x[e] = mid_load(src[tile0 + hi4 * 256 + lo4 + 16 * e]);
-            fwd_round<F1>(x, tw1, p, pinv);
+            fwd_round<Mk::F1>(x, tw1, p, pinv);
 #pragma unroll
             for (int e = 0; e < 16; e++) grp[e * 17 + lo4] = x[e];
             ROW_GROUP_SYNC();
 #pragma unroll
             for (int e = 0; e < 16; e++) x[e] = grp[lo4 * 17 + e];
-            fwd_round<F2>(x, tw2, p, pinv);
+            fwd_round<Mk::F2>(x, tw2, p, pinv);
 #pragma unroll
             for (int e = 0; e < 16; e++) grp[lo4 * 17 + e] = canon(x[e], p, pinv);
             ROW_GROUP_SYNC();
@@ -361,15 +445,15 @@ __device__ __forceinline__ void ntt_v2_rows(const NttV2Args &A, double *lds, int
             ROW_GROUP_SYNC();
 #pragma unroll
             for (int e = 0; e < 16; e++) x[e] = grp[lo4 * 17 + e];
-            inv_round<I1, false>(x, tw2, p, pinv, unused, unused);
+            inv_stages<0, INV_ROW1, P51>(x, tw2, p, pinv, unused, unused);
 #pragma unroll
             for (int e = 0; e < 16; e++) grp[lo4 * 17 + e] = x[e];
             ROW_GROUP_SYNC();
 #pragma unroll
             for (int e = 0; e < 16; e++) x[e] = grp[e * 17 + lo4];
-            inv_round<I2, false>(x, tw1, p, pinv, unused, unused);
+            inv_stages<0, INV_ROW2, P51>(x, tw1, p, pinv, unused, unused);
 #pragma unroll
-            for (int e = 0; e < 16; e++) dst[tile0 + hi4 * 256 + lo4 + 16 * e] = mid_store(x[e], p, pinv);
+            for (int e = 0; e < 16; e++) dst[tile0 + hi4 * 256 + lo4 + 16 * e] = mid_store(x[e]);
         }
         ROW_GROUP_SYNC();
     }

@@ -19,16 +19,16 @@
 __device__ __forceinline__ unsigned wg_pad(unsigned row, unsigned col) { return row * V2_GS + (col >> 4) * 17u + (col & 15u); }
 
 // Forward transform of block `base - 2^S` of a ring of M * 2^S words (base = 1: the whole ring): x in the column layout (word
-// (geo.r + G*e, geo.c0 + geo.c)), at most 2.7p (p < 2^50) or 1.2p (p < 2^51) in magnitude; the balanced-reduced results end in LDS, word (row g,
-// position q) at wg_pad(g, q).  Every row is finished by its own 16 lanes (a row-group sync suffices to read it).
+// (geo.r + G*e, geo.c0 + geo.c)), at most 2.7p (p < 2^50) or 1.2p (p < 2^51) in magnitude; the results end in LDS, balanced-reduced or
+// (LAZY) at most LazyRange::ROWX, word (row g, position q) at wg_pad(g, q).  Every row is finished by its own 16 lanes (a row-group sync suffices to read it).
 // `request` is called once the first row round is done: the place for memory requests whose latency the rest covers.
-template <int LOGM, bool P51, class F>
+template <int LOGM, bool P51, bool LAZY, class F>
 __device__ __forceinline__ void wg_fwd_block(double (&x)[16], const double *tw, unsigned base, double *lds, double p, double pinv, F request) {
     constexpr int Q = LOGM - 12;
     typedef ColsGeom<Q> Geo;
-    typedef ColsMasks<Q, P51> Mk;
+    typedef ColsMasks<Q, P51, P51 ? 308 : 692> Mk;
+    typedef RowMasks<P51, LAZY> Rm;
     constexpr unsigned MR = (1u << LOGM) >> 8;
-    constexpr int RF1 = P51 ? 0xA : 0x8, RF2 = P51 ? 0x2 : 0x0;
     const unsigned tid = threadIdx.x, row = tid >> 4, lo4 = tid & 15;
     const Geo geo(tid & 255u, tid >> 8);
     double *grp = lds + row * V2_GS;
@@ -60,11 +60,10 @@ __device__ __forceinline__ void wg_fwd_block(double (&x)[16], const double *tw, 
         for (int i = 0; i < 16; i++) x[i] = lds[wg_pad(Geo::G * geo.a + (i % Geo::G), geo.c0 + geo.l16 + 16 * (i / Geo::G))];
         fwd_stages<Geo::S0, Mk::F2>(x, tw2, p, pinv);
 #pragma unroll
-        for (int i = 0; i < 16; i++)
-            lds[wg_pad(Geo::G * geo.a + (i % Geo::G), geo.c0 + geo.l16 + 16 * (i / Geo::G))] = reduce_balanced(x[i], p, pinv);
+        for (int i = 0; i < 16; i++) lds[wg_pad(Geo::G * geo.a + (i % Geo::G), geo.c0 + geo.l16 + 16 * (i / Geo::G))] = x[i];
     } else {
 #pragma unroll
-        for (int e = 0; e < 16; e++) lds[wg_pad(e, geo.c0 + geo.c)] = x[e];  // the first round ends reduced
+        for (int e = 0; e < 16; e++) lds[wg_pad(e, geo.c0 + geo.c)] = x[e];
     }
     const unsigned base1 = base * MR + row;
 #pragma unroll
@@ -74,7 +73,7 @@ __device__ __forceinline__ void wg_fwd_block(double (&x)[16], const double *tw, 
     __syncthreads();
 #pragma unroll
     for (int e = 0; e < 16; e++) x[e] = grp[e * 17 + lo4];
-    fwd_round<RF1>(x, tw1, p, pinv);
+    fwd_round<Rm::F1>(x, tw1, p, pinv);
 #pragma unroll
     for (int s = 0; s < 4; s++)
 #pragma unroll
@@ -85,9 +84,9 @@ __device__ __forceinline__ void wg_fwd_block(double (&x)[16], const double *tw, 
     ROW_GROUP_SYNC();
 #pragma unroll
     for (int e = 0; e < 16; e++) x[e] = grp[lo4 * 17 + e];
-    fwd_round<RF2>(x, tw2, p, pinv);
+    fwd_round<Rm::F2>(x, tw2, p, pinv);
 #pragma unroll
-    for (int e = 0; e < 16; e++) grp[lo4 * 17 + e] = reduce_balanced(x[e], p, pinv);
+    for (int e = 0; e < 16; e++) grp[lo4 * 17 + e] = LAZY ? x[e] : reduce_balanced(x[e], p, pinv);
     ROW_GROUP_SYNC();
 }
 
@@ -107,9 +106,7 @@ __device__ __forceinline__ void wg_inv_limb(double (&x)[16], const u64d *src, co
     BODY_TAG(P51);
     constexpr int Q = LOGN - 12;
     typedef ColsGeom<Q> Geo;
-    typedef ColsMasks<Q, P51> Mk;
     constexpr unsigned N = 1u << LOGN, N1 = N >> 8;
-    constexpr int RI1 = P51 ? 0x2 : 0x4, RI2 = P51 ? 0x1 : 0x4;   // row pass, inverse (as ntt_v2_rows)
     const unsigned tid = threadIdx.x, row = tid >> 4, lo4 = tid & 15, pr = row_pair_index(row, lo4, 0);
     const Geo geo(tid & 255u, tid >> 8);
     double *grp = lds + row * V2_GS;
@@ -134,7 +131,7 @@ __device__ __forceinline__ void wg_inv_limb(double (&x)[16], const u64d *src, co
                     }
                     NTT_SCHED_FENCE();
 #pragma unroll
-                    for (int s = 0; s < 4; s++) {  // |sum| <= p/2 + 1 + 1.25p
+                    for (int s = 0; s < 4; s++) {  // one product 1.25p, a sum is reduced
                         const double v0 = mulmod(u2d(a1[s].x), u2d(b1[s].x), p, pinv), v1 = mulmod(u2d(a1[s].y), u2d(b1[s].y), p, pinv);
                         d2[2 * s] = tm ? reduce_balanced(d2[2 * s] + v0, p, pinv) : v0;
                         d2[2 * s + 1] = tm ? reduce_balanced(d2[2 * s + 1] + v1, p, pinv) : v1;
@@ -142,10 +139,9 @@ __device__ __forceinline__ void wg_inv_limb(double (&x)[16], const u64d *src, co
                 }
 #pragma unroll
                 for (int s = 0; s < 4; s++) {
-                    // from the canonical representative, as when d2 comes from memory
                     double *rr = grp + row_pair_lds(lo4, 4 * h + s);
-                    rr[0] = canon(d2[2 * s], p, pinv);
-                    rr[1] = canon(d2[2 * s + 1], p, pinv);
+                    rr[0] = d2[2 * s];
+                    rr[1] = d2[2 * s + 1];
                 }
             }
             LOAD_FENCE();
@@ -180,7 +176,7 @@ __device__ __forceinline__ void wg_inv_limb(double (&x)[16], const u64d *src, co
         ROW_GROUP_SYNC();
 #pragma unroll
         for (int e = 0; e < 16; e++) x[e] = grp[lo4 * 17 + e];
-        inv_round<RI1, false>(x, tw2, p, pinv, unused, unused);
+        inv_stages<0, INV_ROW1, P51>(x, tw2, p, pinv, unused, unused);
 #pragma unroll
         for (int e = 0; e < 16; e++) PIN_VALUE(x[e]);  // the first round is done with its twiddles before the second's arrive
 #pragma unroll
@@ -192,12 +188,9 @@ __device__ __forceinline__ void wg_inv_limb(double (&x)[16], const u64d *src, co
         ROW_GROUP_SYNC();
 #pragma unroll
         for (int e = 0; e < 16; e++) x[e] = grp[e * 17 + lo4];
-        inv_round<RI2, false>(x, tw1, p, pinv, unused, unused);
+        inv_stages<0, INV_ROW2, P51>(x, tw1, p, pinv, unused, unused);
 #pragma unroll
-        for (int e = 0; e < 16; e++) {
-            x[e] = reduce_balanced(x[e], p, pinv);
-            PIN_VALUE(x[e]);
-        }
+        for (int e = 0; e < 16; e++) PIN_VALUE(x[e]);
 #pragma unroll
         for (int e = 0; e < 16; e++) grp[e * 17 + lo4] = x[e];
     }
@@ -209,15 +202,14 @@ __device__ __forceinline__ void wg_inv_limb(double (&x)[16], const u64d *src, co
         if (Q > 0) {
 #pragma unroll
             for (int i = 0; i < 16; i++) x[i] = lds[wg_pad(Geo::G * geo.a + (i % Geo::G), geo.c0 + geo.l16 + 16 * (i / Geo::G))];
-            inv_stages<Geo::S0, Mk::I1, false>(x, tw2u, p, pinv, ninv, wlast);
-            reduce16(x, p, pinv);
+            inv_stages<Geo::S0, INV_COL2, P51>(x, tw2u, p, pinv, ninv, wlast);
 #pragma unroll
             for (int i = 0; i < 16; i++) lds[wg_pad(Geo::G * geo.a + (i % Geo::G), geo.c0 + geo.l16 + 16 * (i / Geo::G))] = x[i];
             __syncthreads();
         }
 #pragma unroll
         for (int e = 0; e < 16; e++) x[e] = lds[wg_pad(geo.r + Geo::G * e, geo.c0 + geo.c)];
-        inv_round<Mk::I2, true>(x, tw1, p, pinv, ninv, wlast);
+        inv_stages<0, INV_COL1, P51>(x, tw1, p, pinv, ninv, wlast);
     }
 }
 
@@ -257,7 +249,7 @@ __device__ __forceinline__ void ntt_wg_body(const NttV2Args &A, double *lds, int
             NTT_SCHED_FENCE();
 #pragma unroll
             for (int e = 0; e < 16; e++) x[e] = u2d(raw[e]);
-            wg_fwd_block<LOGN, P51>(x, tw, 1u, lds, p, pinv, []() {});
+            wg_fwd_block<LOGN, P51, false>(x, tw, 1u, lds, p, pinv, []() {});
             // canonical words out in word pairs: 16 bytes per lane, 256 contiguous bytes per row and store
 #pragma unroll
             for (int s = 0; s < 8; s++) {
