@@ -42,6 +42,32 @@ __device__ __forceinline__ double mulmod(double a, double b, double p, double pi
     return c + l;
 }
 
+// Sum of K = 2 .. 4 products y_k * w_k (0 <= y < 2^51, |w| <= p/2) with ONE reduction, p < 2^50: the sum runs in s, which starts
+// at M = 3*2^51*p (a multiple of p, so large that s never leaves [2^51 p, 2.5*2^52 p] and h = s' - s is exact); what the
+// rounding of s drops, y*w - h, is an integer below 2^50.3 and is collected in l.  4K + 3 instructions against 7K.
+// Three sources in ModUp and in a product's tail at N = 2^16, 64 items of 24 primes: 7216 -> 7046 us for the whole product.
+// |value| <= (0.875 + 1.0 + 1.125 + 1.25)p (the first K of them) + (2 + K/4)p + |addend|, see chain_bound
+struct ProductChain { double s, l; };
+__device__ __forceinline__ double chain_origin(double p) { return 6755399441055744.0 * p; }
+__device__ __forceinline__ ProductChain chain_first(double M, double y, double w) {
+    const double s = fma(y, w, M), h = s - M;
+    return ProductChain{s, fma(y, w, -h)};
+}
+__device__ __forceinline__ void chain_add(ProductChain &c, double y, double w) {
+    const double s = fma(y, w, c.s), h = s - c.s;
+    c.l += fma(y, w, -h);
+    c.s = s;
+}
+__device__ __forceinline__ double chain_value(const ProductChain &c, double p, double pinv) {
+    const double q = rint(c.s * pinv);
+    return fma(-q, p, c.s) + c.l;
+}
+constexpr double chain_bound(int K) {
+    double b = 2.0 + 0.25 * K;
+    for (int k = 1; k <= K; k++) b += 0.5 * (1.5 + 0.25 * k);
+    return b;
+}
+
 __device__ __forceinline__ double reduce_balanced(double x, double p, double pinv) {
     return fma(-rint(x * pinv), p, x);
 }

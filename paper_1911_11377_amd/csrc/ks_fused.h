@@ -199,31 +199,42 @@ __device__ __forceinline__ void inv_cols_in_regs(double (&x)[16], const double *
 // ModDown's; Wc[0] = P^-1 mod p, hsub = ModDown's h mod p, Bm = the rescale's h mod p:
 //     value = (sum_a y_a*conv_a - hA) * P^-1 + y_B - hB     (the two conversion results the last pass would subtract,
 //                                                            brought to one: the transforms are linear)
-template <bool P51, int NSRC, int Q, int VARIANT>
+// SUB: h is subtracted (every mode but ModUp)
+template <bool P51, int NSRC, int Q, int VARIANT, bool SUB>
 __device__ __forceinline__ void modup_cols_target(const double (&yd)[NSRC][16], WMul (&Wc)[NSRC], const double *twl, double *lds, u64d *dst,
                                                   const ColsGeom<Q> &geo, double p, double pinv, double *twl_next, double tw_store, double hsub,
                                                   unsigned long long vpack, double Bm, const double *ybl = nullptr) {
     typedef ColsGeom<Q> Geo;
-    // what enters the first stage, in 1/256 p: p + NSRC * 0.75p, an overshoot's reduced term + NSRC * 0.75p, or (one conversion
-    // for two divisions) a product of at most 0.91p + y_B below 2p + p
-    constexpr int ENTRY = VARIANT == 0 ? 256 + 192 * NSRC : VARIANT == 1 ? 131 + 192 * NSRC : 1001;
+    constexpr int NPROD = VARIANT == 2 ? NSRC - 1 : NSRC;
+    constexpr bool CHAIN = !P51 && NPROD >= 2 && !(VARIANT == 0 && NSRC == 4);  // four products and h could pass 2^53
+    // bounds, in units of p: the sum of products, and what enters the first stage (with h <= p, the reduced overshoot term, or, one
+    // conversion for two divisions, a prepared product of the sum, y_B below 2p and h)
+    constexpr double SUM = CHAIN ? chain_bound(NPROD) : 0.75 * NPROD;
+    constexpr double IN = VARIANT == 0 ? SUM + (SUB ? 1.0 : 0.0) : VARIANT == 1 ? SUM + LAZY_REDUCED : (P51 ? 0.64 : 0.5 + (SUM + 1.0) / 8.0) + 3.0;
+    constexpr int ENTRY = (int)(256.0 * IN + 0.999);
+    static_assert(IN <= LazyRange<P51>::LIM, "the sum leaves the exact range");
     typedef ColsMasks<Q, P51, ENTRY> Mk;
     BODY_TAG(P51);
     if (VARIANT == 2) {  // the products by these constants would be moved above the branch all the same: 350 registers spilled
 #pragma unroll
         for (int a = 0; a < NSRC; a++) PIN_UNIFORM(Wc[a].w);
     }
+    const double M = CHAIN ? chain_origin(p) : 0.0;
     double x[16];
 #pragma unroll
     for (int e = 0; e < 16; e++) {
         double v = -hsub;
         if (VARIANT == 1) v = -reduce_balanced(hsub + (double)(unsigned)((vpack >> (3 * e)) & 7u) * Bm, p, pinv);  // v <= 3: below 4p, exact
+        ProductChain c{0.0, 0.0};
 #pragma unroll
-        for (int a = (VARIANT == 2 ? 1 : 0); a < NSRC; a++) {
+        for (int a = NSRC - NPROD; a < NSRC; a++) {
             const double ya = (VARIANT == 0 && NSRC == 3 && a == 0 && ybl) ? ybl[e * 256 + threadIdx.x] : yd[a][e];
-            v += mulmod_w(ya, Wc[a].w, Wc[a].wp, p);
+            if (!CHAIN) v += mulmod_w(ya, Wc[a].w, Wc[a].wp, p);
+            else if (a == NSRC - NPROD) c = chain_first(M, ya, Wc[a].w);
+            else chain_add(c, ya, Wc[a].w);
         }
-        x[e] = v;  // |v| <= p + NSRC * 0.75p
+        if (CHAIN) v = SUB ? v + chain_value(c, p, pinv) : chain_value(c, p, pinv);
+        x[e] = v;
         if (VARIANT == 2) {  // y_B is below the dropped prime, which has as many bits as p: below 2p
             x[e] = mulmod_w(P51 ? reduce_balanced(v, p, pinv) : v, Wc[0].w, Wc[0].wp, p) + ybl[e * 256 + threadIdx.x] - Bm;
         }
@@ -404,9 +415,9 @@ __global__ __launch_bounds__(V2_THREADS, (NSRC >= 4 && MODE == 2) ? 1 : 2) void 
         constexpr bool ONE_BUF = MODE == 3 || SRC0_LDS;  // the second buffer holds y_B / the first source tile
         double *xbuf = ONE_BUF ? lds[0] : lds[(k - k0) & 1];
         if (is_p51(A.p51, t))
-            modup_cols_target<true, NSRC, Q, (MODE >= 2 ? MODE - 1 : 0)>(yd, Wc, tcur, xbuf, dst, geo, p, pinv, tnext, tw_store, hsub, vpack, Bm, (MODE == 3 || SRC0_LDS) ? lds[1] : nullptr);
+            modup_cols_target<true, NSRC, Q, (MODE >= 2 ? MODE - 1 : 0), MODE != 0>(yd, Wc, tcur, xbuf, dst, geo, p, pinv, tnext, tw_store, hsub, vpack, Bm, (MODE == 3 || SRC0_LDS) ? lds[1] : nullptr);
         else
-            modup_cols_target<false, NSRC, Q, (MODE >= 2 ? MODE - 1 : 0)>(yd, Wc, tcur, xbuf, dst, geo, p, pinv, tnext, tw_store, hsub, vpack, Bm, (MODE == 3 || SRC0_LDS) ? lds[1] : nullptr);
+            modup_cols_target<false, NSRC, Q, (MODE >= 2 ? MODE - 1 : 0), MODE != 0>(yd, Wc, tcur, xbuf, dst, geo, p, pinv, tnext, tw_store, hsub, vpack, Bm, (MODE == 3 || SRC0_LDS) ? lds[1] : nullptr);
         if (ONE_BUF) __syncthreads();  // single exchange buffer: everybody has read it before the next target writes
     }
 }

@@ -140,7 +140,7 @@ __device__ __forceinline__ void inner_wg_body(const InnerWgArgs &A, const KeyTab
                 for (int e = 0; e < CH; e++) {
                     double u[1 << S];
 #pragma unroll
-                    for (int q = 0; q < (1 << S); q++) u[q] = conv_word<NSRC>(src[e][q], Wc, 0.0, p, pinv);
+                    for (int q = 0; q < (1 << S); q++) u[q] = conv_word<NSRC, P51>(src[e][q], Wc, 0.0, p, pinv);
 #pragma unroll
                     for (int q1 = 0; q1 < S; q1++)
 #pragma unroll

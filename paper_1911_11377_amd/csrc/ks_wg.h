@@ -51,27 +51,35 @@ __device__ __forceinline__ bool conv_final_place(const ConvFinalArgs &A, int S, 
     return row < (unsigned)A.F.rows;
 }
 
+// sum_a y_a * conv_a - h, at most p + SUM of chain_bound / 0.75p per product (four products and h of a 50-bit prime could pass 2^53
+// as a ProductChain: they are summed one by one)
+template <int NPROD, bool P51>
+__device__ __forceinline__ double conv_sum(const double *y, const WMul *Wc, double hsub, double p, double pinv) {
+    if (P51 || NPROD < 2 || NPROD > 3) {
+        double v = -hsub;
+#pragma unroll
+        for (int a = 0; a < NPROD; a++) v += mulmod_w(y[a], Wc[a].w, Wc[a].wp, p);
+        return v;
+    }
+    ProductChain c = chain_first(chain_origin(p), y[0], Wc[0].w);
+#pragma unroll
+    for (int a = 1; a < NPROD; a++) chain_add(c, y[a], Wc[a].w);
+    return chain_value(c, p, pinv) - hsub;
+}
+
 // One converted coefficient, balanced-reduced: sum_a y_a * conv_a - h.  A single source has conv = 1 (the empty product).
-template <int NSRC>
+template <int NSRC, bool P51>
 __device__ __forceinline__ double conv_word(const double (&y)[NSRC], const WMul (&Wc)[NSRC], double hsub, double p, double pinv) {
     if (NSRC == 1) return reduce_balanced(y[0] - hsub, p, pinv);  // below 2^51 + p
-    double v = -hsub;
-#pragma unroll
-    for (int a = 0; a < NSRC; a++) v += mulmod_w(y[a], Wc[a].w, Wc[a].wp, p);
-    return reduce_balanced(v, p, pinv);  // |v| <= p + NSRC * 0.75p
+    return reduce_balanced(conv_sum<NSRC, P51>(y, Wc, hsub, p, pinv), p, pinv);
 }
 
 // The same for ModDown followed by rescale as one conversion (see modup_cols_kernel MODE 3): y[0] is the rescale's conversion
 // input y_B, y[1 ..] ModDown's; the value is (sum_a y_a * conv_a - hA) * P^-1 + y_B - hB.
-template <int NSRC>
+template <int NSRC, bool P51>
 __device__ __forceinline__ double tail_word(const double (&y)[NSRC], const WMul (&Wc)[NSRC], double hA, WMul Pinv, double hB, double p, double pinv) {
-    double v = -hA;
-    if (NSRC == 2) {
-        v += y[1];  // one special prime: its constant is 1; below 2^51 + p
-    } else {
-#pragma unroll
-        for (int a = 1; a < NSRC; a++) v += mulmod_w(y[a], Wc[a].w, Wc[a].wp, p);
-    }
+    // one special prime: its constant is 1; below 2^51 + p
+    const double v = NSRC == 2 ? y[1] - hA : conv_sum<NSRC - 1, P51>(&y[1], &Wc[1], hA, p, pinv);
     return reduce_balanced(mulmod_w(reduce_balanced(v, p, pinv), Pinv.w, Pinv.wp, p) + y[0] - hB, p, pinv);
 }
 
@@ -124,7 +132,7 @@ __device__ __forceinline__ void conv_final_body(const ConvFinalArgs &A, double *
                 double u[1 << S];
 #pragma unroll
                 for (int q = 0; q < (1 << S); q++)
-                    u[q] = FIN == 4 ? tail_word<NSRC>(src[e][q], Wc, hsub, Pinv, hB, p, pinv) : conv_word<NSRC>(src[e][q], Wc, hsub, p, pinv);
+                    u[q] = FIN == 4 ? tail_word<NSRC, P51>(src[e][q], Wc, hsub, Pinv, hB, p, pinv) : conv_word<NSRC, P51>(src[e][q], Wc, hsub, p, pinv);
                 // stage t joins the words 2^(S-1-t) * M apart
 #pragma unroll
                 for (int t = 0; t < S; t++)

@@ -17,3 +17,36 @@ extern "C" int emu_probe_missing_kernel(ckksmi_ctx *c, int which) {
     }
     return g.rc();
 }
+
+// Sum of K products as a conversion forms it (y canonical, w balanced, p < 2^50)
+extern "C" double emu_probe_product_chain(const double *y, const double *w, int K, double p) {
+    ProductChain c = chain_first(chain_origin(p), y[0], w[0]);
+    for (int a = 1; a < K; a++) chain_add(c, y[a], w[a]);
+    return chain_value(c, p, 1.0 / p);
+}
+extern "C" double emu_probe_chain_bound(int K) { return chain_bound(K); }
+
+// The register rounds of a pass on 16 words, with their reductions: forward the two of a row pass whose results a pointwise step takes
+// as they are, inverse the two of a row pass and the round that follows it in a column pass of 2^8 rows.  Returns the bound at the end.
+template <bool P51>
+static double probe_rounds(bool inverse, double (&x)[16], const double (&tw)[15], double p) {
+    typedef RowMasks<P51, true> Mk;
+    const WMul unused{0.0, 0.0};
+    if (!inverse) {
+        fwd_round<Mk::F1>(x, tw, p, 1.0 / p);
+        fwd_round<Mk::F2>(x, tw, p, 1.0 / p);
+        return LazyRange<P51>::ROWX;
+    }
+    inv_stages<0, INV_ROW1, P51>(x, tw, p, 1.0 / p, unused, unused);
+    inv_stages<0, INV_ROW2, P51>(x, tw, p, 1.0 / p, unused, unused);
+    inv_stages<0, INV_COL2, P51>(x, tw, p, 1.0 / p, unused, unused);
+    return LazyRange<P51>::INV1;
+}
+extern "C" double emu_probe_lazy_rounds(int p51, int inverse, double *x, const double *tw, double p) {
+    double xx[16], t[15];
+    memcpy(xx, x, sizeof(xx));
+    memcpy(t, tw, sizeof(t));
+    const double b = p51 ? probe_rounds<true>(inverse != 0, xx, t, p) : probe_rounds<false>(inverse != 0, xx, t, p);
+    memcpy(x, xx, sizeof(xx));
+    return b;
+}

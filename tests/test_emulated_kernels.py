@@ -2,6 +2,10 @@
 and run fibre by fibre on tiny shapes with guard pages behind every buffer, compared
 with the oracle.  This checks indexing and launch shapes on the CPU before a GPU ever
 runs them; the parity claims themselves come from the GPU tests."""
+import ctypes
+import itertools
+
+import numpy as np
 import pytest
 
 import parity_cases as pc
@@ -364,3 +368,57 @@ def test_emulated_edge_values_on_chip(be, shape):
     """the on-chip key switch and tail on residues at the ends of [0, q), key of all q-1"""
     with be.tuned(64):
         pc.case_edge_values(be, shape, seed=196, conv=False, pairs=FEW_PAIRS[:2], seeded_key=False, expect=["inner_wg_kernel", "tail_sources_kernel"])
+
+
+def _doubles(values):
+    return (ctypes.c_double * len(values))(*[float(v) for v in values])
+
+
+@pytest.mark.parametrize("terms", [2, 3, 4])
+@pytest.mark.parametrize("bits", [40, 50])
+def test_product_chain_is_exact_at_the_ends_of_its_range(be, terms, bits):
+    """a conversion's sum of products with one reduction: an integer congruent to the exact sum and within its bound"""
+    be.lib.emu_probe_product_chain.restype = be.lib.emu_probe_chain_bound.restype = ctypes.c_double
+    rng = np.random.default_rng(bits + terms)
+    for p in (2**bits - 27, 2 ** (bits - 1) + 9):
+        half = p // 2
+        ends = [(2**51 - 1, half), (2**51 - 1, -half), (2**51 - 1, half - 1), (0, half), (1, -1), (2**50 - 1, half)]
+        cases = list(itertools.product(ends, repeat=terms))
+        cases += [[(int(rng.integers(0, 2**51)), int(rng.integers(-half, half + 1))) for _ in range(terms)] for _ in range(500)]
+        for c in cases:
+            v = be.lib.emu_probe_product_chain(_doubles([y for y, _ in c]), _doubles([w for _, w in c]), terms, ctypes.c_double(p))
+            assert v == int(v) and abs(v) <= be.lib.emu_probe_chain_bound(terms) * p
+            assert (int(v) - sum(y * w for y, w in c)) % p == 0
+
+
+def _exact_rounds(x, tw, p, inverse):
+    """the rounds of emu_probe_lazy_rounds on integers"""
+    x = list(x)
+    for _ in range(3 if inverse else 2):
+        for s in (range(3, -1, -1) if inverse else range(4)):
+            span = 8 >> s
+            for b in range(1 << s):
+                for lo in range(2 * span * b, 2 * span * b + span):
+                    u, v, w = x[lo], x[lo + span], tw[(1 << s) - 1 + b]
+                    x[lo], x[lo + span] = ((u + v) % p, (u - v) * w % p) if inverse else ((u + v * w) % p, (u - v * w) % p)
+    return x
+
+
+@pytest.mark.parametrize("inverse", [0, 1])
+@pytest.mark.parametrize("p51", [0, 1])
+def test_lazy_rounds_stay_exact_from_the_ends_of_their_range(be, p51, inverse):
+    """register rounds from words at their entry bound (the largest sums a pass can form), twiddles at +-p/2"""
+    be.lib.emu_probe_lazy_rounds.restype = ctypes.c_double
+    p = 2 ** (50 + p51) - 27
+    entry = 1.25 if inverse else (2.5 if p51 else 3.5)
+    top, half = int(entry * p) - 1, p // 2
+    rng = np.random.default_rng(p51 * 2 + inverse)
+    words = [[top] * 16, [-top] * 16, [top if i % 2 else -top for i in range(16)], [top if i < 8 else -top for i in range(16)]]
+    words += [[int(v) for v in rng.integers(-top, top + 1, 16)] for _ in range(40)]
+    words += [[int(v) for v in rng.choice([-top, top], 16)] for _ in range(40)]
+    for x in words:
+        for tw in ([half] * 15, [-half] * 15, [int(v) for v in rng.integers(-half, half + 1, 15)]):
+            buf = _doubles(x)
+            bound = be.lib.emu_probe_lazy_rounds(p51, inverse, buf, _doubles(tw), ctypes.c_double(p))
+            assert all(v == int(v) and abs(v) <= bound * p for v in buf)
+            assert [int(v) % p for v in buf] == _exact_rounds(x, tw, p, inverse)
