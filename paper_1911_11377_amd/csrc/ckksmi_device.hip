@@ -30,6 +30,13 @@
         if (pr_) (void)hipEventRecord((hipEvent_t)pr_->stop, (st));                     \
     } while (0)
 
+// ... one of two instances of a kernel template
+#define KL2(c, kid, units, first, kern1, kern2, grid, block, st, ...)              \
+    do {                                                                            \
+        if (first) KL(c, kid, units, kern1, grid, block, st, __VA_ARGS__);          \
+        else KL(c, kid, units, kern2, grid, block, st, __VA_ARGS__);                \
+    } while (0)
+
 // Scratch memory of ckksmi_rescale_static, the one entry point that takes no workspace: a file-scope device array, one copy
 // per GPU, held until the process ends.  Host code never uses the array's name as an address: every device's copy is
 // looked up once (hipGetSymbolAddress, with that device current) when the first context on that device is created.
@@ -101,6 +108,14 @@ LimbMap table_map(const int *index, int n_limbs, size_t src_stride, size_t dst_s
     return M;
 }
 
+// How much of a launch that moves `bytes` (operands of its own plus results) is streamed past the caches.  Results that leave for
+// good, or that the next kernel reads only after this one has written more than the L2s hold, do better without displacing what
+// is re-used (twiddles, keys, sources); once a launch moves more than the last-level cache holds (256 MB) its operands do too.
+// In between they are found there when the same buffers come back: plain transforms of 12 MB to 200 MB ran 1.1 - 1.2 x
+// slower with streamed operands, of 800 MB 1.05 x faster; products of one ciphertext lose 2 - 3 % with streamed results (12 MB).
+// 256 products at N = 2^14, 8 primes 2068 -> 1965 us, 64 at 2^16, 24 primes 7046 -> 6794, rescale of 16 ciphertexts at 2^15, 16 primes 102 -> 91.
+inline int stream_level(double bytes) { return bytes > 268435456.0 ? STREAM_ALL : bytes >= 16777216.0 ? STREAM_STORES : STREAM_NONE; }
+
 // transform `items` groups of map.per_item limbs; forward: coefficient -> evaluation
 // passes: 3 = whole transform, 2 = contiguous (row) pass only (register-tiled sizes)
 // out_f64 (inverse, register-tiled sizes): the coefficients leave as doubles, with the last-stage constants fin or *fin_val
@@ -135,6 +150,7 @@ void launch_ntt(ckksmi_ctx *c, bool forward, const u64 *src, u64 *dst, const Lim
     V.src = A.src; V.dst = A.dst; V.modc = A.modc; V.tw = forward ? c->d_tww_fwd : c->d_tww_inv; V.tw_ninv = c->d_tw_ninv;
     V.tw_last = A.tw_last; V.fin = fin; V.logN = A.logN; V.map = M; V.p51 = c->p51mask;
     V.items = (int)items;
+    const bool nt = stream_level(8.0 * N * limbs) == STREAM_ALL;  // in place as a rule: results and operands are one
     const unsigned tiles = N >= 4096u ? N / 4096u : 1u;
     // enough workgroups to fill the chip, otherwise as many items per workgroup as possible (twiddle reuse)
     unsigned zchunks = ((unsigned)c->ntt_target_wgs + tiles * M.per_item - 1) / (tiles * M.per_item);
@@ -155,11 +171,11 @@ void launch_ntt(ckksmi_ctx *c, bool forward, const u64 *src, u64 *dst, const Lim
         const dim3 gw(M.per_item, zc), bw((unsigned)(N / 16));
 #define NTT_WG_CASE(LN)                                                                                        \
     case LN:                                                                                                   \
-        if (forward) KL(c, CKKSMI_K_NTT_LDS, limbs_work, (ntt_wg_kernel<false, LN>), gw, bw, st, V);           \
+        if (forward) KL2(c, CKKSMI_K_NTT_LDS, limbs_work, nt, (ntt_wg_kernel<false, LN, true>), (ntt_wg_kernel<false, LN, false>), gw, bw, st, V); \
         else if (LN < 14 && ten) KL(c, CKKSMI_K_TENSOR_WG, limbs_work, tensor_wg_kernel<LN < 14 ? LN : 13>, gw, bw, st, V, *ten); \
         else if (LN < 14 && gal) KL(c, CKKSMI_K_NTT_LDS_GAL, limbs_work, ntt_wg_inv_gal_kernel<LN < 14 ? LN : 13>, gw, bw, st, V, *gal); \
-        else if (out_f64) KL(c, CKKSMI_K_NTT_LDS, limbs_work, (ntt_wg_kernel<true, LN, true>), gw, bw, st, V); \
-        else KL(c, CKKSMI_K_NTT_LDS, limbs_work, (ntt_wg_kernel<true, LN>), gw, bw, st, V);                    \
+        else if (out_f64) KL(c, CKKSMI_K_NTT_LDS, limbs_work, (ntt_wg_kernel<true, LN, false, true>), gw, bw, st, V); \
+        else KL2(c, CKKSMI_K_NTT_LDS, limbs_work, nt, (ntt_wg_kernel<true, LN, true>), (ntt_wg_kernel<true, LN, false>), gw, bw, st, V); \
         break;
         switch (c->logN) {
             NTT_WG_CASE(12) NTT_WG_CASE(13) NTT_WG_CASE(14)
@@ -169,7 +185,7 @@ void launch_ntt(ckksmi_ctx *c, bool forward, const u64 *src, u64 *dst, const Lim
     }
     if (forward) {
         if (two_pass && (passes & 1)) {
-            if (v2_cols) KL(c, CKKSMI_K_NTT_FWD_COL, limbs_work, (ntt_v2_kernel<false, true>), gv2, dim3(V2_THREADS), st, V);
+            if (v2_cols) KL2(c, CKKSMI_K_NTT_FWD_COL, limbs_work, nt, (ntt_v2_kernel<false, true, true>), (ntt_v2_kernel<false, true, false>), gv2, dim3(V2_THREADS), st, V);
             else KL(c, CKKSMI_K_NTT_FWD_COL, limbs_work, ntt_fwd_kernel<true>, gcol, dim3(NTT_THREADS), st, A);
             // second pass works in place on dst
             A.src = (const u64d *)dst;
@@ -178,21 +194,21 @@ void launch_ntt(ckksmi_ctx *c, bool forward, const u64 *src, u64 *dst, const Lim
             V.map.src_item_stride = V.map.dst_item_stride;
         }
         if (passes & 2) {
-            if (v2_rows) KL(c, CKKSMI_K_NTT_FWD_ROW, limbs_work, (ntt_v2_kernel<false, false>), gv2, dim3(V2_THREADS), st, V);
+            if (v2_rows) KL2(c, CKKSMI_K_NTT_FWD_ROW, limbs_work, nt, (ntt_v2_kernel<false, false, true>), (ntt_v2_kernel<false, false, false>), gv2, dim3(V2_THREADS), st, V);
             else KL(c, CKKSMI_K_NTT_FWD_ROW, limbs_work, ntt_fwd_kernel<false>, grow, dim3(NTT_THREADS), st, A);
         }
     } else {
         // inverse: passes 2 = contiguous (row) pass only, leaving the reduced-double intermediate (register-tiled sizes)
         if (v2_rows && gal) KL(c, CKKSMI_K_NTT_INV_ROW, limbs_work, ntt_v2_inv_rows_gal_kernel, gv2, dim3(V2_THREADS), st, V, *gal);
-        else if (v2_rows) KL(c, CKKSMI_K_NTT_INV_ROW, limbs_work, (ntt_v2_kernel<true, false>), gv2, dim3(V2_THREADS), st, V);
+        else if (v2_rows) KL2(c, CKKSMI_K_NTT_INV_ROW, limbs_work, nt, (ntt_v2_kernel<true, false, true>), (ntt_v2_kernel<true, false, false>), gv2, dim3(V2_THREADS), st, V);
         else KL(c, CKKSMI_K_NTT_INV_ROW, limbs_work, ntt_inv_kernel<false>, grow, dim3(NTT_THREADS), st, A);
         if (two_pass && (passes & 1)) {
             A.src = (const u64d *)dst;
             A.map.src_item_stride = A.map.dst_item_stride;
             V.src = A.src;
             V.map.src_item_stride = V.map.dst_item_stride;
-            if (v2_cols && out_f64) KL(c, CKKSMI_K_NTT_INV_COL, limbs_work, (ntt_v2_kernel<true, true, true>), gv2, dim3(V2_THREADS), st, V);
-            else if (v2_cols) KL(c, CKKSMI_K_NTT_INV_COL, limbs_work, (ntt_v2_kernel<true, true>), gv2, dim3(V2_THREADS), st, V);
+            if (v2_cols && out_f64) KL(c, CKKSMI_K_NTT_INV_COL, limbs_work, (ntt_v2_kernel<true, true, false, true>), gv2, dim3(V2_THREADS), st, V);
+            else if (v2_cols) KL2(c, CKKSMI_K_NTT_INV_COL, limbs_work, nt, (ntt_v2_kernel<true, true, true>), (ntt_v2_kernel<true, true, false>), gv2, dim3(V2_THREADS), st, V);
             else KL(c, CKKSMI_K_NTT_INV_COL, limbs_work, ntt_inv_kernel<true>, gcol, dim3(NTT_THREADS), st, A);
         }
     }
@@ -257,6 +273,7 @@ void launch_modup_cols(ckksmi_ctx *c, int mode, const u64 *y, size_t y_stride, u
     if (chunks < 1) chunks = 1;
     if (chunks > n_targets) chunks = n_targets;
     A.targets_per_wg = (n_targets + chunks - 1) / chunks;
+    A.stream = stream_level(8.0 * c->N * (double)ygrid * n_targets);
     const unsigned z = (unsigned)((n_targets + A.targets_per_wg - 1) / A.targets_per_wg);
     const dim3 grid(tiles, (unsigned)ygrid, z), block(V2_THREADS);
     const int nsrc = mode == 0 ? c->alpha : D->nb;
@@ -299,14 +316,15 @@ void launch_rows_final(ckksmi_ctx *c, const u64 *tmpA, const u64 *x, size_t x_ro
     A.out = (u64d *)out; A.modc = c->d_mod; A.tw = c->d_tww_fwd; A.Binv = Binv; A.logN = c->logN; A.nc = nc;
     A.rows = rows;
     A.p51 = c->p51mask;
+    A.stream = stream_level(16.0 * c->N * rows * nz);
     const unsigned tiles = (unsigned)(c->N / 4096);
     const unsigned xch = zchunks_for(c, tiles * nz, rows, A.rows_per_x);
     if (stab)
-        KL(c, CKKSMI_K_ROWS_FINAL, (double)rows * nz, rows_final_scalar_kernel, dim3(xch, tiles, nz), dim3(V2_THREADS), st, A, *stab);
+        KL2(c, CKKSMI_K_ROWS_FINAL, (double)rows * nz, A.stream != STREAM_NONE, rows_final_scalar_kernel<true>, rows_final_scalar_kernel<false>, dim3(xch, tiles, nz), dim3(V2_THREADS), st, A, *stab);
     else if (gal)
-        KL(c, CKKSMI_K_ROWS_FINAL, (double)rows * nz, rows_final_gal_kernel, dim3(xch, tiles, nz), dim3(V2_THREADS), st, A, *gal);
+        KL2(c, CKKSMI_K_ROWS_FINAL, (double)rows * nz, A.stream != STREAM_NONE, rows_final_gal_kernel<true>, rows_final_gal_kernel<false>, dim3(xch, tiles, nz), dim3(V2_THREADS), st, A, *gal);
     else
-        KL(c, CKKSMI_K_ROWS_FINAL, (double)rows * nz, rows_final_kernel, dim3(xch, tiles, nz), dim3(V2_THREADS), st, A);
+        KL2(c, CKKSMI_K_ROWS_FINAL, (double)rows * nz, A.stream != STREAM_NONE, rows_final_kernel<true>, rows_final_kernel<false>, dim3(xch, tiles, nz), dim3(V2_THREADS), st, A);
 }
 
 // Which divisions run as ONE kernel after the inverse transform of the dropped limb (ks_wg.h): one source (rescale, or ModDown with
@@ -341,6 +359,8 @@ void launch_conv_final(ckksmi_ctx *c, int fin_kind, const u64 *y, size_t y_strid
     F.addend = (const u64d *)addend; F.add_item_stride = add_item_stride; F.add_comp_stride = add_comp_stride;
     F.out = (u64d *)out; F.out_row_stride = (size_t)nc * c->N; F.modc = c->d_mod; F.tw = c->d_tww_fwd; F.Binv = D2 ? D2->Binv : D.Binv;
     F.logN = c->logN; F.nc = nc; F.rows = rows; F.p51 = c->p51mask;
+    F.stream = stream_level(16.0 * c->N * rows * nc);
+    const bool nts = F.stream != STREAM_NONE;
     A.y = (const double *)y; A.y_row_stride = y_stride; A.D = D; A.T = c->T;
     // Blocks per limb: M = N >> S words per workgroup.  Kernel time of rescales of 256 ciphertexts of 8 (N <= 2^14), 200 of 16 (2^15) or 64 of
     // 24 primes (2^16), us per 2^14 words: N = 2^12 whole 0.070; 2^13 halved 0.081; 2^14 halved 0.094, quartered 0.101; 2^15 halved 0.094,
@@ -363,13 +383,13 @@ void launch_conv_final(ckksmi_ctx *c, int fin_kind, const u64 *y, size_t y_strid
     const double units = (double)rows * nc;
 #define CONV_FINAL_CASE(LN, SS)                                                                                                  \
     case LN * 4 + SS:                                                                                                                         \
-        if (fin_kind == 0) KL(c, CKKSMI_K_CONV_FINAL, units, (conv_final_kernel<LN - SS, SS, 1, 0>), grid, block, st, A);                 \
-        else if (fin_kind == 1) KL(c, CKKSMI_K_CONV_FINAL, units, (conv_final_kernel<LN - SS, SS, 1, 1>), grid, block, st, A);            \
-        else if (fin_kind == 2) KL(c, CKKSMI_K_CONV_FINAL, units, (conv_final_scalar_kernel<LN - SS, SS>), grid, block, st, A, *stab);    \
-        else KL(c, CKKSMI_K_CONV_FINAL, units, (conv_final_gal_kernel<LN - SS, SS, 1>), grid, block, st, A, *gal);                        \
+        if (fin_kind == 0) KL2(c, CKKSMI_K_CONV_FINAL, units, nts, (conv_final_kernel<LN - SS, SS, 1, 0, true>), (conv_final_kernel<LN - SS, SS, 1, 0, false>), grid, block, st, A);                 \
+        else if (fin_kind == 1) KL2(c, CKKSMI_K_CONV_FINAL, units, nts, (conv_final_kernel<LN - SS, SS, 1, 1, true>), (conv_final_kernel<LN - SS, SS, 1, 1, false>), grid, block, st, A);            \
+        else if (fin_kind == 2) KL2(c, CKKSMI_K_CONV_FINAL, units, nts, (conv_final_scalar_kernel<LN - SS, SS, true>), (conv_final_scalar_kernel<LN - SS, SS, false>), grid, block, st, A, *stab);    \
+        else KL2(c, CKKSMI_K_CONV_FINAL, units, nts, (conv_final_gal_kernel<LN - SS, SS, 1, true>), (conv_final_gal_kernel<LN - SS, SS, 1, false>), grid, block, st, A, *gal);                        \
         break;
     if (fin_kind == 4) {  // sizes of tail_wg_ok
-#define CONV_TAIL_CASE(LN, SS, NS) case (LN * 4 + SS) * 8 + NS: KL(c, CKKSMI_K_CONV_FINAL, units, (conv_final_kernel<LN - SS, SS, NS, 4>), grid, block, st, A); break;
+#define CONV_TAIL_CASE(LN, SS, NS) case (LN * 4 + SS) * 8 + NS: KL2(c, CKKSMI_K_CONV_FINAL, units, nts, (conv_final_kernel<LN - SS, SS, NS, 4, true>), (conv_final_kernel<LN - SS, SS, NS, 4, false>), grid, block, st, A); break;
         switch ((c->logN * 4 + S) * 8 + c->k + 1) {
             CONV_TAIL_CASE(12, 0, 2) CONV_TAIL_CASE(12, 0, 3) CONV_TAIL_CASE(12, 0, 4)
             CONV_TAIL_CASE(13, 1, 2)
@@ -509,7 +529,7 @@ void launch_tensor_rows(ckksmi_ctx *c, const u64 *a, const u64 *b, u64 *ymid, in
     TensorRowsArgs A;
     A.terms = terms;
     A.a = (const u64d *)a; A.b = (const u64d *)b; A.ymid = (u64d *)ymid; A.modc = c->d_mod; A.tw_inv = c->d_tww_inv;
-    A.logN = c->logN; A.level = level; A.p51 = c->p51mask;
+    A.logN = c->logN; A.level = level; A.p51 = c->p51mask; A.stream = stream_level(8.0 * c->N * items * level);
     KL(c, CKKSMI_K_TENSOR_ROWS, (double)items * level, tensor_rows_kernel, dim3((unsigned)(c->N / 4096), level, items), dim3(V2_THREADS), st, A);
 }
 
@@ -624,6 +644,7 @@ void ks_core_fused(ckksmi_ctx *c, const u64 *d_eval, size_t d_stride, const KeyT
     const unsigned tiles = (unsigned)(N / 4096);
     RI.kt = tiles < 8 ? tiles : 8;
     RI.p51 = c->p51mask;
+    RI.stream = stream_level(8.0 * N * items * E * (on_chip ? 2 : beta));
     // the ciphertext limbs leave the inner product as z = x * P^-1 + addend, which is what ModDown's last pass (and the
     // one-conversion tail) read; the merged division wants the accumulators themselves
     RI.fold_tail = (merged || !addend || ta) ? 0 : (add_both ? 1 : 2);
@@ -631,8 +652,8 @@ void ks_core_fused(ckksmi_ctx *c, const u64 *d_eval, size_t d_stride, const KeyT
     RI.addend = (const u64d *)addend; RI.add_item_stride = add_item_stride; RI.add_comp_stride = add_comp_stride;
     RI.ta = (const u64d *)ta; RI.tb = (const u64d *)tb; RI.terms = terms; RI.keep_acc = merged ? 1 : 0; RI.Pmod = c->d_pmod;
     if (on_chip) launch_inner_wg(c, RI, K, ymid, items, st, gal);
-    else if (gal) KL(c, CKKSMI_K_ROWS_INNER, (double)items * E, rows_inner_gal_kernel, dim3(RI.kt * items, tiles / RI.kt, E), dim3(V2_THREADS), st, RI, K, *gal);
-    else KL(c, CKKSMI_K_ROWS_INNER, (double)items * E, rows_inner_kernel, dim3(RI.kt * items, tiles / RI.kt, E), dim3(V2_THREADS), st, RI, K);
+    else if (gal) KL2(c, CKKSMI_K_ROWS_INNER, (double)items * E, RI.stream != STREAM_NONE, rows_inner_gal_kernel<true>, rows_inner_gal_kernel<false>, dim3(RI.kt * items, tiles / RI.kt, E), dim3(V2_THREADS), st, RI, K, *gal);
+    else KL2(c, CKKSMI_K_ROWS_INNER, (double)items * E, RI.stream != STREAM_NONE, rows_inner_kernel<true>, rows_inner_kernel<false>, dim3(RI.kt * items, tiles / RI.kt, E), dim3(V2_THREADS), st, RI, K);
     if (merged) {
         merged_division(c, acc, ta ? nullptr : addend, add_item_stride, add_comp_stride, out, tmp, items, level, st);
         return;
@@ -1494,19 +1515,20 @@ extern "C" int ckksmi_encrypt_device(ckksmi_ctx *c, const uint64_t *pk, const ui
             memset(&V, 0, sizeof(V));
             V.modc = c->d_mod; V.tw = c->d_tww_fwd; V.logN = c->logN; V.p51 = c->p51mask; V.items = items;
             V.map = table_map(idx, level, N, (size_t)3 * level * N);  // source: one int64 polynomial per item
+            const bool nt = stream_level(8.0 * N * items * level) != STREAM_NONE;
             const unsigned tiles = (unsigned)(N / 4096);
             const unsigned zc = zchunks_for(c, tiles * level, items, V.items_per_z);
             for (int which = 0; which < 3; which++) {
                 V.src = (const u64d *)(src[which] + (size_t)b0 * N);
                 V.dst = (u64d *)(small + (size_t)which * level * N);
-                KL(c, CKKSMI_K_ENCRYPT, (double)items * level, ntt_v2_fwd_cols_small_kernel, dim3(tiles, level, zc), dim3(V2_THREADS), st, V);
+                KL2(c, CKKSMI_K_ENCRYPT, (double)items * level, nt, ntt_v2_fwd_cols_small_kernel<true>, ntt_v2_fwd_cols_small_kernel<false>, dim3(tiles, level, zc), dim3(V2_THREADS), st, V);
             }
             EncryptRowsArgs E;
             E.mid = (const u64d *)small; E.pk = (const u64d *)pk; E.pt = (const u64d *)(pt + (size_t)b0 * level * N);
             E.ct = (u64d *)(ct + (size_t)b0 * 2 * level * N); E.modc = c->d_mod; E.tw = c->d_tww_fwd; E.logN = c->logN; E.level = level;
-            E.n_q = c->n_q; E.items = items; E.p51 = c->p51mask;
+            E.n_q = c->n_q; E.items = items; E.p51 = c->p51mask; E.stream = stream_level(40.0 * N * items * level);
             const unsigned xc = zchunks_for(c, tiles * level, items, E.items_per_x);
-            KL(c, CKKSMI_K_ENCRYPT, (double)items * level, encrypt_rows_kernel, dim3(xc, tiles, level), dim3(V2_THREADS), st, E);
+            KL2(c, CKKSMI_K_ENCRYPT, (double)items * level, E.stream != STREAM_NONE, encrypt_rows_kernel<true>, encrypt_rows_kernel<false>, dim3(xc, tiles, level), dim3(V2_THREADS), st, E);
             continue;
         }
         const size_t rows_total = (size_t)items * N;

@@ -168,10 +168,11 @@ struct EncryptRowsArgs {
     const ModConst *modc;
     const double *tw;  // forward twiddles
     int logN, level, n_q, items, items_per_x;
+    int stream;        // STREAM_*
     P51Mask p51;
 };
 
-template <bool P51>
+template <bool P51, bool NTS>
 __device__ __forceinline__ void encrypt_rows_body(const EncryptRowsArgs &A, double *lds, double *tw1_lds, int i) {
     const unsigned N = 1u << A.logN, N1 = N >> 8;
     const double p = A.modc[i].p, pinv = A.modc[i].pinv;
@@ -193,7 +194,7 @@ __device__ __forceinline__ void encrypt_rows_body(const EncryptRowsArgs &A, doub
         ulonglong2 mm[8];
 #pragma unroll
         for (int s = 0; s < 8; s++) mm[s] = ((const ulonglong2 *)(A.pt + ((size_t)it * A.level + i) * N + tile0))[row_pair_index(hi4, lo4, s)];
-        rows_fwd_to_lds<P51, false>(mid, lds, tw1_lds, tw2, p, pinv, hi4, lo4);
+        rows_fwd_to_lds<P51, false>(mid, lds, tw1_lds, tw2, p, pinv, hi4, lo4, A.stream == STREAM_ALL);
         double r[16];
 #pragma unroll
         for (int s = 0; s < 8; s++) {
@@ -202,7 +203,7 @@ __device__ __forceinline__ void encrypt_rows_body(const EncryptRowsArgs &A, doub
             r[2 * s + 1] = rr[1];
         }
         ROW_GROUP_SYNC();
-        rows_fwd_to_lds<P51, true>(mid + st, lds, tw1_lds, tw2, p, pinv, hi4, lo4);
+        rows_fwd_to_lds<P51, true>(mid + st, lds, tw1_lds, tw2, p, pinv, hi4, lo4, A.stream == STREAM_ALL);
         u64d *c0 = A.ct + ((size_t)it * 2 * A.level + i) * N + tile0, *c1 = c0 + st;
 #pragma unroll
         for (int s = 0; s < 8; s++) {
@@ -210,30 +211,31 @@ __device__ __forceinline__ void encrypt_rows_body(const EncryptRowsArgs &A, doub
             const double *ee = lds + hi4 * V2_GS + row_pair_lds(lo4, s);
             const double v0 = mulmod(r[2 * s], u2d(kb[s].x), p, pinv) + ee[0] + u2d(mm[s].x);
             const double v1 = mulmod(r[2 * s + 1], u2d(kb[s].y), p, pinv) + ee[1] + u2d(mm[s].y);
-            ((ulonglong2 *)c0)[row_pair_index(hi4, lo4, s)] = make_ulonglong2(d2u(canon(v0, p, pinv)), d2u(canon(v1, p, pinv)));
+            stream_store<NTS>((ulonglong2 *)c0 + row_pair_index(hi4, lo4, s), make_ulonglong2(d2u(canon(v0, p, pinv)), d2u(canon(v1, p, pinv))));
         }
         ROW_GROUP_SYNC();
-        rows_fwd_to_lds<P51, true>(mid + 2 * st, lds, tw1_lds, tw2, p, pinv, hi4, lo4);
+        rows_fwd_to_lds<P51, true>(mid + 2 * st, lds, tw1_lds, tw2, p, pinv, hi4, lo4, A.stream == STREAM_ALL);
 #pragma unroll
         for (int s = 0; s < 8; s++) {
             const double *ee = lds + hi4 * V2_GS + row_pair_lds(lo4, s);
             const double v0 = mulmod(r[2 * s], u2d(ka[s].x), p, pinv) + ee[0];
             const double v1 = mulmod(r[2 * s + 1], u2d(ka[s].y), p, pinv) + ee[1];
-            ((ulonglong2 *)c1)[row_pair_index(hi4, lo4, s)] = make_ulonglong2(d2u(canon(v0, p, pinv)), d2u(canon(v1, p, pinv)));
+            stream_store<NTS>((ulonglong2 *)c1 + row_pair_index(hi4, lo4, s), make_ulonglong2(d2u(canon(v0, p, pinv)), d2u(canon(v1, p, pinv))));
         }
         ROW_GROUP_SYNC();
     }
 }
 
 // grid: x = chunk of items, y = row tile (N/4096), z = limb
+template <bool NTS>
 __global__ __launch_bounds__(V2_THREADS) void encrypt_rows_kernel(EncryptRowsArgs A) {
     __shared__ double lds[16 * V2_GS];
     __shared__ double tw1_lds[16 * 16];
     const int i = (int)blockIdx.z;
     if (is_p51(A.p51, i))
-        encrypt_rows_body<true>(A, lds, tw1_lds, i);
+        encrypt_rows_body<true, NTS>(A, lds, tw1_lds, i);
     else
-        encrypt_rows_body<false>(A, lds, tw1_lds, i);
+        encrypt_rows_body<false, NTS>(A, lds, tw1_lds, i);
 }
 
 // ---------------------------------------------------------------- sampling

@@ -38,6 +38,7 @@ struct TensorRowsArgs {
     const double *tw_inv;
     int logN, level;
     int terms;
+    int stream;          // STREAM_*
     P51Mask p51;
 };
 
@@ -103,8 +104,10 @@ __device__ __forceinline__ void tensor_rows_body(const TensorRowsArgs &A, double
     for (int e = 0; e < 16; e++) x[e] = grp[e * 17 + lo4];
     inv_stages<0, INV_ROW2, P51>(x, tw1, p, pinv, unused, unused);
     u64d *ym = A.ymid + ((size_t)item * A.level + i) * N + tile0;
+    stream_if(A.stream != STREAM_NONE, [&](auto nt) {
 #pragma unroll
-    for (int e = 0; e < 16; e++) ym[hi4 * 256 + lo4 + 16 * e] = mid_store(x[e]);
+        for (int e = 0; e < 16; e++) stream_store<nt>(&ym[hi4 * 256 + lo4 + 16 * e], mid_store(x[e]));
+    });
 }
 
 // grid: x = tile (N/4096), y = limb, z = item
@@ -144,6 +147,7 @@ struct ModupColsArgs {
     DivRoundDev D;                // MODE 1 constants
     int logN, level, E, n_q, alpha, beta, T, nc;
     int targets_per_wg;
+    int stream;                   // STREAM_*
     P51Mask p51;
     // y holds the output of the inverse ROW pass (reduced doubles); the inverse column pass with its folded
     // constants runs in the workgroup's prologue and the conversion inputs never go through memory
@@ -203,7 +207,7 @@ __device__ __forceinline__ void inv_cols_in_regs(double (&x)[16], const double *
 template <bool P51, int NSRC, int Q, int VARIANT, bool SUB>
 __device__ __forceinline__ void modup_cols_target(const double (&yd)[NSRC][16], WMul (&Wc)[NSRC], const double *twl, double *lds, u64d *dst,
                                                   const ColsGeom<Q> &geo, double p, double pinv, double *twl_next, double tw_store, double hsub,
-                                                  unsigned long long vpack, double Bm, const double *ybl = nullptr) {
+                                                  unsigned long long vpack, double Bm, bool stream, const double *ybl = nullptr) {
     typedef ColsGeom<Q> Geo;
     constexpr int NPROD = VARIANT == 2 ? NSRC - 1 : NSRC;
     constexpr bool CHAIN = !P51 && NPROD >= 2 && !(VARIANT == 0 && NSRC == 4);  // four products and h could pass 2^53
@@ -266,8 +270,10 @@ __device__ __forceinline__ void modup_cols_target(const double (&yd)[NSRC][16], 
             }
         fwd_stages<Geo::S0, Mk::F2>(x, tw2, p, pinv);
     }
+    stream_if(stream, [&](auto nt) {
 #pragma unroll
-    for (int i = 0; i < 16; i++) dst[geo.g2(i)] = mid_store(x[i]);
+        for (int i = 0; i < 16; i++) stream_store<nt>(&dst[geo.g2(i)], mid_store(x[i]));
+    });
 }
 
 // grid: x = column tile (N/4096), y = item * beta + digit, z = chunk of targets_per_wg target limbs
@@ -415,9 +421,9 @@ __global__ __launch_bounds__(V2_THREADS, (NSRC >= 4 && MODE == 2) ? 1 : 2) void 
         constexpr bool ONE_BUF = MODE == 3 || SRC0_LDS;  // the second buffer holds y_B / the first source tile
         double *xbuf = ONE_BUF ? lds[0] : lds[(k - k0) & 1];
         if (is_p51(A.p51, t))
-            modup_cols_target<true, NSRC, Q, (MODE >= 2 ? MODE - 1 : 0), MODE != 0>(yd, Wc, tcur, xbuf, dst, geo, p, pinv, tnext, tw_store, hsub, vpack, Bm, (MODE == 3 || SRC0_LDS) ? lds[1] : nullptr);
+            modup_cols_target<true, NSRC, Q, (MODE >= 2 ? MODE - 1 : 0), MODE != 0>(yd, Wc, tcur, xbuf, dst, geo, p, pinv, tnext, tw_store, hsub, vpack, Bm, A.stream != STREAM_NONE, (MODE == 3 || SRC0_LDS) ? lds[1] : nullptr);
         else
-            modup_cols_target<false, NSRC, Q, (MODE >= 2 ? MODE - 1 : 0), MODE != 0>(yd, Wc, tcur, xbuf, dst, geo, p, pinv, tnext, tw_store, hsub, vpack, Bm, (MODE == 3 || SRC0_LDS) ? lds[1] : nullptr);
+            modup_cols_target<false, NSRC, Q, (MODE >= 2 ? MODE - 1 : 0), MODE != 0>(yd, Wc, tcur, xbuf, dst, geo, p, pinv, tnext, tw_store, hsub, vpack, Bm, A.stream != STREAM_NONE, (MODE == 3 || SRC0_LDS) ? lds[1] : nullptr);
         if (ONE_BUF) __syncthreads();  // single exchange buffer: everybody has read it before the next target writes
     }
 }
@@ -444,12 +450,14 @@ __device__ __forceinline__ void load_row_twiddles(const double *tw, unsigned N1,
 // Every row is handled by its own 16 lanes: ends with a row-group sync, and the caller puts one before the next call.
 template <bool P51, bool LAZY>
 __device__ __forceinline__ void rows_fwd_to_lds(const u64d *tile, double *lds, const double *tw1_lds, const double (&tw2)[15], double p,
-                                                double pinv, unsigned hi4, unsigned lo4) {
+                                                double pinv, unsigned hi4, unsigned lo4, bool stream) {
     typedef RowMasks<P51, LAZY> Mk;
     double *grp = lds + hi4 * V2_GS;
     double x[16];
+    stream_if(stream, [&](auto nt) {
 #pragma unroll
-    for (int e = 0; e < 16; e++) x[e] = mid_load(tile[hi4 * 256 + lo4 + 16 * e]);
+        for (int e = 0; e < 16; e++) x[e] = mid_load(stream_load<nt>(&tile[hi4 * 256 + lo4 + 16 * e]));
+    });
     {
         // round-1 twiddles are the same for the 16 lanes of a row: kept in LDS, not in registers
         double tw1[15];
@@ -478,6 +486,7 @@ struct RowsInnerArgs {
     const double *tw;    // forward twiddles
     int logN, level, E, n_q, alpha, beta, T;
     unsigned kt;         // min(N/4096, 8): see the grid mapping in rows_inner_body
+    int stream;          // STREAM_*
     P51Mask p51;
     // fold_tail: the ciphertext limbs leave this kernel as z = acc * P^-1 + d (d = the addend of the same row: the product's
     // component, or sigma(c0) for the first row of a rotation), which is what the ModDown (and rescale) that follows reads.
@@ -582,7 +591,7 @@ __device__ __forceinline__ void inner_own_digit(const RowsInnerArgs &A, const u6
 }
 
 // The accumulators leave as z (folded tail), as acc + P*d, or as they are
-template <bool GAL>
+template <bool GAL, bool NTS>
 __device__ __forceinline__ void inner_store(const RowsInnerArgs &A, unsigned item, int t, unsigned x, bool tensor_mode, size_t tile0, unsigned hi4,
                                             unsigned lo4, double p, double pinv, const double (&a0)[16], const double (&a1)[16], const GaloisTab *gal) {
     const unsigned N = 1u << A.logN;
@@ -595,8 +604,8 @@ __device__ __forceinline__ void inner_store(const RowsInnerArgs &A, unsigned ite
         for (int s = 0; s < 8; s++) {
             const double z00 = mulmod_w(a0[2 * s], Pi.w, Pi.wp, p), z01 = mulmod_w(a0[2 * s + 1], Pi.w, Pi.wp, p);
             const double z10 = mulmod_w(a1[2 * s], Pi.w, Pi.wp, p), z11 = mulmod_w(a1[2 * s + 1], Pi.w, Pi.wp, p);
-            ((ulonglong2 *)o0)[row_pair_index(hi4, lo4, s)] = make_ulonglong2(d2u(canon(z00, p, pinv)), d2u(canon(z01, p, pinv)));
-            ((ulonglong2 *)o1)[row_pair_index(hi4, lo4, s)] = make_ulonglong2(d2u(canon(z10, p, pinv)), d2u(canon(z11, p, pinv)));
+            stream_store<NTS>((ulonglong2 *)o0 + row_pair_index(hi4, lo4, s), make_ulonglong2(d2u(canon(z00, p, pinv)), d2u(canon(z01, p, pinv))));
+            stream_store<NTS>((ulonglong2 *)o1 + row_pair_index(hi4, lo4, s), make_ulonglong2(d2u(canon(z10, p, pinv)), d2u(canon(z11, p, pinv))));
         }
         return;
     }
@@ -623,21 +632,21 @@ __device__ __forceinline__ void inner_store(const RowsInnerArgs &A, unsigned ite
             // accumulators are below 2^53: the prepared product is exact for them as they are
             const double z00 = mulmod_w(a0[2 * s], Pi.w, Pi.wp, p) + u2d(dw0[s].x), z01 = mulmod_w(a0[2 * s + 1], Pi.w, Pi.wp, p) + u2d(dw0[s].y);
             const double z10 = mulmod_w(a1[2 * s], Pi.w, Pi.wp, p) + has1 * u2d(dw1[s].x), z11 = mulmod_w(a1[2 * s + 1], Pi.w, Pi.wp, p) + has1 * u2d(dw1[s].y);
-            ((ulonglong2 *)o0)[row_pair_index(hi4, lo4, s)] = make_ulonglong2(d2u(canon(z00, p, pinv)), d2u(canon(z01, p, pinv)));
-            ((ulonglong2 *)o1)[row_pair_index(hi4, lo4, s)] = make_ulonglong2(d2u(canon(z10, p, pinv)), d2u(canon(z11, p, pinv)));
+            stream_store<NTS>((ulonglong2 *)o0 + row_pair_index(hi4, lo4, s), make_ulonglong2(d2u(canon(z00, p, pinv)), d2u(canon(z01, p, pinv))));
+            stream_store<NTS>((ulonglong2 *)o1 + row_pair_index(hi4, lo4, s), make_ulonglong2(d2u(canon(z10, p, pinv)), d2u(canon(z11, p, pinv))));
         }
         return;
     }
 #pragma unroll
     for (int s = 0; s < 8; s++) {
-        ((ulonglong2 *)o0)[row_pair_index(hi4, lo4, s)] = make_ulonglong2(d2u(canon(a0[2 * s], p, pinv)), d2u(canon(a0[2 * s + 1], p, pinv)));
-        ((ulonglong2 *)o1)[row_pair_index(hi4, lo4, s)] = make_ulonglong2(d2u(canon(a1[2 * s], p, pinv)), d2u(canon(a1[2 * s + 1], p, pinv)));
+        stream_store<NTS>((ulonglong2 *)o0 + row_pair_index(hi4, lo4, s), make_ulonglong2(d2u(canon(a0[2 * s], p, pinv)), d2u(canon(a0[2 * s + 1], p, pinv))));
+        stream_store<NTS>((ulonglong2 *)o1 + row_pair_index(hi4, lo4, s), make_ulonglong2(d2u(canon(a1[2 * s], p, pinv)), d2u(canon(a1[2 * s + 1], p, pinv))));
     }
 }
 
 // GAL (a rotation): the source polynomial d_eval and the addend are read through the automorphism X -> X^g of their item
 // (gal->g[item]), so that no rotated copy of the ciphertext is ever written
-template <bool P51, bool GAL = false>
+template <bool P51, bool GAL, bool NTS>
 __device__ __forceinline__ void rows_inner_body(const RowsInnerArgs &A, const KeyTab &K, double *lds, double *tw1_lds, double *tw2_lds, int t,
                                                 unsigned x, const GaloisTab *gal = nullptr) {
     BODY_TAG(P51);
@@ -679,8 +688,10 @@ __device__ __forceinline__ void rows_inner_body(const RowsInnerArgs &A, const Ke
     u64d xr[16];
     if (j < A.beta) {
         const u64d *src = A.dtA + (((size_t)item * A.beta + j) * A.E + x) * N + tile0;
+        stream_if(A.stream == STREAM_ALL, [&](auto nt) {
 #pragma unroll
-        for (int i = 0; i < 16; i++) xr[i] = src[hi4 * 256 + lo4 + 16 * i];
+            for (int i = 0; i < 16; i++) xr[i] = stream_load<nt>(&src[hi4 * 256 + lo4 + 16 * i]);
+        });
     }
     while (j < A.beta) {
         const u64d *k0 = key + (((size_t)j * 2 + 0) * A.T + t) * N + tile0;
@@ -721,8 +732,10 @@ __device__ __forceinline__ void rows_inner_body(const RowsInnerArgs &A, const Ke
         if (jn == j_own) jn++;
         if (jn < A.beta) {
             const u64d *src = A.dtA + (((size_t)item * A.beta + jn) * A.E + x) * N + tile0;
+            stream_if(A.stream == STREAM_ALL, [&](auto nt) {
 #pragma unroll
-            for (int i = 0; i < 16; i++) xr[i] = src[hi4 * 256 + lo4 + 16 * i];
+                for (int i = 0; i < 16; i++) xr[i] = stream_load<nt>(&src[hi4 * 256 + lo4 + 16 * i]);
+            });
         }
         SCHED_FENCE();
 #pragma unroll
@@ -747,10 +760,11 @@ __device__ __forceinline__ void rows_inner_body(const RowsInnerArgs &A, const Ke
         ROW_GROUP_SYNC();  // the row's lanes have read its words before the next digit overwrites them
         j = jn;
     }
-    inner_store<GAL>(A, item, t, x, tensor_mode, tile0, hi4, lo4, p, pinv, a0, a1, gal);
+    inner_store<GAL, NTS>(A, item, t, x, tensor_mode, tile0, hi4, lo4, p, pinv, a0, a1, gal);
 }
 
 // grid: x = (row tile mod kt) + kt * item, y = row tile / kt, z = extended limb
+template <bool NTS>
 __global__ __launch_bounds__(V2_THREADS, 2) void rows_inner_kernel(RowsInnerArgs A, KeyTab K) {
     __shared__ double lds[16 * V2_GS];
     __shared__ double tw1_lds[16 * 16];
@@ -758,12 +772,13 @@ __global__ __launch_bounds__(V2_THREADS, 2) void rows_inner_kernel(RowsInnerArgs
     const unsigned x = blockIdx.z;
     const int t = (int)x < A.level ? (int)x : A.n_q + (int)x - A.level;
     if (is_p51(A.p51, t))
-        rows_inner_body<true>(A, K, lds, tw1_lds, tw2_lds, t, x);
+        rows_inner_body<true, false, NTS>(A, K, lds, tw1_lds, tw2_lds, t, x);
     else
-        rows_inner_body<false>(A, K, lds, tw1_lds, tw2_lds, t, x);
+        rows_inner_body<false, false, NTS>(A, K, lds, tw1_lds, tw2_lds, t, x);
 }
 
 // the same for rotations: source polynomial and addend read through the items' automorphisms (no tensor mode here)
+template <bool NTS>
 __global__ __launch_bounds__(V2_THREADS, 2) void rows_inner_gal_kernel(RowsInnerArgs A, KeyTab K, GaloisTab G) {
     __shared__ double lds[16 * V2_GS];
     __shared__ double tw1_lds[16 * 16];
@@ -771,9 +786,9 @@ __global__ __launch_bounds__(V2_THREADS, 2) void rows_inner_gal_kernel(RowsInner
     const unsigned x = blockIdx.z;
     const int t = (int)x < A.level ? (int)x : A.n_q + (int)x - A.level;
     if (is_p51(A.p51, t))
-        rows_inner_body<true, true>(A, K, lds, tw1_lds, tw2_lds, t, x, &G);
+        rows_inner_body<true, true, NTS>(A, K, lds, tw1_lds, tw2_lds, t, x, &G);
     else
-        rows_inner_body<false, true>(A, K, lds, tw1_lds, tw2_lds, t, x, &G);
+        rows_inner_body<false, true, NTS>(A, K, lds, tw1_lds, tw2_lds, t, x, &G);
 }
 
 // ------------------------------------------------------------------ row pass + DivRound final step
@@ -793,6 +808,7 @@ struct RowsFinalArgs {
     int zsub;            // 1: x already holds x*Binv + addend: out = x - r * Binv
     int logN, nc;
     int limb0;             // first limb handled (grid z counts from it)
+    int stream;            // STREAM_*
     int rows, rows_per_x;  // a workgroup loops over rows_per_x rows (same limb, same tile: twiddles reused)
     P51Mask p51;
 };
@@ -802,7 +818,7 @@ struct RowsFinalArgs {
 // A.add_item_stride = words between the items' ciphertexts)
 struct RowsFinalGal { int R; unsigned g[CKKSMI_MAX_KEYS]; };
 
-template <bool P51, bool GAL = false>
+template <bool P51, bool NTS, bool GAL = false>
 __device__ __forceinline__ void rows_final_body(const RowsFinalArgs &A, double *lds, double *tw1_lds, int i, bool xm_val = false,
                                                 WMul xmv = WMul{0.0, 0.0}, const RowsFinalGal *gal = nullptr) {
     const unsigned N = 1u << A.logN, N1 = N >> 8;
@@ -837,7 +853,7 @@ __device__ __forceinline__ void rows_final_body(const RowsFinalArgs &A, double *
             }
         }
         SCHED_FENCE();
-        rows_fwd_to_lds<P51, true>(A.tmpA + ((size_t)row * A.nc + i) * N + tile0, lds, tw1_lds, tw2, p, pinv, hi4, lo4);
+        rows_fwd_to_lds<P51, true>(A.tmpA + ((size_t)row * A.nc + i) * N + tile0, lds, tw1_lds, tw2, p, pinv, hi4, lo4, A.stream == STREAM_ALL);
 #pragma unroll
         for (int s = 0; s < 8; s++) {
             const double *rr = lds + hi4 * V2_GS + row_pair_lds(lo4, s);
@@ -862,42 +878,45 @@ __device__ __forceinline__ void rows_final_body(const RowsFinalArgs &A, double *
                 v0 += u2d(ar[s].x);
                 v1 += u2d(ar[s].y);
             }
-            ((ulonglong2 *)out)[row_pair_index(hi4, lo4, s)] = make_ulonglong2(d2u(canon(v0, p, pinv)), d2u(canon(v1, p, pinv)));
+            stream_store<NTS>((ulonglong2 *)out + row_pair_index(hi4, lo4, s), make_ulonglong2(d2u(canon(v0, p, pinv)), d2u(canon(v1, p, pinv))));
         }
         ROW_GROUP_SYNC();
     }
 }
 
 // grid: x = chunk of rows (item, component), y = row tile (N/4096), z = kept limb
+template <bool NTS>
 __global__ __launch_bounds__(V2_THREADS) void rows_final_kernel(RowsFinalArgs A) {
     __shared__ double lds[16 * V2_GS];
     __shared__ double tw1_lds[16 * 16];
     const int i = A.limb0 + (int)blockIdx.z;
     if (is_p51(A.p51, i))
-        rows_final_body<true>(A, lds, tw1_lds, i);
+        rows_final_body<true, NTS>(A, lds, tw1_lds, i);
     else
-        rows_final_body<false>(A, lds, tw1_lds, i);
+        rows_final_body<false, NTS>(A, lds, tw1_lds, i);
 }
 
 // the same for rotations from a shared ModUp: the addend sigma_r(c0) is read through the automorphism
+template <bool NTS>
 __global__ __launch_bounds__(V2_THREADS) void rows_final_gal_kernel(RowsFinalArgs A, RowsFinalGal G) {
     __shared__ double lds[16 * V2_GS];
     __shared__ double tw1_lds[16 * 16];
     const int i = A.limb0 + (int)blockIdx.z;
     if (is_p51(A.p51, i))
-        rows_final_body<true, true>(A, lds, tw1_lds, i, false, WMul{0.0, 0.0}, &G);
+        rows_final_body<true, NTS, true>(A, lds, tw1_lds, i, false, WMul{0.0, 0.0}, &G);
     else
-        rows_final_body<false, true>(A, lds, tw1_lds, i, false, WMul{0.0, 0.0}, &G);
+        rows_final_body<false, NTS, true>(A, lds, tw1_lds, i, false, WMul{0.0, 0.0}, &G);
 }
 
 // the same with the kept limb multiplied by a per-call scalar first: out = (c*x - r) * Binv (+ addend): rescale of c*x
+template <bool NTS>
 __global__ __launch_bounds__(V2_THREADS) void rows_final_scalar_kernel(RowsFinalArgs A, ScalarTab S) {
     __shared__ double lds[16 * V2_GS];
     __shared__ double tw1_lds[16 * 16];
     const int i = A.limb0 + (int)blockIdx.z;
     const WMul xmv = S.c[i];
     if (is_p51(A.p51, i))
-        rows_final_body<true>(A, lds, tw1_lds, i, true, xmv);
+        rows_final_body<true, NTS>(A, lds, tw1_lds, i, true, xmv);
     else
-        rows_final_body<false>(A, lds, tw1_lds, i, true, xmv);
+        rows_final_body<false, NTS>(A, lds, tw1_lds, i, true, xmv);
 }

@@ -182,7 +182,7 @@ __device__ __forceinline__ void inner_wg_body(const InnerWgArgs &A, const KeyTab
             pending = 0;
         }
     }
-    inner_store<GAL>(R, item, t, x, tensor_mode, tile0, prow, lo4, p, pinv, a0, a1, gal);
+    inner_store<GAL, false>(R, item, t, x, tensor_mode, tile0, prow, lo4, p, pinv, a0, a1, gal);
 }
 
 // Consecutive workgroups go to the 8 XCDs in turn: an item's blocks sit on one XCD (they read the same sources), the items of an

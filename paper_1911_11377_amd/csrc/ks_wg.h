@@ -86,7 +86,7 @@ __device__ __forceinline__ double tail_word(const double (&y)[NSRC], const WMul 
 // FIN 0: out = (x - r) * Binv;  1: out = x - r * Binv (x holds x * Binv + addend);  2: out = (x * xmv - r) * Binv (+ addend);
 // 3: out = (x - r) * Binv + sigma_g(addend) on even rows (rotations from a shared ModUp, see RowsFinalGal);  4: FIN 0 for ModDown
 // followed by rescale in one conversion (sources from tail_sources_kernel; D describes the ModDown, F.Binv the rescale)
-template <int LOGM, int S, int NSRC, int FIN, bool P51>
+template <int LOGM, int S, int NSRC, int FIN, bool P51, bool NTS>
 __device__ __forceinline__ void conv_final_body(const ConvFinalArgs &A, double *lds, int i, unsigned row, unsigned blk, WMul xmv,
                                                 const RowsFinalGal *gal) {
     typedef ColsGeom<LOGM - 12> Geo;
@@ -150,8 +150,10 @@ __device__ __forceinline__ void conv_final_body(const ConvFinalArgs &A, double *
     const unsigned pr = row_pair_index(prow, lo4, 0);
     ulonglong2 xr[8];
     wg_fwd_block<LOGM, P51, true>(x, tw, base, lds, p, pinv, [&]() {
+        stream_if(F.stream == STREAM_ALL, [&](auto nt) {
 #pragma unroll
-        for (int s = 0; s < 8; s++) xr[s] = (xin + 16 * s)[pr];
+            for (int s = 0; s < 8; s++) xr[s] = stream_load<nt>(xin + 16 * s + pr);
+        });
     });
     const WMul W = F.Binv[i];
     const bool add = F.addend != nullptr && (FIN == 2 || (FIN == 3 && (row & 1u) == 0));
@@ -169,7 +171,7 @@ __device__ __forceinline__ void conv_final_body(const ConvFinalArgs &A, double *
             v0 += u2d(ar.x);
             v1 += u2d(ar.y);
         }
-        (out + 16 * s)[pr] = make_ulonglong2(d2u(canon(v0, p, pinv)), d2u(canon(v1, p, pinv)));
+        stream_store<NTS>(out + 16 * s + pr, make_ulonglong2(d2u(canon(v0, p, pinv)), d2u(canon(v1, p, pinv))));
     };
     if (FIN < 2 || FIN == 4 || !add) {
 #pragma unroll
@@ -192,36 +194,36 @@ __device__ __forceinline__ void conv_final_body(const ConvFinalArgs &A, double *
 }
 
 // grid: x = rows_x * 2^S * rows_g * nc * (row groups), see conv_final_place; block = M/16 threads
-template <int LOGM, int S, int NSRC, int FIN>
+template <int LOGM, int S, int NSRC, int FIN, bool NTS>
 __global__ __launch_bounds__((1 << LOGM) / 16, 4) void conv_final_kernel(ConvFinalArgs A) {
     __shared__ double lds[((1 << LOGM) >> 8) * V2_GS];
     unsigned row, blk;
     int i;
     if (!conv_final_place(A, S, row, blk, i)) return;
-    if (is_p51(A.F.p51, i)) conv_final_body<LOGM, S, NSRC, FIN, true>(A, lds, i, row, blk, WMul{0.0, 0.0}, nullptr);
-    else conv_final_body<LOGM, S, NSRC, FIN, false>(A, lds, i, row, blk, WMul{0.0, 0.0}, nullptr);
+    if (is_p51(A.F.p51, i)) conv_final_body<LOGM, S, NSRC, FIN, true, NTS>(A, lds, i, row, blk, WMul{0.0, 0.0}, nullptr);
+    else conv_final_body<LOGM, S, NSRC, FIN, false, NTS>(A, lds, i, row, blk, WMul{0.0, 0.0}, nullptr);
 }
 
 // the kept limb multiplied by a per-call scalar first (rescale of a scalar multiple)
-template <int LOGM, int S>
+template <int LOGM, int S, bool NTS>
 __global__ __launch_bounds__((1 << LOGM) / 16, 4) void conv_final_scalar_kernel(ConvFinalArgs A, ScalarTab Sc) {
     __shared__ double lds[((1 << LOGM) >> 8) * V2_GS];
     unsigned row, blk;
     int i;
     if (!conv_final_place(A, S, row, blk, i)) return;
-    if (is_p51(A.F.p51, i)) conv_final_body<LOGM, S, 1, 2, true>(A, lds, i, row, blk, Sc.c[i], nullptr);
-    else conv_final_body<LOGM, S, 1, 2, false>(A, lds, i, row, blk, Sc.c[i], nullptr);
+    if (is_p51(A.F.p51, i)) conv_final_body<LOGM, S, 1, 2, true, NTS>(A, lds, i, row, blk, Sc.c[i], nullptr);
+    else conv_final_body<LOGM, S, 1, 2, false, NTS>(A, lds, i, row, blk, Sc.c[i], nullptr);
 }
 
 // rotations from a shared ModUp
-template <int LOGM, int S, int NSRC>
+template <int LOGM, int S, int NSRC, bool NTS>
 __global__ __launch_bounds__((1 << LOGM) / 16, 4) void conv_final_gal_kernel(ConvFinalArgs A, RowsFinalGal G) {
     __shared__ double lds[((1 << LOGM) >> 8) * V2_GS];
     unsigned row, blk;
     int i;
     if (!conv_final_place(A, S, row, blk, i)) return;
-    if (is_p51(A.F.p51, i)) conv_final_body<LOGM, S, NSRC, 3, true>(A, lds, i, row, blk, WMul{0.0, 0.0}, &G);
-    else conv_final_body<LOGM, S, NSRC, 3, false>(A, lds, i, row, blk, WMul{0.0, 0.0}, &G);
+    if (is_p51(A.F.p51, i)) conv_final_body<LOGM, S, NSRC, 3, true, NTS>(A, lds, i, row, blk, WMul{0.0, 0.0}, &G);
+    else conv_final_body<LOGM, S, NSRC, 3, false, NTS>(A, lds, i, row, blk, WMul{0.0, 0.0}, &G);
 }
 
 // ------------------------------------------------------------------ sources of ModDown followed by rescale

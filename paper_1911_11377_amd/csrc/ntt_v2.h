@@ -92,6 +92,47 @@ __device__ __forceinline__ double table_load(const double *t, unsigned i) { retu
 #endif
 __device__ __forceinline__ WMul table_load(const WMul *t) { return WMul{table_load((const double *)t, 0), table_load((const double *)t, 1)}; }
 
+// Streamed accesses (non-temporal): words that the caches could not keep until they are wanted again.  How much of a launch is
+// streamed is decided on the host from the bytes it moves (stream_level, ckksmi_device.hip): STREAM_STORES results only,
+// STREAM_ALL operands too.  It is a template parameter of the kernel, or where that would double many instances a loop of
+// accesses behind one uniform branch:
+//     stream_if(A.stream != STREAM_NONE, [&](auto nt) { for (...) stream_store<nt>(p, v); });
+enum { STREAM_NONE, STREAM_STORES, STREAM_ALL };
+template <bool V> struct StreamFlag { constexpr operator bool() const { return V; } };
+#ifdef CKKSMI_EMULATE
+#define STREAM_TAG(T) ((void)0)
+template <bool NT, class P> static inline auto stream_load(P p) { return *p; }
+template <bool NT, class P, class V> static inline void stream_store(P p, V v) { *p = v; }
+#else
+// (the compiler merges accesses of both branches that differ in the hint only, into plain ones: the notes keep them apart)
+#define STREAM_TAG(T) asm volatile("; " T ::: "memory")
+typedef unsigned long long u64pair __attribute__((ext_vector_type(2)));
+template <bool NT, class P> __device__ __forceinline__ auto stream_load(P p) {
+    if constexpr (NT) return __builtin_nontemporal_load(p);
+    else return *p;
+}
+template <bool NT> __device__ __forceinline__ ulonglong2 stream_load(const ulonglong2 *p) {
+    const u64pair v = stream_load<NT>((const u64pair *)p);
+    return make_ulonglong2(v.x, v.y);
+}
+template <bool NT, class P, class V> __device__ __forceinline__ void stream_store(P p, V v) {
+    if constexpr (NT) __builtin_nontemporal_store(v, p);
+    else *p = v;
+}
+template <bool NT> __device__ __forceinline__ void stream_store(ulonglong2 *p, ulonglong2 v) { stream_store<NT>((u64pair *)p, u64pair{v.x, v.y}); }
+#endif
+template <class F> __device__ __forceinline__ void stream_if(bool on, F f) {
+    if (on) {
+        STREAM_TAG("streamed");
+        f(StreamFlag<true>());
+        STREAM_TAG("streamed, end");
+    } else {
+        STREAM_TAG("cached");
+        f(StreamFlag<false>());
+        STREAM_TAG("cached, end");
+    }
+}
+
 #define V2_GS 272  // doubles per padded 16x17 group in LDS (row pass)
 
 // Row pass: the 16 lanes that work on one row of 256 words exchange their words through that row's own LDS group and
@@ -321,7 +362,8 @@ struct RowMasks {
 // SMALL (forward only): the source is a polynomial with small signed coefficients, one int64 per coefficient and the same
 // for every limb (item i at (const long long *)A.src + i * src_item_stride): its residues are the values themselves
 // F64 (inverse only): the canonical coefficients leave as doubles (the input of a conversion, never visible outside)
-template <bool INV, int Q, bool P51, bool SMALL = false, bool F64 = false>
+// NT: operands and results are streamed
+template <bool INV, int Q, bool P51, bool SMALL, bool F64, bool NT>
 __device__ __forceinline__ void ntt_v2_cols(const NttV2Args &A, double *lds, int t, unsigned li) {
     typedef ColsGeom<Q> Geo;
     typedef ColsMasks<Q, P51, 256> Mk;
@@ -354,7 +396,7 @@ __device__ __forceinline__ void ntt_v2_cols(const NttV2Args &A, double *lds, int
                     const long long v = ((const long long *)A.src + (size_t)it * A.map.src_item_stride)[geo.g1(e)];
                     x[e] = reduce_balanced(u2d((unsigned long long)(v + (1ll << 51))) - 2251799813685248.0, p, pinv);
                 }
-                else x[e] = u2d(src[geo.g1(e)]);
+                else x[e] = u2d(stream_load<NT>(&src[geo.g1(e)]));
             }
             fwd_round<Mk::F1>(x, tw1, p, pinv);
 #pragma unroll
@@ -364,10 +406,10 @@ __device__ __forceinline__ void ntt_v2_cols(const NttV2Args &A, double *lds, int
             for (int i = 0; i < 16; i++) x[i] = lds[geo.l2(i)];
             fwd_stages<Geo::S0, Mk::F2>(x, tw2, p, pinv);
 #pragma unroll
-            for (int i = 0; i < 16; i++) dst[geo.g2(i)] = mid_store(x[i]);
+            for (int i = 0; i < 16; i++) stream_store<NT>(&dst[geo.g2(i)], mid_store(x[i]));
         } else {
 #pragma unroll
-            for (int i = 0; i < 16; i++) x[i] = mid_load(src[geo.g2(i)]);
+            for (int i = 0; i < 16; i++) x[i] = mid_load(stream_load<NT>(&src[geo.g2(i)]));
             inv_stages<Geo::S0, INV_COL2, P51>(x, tw2, p, pinv, ninv, wlast);
 #pragma unroll
             for (int i = 0; i < 16; i++) lds[geo.l2(i)] = x[i];
@@ -378,7 +420,7 @@ __device__ __forceinline__ void ntt_v2_cols(const NttV2Args &A, double *lds, int
 #pragma unroll
             for (int e = 0; e < 16; e++) {
                 const double v = canon(x[e] + cadd, p, pinv);
-                dst[geo.g1(e)] = F64 ? (u64d)__double_as_longlong(v) : d2u(v);
+                stream_store<NT>(&dst[geo.g1(e)], F64 ? (u64d)__double_as_longlong(v) : d2u(v));
             }
         }
         __syncthreads();
@@ -387,7 +429,7 @@ __device__ __forceinline__ void ntt_v2_cols(const NttV2Args &A, double *lds, int
 
 // GAL (inverse only): the input is read through the automorphism X -> X^g of its item (G->g[item]): a rotation's
 // polynomial enters its key switch without a pass of its own
-template <bool INV, bool P51, bool GAL = false>
+template <bool INV, bool P51, bool NT, bool GAL = false>
 __device__ __forceinline__ void ntt_v2_rows(const NttV2Args &A, double *lds, int t, unsigned li, const GaloisTab *G = nullptr) {
     const unsigned N = 1u << A.logN, N1 = N >> 8;
     const double p = A.modc[t].p, pinv = A.modc[t].pinv;
@@ -407,7 +449,7 @@ __device__ __forceinline__ void ntt_v2_rows(const NttV2Args &A, double *lds, int
         double x[16];
         if (!INV) {
 #pragma unroll
-            for (int e = 0; e < 16; e++) x[e] = mid_load(src[tile0 + hi4 * 256 + lo4 + 16 * e]);
+            for (int e = 0; e < 16; e++) x[e] = mid_load(stream_load<NT>(&src[tile0 + hi4 * 256 + lo4 + 16 * e]));
             fwd_round<Mk::F1>(x, tw1, p, pinv);
 #pragma unroll
             for (int e = 0; e < 16; e++) grp[e * 17 + lo4] = x[e];
@@ -422,17 +464,19 @@ __device__ __forceinline__ void ntt_v2_rows(const NttV2Args &A, double *lds, int
 #pragma unroll
             for (int s = 0; s < 8; s++) {
                 const double *rr = grp + row_pair_lds(lo4, s);
-                ((ulonglong2 *)(dst + tile0))[row_pair_index(hi4, lo4, s)] = make_ulonglong2(d2u(rr[0]), d2u(rr[1]));
+                stream_store<NT>((ulonglong2 *)(dst + tile0) + row_pair_index(hi4, lo4, s), make_ulonglong2(d2u(rr[0]), d2u(rr[1])));
             }
         } else {
             {
                 // all 16 words requested before the first is used: one memory latency per item, not sixteen
                 // (row-pair layout: 16 bytes per lane and load)
                 ulonglong2 raw[8];
+                if (GAL) {
 #pragma unroll
-                for (int s = 0; s < 8; s++) {
-                    if (GAL) raw[s] = galois_pair_load(src, (unsigned)tile0 + hi4 * 256u + 32u * s + 2u * lo4, G->g[it], A.logN);
-                    else raw[s] = ((const ulonglong2 *)(src + tile0))[row_pair_index(hi4, lo4, s)];
+                    for (int s = 0; s < 8; s++) raw[s] = galois_pair_load(src, (unsigned)tile0 + hi4 * 256u + 32u * s + 2u * lo4, G->g[it], A.logN);
+                } else {
+#pragma unroll
+                    for (int s = 0; s < 8; s++) raw[s] = stream_load<NT>((const ulonglong2 *)(src + tile0) + row_pair_index(hi4, lo4, s));
                 }
                 NTT_SCHED_FENCE();
 #pragma unroll
@@ -453,7 +497,7 @@ __device__ __forceinline__ void ntt_v2_rows(const NttV2Args &A, double *lds, int
             for (int e = 0; e < 16; e++) x[e] = grp[e * 17 + lo4];
             inv_stages<0, INV_ROW2, P51>(x, tw1, p, pinv, unused, unused);
 #pragma unroll
-            for (int e = 0; e < 16; e++) dst[tile0 + hi4 * 256 + lo4 + 16 * e] = mid_store(x[e]);
+            for (int e = 0; e < 16; e++) stream_store<NT>(&dst[tile0 + hi4 * 256 + lo4 + 16 * e], mid_store(x[e]));
         }
         ROW_GROUP_SYNC();
     }
@@ -461,6 +505,7 @@ __device__ __forceinline__ void ntt_v2_rows(const NttV2Args &A, double *lds, int
 
 // forward column pass of polynomials given as small signed integers (|coefficient| far below every modulus): same grid as
 // ntt_v2_kernel; the residues are never written out limb by limb
+template <bool NT>
 __global__ __launch_bounds__(V2_THREADS) void ntt_v2_fwd_cols_small_kernel(NttV2Args A) {
     __shared__ double lds[16 * V2_GS];
     unsigned item_unused, li;
@@ -468,11 +513,11 @@ __global__ __launch_bounds__(V2_THREADS) void ntt_v2_fwd_cols_small_kernel(NttV2
     if (t < 0) return;
     const bool p51 = is_p51(A.p51, t);
     switch (A.logN) {
-        case 12: if (p51) ntt_v2_cols<false, 0, true, true>(A, lds, t, li); else ntt_v2_cols<false, 0, false, true>(A, lds, t, li); break;
-        case 13: if (p51) ntt_v2_cols<false, 1, true, true>(A, lds, t, li); else ntt_v2_cols<false, 1, false, true>(A, lds, t, li); break;
-        case 14: if (p51) ntt_v2_cols<false, 2, true, true>(A, lds, t, li); else ntt_v2_cols<false, 2, false, true>(A, lds, t, li); break;
-        case 15: if (p51) ntt_v2_cols<false, 3, true, true>(A, lds, t, li); else ntt_v2_cols<false, 3, false, true>(A, lds, t, li); break;
-        default: if (p51) ntt_v2_cols<false, 4, true, true>(A, lds, t, li); else ntt_v2_cols<false, 4, false, true>(A, lds, t, li); break;
+        case 12: if (p51) ntt_v2_cols<false, 0, true, true, false, NT>(A, lds, t, li); else ntt_v2_cols<false, 0, false, true, false, NT>(A, lds, t, li); break;
+        case 13: if (p51) ntt_v2_cols<false, 1, true, true, false, NT>(A, lds, t, li); else ntt_v2_cols<false, 1, false, true, false, NT>(A, lds, t, li); break;
+        case 14: if (p51) ntt_v2_cols<false, 2, true, true, false, NT>(A, lds, t, li); else ntt_v2_cols<false, 2, false, true, false, NT>(A, lds, t, li); break;
+        case 15: if (p51) ntt_v2_cols<false, 3, true, true, false, NT>(A, lds, t, li); else ntt_v2_cols<false, 3, false, true, false, NT>(A, lds, t, li); break;
+        default: if (p51) ntt_v2_cols<false, 4, true, true, false, NT>(A, lds, t, li); else ntt_v2_cols<false, 4, false, true, false, NT>(A, lds, t, li); break;
     }
 }
 
@@ -482,12 +527,12 @@ __global__ __launch_bounds__(V2_THREADS) void ntt_v2_inv_rows_gal_kernel(NttV2Ar
     unsigned item_unused, li;
     const int t = resolve_limb(A.map, blockIdx.y, item_unused, li);
     if (t < 0) return;
-    if (is_p51(A.p51, t)) ntt_v2_rows<true, true, true>(A, lds, t, li, &G);
-    else ntt_v2_rows<true, false, true>(A, lds, t, li, &G);
+    if (is_p51(A.p51, t)) ntt_v2_rows<true, true, false, true>(A, lds, t, li, &G);
+    else ntt_v2_rows<true, false, false, true>(A, lds, t, li, &G);
 }
 
 // grid: x = tile (N/4096), y = limb slot within an item, z = chunk of items (column pass: N >= 2^14, smaller rings go through ntt_wg_kernel)
-template <bool INV, bool COLS, bool F64 = false>
+template <bool INV, bool COLS, bool NT, bool F64 = false>
 __global__ __launch_bounds__(V2_THREADS) void ntt_v2_kernel(NttV2Args A) {
     __shared__ double lds[16 * V2_GS];
     unsigned item_unused, li;
@@ -495,13 +540,13 @@ __global__ __launch_bounds__(V2_THREADS) void ntt_v2_kernel(NttV2Args A) {
     if (t < 0) return;
     const bool p51 = is_p51(A.p51, t);
     if (!COLS) {
-        if (p51) ntt_v2_rows<INV, true>(A, lds, t, li);
-        else ntt_v2_rows<INV, false>(A, lds, t, li);
+        if (p51) ntt_v2_rows<INV, true, NT>(A, lds, t, li);
+        else ntt_v2_rows<INV, false, NT>(A, lds, t, li);
     } else {
         switch (A.logN) {
-            case 14: if (p51) ntt_v2_cols<INV, 2, true, false, F64>(A, lds, t, li); else ntt_v2_cols<INV, 2, false, false, F64>(A, lds, t, li); break;
-            case 15: if (p51) ntt_v2_cols<INV, 3, true, false, F64>(A, lds, t, li); else ntt_v2_cols<INV, 3, false, false, F64>(A, lds, t, li); break;
-            case 16: if (p51) ntt_v2_cols<INV, 4, true, false, F64>(A, lds, t, li); else ntt_v2_cols<INV, 4, false, false, F64>(A, lds, t, li); break;
+            case 14: if (p51) ntt_v2_cols<INV, 2, true, false, F64, NT>(A, lds, t, li); else ntt_v2_cols<INV, 2, false, false, F64, NT>(A, lds, t, li); break;
+            case 15: if (p51) ntt_v2_cols<INV, 3, true, false, F64, NT>(A, lds, t, li); else ntt_v2_cols<INV, 3, false, false, F64, NT>(A, lds, t, li); break;
+            case 16: if (p51) ntt_v2_cols<INV, 4, true, false, F64, NT>(A, lds, t, li); else ntt_v2_cols<INV, 4, false, false, F64, NT>(A, lds, t, li); break;
         }
     }
 }

@@ -214,7 +214,7 @@ __device__ __forceinline__ void wg_inv_limb(double (&x)[16], const u64d *src, co
 }
 
 // SRC (inverse only): see wg_inv_limb
-template <bool INV, int LOGN, bool P51, bool F64, int SRC = 0>
+template <bool INV, int LOGN, bool P51, bool F64, bool NT, int SRC = 0>
 __device__ __forceinline__ void ntt_wg_body(const NttV2Args &A, double *lds, int t, unsigned li, const GaloisTab *gal = nullptr,
                                             const TensorSrc *ten = nullptr) {
     BODY_TAG(P51);
@@ -245,7 +245,7 @@ __device__ __forceinline__ void ntt_wg_body(const NttV2Args &A, double *lds, int
         if (!INV) {
             u64d raw[16];
 #pragma unroll
-            for (int e = 0; e < 16; e++) raw[e] = scalar_base(src + Geo::G * 256u * e)[voff];
+            for (int e = 0; e < 16; e++) raw[e] = stream_load<NT>(scalar_base(src + Geo::G * 256u * e) + voff);
             NTT_SCHED_FENCE();
 #pragma unroll
             for (int e = 0; e < 16; e++) x[e] = u2d(raw[e]);
@@ -254,14 +254,14 @@ __device__ __forceinline__ void ntt_wg_body(const NttV2Args &A, double *lds, int
 #pragma unroll
             for (int s = 0; s < 8; s++) {
                 const double *rr = grp + row_pair_lds(lo4, s);
-                ((ulonglong2 *)dst + 16 * s)[pr] = make_ulonglong2(d2u(canon_small(rr[0], p)), d2u(canon_small(rr[1], p)));
+                stream_store<NT>((ulonglong2 *)dst + 16 * s + pr, make_ulonglong2(d2u(canon_small(rr[0], p)), d2u(canon_small(rr[1], p))));
             }
         } else {
             wg_inv_limb<LOGN, P51, SRC>(x, src, tw, lds, p, pinv, ninv, wlast, li, it, gal, ten);
 #pragma unroll
             for (int e = 0; e < 16; e++) {
                 const double v = canon(x[e] + cadd, p, pinv);
-                scalar_base(dst + Geo::G * 256u * e)[voff] = F64 ? (u64d)__double_as_longlong(v) : d2u(v);
+                stream_store<NT>(scalar_base(dst + Geo::G * 256u * e) + voff, F64 ? (u64d)__double_as_longlong(v) : d2u(v));
             }
         }
         __syncthreads();  // the matrix is free for the next item
@@ -269,16 +269,16 @@ __device__ __forceinline__ void ntt_wg_body(const NttV2Args &A, double *lds, int
 }
 
 // grid: x = limb slot within an item, y = chunk of items; block = N/16 threads
-template <bool INV, int LOGN, bool F64 = false>
+template <bool INV, int LOGN, bool NT, bool F64 = false>
 __global__ __launch_bounds__((1 << LOGN) / 16) void ntt_wg_kernel(NttV2Args A) {
     __shared__ double lds[((1 << LOGN) >> 8) * V2_GS];
     unsigned item_unused, li;
     const int t = resolve_limb(A.map, blockIdx.x, item_unused, li);
     if (t < 0) return;
     if (is_p51(A.p51, t))
-        ntt_wg_body<INV, LOGN, true, F64>(A, lds, t, li);
+        ntt_wg_body<INV, LOGN, true, F64, NT>(A, lds, t, li);
     else
-        ntt_wg_body<INV, LOGN, false, F64>(A, lds, t, li);
+        ntt_wg_body<INV, LOGN, false, F64, NT>(A, lds, t, li);
 }
 
 // conversion inputs of a key switch (doubles), same grid: a rotation's polynomial, a product's third tensor component
@@ -288,8 +288,8 @@ __global__ __launch_bounds__((1 << LOGN) / 16) void ntt_wg_inv_gal_kernel(NttV2A
     unsigned item_unused, li;
     const int t = resolve_limb(A.map, blockIdx.x, item_unused, li);
     if (t < 0) return;
-    if (is_p51(A.p51, t)) ntt_wg_body<true, LOGN, true, true, 1>(A, lds, t, li, &G);
-    else ntt_wg_body<true, LOGN, false, true, 1>(A, lds, t, li, &G);
+    if (is_p51(A.p51, t)) ntt_wg_body<true, LOGN, true, true, false, 1>(A, lds, t, li, &G);
+    else ntt_wg_body<true, LOGN, false, true, false, 1>(A, lds, t, li, &G);
 }
 template <int LOGN>
 __global__ __launch_bounds__((1 << LOGN) / 16) void tensor_wg_kernel(NttV2Args A, TensorSrc T) {
@@ -297,6 +297,6 @@ __global__ __launch_bounds__((1 << LOGN) / 16) void tensor_wg_kernel(NttV2Args A
     unsigned item_unused, li;
     const int t = resolve_limb(A.map, blockIdx.x, item_unused, li);
     if (t < 0) return;
-    if (is_p51(A.p51, t)) ntt_wg_body<true, LOGN, true, true, 2>(A, lds, t, li, nullptr, &T);
-    else ntt_wg_body<true, LOGN, false, true, 2>(A, lds, t, li, nullptr, &T);
+    if (is_p51(A.p51, t)) ntt_wg_body<true, LOGN, true, true, false, 2>(A, lds, t, li, nullptr, &T);
+    else ntt_wg_body<true, LOGN, false, true, false, 2>(A, lds, t, li, nullptr, &T);
 }

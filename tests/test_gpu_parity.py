@@ -776,3 +776,46 @@ def test_tail_route(be, batch, level, on_chip):
     announce("tail route batch %d level %d" % (batch, level))
     names = ["conv_final_kernel"], ["modup_cols_kernel<2, 2, 3>"]
     pc.case_product_route(be, (14, 5, 50, 1, 51, 1), seed=366, batch=batch, level=level, expect=names[not on_chip], absent=names[on_chip], sample=[0, batch - 1])
+
+
+@pytest.mark.parametrize("logN,n_q,batch", [(12, 3, 2800), (13, 3, 1401), (14, 3, 701), (15, 3, 350), (16, 3, 171)])
+def test_streamed_transforms_match_cached_ones(logN, n_q, batch):
+    """a transform of more than 256 MB (operands and results past the caches) and the same items a few at a time"""
+    import torch
+
+    announce("streamed transforms 2^%d" % logN)
+    ctx = ckksmi.Context(logN, n_q, 50, 0, 51, 1, device=0)
+    gen = torch.Generator(device="cuda:0").manual_seed(logN)
+    x = torch.randint(0, min(ctx.q), (batch, n_q, ctx.N), dtype=torch.int64, device="cuda:0", generator=gen)
+    assert x.nbytes > 256 << 20
+    for f in (ctx.ntt, ctx.intt):
+        whole, parts = x.clone(), x.clone()
+        f(whole, range(n_q), batch)
+        step = batch // 7 + 1
+        for b in range(0, batch, step):
+            f(parts[b:b + step], range(n_q), min(step, batch - b))
+        assert torch.equal(whole, parts)
+    ctx.close()
+
+
+@pytest.mark.parametrize("logN,n_q,k,alpha,batch", [(14, 4, 1, 1, 97), (14, 4, 3, 3, 61), (16, 4, 3, 3, 23)])
+def test_streamed_products_match_cached_ones(logN, n_q, k, alpha, batch):
+    """a batch whose launches stream their results, and its items one at a time"""
+    import torch
+
+    announce("streamed products 2^%d" % logN)
+    ctx = ckksmi.Context(logN, n_q, 50, k, 51, alpha, device=0)
+    gen = torch.Generator(device="cuda:0").manual_seed(logN + k)
+    low = min(ctx.moduli)
+
+    def words(*shape):
+        return torch.randint(0, low, shape, dtype=torch.int64, device="cuda:0", generator=gen)
+
+    a, b, key = words(batch, 2, n_q, ctx.N), words(batch, 2, n_q, ctx.N), words(ctx.beta_top, 2, ctx.T, ctx.N)
+    out, one = words(batch, 2, n_q - 1, ctx.N), words(1, 2, n_q - 1, ctx.N)
+    ws = words(ctx.workspace_bytes(ckksmi.OP_HMUL_RELIN_RESCALE, n_q, batch) // 8 + 2)
+    ctx.hmul_relin_rescale(a, b, key, out, n_q, batch, ws)
+    for i in range(0, batch, 11):
+        ctx.hmul_relin_rescale(a[i:i + 1], b[i:i + 1], key, one, n_q, 1, ws)
+        assert torch.equal(out[i:i + 1], one)
+    ctx.close()
