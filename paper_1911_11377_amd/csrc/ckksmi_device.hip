@@ -20,6 +20,7 @@
 #include "ks_inner_wg.h"
 #include "encode_device.h"
 #include "mac_mfma.h"
+#include "mac_rns.h"
 
 // Launch `kern`; when profiling is on, bracket it with two events on the same stream and
 // remember them under kernel class `kid` together with `units` of algorithmic work.
@@ -1636,6 +1637,9 @@ struct MacShape {
     int quad;       // its last step covers at most 16 taps, as a quad step
     int Kb, Mg;     // steps (64 taps, or the quad step), 32-channel groups
     size_t afrag_bytes, taps_bytes, off_bytes, tapoff_bytes, wsum_bytes, mfma_bytes;
+    bool rns;       // many taps and channels: the residue kernel
+    int rns_Mg;     // its channel groups
+    size_t rns_afrag_bytes, rns_bytes;
 };
 MacShape mac_shape(const ckksmi_ctx *c, int C, int O, int kh, int kw, int stride, int out_rows, int Wo, int level) {
     MacShape s;
@@ -1666,6 +1670,13 @@ MacShape mac_shape(const ckksmi_ctx *c, int C, int O, int kh, int kw, int stride
     s.mfma_bytes = s.afrag_bytes + s.taps_bytes + s.off_bytes + s.tapoff_bytes + s.wsum_bytes;
     // below 8 output channels most of a 32-channel group would multiply zeros: the vector kernel is faster there
     s.mfma_ok = c->N >= MM_WORDS && O >= 8 && K <= MM_KMAX - 63;
+    // Residues cost per group of 128 channels what digits cost per 3.3 groups of 32 (784 to 3136 taps: 112 channels 0.32 against 0.36 ms,
+    // 160: 0.58 / 0.45, 192: 0.59 / 0.54, 200: 2.68 / 2.93, 256: 6.6 / 8.5 - 8.9); below 7 steps their longer prologue and last
+    // part outweigh it (300 taps: 0.34 / 0.32, 448: 1.15 / 1.23).
+    s.rns = s.mfma_ok && s.Kb >= 7 && 2 * s.Mg >= 7 * ((O + MR_CH - 1) / MR_CH);
+    s.rns_Mg = s.rns ? (O + MR_CH - 1) / MR_CH : 0;
+    s.rns_afrag_bytes = (size_t)level * s.Kb * s.rns_Mg * MR_NM * MR_AFRAG * 16;
+    s.rns_bytes = s.rns_afrag_bytes + s.taps_bytes + (size_t)level * MR_CRT * sizeof(double);
     return s;
 }
 }  // namespace
@@ -1690,7 +1701,9 @@ extern "C" int ckksmi_conv2d_mac_rows(ckksmi_ctx *c, const uint64_t *in, const i
     const size_t n_weights = (size_t)O * C * kh * kw;
     Guard g(c);
     MacShape ms = mac_shape(c, C, O, kh, kw, stride, out_rows, Wo, level);
-    if (ms.mfma_ok && ws_bytes >= ms.mfma_bytes && (size_t)C * in_rows * W < MM_TAP_DELTA_MAX && kh <= MM_TAP_KMAX && kw <= MM_TAP_KMAX) {
+    // ... and the residue kernel has one large workgroup per compute unit: two rounds of them at least (512 of the 8192 target)
+    if (ms.rns && (ws_bytes < ms.rns_bytes || (size_t)out_rows * Wo * ms.rns_Mg * (c->N / MR_WORDS) * 2 * level < (size_t)c->ntt_target_wgs / 16)) ms.rns = false;
+    if (ms.mfma_ok && ws_bytes >= (ms.rns ? ms.rns_bytes : ms.mfma_bytes) && (size_t)C * in_rows * W < MM_TAP_DELTA_MAX && kh <= MM_TAP_KMAX && kw <= MM_TAP_KMAX) {
         const unsigned positions = (unsigned)(out_rows * Wo);
         // resident kernel: each workgroup takes `run` positions of a 64-word block, nrun workgroups share the block;
         // strip kernel: `run` tiles (four positions of a row) of a 16-word block
@@ -1703,12 +1716,29 @@ extern "C" int ckksmi_conv2d_mac_rows(ckksmi_ctx *c, const uint64_t *in, const i
         const unsigned want_nrun = (unsigned)std::min<size_t>(units_per_block, (target + blocks - 1) / blocks);
         const unsigned run = std::max(1u, std::min(ms.strip ? 64u : 8u, units_per_block / std::max(1u, want_nrun)));
         const unsigned nrun = (units_per_block + run - 1) / run;
-        const size_t real = ms.strip      ? (size_t)nrun * (c->N / 16) * 2 * level
+        const size_t real = ms.rns       ? (size_t)positions * ms.rns_Mg * (c->N / MR_WORDS) * 2 * level
+                            : ms.strip      ? (size_t)nrun * (c->N / 16) * 2 * level
                             : ms.resident ? (size_t)nrun * (c->N / MM_WORDS) * 2 * level
                                           : (size_t)positions * ms.Mg * (c->N / MM_WORDS) * 2 * level;
         const size_t xdim = (real + 7) / 8 * 8;
         if (xdim > 0x7fffffffu) return CKKSMI_EUNSUPPORTED;
         char *wp = (char *)ws;  // every part is a multiple of 16 bytes
+        const double units = (double)O * out_rows * Wo * 2 * level;
+        MacMfmaArgs A;
+        A.in = (const u64d *)in; A.out = (u64d *)out; A.modc = c->d_mod; A.pow24 = c->d_pow24;
+        A.logN = c->logN; A.level = level; A.C = C; A.H = H; A.W = W; A.O = O; A.kh = kh; A.kw = kw; A.stride = stride; A.pad = pad; A.Wo = Wo;
+        A.in_row0 = in_row0; A.in_rows = in_rows; A.out_row0 = out_row0; A.out_rows = out_rows; A.Kb = ms.Kb; A.Mg = ms.Mg; A.quad = ms.quad;
+        A.positions = positions; A.nrun = nrun; A.run = run; A.TY = ms.TY; A.TX = ms.TX; A.SR = ms.SR; A.SC = ms.SC; A.spr = spr; A.total_wgs = xdim; A.real_wgs = real;
+        if (ms.rns) {
+            v4i *const rfrag = (v4i *)wp; wp += ms.rns_afrag_bytes;
+            TapEnt *const rtaps = (TapEnt *)wp; wp += ms.taps_bytes;
+            const size_t prep = std::max({ms.rns_afrag_bytes / 16 / MR_NM, (size_t)ms.Kb * 64, (size_t)level});
+            KL(c, CKKSMI_K_MACPREP_MFMA, 1, mac_prepare_rns_kernel, dim3(ew_blocks(prep)), dim3(EW_THREADS), S(stream), (const long long *)w, rfrag, rtaps, (double *)wp,
+               c->d_mod, level, O, C, kh, kw, in_rows, W, ms.Kb, ms.rns_Mg);
+            A.afrag = rfrag; A.taps = rtaps; A.crt = (const double *)wp; A.Mg = ms.rns_Mg;
+            KL(c, CKKSMI_K_MAC_MFMA, units, conv_mac_rns_kernel, dim3((unsigned)xdim), dim3(MR_THREADS), S(stream), A);
+            return g.rc();
+        }
         v4i *afrag = (v4i *)wp; wp += ms.afrag_bytes;
         TapEnt *taps = (TapEnt *)wp; wp += ms.taps_bytes;
         unsigned long long *off64 = (unsigned long long *)wp; wp += ms.off_bytes;
@@ -1719,13 +1749,7 @@ extern "C" int ckksmi_conv2d_mac_rows(ckksmi_ctx *c, const uint64_t *in, const i
            off64, tapoff, ms.SR, ms.SC, c->d_mod, level, c->logN, O, C, kh, kw, in_rows, W, ms.Kb, ms.Mg, ms.quad);
         KL(c, CKKSMI_K_MACWSUM_MFMA, (double)ms.Mg * MM_CH * level, mac_wsum_kernel, dim3((unsigned)(ms.Mg * MM_CH), (unsigned)level), dim3(EW_THREADS), S(stream), (const long long *)w, wsum, c->d_mod,
            O, C * kh * kw);
-        MacMfmaArgs A;
-        A.in = (const u64d *)in; A.out = (u64d *)out; A.afrag = afrag; A.taps = taps; A.off64 = off64; A.tapoff = tapoff; A.wsum = wsum; A.modc = c->d_mod;
-        A.pow24 = c->d_pow24;
-        A.logN = c->logN; A.level = level; A.C = C; A.H = H; A.W = W; A.O = O; A.kh = kh; A.kw = kw; A.stride = stride; A.pad = pad; A.Wo = Wo;
-        A.in_row0 = in_row0; A.in_rows = in_rows; A.out_row0 = out_row0; A.out_rows = out_rows; A.Kb = ms.Kb; A.Mg = ms.Mg; A.quad = ms.quad;
-        A.positions = positions; A.nrun = nrun; A.run = run; A.TY = ms.TY; A.TX = ms.TX; A.SR = ms.SR; A.SC = ms.SC; A.spr = spr; A.total_wgs = xdim; A.real_wgs = real;
-        const double units = (double)O * out_rows * Wo * 2 * level;
+        A.afrag = afrag; A.taps = taps; A.off64 = off64; A.tapoff = tapoff; A.wsum = wsum;
         if (ms.strip) {
             const dim3 grid((unsigned)xdim), block(256);
 #define MAC_STRIP(KB, Q)                                                                                                            \
@@ -1777,7 +1801,7 @@ extern "C" int ckksmi_conv2d_workspace_bytes(const ckksmi_ctx *c, int C, int O, 
     if (level < 1 || level > c->n_q) return CKKSMI_ELEVEL;
     const MacShape ms = mac_shape(c, C, O, kh, kw, 1, 1, 1, level);
     const size_t valu = (size_t)O * C * kh * kw * level * sizeof(WMul);
-    *bytes = ms.mfma_ok ? std::max(valu, ms.mfma_bytes) : valu;
+    *bytes = ms.mfma_ok ? std::max({valu, ms.mfma_bytes, ms.rns_bytes}) : valu;
     return CKKSMI_OK;
 }
 

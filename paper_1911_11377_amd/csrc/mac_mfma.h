@@ -25,6 +25,8 @@
 //                diagonal d are covered by fragments i0 = min(6, d), min(6, d) - 4, ... down to max(0, d - 6); pairs a
 //                fragment reaches beyond the diagonal's ends have a zero digit on one side.  18 instructions instead of 49.
 //
+// Layers with many taps and channels use residues modulo small numbers instead of digits (mac_rns.h).
+//
 // Three kernels.  All: workgroup = 4 waves, a wave works on 16 consecutive words, 32 output channels per workgroup, the A
 // fragments (weight digits, 14 KB per step) are shared through LDS; per step a lane takes the 16 words of its taps,
 // flips the top bits, transposes the bytes into the 7 B fragments (v_perm_b32) and issues the matrix instructions.
@@ -68,10 +70,13 @@ static inline unsigned emu_perm_b32(unsigned hi, unsigned lo, unsigned sel) {
 #define MM_MFMA(a, b, c) emu_mfma_i32_16x16x64_i8(a, b, c)
 #define MM_PERM(hi, lo, sel) emu_perm_b32(hi, lo, sel)
 #define MM_UNIFORM(v) (v)
+// matrix instructions that this wave leaves out and others of the block issue (the emulated exchange is a barrier)
+#define MM_MFMA_ABSENT(n) do { for (int a_ = 0; a_ < (n); a_++) (void)emu_mfma_i32_16x16x64_i8(v4i{}, v4i{}, v4i{}); } while (0)
 #else
 typedef int v4i __attribute__((ext_vector_type(4)));
 #define MM_MFMA(a, b, c) __builtin_amdgcn_mfma_i32_16x16x64_i8(a, b, c, 0, 0, 0)
 #define MM_PERM(hi, lo, sel) __builtin_amdgcn_perm(hi, lo, sel)
+#define MM_MFMA_ABSENT(n) (void)0
 #define MM_UNIFORM(v) __builtin_amdgcn_readfirstlane(v)  // the same in every lane of the wave: keep it in a scalar register
 #endif
 
@@ -92,6 +97,7 @@ struct MacMfmaArgs {
     const TapEnt *taps;   // [2][Kb*64]: packed entries, then premultiplied limb-row offsets
     const unsigned long long *off64;  // [Kb*64] premultiplied byte offsets
     const double *wsum;   // [level][Mg*MM_CH]  B * sum_tap w mod p, canonical
+    const double *crt;    // [level][MR_CRT]  residue kernel (mac_rns.h): constants of the recombination
     const unsigned *tapoff;  // [Kb*64] strip kernel: byte offset of the tap's line in the strip, ((c*SR + u)*SC + v)*128
     const ModConst *modc;
     const WMul *pow24;    // 2^24 mod p per modulus
@@ -122,6 +128,19 @@ __device__ __forceinline__ long long mm_balanced(long long w, long long q, doubl
     return r;
 }
 
+// Slot `slot` of both 32-bit tap tables (the second one `slots` entries on) for tap k
+__device__ __forceinline__ unsigned mm_tap_entry(int slot, int k, int K, TapEnt *taps, size_t slots, int level, int kh, int kw, int in_rows, int W) {
+    TapEnt e = 31u << 22;
+    if (k < K) {
+        const unsigned c = k / (kh * kw), u = (k / kw) % kh, v = k % kw;
+        e = ((c * in_rows + u) * W + v) | (u << 22) | (v << 27);
+    }
+    taps[slot] = e;
+    const unsigned rows = k < K ? (e & (MM_TAP_DELTA_MAX - 1)) * (unsigned)(2 * level) : 0u;
+    taps[slots + slot] = rows;
+    return rows;
+}
+
 // A fragments (one thread per 16 taps of one channel: all seven digit chunks, so that every weight is reduced once per modulus)
 // and tap-table slots.  The weights of a 3136 -> 256 layer at 8 primes take 0.06 ms; one thread per digit chunk, with an
 // integer division per weight and the sums below made by a thread each, took 2.16 ms.
@@ -133,14 +152,7 @@ __global__ __launch_bounds__(EW_THREADS) void mac_prepare_mfma_kernel(const long
     if (idx < (size_t)Kb * 64) {
         const int slot = (int)idx;
         const int k = mm_slot_tap(slot / 64, (slot % 64) / 16, slot % 16, Kb, quad);
-        TapEnt e = 31u << 22;
-        if (k < K) {
-            const unsigned c = k / (kh * kw), u = (k / kw) % kh, v = k % kw;
-            e = ((c * in_rows + u) * W + v) | (u << 22) | (v << 27);
-        }
-        taps[slot] = e;
-        const unsigned rows = k < K ? (e & (MM_TAP_DELTA_MAX - 1)) * (unsigned)(2 * level) : 0u;
-        taps[(size_t)Kb * 64 + slot] = rows;
+        const unsigned rows = mm_tap_entry(slot, k, K, taps, (size_t)Kb * 64, level, kh, kw, in_rows, W);
         off64[slot] = ((unsigned long long)rows << logN) * 8ull;
         tapoff[slot] = k < K ? (unsigned)((((k / (kh * kw)) * SR + (k / kw) % kh) * SC + k % kw) * 128) : 0u;
     }

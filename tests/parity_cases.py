@@ -955,6 +955,37 @@ def case_conv(be, shape, seed, Cin, H, W, Oc, kh, stride, pad, level=None, rows_
     ctx.close()
 
 
+def case_conv_channels(be, shape, seed, Cin, H, W, Oc, kh, stride, pad, residues, rows=None, extreme=False):
+    """many taps: residues or digits, told apart by the digit kernels' sums of weights; `rows`: one strip of output rows;
+    `extreme`: every word p - 1 and every weight (p - 1) / 2, the largest sum that the residues have to tell apart"""
+    M = make_material(shape, seed)
+    O = M.O
+    ctx = be.context(*shape)
+    level = O.n_q
+    x = wl.uniform_limbs(O.q[:level], O.N, seed, "x", lead=(Cin, H, W, 2))
+    wi = np.rint(wl.weights_float((Oc, Cin, kh, kh), seed) * O.q[level - 1]).astype(np.int64)
+    wi.flat[0] = -(1 << 62) + 7
+    if extreme:
+        for i in range(level):
+            x[..., i, :] = O.q[i] - 1
+        wi[...] = (O.q[0] - 1) // 2
+        wi[1] *= -1
+    Ho, Wo = (H + 2 * pad - kh) // stride + 1, (W + 2 * pad - kh) // stride + 1
+    want = O.conv2d_mac(x, wi, stride, pad, level)
+    r0, r1 = rows or (0, Ho)
+    i0, i1 = max(0, r0 * stride - pad), min(H, (r1 - 1) * stride - pad + kh)
+    out, ws = be.empty(Oc, r1 - r0, Wo, 2, level, O.N), be.ws(ctx.conv2d_workspace_bytes(Cin, Oc, kh, kh, level))
+    ctx.profile_enable(True)
+    ctx.conv2d_mac_rows(be.to_dev(np.ascontiguousarray(x[:, i0:i1])), be.to_dev(wi, np.int64), Cin, H, W, Oc, kh, kh, stride, pad, i0, i1 - i0, r0, r1 - r0, out,
+                        level, ws, stream=be.stream)
+    got = be.to_host(out).reshape(Oc, r1 - r0, Wo, 2, level, O.N)
+    ran = ctx.profile_read()
+    ctx.profile_enable(False)
+    assert "conv_mac_mfma_kernel" in ran and ("mac_wsum_kernel" not in ran) == residues, list(ran)
+    assert np.array_equal(got, want[:, r0:r1])
+    ctx.close()
+
+
 def case_cnn(be, shape, seed, topology, workers=1):
     """conv - square - conv - square - conv - pool - fc - square - fc on per-pixel ciphertexts, every activation
     resident, against the oracle's layer-by-layer network; plus the first conv layer again in strips of rows"""

@@ -90,6 +90,17 @@ def test_emulated_conv_matrix_cores(be):
         pc.case_conv(be, (6, 1, 50, 0, 51, 1), seed=122, Cin=7, H=4, W=16, Oc=9, kh=3, stride=3, pad=1, fc_check=False)
 
 
+def test_emulated_conv_residues(be):
+    """the matrix-core kernel on residues: 449 taps end in a step of one tap, 385 in seven steps; ragged channel groups, padding with a strip
+    of rows, 51-bit primes at the largest sum; its rule's other side (as many taps, too few channels) stays on digits"""
+    with be.tuned(8):
+        pc.case_conv_channels(be, (6, 2, 51, 0, 52, 1), 210, 449, 1, 1, 97, 1, 1, 0, residues=True)
+        pc.case_conv_channels(be, (6, 1, 50, 0, 51, 1), 211, 43, 3, 3, 98, 3, 2, 1, residues=True, rows=(1, 2))
+        pc.case_conv_channels(be, (6, 1, 51, 0, 52, 1), 212, 385, 1, 1, 193, 1, 1, 0, residues=True, extreme=True)
+        pc.case_conv_channels(be, (6, 1, 50, 0, 51, 1), 213, 449, 1, 1, 96, 1, 1, 0, residues=False)
+        pc.case_conv_channels(be, (6, 1, 50, 0, 51, 1), 214, 384, 1, 1, 97, 1, 1, 0, residues=False)
+
+
 def test_emulated_pooling(be):
     """(whole networks: the Table-1-like one below; the square-activation network runs on the GPU)"""
     pc.case_pool(be, TINY, seed=112, Cin=2, H=5, W=4, k=2)

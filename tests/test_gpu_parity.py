@@ -107,6 +107,18 @@ def test_conv_matrix_cores_shapes(be):
         pc.case_conv(be, (7, 2, 50, 0, 51, 1), seed=319, Cin=29, H=3, W=3, Oc=8, kh=3, stride=1, pad=1)    # 261 taps: streaming kernel
 
 
+def test_conv_residues(be):
+    """many taps and channels: the matrix-core kernel on residues (last steps of one tap, ragged channel groups, windows on padding, 51-bit primes
+    at the largest sum of the most taps, a strip of rows), and the digit kernels where a launch is too small for it"""
+    announce("conv on residues")
+    pc.case_conv_channels(be, (10, 3, 50, 0, 51, 1), 330, 449, 1, 2, 97, 1, 1, 0, residues=False)    # 384 workgroups
+    with be.tuned(8):
+        pc.case_conv_channels(be, (10, 3, 50, 0, 51, 1), 330, 449, 1, 2, 97, 1, 1, 0, residues=True)
+        pc.case_conv_channels(be, (8, 2, 40, 0, 41, 1), 331, 43, 5, 4, 200, 3, 1, 1, residues=True, rows=(1, 4))
+        announce("conv on residues, 16321 taps")
+        pc.case_conv_channels(be, (6, 1, 51, 0, 52, 1), 332, 16321, 1, 1, 128, 1, 1, 0, residues=True, extreme=True)
+
+
 def test_conv_at_layer_shape_slice(be):
     """N=2^15, 16x50-bit limbs, 3 input channels, 5x5 stride 2: one output position, three filters"""
     announce("conv N=2^15 level 16 slice")
