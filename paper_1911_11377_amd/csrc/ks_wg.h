@@ -194,7 +194,7 @@ __device__ __forceinline__ void conv_final_body(const ConvFinalArgs &A, double *
 }
 
 // grid: x = rows_x * 2^S * rows_g * nc * (row groups), see conv_final_place; block = M/16 threads
-template <int LOGM, int S, int NSRC, int FIN, bool NTS>
+template <int LOGM, int S, int NSRC, int FIN, bool NTS = false>
 __global__ __launch_bounds__((1 << LOGM) / 16, 4) void conv_final_kernel(ConvFinalArgs A) {
     __shared__ double lds[((1 << LOGM) >> 8) * V2_GS];
     unsigned row, blk;
@@ -216,7 +216,7 @@ __global__ __launch_bounds__((1 << LOGM) / 16, 4) void conv_final_scalar_kernel(
 }
 
 // rotations from a shared ModUp
-template <int LOGM, int S, int NSRC, bool NTS>
+template <int LOGM, int S, int NSRC, bool NTS = false>
 __global__ __launch_bounds__((1 << LOGM) / 16, 4) void conv_final_gal_kernel(ConvFinalArgs A, RowsFinalGal G) {
     __shared__ double lds[((1 << LOGM) >> 8) * V2_GS];
     unsigned row, blk;

@@ -269,7 +269,7 @@ __device__ __forceinline__ void ntt_wg_body(const NttV2Args &A, double *lds, int
 }
 
 // grid: x = limb slot within an item, y = chunk of items; block = N/16 threads
-template <bool INV, int LOGN, bool NT, bool F64 = false>
+template <bool INV, int LOGN, bool NT = false, bool F64 = false>
 __global__ __launch_bounds__((1 << LOGN) / 16) void ntt_wg_kernel(NttV2Args A) {
     __shared__ double lds[((1 << LOGN) >> 8) * V2_GS];
     unsigned item_unused, li;
