@@ -166,8 +166,7 @@ __device__ __forceinline__ void conv_mac_rns_body(const MacMfmaArgs &A, v4i *fra
     const unsigned twoL = 2u * (unsigned)A.level;
 
     // This thread's word and taps.  16 lanes take the words of one 16-word tile at four taps (128 bytes per tap), the next 16 lanes the
-    // same words in the next k-group: a half wave then writes its residues to 32 neighbouring chunks (512 bytes).  With 32 words
-    // of one k-group per half wave, in two pieces 1 KB apart, the 3136 -> 256 layer took 7.3 ms.
+    // same words in the next k-group: a half wave writes its residues to 32 neighbouring chunks (512 bytes).
     const unsigned cw = wave % 2 * 16 + lane % 16, kg = wave / 2 % 2 * 2 + lane / 16 % 2, quad = wave / 4 * 2 + lane / 32;
     const u64d *inw = A.in + (size_t)lc * N + wb * MR_WORDS + cw;
     const TapEnt *tp = A.taps + (INTERIOR ? (size_t)A.Kb * 64 : 0) + 16 * kg + 4 * quad;
