@@ -97,6 +97,7 @@ __device__ __forceinline__ void tensor_rows_body(const TensorRowsArgs &A, double
 #pragma unroll
     for (int e = 0; e < 16; e++) x[e] = grp[lo4 * 17 + e];
     inv_stages<0, INV_ROW1, P51>(x, tw2, p, pinv, unused, unused);
+    INV_JOIN(P51, INV_ROW1, INV_ROW2);
 #pragma unroll
     for (int e = 0; e < 16; e++) grp[lo4 * 17 + e] = x[e];
     ROW_GROUP_SYNC();
@@ -181,7 +182,9 @@ __device__ __forceinline__ void inv_cols_in_regs(double (&x)[16], const double *
                     tw2[(1 << s) - 1 + b] = 0.0;
                 }
             }
+        INV_JOIN(P51, INV_ROW2, INV_COL2);
         inv_stages<Geo::S0, INV_COL2, P51>(x, tw2, p, pinv, unused, unused);
+        INV_JOIN(P51, INV_COL2, INV_COL1);
     }
 #pragma unroll
     for (int i = 0; i < 16; i++) lds[geo.l2(i)] = x[i];

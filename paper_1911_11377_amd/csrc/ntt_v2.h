@@ -263,16 +263,27 @@ __device__ __forceinline__ void fwd_round(double (&x)[16], const double (&tw)[15
     fwd_stages<0, MASK>(x, tw, p, pinv);
 }
 
-// the same stages undone, 3 down to S0 (spans 1,2,..), with the reductions of inv_plan; B: where the round stands (the bounds
-// of its words, InvRound); FINAL folds 1/N into the very last stage (s = 0) of the whole transform
-enum InvRound { INV_ROW1, INV_ROW2, INV_COL2, INV_COL1 };
+// the same stages undone, 3 down to S0 (spans 1,2,..), with the reductions of inv_plan; B: where the round stands, which gives the
+// bounds of its words; FINAL folds 1/N into the very last stage (s = 0) of the whole transform.  The rounds follow one another as
+// they are listed.  In a workgroup that holds all 2^12 words of a ring INV_COL2 is left out (the column pass has one round), and
+// the row pass ends with INV_ROW2_12 instead, within what INV_COL1 takes.
+enum InvRound { INV_ROW1, INV_ROW2, INV_COL2, INV_COL1, INV_ROW2_12 };
+template <bool P51>
+constexpr double inv_entry(InvRound B) {
+    typedef LazyRange<P51> R;
+    return B == INV_ROW1 ? R::INV0 : B == INV_COL2 ? R::MIDI : R::INV1;
+}
+template <bool P51>
+constexpr double inv_exit(InvRound B) {
+    typedef LazyRange<P51> R;
+    return B == INV_ROW2 ? R::MIDI : B == INV_COL1 ? R::LIM : R::INV1;
+}
+// stands where the words of round A become those of round B
+#define INV_JOIN(P51, A, B) static_assert(inv_exit<P51>(A) <= inv_entry<P51>(B), "the second round takes less than the first one leaves")
 template <int S0, InvRound B, bool P51>
 __device__ __forceinline__ void inv_stages(double (&x)[16], const double (&tw)[15], double p, double pinv, WMul ninv, WMul wlast) {
-    typedef LazyRange<P51> R;
     constexpr bool FINAL = B == INV_COL1;
-    constexpr double ENTRY = B == INV_ROW1 ? R::INV0 : B == INV_COL2 ? R::MIDI : R::INV1;
-    constexpr double EXIT = B == INV_ROW2 ? R::MIDI : FINAL ? R::LIM : R::INV1;
-    constexpr InvPlan PL = inv_plan(P51, ENTRY, S0, EXIT, FINAL);
+    constexpr InvPlan PL = inv_plan(P51, inv_entry<P51>(B), S0, inv_exit<P51>(B), FINAL);
 #pragma unroll
     for (int k = 0; k < 4 - S0; k++) {
         const int s = 3 - k, span = 8 >> s;
@@ -410,7 +421,9 @@ __device__ __forceinline__ void ntt_v2_cols(const NttV2Args &A, double *lds, int
         } else {
 #pragma unroll
             for (int i = 0; i < 16; i++) x[i] = mid_load(stream_load<NT>(&src[geo.g2(i)]));
+            INV_JOIN(P51, INV_ROW2, INV_COL2);
             inv_stages<Geo::S0, INV_COL2, P51>(x, tw2, p, pinv, ninv, wlast);
+            INV_JOIN(P51, INV_COL2, INV_COL1);
 #pragma unroll
             for (int i = 0; i < 16; i++) lds[geo.l2(i)] = x[i];
             __syncthreads();
@@ -490,6 +503,7 @@ __device__ __forceinline__ void ntt_v2_rows(const NttV2Args &A, double *lds, int
 #pragma unroll
             for (int e = 0; e < 16; e++) x[e] = grp[lo4 * 17 + e];
             inv_stages<0, INV_ROW1, P51>(x, tw2, p, pinv, unused, unused);
+            INV_JOIN(P51, INV_ROW1, INV_ROW2);
 #pragma unroll
             for (int e = 0; e < 16; e++) grp[lo4 * 17 + e] = x[e];
             ROW_GROUP_SYNC();

@@ -107,6 +107,10 @@ __device__ __forceinline__ void wg_inv_limb(double (&x)[16], const u64d *src, co
     constexpr int Q = LOGN - 12;
     typedef ColsGeom<Q> Geo;
     constexpr unsigned N = 1u << LOGN, N1 = N >> 8;
+    constexpr InvRound ROW2 = Q ? INV_ROW2 : INV_ROW2_12, AFTER_ROW2 = Q ? INV_COL2 : INV_COL1;
+    INV_JOIN(P51, INV_ROW1, ROW2);
+    INV_JOIN(P51, ROW2, AFTER_ROW2);
+    INV_JOIN(P51, INV_COL2, INV_COL1);
     const unsigned tid = threadIdx.x, row = tid >> 4, lo4 = tid & 15, pr = row_pair_index(row, lo4, 0);
     const Geo geo(tid & 255u, tid >> 8);
     double *grp = lds + row * V2_GS;
@@ -188,7 +192,7 @@ __device__ __forceinline__ void wg_inv_limb(double (&x)[16], const u64d *src, co
         ROW_GROUP_SYNC();
 #pragma unroll
         for (int e = 0; e < 16; e++) x[e] = grp[e * 17 + lo4];
-        inv_stages<0, INV_ROW2, P51>(x, tw1, p, pinv, unused, unused);
+        inv_stages<0, ROW2, P51>(x, tw1, p, pinv, unused, unused);
 #pragma unroll
         for (int e = 0; e < 16; e++) PIN_VALUE(x[e]);
 #pragma unroll

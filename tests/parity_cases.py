@@ -141,6 +141,54 @@ def case_ntt(be, shape, seed, batch=2):
     ctx.close()
 
 
+# Words of the first four rows (256 words each) of a limb of 2^12 words, modulo the second largest 50-bit prime of that ring, as 16 seeds: group
+# (row, j) is the 64 words at 64*j of the row, drawn by default_rng([row, j, seed]).  Each makes the j-th of four products that the row pass adds up
+# at column 63 come out as a positive representative above p/2; the 16 of them add up to 1.04 * 2^53, an odd sum.
+HARD_2E12_SEEDS = ((2963, 3137, 323, 1227), (3884, 3709, 1016, 1465), (2114, 1180, 1500, 1494), (2827, 924, 1214, 3119))
+
+
+def case_inverse_hard_words(be, seed):
+    """canonical words whose inverse transform at N = 2^12 comes to the end of the exact range: plain, as a dropped limb, as the polynomial of a
+    rotation (through its automorphism), and as the third component of a product (by a second operand of ones)"""
+    shape = (12, 2, 50, 1, 51, 1)
+    M = make_material(shape, seed, rotations=(3,))
+    O = M.O
+    ctx = be.context(*shape)
+    check_moduli(ctx, M)
+    q = O.q[1]
+    hard = wl.uniform_limbs([q], O.N, seed, "hard")[0]
+    for row, seeds in enumerate(HARD_2E12_SEEDS):
+        for j, sd in enumerate(seeds):
+            hard[row * 256 + 64 * j:][:64] = np.random.default_rng([row, j, sd]).integers(0, q, 64)
+    assert int(hard[:1024].sum()) == 588297637103541467, "not the words that the seeds were chosen for"
+
+    d = be.to_dev(hard)
+    ctx.intt(d, [1], 1, stream=be.stream)
+    assert np.array_equal(be.to_host(d).reshape(-1), O.intt_limbs(hard[None], [1])[0]), "inverse transform"
+
+    a = random_cts(M, 2, 1, seed, "hard.a")
+    a[0, :, 1] = hard
+    da, out = be.to_dev(a), be.empty(2, 1, O.N)
+    ctx.rescale(da, out, 2, 1, be.ws(ctx.workspace_bytes(ckksmi.OP_RESCALE, 2, 1)), stream=be.stream)
+    assert np.array_equal(be.to_host(out).reshape(2, 1, O.N), O.rescale(a[0], 2)), "rescale"
+
+    evk = be.to_dev(M.rlk)
+    b = np.ones_like(a)
+    out = be.empty(2, 1, O.N)
+    with _kernels(ctx, ["tensor_wg_kernel"]):
+        ctx.hmul_relin_rescale(da, be.to_dev(b), evk, out, 2, 1, be.ws(ctx.workspace_bytes(ckksmi.OP_HMUL_RELIN_RESCALE, 2, 1)), stream=be.stream)
+    assert np.array_equal(be.to_host(out).reshape(2, 1, O.N), O.hmul_relin_rescale(a[0], b[0], M.rlk, 2)), "product"
+
+    source = O.automorphism_eval(np.arange(O.N, dtype=np.uint64), orc.galois_element(12, 3)).astype(np.int64)
+    a[0, 1, 1][source] = hard
+    ctx.galois_key_register(3, be.to_dev(M.gk[3]))
+    out = be.empty(2, 2, O.N)
+    with _kernels(ctx, ["ntt_wg_inv_gal_kernel"]):
+        ctx.rotate(be.to_dev(a), [3], out, 2, 1, be.ws(ctx.workspace_bytes(ckksmi.OP_ROTATE, 2, 1)), stream=be.stream)
+    assert np.array_equal(be.to_host(out).reshape(2, 2, O.N), O.rotate(a[0], 3, M.gk[3], 2)), "rotation"
+    ctx.close()
+
+
 def case_elementwise(be, shape, seed, batch=3):
     M = make_material(shape, seed)
     O = M.O

@@ -29,6 +29,11 @@ def test_emulated_ntt(be, shape):
     pc.case_ntt(be, shape, seed=100)
 
 
+def test_emulated_inverse_of_hard_words(be):
+    with be.tuned(64):
+        pc.case_inverse_hard_words(be, seed=217)
+
+
 @pytest.mark.parametrize("shape", [TINY, HYBRID3])
 def test_emulated_elementwise(be, shape):
     pc.case_elementwise(be, shape, seed=101)

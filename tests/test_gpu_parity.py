@@ -34,6 +34,12 @@ def test_ntt_matches_oracle(be, shape):
     pc.case_ntt(be, shape, seed=300, batch=3)
 
 
+def test_inverse_of_hard_words(be):
+    announce("inverse transforms at 2^12 that come to the end of the exact range")
+    with be.tuned(64):
+        pc.case_inverse_hard_words(be, seed=217)
+
+
 @pytest.mark.parametrize("shape", [TINY, (14, 3, 50, 1, 51, 1), (5, 7, 50, 3, 51, 3)])
 def test_elementwise_matches_oracle(be, shape):
     announce("elementwise %r" % (shape,))
