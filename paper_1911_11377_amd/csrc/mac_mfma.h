@@ -81,7 +81,8 @@ typedef int v4i __attribute__((ext_vector_type(4)));
 #endif
 
 // One tap packed in 32 bits: bits 0..21 (c*in_rows + u)*W + v = ciphertext index relative to the window origin,
-// bits 22..26 kernel row u, bits 27..31 kernel column v; u = 31 marks a padding entry beyond the last tap.
+// bits 22..26 kernel row u, bits 27..31 kernel column v; u = MM_TAP_NONE marks an entry beyond the last tap (above every kernel's
+// rows, but a row 31 may well lie inside the image: the mark is tested as such, mm_tap_row).
 // Table slot kb*64 + 16*g + t belongs to step kb, k-group g, byte t.  For windows that lie wholly inside the image no tap
 // needs a bounds check; they use premultiplied offsets instead: a second 32-bit table holds delta * 2*level (limb rows), a
 // 64-bit table the same in bytes (delta * 2*level * N * 8).  Entries beyond the last tap are 0 there: their weights are
@@ -89,6 +90,8 @@ typedef int v4i __attribute__((ext_vector_type(4)));
 typedef unsigned TapEnt;
 #define MM_TAP_DELTA_MAX (1u << 22)
 #define MM_TAP_KMAX 30  // largest kernel height / width
+#define MM_TAP_NONE 31u
+static_assert(MM_TAP_KMAX <= MM_TAP_NONE, "the mark is no kernel row");
 
 struct MacMfmaArgs {
     const u64d *in;       // [C][in_rows][W] ciphertexts
@@ -130,7 +133,7 @@ __device__ __forceinline__ long long mm_balanced(long long w, long long q, doubl
 
 // Slot `slot` of both 32-bit tap tables (the second one `slots` entries on) for tap k
 __device__ __forceinline__ unsigned mm_tap_entry(int slot, int k, int K, TapEnt *taps, size_t slots, int level, int kh, int kw, int in_rows, int W) {
-    TapEnt e = 31u << 22;
+    TapEnt e = MM_TAP_NONE << 22;
     if (k < K) {
         const unsigned c = k / (kh * kw), u = (k / kw) % kh, v = k % kw;
         e = ((c * in_rows + u) * W + v) | (u << 22) | (v << 27);
@@ -139,6 +142,16 @@ __device__ __forceinline__ unsigned mm_tap_entry(int slot, int k, int K, TapEnt 
     const unsigned rows = k < K ? (e & (MM_TAP_DELTA_MAX - 1)) * (unsigned)(2 * level) : 0u;
     taps[slots + slot] = rows;
     return rows;
+}
+
+// Limb row (ciphertext index * 2*level, below 2^30) of the tap of entry e in the window at (iy0, ix0), for windows that reach beyond the image;
+// false: the tap lies on padding, or the entry stands for none.  Its word counts as zero then, and limb row 0 is read (always valid).
+__device__ __forceinline__ bool mm_tap_row(const MacMfmaArgs &A, TapEnt e, int iy0, int ix0, int origin, unsigned &row) {
+    const unsigned u = (e >> 22) & 31u;
+    const int iy = iy0 + (int)u, ix = ix0 + (int)(e >> 27);
+    const bool ok = u != MM_TAP_NONE && (unsigned)iy < (unsigned)A.H && (unsigned)ix < (unsigned)A.W;
+    row = ok ? __umul24((unsigned)(origin + (int)(e & (MM_TAP_DELTA_MAX - 1))), 2u * (unsigned)A.level) : 0u;
+    return ok;
 }
 
 // A fragments (one thread per 16 taps of one channel: all seven digit chunks, so that every weight is reduced once per modulus)
@@ -340,14 +353,11 @@ __device__ __forceinline__ unsigned mm_issue_loads(const MacMfmaArgs &A, const T
 #pragma unroll
     for (int t = 0; t < 16; t++) {
         const unsigned e = ent[t];
-        unsigned row;  // limb row of the tap's ciphertext: ciphertext index * 2*level, below 2^30
+        unsigned row;
         if (INTERIOR) {
             row = e + (unsigned)origin * twoL;
         } else {
-            const int iy = iy0 + (int)((e >> 22) & 31u), ix = ix0 + (int)(e >> 27);
-            const bool ok = (unsigned)iy < (unsigned)A.H && (unsigned)ix < (unsigned)A.W;
-            row = ok ? __umul24((unsigned)(origin + (int)(e & (MM_TAP_DELTA_MAX - 1))), twoL) : 0u;
-            mask |= ok ? 1u << t : 0u;
+            mask |= mm_tap_row(A, e, iy0, ix0, origin, row) ? 1u << t : 0u;
         }
         x[t] = inw[(size_t)row << A.logN];
     }
@@ -483,11 +493,8 @@ __device__ __forceinline__ unsigned mm_resident_loads(const MacMfmaArgs &A, cons
     unsigned mask = 0;
 #pragma unroll
     for (int t = 0; t < 16; t++) {
-        const unsigned e = ent_lds[kb * 64 + 16 * g + t];
-        const int iy = P.iy0 + (int)((e >> 22) & 31u), ix = P.ix0 + (int)(e >> 27);
-        const bool ok = (unsigned)iy < (unsigned)A.H && (unsigned)ix < (unsigned)A.W;
-        const unsigned row = ok ? __umul24((unsigned)(P.origin + (int)(e & (MM_TAP_DELTA_MAX - 1))), twoL) : 0u;
-        mask |= ok ? 1u << t : 0u;
+        unsigned row;
+        mask |= mm_tap_row(A, ent_lds[kb * 64 + 16 * g + t], P.iy0, P.ix0, P.origin, row) ? 1u << t : 0u;
         x[t] = inw[(size_t)row << A.logN];
     }
     return mask;

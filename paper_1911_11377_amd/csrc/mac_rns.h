@@ -188,11 +188,8 @@ __device__ __forceinline__ void conv_mac_rns_body(const MacMfmaArgs &A, v4i *fra
             unsigned row;
             if (INTERIOR) {
                 row = e + (unsigned)origin * twoL;
-            } else {  // a tap on padding reads limb row 0 (always valid) and counts as zero
-                const int iy = iy0 + (int)((e >> 22) & 31u), ix = ix0 + (int)(e >> 27);
-                const bool ok = (unsigned)iy < (unsigned)A.H && (unsigned)ix < (unsigned)A.W;
-                row = ok ? (unsigned)(origin + (int)(e & (MM_TAP_DELTA_MAX - 1))) * twoL : 0u;
-                real |= ok ? 1u << t : 0u;
+            } else {
+                real |= mm_tap_row(A, e, iy0, ix0, origin, row) ? 1u << t : 0u;
             }
             x[t] = inw[(size_t)row << A.logN];
         }

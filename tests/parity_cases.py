@@ -1003,8 +1003,8 @@ def case_conv(be, shape, seed, Cin, H, W, Oc, kh, stride, pad, level=None, rows_
     ctx.close()
 
 
-def case_conv_channels(be, shape, seed, Cin, H, W, Oc, kh, stride, pad, residues, rows=None, extreme=False):
-    """many taps: residues or digits, told apart by the digit kernels' sums of weights; `rows`: one strip of output rows;
+def case_conv_channels(be, shape, seed, Cin, H, W, Oc, kh, stride, pad, residues, rows=None, extreme=False, kernel="conv_mac_mfma_kernel"):
+    """one layer: residues or digits, told apart by the digit kernels' sums of weights; `rows`: one strip of output rows;
     `extreme`: every word p - 1 and every weight (p - 1) / 2, the largest sum that the residues have to tell apart"""
     M = make_material(shape, seed)
     O = M.O
@@ -1022,6 +1022,8 @@ def case_conv_channels(be, shape, seed, Cin, H, W, Oc, kh, stride, pad, residues
     want = O.conv2d_mac(x, wi, stride, pad, level)
     r0, r1 = rows or (0, Ho)
     i0, i1 = max(0, r0 * stride - pad), min(H, (r1 - 1) * stride - pad + kh)
+    i0 = min(i0, H - 1)
+    i1 = max(i1, i0 + 1)  # windows on padding altogether: any row of the image
     out, ws = be.empty(Oc, r1 - r0, Wo, 2, level, O.N), be.ws(ctx.conv2d_workspace_bytes(Cin, Oc, kh, kh, level))
     ctx.profile_enable(True)
     ctx.conv2d_mac_rows(be.to_dev(np.ascontiguousarray(x[:, i0:i1])), be.to_dev(wi, np.int64), Cin, H, W, Oc, kh, kh, stride, pad, i0, i1 - i0, r0, r1 - r0, out,
@@ -1029,9 +1031,25 @@ def case_conv_channels(be, shape, seed, Cin, H, W, Oc, kh, stride, pad, residues
     got = be.to_host(out).reshape(Oc, r1 - r0, Wo, 2, level, O.N)
     ran = ctx.profile_read()
     ctx.profile_enable(False)
-    assert "conv_mac_mfma_kernel" in ran and ("mac_wsum_kernel" not in ran) == residues, list(ran)
+    assert kernel in ran and ("mac_wsum_kernel" not in ran) == residues, list(ran)
     assert np.array_equal(got, want[:, r0:r1])
     ctx.close()
+
+
+# (Cin, H, W, Oc, kh, stride, pad, residues, rows, kernel): table slots beyond the last tap, windows on the top edge, images so high that row 31
+# of such a window lies inside; also windows that lie on padding altogether
+PADDED_LAYERS = [(cin, h, h if square else 3, oc, 3, 1, 1, residues, rows, kernel)
+                 for cin, oc, square, residues, kernel in ((43, 98, False, True, "conv_mac_mfma_kernel"), (32, 8, False, False, "conv_mac_mfma_kernel"),
+                                                           (15, 8, True, False, "conv_mac_mfma_resident_kernel"), (20, 8, True, False, "conv_mac_mfma_resident_kernel"))
+                 for h, rows in ((31, (0, 2)), (32, (0, 2)), (33, (0, 1)), (33, (32, 33)))]
+PADDED_LAYERS += [(5, 28, 6, 8, 5, 2, 4, False, (0, 3), "conv_mac_mfma_resident_kernel"), (20, 30, 2, 8, 3, 1, 4, False, (0, 3), "conv_mac_mfma_resident_kernel"),
+                  (43, 30, 2, 98, 3, 1, 4, True, (0, 3), "conv_mac_mfma_kernel"), (43, 30, 2, 98, 3, 1, 4, True, (35, 36), "conv_mac_mfma_kernel"),
+                  (3, 33, 4, 9, 3, 1, 1, False, (0, 2), "conv_mac_mfma_strip_kernel")]
+
+
+def case_padded_layer(be, layer, seed):
+    cin, h, w, oc, kh, stride, pad, residues, rows, kernel = layer
+    case_conv_channels(be, (6, 1, 50, 0, 51, 1), seed, cin, h, w, oc, kh, stride, pad, residues=residues, rows=rows, kernel=kernel)
 
 
 def case_cnn(be, shape, seed, topology, workers=1):

@@ -106,6 +106,13 @@ def test_emulated_conv_residues(be):
         pc.case_conv_channels(be, (6, 1, 50, 0, 51, 1), 214, 384, 1, 1, 97, 1, 1, 0, residues=False)
 
 
+@pytest.mark.parametrize("layer", pc.PADDED_LAYERS)
+def test_emulated_padded_layers_of_high_images(be, layer):
+    """(with the bounds of the caller's buffers guarded)"""
+    with be.tuned(8):
+        pc.case_padded_layer(be, layer, seed=218)
+
+
 def test_emulated_pooling(be):
     """(whole networks: the Table-1-like one below; the square-activation network runs on the GPU)"""
     pc.case_pool(be, TINY, seed=112, Cin=2, H=5, W=4, k=2)

@@ -788,6 +788,13 @@ def test_division_route(be, shape, batch, level, one_kernel):
     pc.case_division_route(be, shape, seed=365, batch=batch, level=level, one_kernel=one_kernel, sample=[0, batch - 1])
 
 
+@pytest.mark.parametrize("layer", pc.PADDED_LAYERS)
+def test_padded_layers_of_high_images(be, layer):
+    announce("padded layer %r" % (layer,))
+    with be.tuned(8):
+        pc.case_padded_layer(be, layer, seed=218)
+
+
 @pytest.mark.parametrize("batch,level,on_chip", [(32, 2, False), (63, 2, False), (32, 3, False), (40, 3, True), (32, 4, True), (31, 5, False)])
 def test_tail_route(be, batch, level, on_chip):
     """N = 2^14, one special prime: ModDown followed by rescale on either side of the rows and kept limbs that the on-chip form needs"""
