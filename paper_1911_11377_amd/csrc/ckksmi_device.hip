@@ -1703,7 +1703,10 @@ extern "C" int ckksmi_conv2d_mac_rows(ckksmi_ctx *c, const uint64_t *in, const i
     MacShape ms = mac_shape(c, C, O, kh, kw, stride, out_rows, Wo, level);
     // ... and the residue kernel has one large workgroup per compute unit: two rounds of them at least (512 of the 8192 target)
     if (ms.rns && (ws_bytes < ms.rns_bytes || (size_t)out_rows * Wo * ms.rns_Mg * (c->N / MR_WORDS) * 2 * level < (size_t)c->ntt_target_wgs / 16)) ms.rns = false;
-    if (ms.mfma_ok && ws_bytes >= (ms.rns ? ms.rns_bytes : ms.mfma_bytes) && (size_t)C * in_rows * W < MM_TAP_DELTA_MAX && kh <= MM_TAP_KMAX && kw <= MM_TAP_KMAX) {
+    // a tap's offset fits its 22 bits: of those inside the strip, and, where the kernel is higher than the strip, of the last tap
+    const bool taps_ok = kh <= MM_TAP_KMAX && kw <= MM_TAP_KMAX && (size_t)C * in_rows * W < MM_TAP_DELTA_MAX &&
+                         ((size_t)(C - 1) * in_rows + kh - 1) * W + kw - 1 < MM_TAP_DELTA_MAX;
+    if (ms.mfma_ok && taps_ok && ws_bytes >= (ms.rns ? ms.rns_bytes : ms.mfma_bytes)) {
         const unsigned positions = (unsigned)(out_rows * Wo);
         // resident kernel: each workgroup takes `run` positions of a 64-word block, nrun workgroups share the block;
         // strip kernel: `run` tiles (four positions of a row) of a 16-word block

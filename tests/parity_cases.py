@@ -1004,7 +1004,7 @@ def case_conv(be, shape, seed, Cin, H, W, Oc, kh, stride, pad, level=None, rows_
 
 
 def case_conv_channels(be, shape, seed, Cin, H, W, Oc, kh, stride, pad, residues, rows=None, extreme=False, kernel="conv_mac_mfma_kernel"):
-    """one layer: residues or digits, told apart by the digit kernels' sums of weights; `rows`: one strip of output rows;
+    """one layer: residues or digits, told apart by the digit kernels' sums of weights, or neither (conv_mac_kernel); `rows`: one strip of output rows;
     `extreme`: every word p - 1 and every weight (p - 1) / 2, the largest sum that the residues have to tell apart"""
     M = make_material(shape, seed)
     O = M.O
@@ -1031,7 +1031,8 @@ def case_conv_channels(be, shape, seed, Cin, H, W, Oc, kh, stride, pad, residues
     got = be.to_host(out).reshape(Oc, r1 - r0, Wo, 2, level, O.N)
     ran = ctx.profile_read()
     ctx.profile_enable(False)
-    assert kernel in ran and ("mac_wsum_kernel" not in ran) == residues, list(ran)
+    digits = kernel != "conv_mac_kernel" and not residues
+    assert kernel in ran and ("mac_wsum_kernel" in ran) == digits, list(ran)
     assert np.array_equal(got, want[:, r0:r1])
     ctx.close()
 
@@ -1045,6 +1046,10 @@ PADDED_LAYERS = [(cin, h, h if square else 3, oc, 3, 1, 1, residues, rows, kerne
 PADDED_LAYERS += [(5, 28, 6, 8, 5, 2, 4, False, (0, 3), "conv_mac_mfma_resident_kernel"), (20, 30, 2, 8, 3, 1, 4, False, (0, 3), "conv_mac_mfma_resident_kernel"),
                   (43, 30, 2, 98, 3, 1, 4, True, (0, 3), "conv_mac_mfma_kernel"), (43, 30, 2, 98, 3, 1, 4, True, (35, 36), "conv_mac_mfma_kernel"),
                   (3, 33, 4, 9, 3, 1, 1, False, (0, 2), "conv_mac_mfma_strip_kernel")]
+
+
+# one row of so many pixels that a kernel far higher than the image passes the range of a tap's offset
+WIDE_LAYER = (1, 1, 144700, 8, 30, 50000, 29, False, (0, 1), "conv_mac_kernel")
 
 
 def case_padded_layer(be, layer, seed):

@@ -113,6 +113,10 @@ def test_emulated_padded_layers_of_high_images(be, layer):
         pc.case_padded_layer(be, layer, seed=218)
 
 
+def test_emulated_padded_layer_of_a_wide_image(be):
+    pc.case_padded_layer(be, pc.WIDE_LAYER, seed=219)
+
+
 def test_emulated_pooling(be):
     """(whole networks: the Table-1-like one below; the square-activation network runs on the GPU)"""
     pc.case_pool(be, TINY, seed=112, Cin=2, H=5, W=4, k=2)
