@@ -50,3 +50,36 @@ extern "C" double emu_probe_lazy_rounds(int p51, int inverse, double *x, const d
     memcpy(x, xx, sizeof(xx));
     return b;
 }
+
+// One inverse register round (an InvRound, from register stage S0 on) on 16 words; returns the bound of what it leaves.  x == nullptr: the bound alone
+template <bool P51, InvRound B>
+static double probe_inv_round(int S0, double *x, const double *tw, double ninv, double wlast, double p) {
+    if (x) {
+        double xx[16], t[15];
+        memcpy(xx, x, sizeof(xx));
+        memcpy(t, tw, sizeof(t));
+        const WMul n{ninv, ninv / p}, w{wlast, wlast / p};
+        switch (S0) {
+            case 0: inv_stages<0, B, P51>(xx, t, p, 1.0 / p, n, w); break;
+            case 1: inv_stages<1, B, P51>(xx, t, p, 1.0 / p, n, w); break;
+            case 2: inv_stages<2, B, P51>(xx, t, p, 1.0 / p, n, w); break;
+            case 3: inv_stages<3, B, P51>(xx, t, p, 1.0 / p, n, w); break;
+            default: inv_stages<4, B, P51>(xx, t, p, 1.0 / p, n, w); break;
+        }
+        memcpy(x, xx, sizeof(xx));
+    }
+    return inv_exit<P51>(B);
+}
+template <bool P51>
+static double probe_inv_named(int round, int S0, double *x, const double *tw, double ninv, double wlast, double p) {
+    switch (round) {
+        case INV_ROW1: return probe_inv_round<P51, INV_ROW1>(S0, x, tw, ninv, wlast, p);
+        case INV_ROW2: return probe_inv_round<P51, INV_ROW2>(S0, x, tw, ninv, wlast, p);
+        case INV_ROW2_12: return probe_inv_round<P51, INV_ROW2_12>(S0, x, tw, ninv, wlast, p);
+        case INV_COL2: return probe_inv_round<P51, INV_COL2>(S0, x, tw, ninv, wlast, p);
+        default: return probe_inv_round<P51, INV_COL1>(S0, x, tw, ninv, wlast, p);
+    }
+}
+extern "C" double emu_probe_inv_round(int p51, int round, int S0, double *x, const double *tw, double ninv, double wlast, double p) {
+    return p51 ? probe_inv_named<true>(round, S0, x, tw, ninv, wlast, p) : probe_inv_named<false>(round, S0, x, tw, ninv, wlast, p);
+}

@@ -449,3 +449,38 @@ def test_lazy_rounds_stay_exact_from_the_ends_of_their_range(be, p51, inverse):
             bound = be.lib.emu_probe_lazy_rounds(p51, inverse, buf, _doubles(tw), ctypes.c_double(p))
             assert all(v == int(v) and abs(v) <= bound * p for v in buf)
             assert [int(v) % p for v in buf] == _exact_rounds(x, tw, p, inverse)
+
+
+INV_ROW1, INV_ROW2, INV_COL2, INV_COL1, INV_ROW2_12 = range(5)
+# (round, first register stage) in the order in which a kernel runs them: a ring of 2^12 words in one workgroup, and as two passes; 2^13 .. 2^16
+INV_CHAINS = [[(INV_ROW1, 0), (INV_ROW2_12, 0), (INV_COL1, 0)]] + [[(INV_ROW1, 0), (INV_ROW2, 0), (INV_COL2, 4 - Q), (INV_COL1, 0)] for Q in range(5)]
+
+
+@pytest.mark.parametrize("chain", INV_CHAINS)
+@pytest.mark.parametrize("p51", [0, 1])
+def test_inverse_rounds_take_what_the_round_before_leaves(be, p51, chain):
+    """every inverse round, the last one with its folded constants too, from words at the bound that the round before it declares: exact, and within
+    its own bound.  (The words of a round come from 16 threads' rounds before it, so that all of them can be at the same register's bound.)"""
+    probe = be.lib.emu_probe_inv_round
+    probe.restype = ctypes.c_double
+    p = 2 ** (50 + p51) - 27
+    half, rng = p // 2, np.random.default_rng(p51)
+    bound = 1.25  # a product of two canonical words
+    for rnd, S0 in chain:
+        top = int(bound * p)
+        words = [[top] * 16, [-top] * 16, [top - 1] * 15 + [top], [top if i % 2 else -top for i in range(16)], [top if i < 8 else -top for i in range(16)]]
+        words += [[int(v) for v in rng.choice([-top, 1 - top, top - 1, top], 16)] for _ in range(40)]
+        words += [[top - int(v) for v in rng.integers(0, 2, 16)] for _ in range(40)]
+        for x in words:
+            for tw in ([half] * 17, [-half] * 17, [int(v) for v in rng.integers(-half, half + 1, 17)]):
+                buf = _doubles(x)
+                bound = probe(p51, rnd, S0, buf, _doubles(tw[:15]), ctypes.c_double(tw[15]), ctypes.c_double(tw[16]), ctypes.c_double(p))
+                want = list(x)
+                for s in range(3, S0 - 1, -1):
+                    span = 8 >> s
+                    for lo in (i for i in range(16) if not i & span):
+                        u, v = want[lo] + want[lo + span], want[lo] - want[lo + span]
+                        last = rnd == INV_COL1 and s == 0
+                        want[lo], want[lo + span] = (u * tw[15], v * tw[16]) if last else (u, v * tw[(1 << s) - 1 + lo // (2 * span)])
+                assert all(v == int(v) and abs(v) <= bound * p for v in buf)
+                assert all((int(v) - w) % p == 0 for v, w in zip(buf, want))

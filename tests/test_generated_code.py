@@ -10,7 +10,10 @@ from paper_1911_11377_amd import build as lib_build
 
 KERNELS = ["ntt_wg_kernel<false, 13>(NttV2Args)", "ntt_wg_kernel<true, 14>(NttV2Args)", "conv_final_kernel<14, 1, 1, 0>(ConvFinalArgs)",
            "conv_final_gal_kernel<14, 2, 1>(ConvFinalArgs, RowsFinalGal)", "tail_sources_kernel<13>(TailSourcesArgs)",
-           "inner_wg_gal_kernel<12, 0, 3>(InnerWgArgs, KeyTab, GaloisTab)"]
+           "inner_wg_gal_kernel<12, 0, 3>(InnerWgArgs, KeyTab, GaloisTab)",
+           # the streamed instances
+           "ntt_wg_kernel<false, 13, true>(NttV2Args)", "ntt_wg_kernel<true, 14, true>(NttV2Args)", "conv_final_kernel<14, 1, 1, 0, true>(ConvFinalArgs)",
+           "conv_final_gal_kernel<14, 2, 1, true>(ConvFinalArgs, RowsFinalGal)"]
 
 
 @pytest.mark.skipif(not os.path.exists(lib_build.HIPCC), reason="no hipcc")

@@ -823,9 +823,10 @@ def test_streamed_transforms_match_cached_ones(logN, n_q, batch):
     ctx.close()
 
 
-@pytest.mark.parametrize("logN,n_q,k,alpha,batch", [(14, 4, 1, 1, 97), (14, 4, 3, 3, 61), (16, 4, 3, 3, 23)])
+@pytest.mark.parametrize("logN,n_q,k,alpha,batch", [(14, 4, 1, 1, 97), (14, 4, 3, 3, 61), (16, 4, 3, 3, 23), (14, 4, 1, 1, 175), (14, 4, 3, 3, 175), (16, 4, 3, 3, 45)])
 def test_streamed_products_match_cached_ones(logN, n_q, k, alpha, batch):
-    """a batch whose launches stream their results, and its items one at a time"""
+    """a batch whose launches stream their results, and in the last three shapes their operands too (every launch of the inner product, the last
+    passes and the one-kernel division moves more than 256 MB), and its items one at a time"""
     import torch
 
     announce("streamed products 2^%d" % logN)
@@ -842,5 +843,31 @@ def test_streamed_products_match_cached_ones(logN, n_q, k, alpha, batch):
     ctx.hmul_relin_rescale(a, b, key, out, n_q, batch, ws)
     for i in range(0, batch, 11):
         ctx.hmul_relin_rescale(a[i:i + 1], b[i:i + 1], key, one, n_q, 1, ws)
+        assert torch.equal(out[i:i + 1], one)
+    ctx.close()
+
+
+@pytest.mark.parametrize("logN,n_q,batch", [(12, 4, 411), (14, 4, 104), (16, 3, 35)])
+def test_streamed_encryption_matches_cached_one(logN, n_q, batch):
+    """a batch whose column passes stream their results (more than 16 MB) and whose row pass streams operands too (more than 256 MB), and its items
+    one at a time"""
+    import torch
+
+    announce("streamed encryption 2^%d" % logN)
+    ctx = ckksmi.Context(logN, n_q, 50, 0, 51, 1, device=0)
+    gen = torch.Generator(device="cuda:0").manual_seed(logN)
+
+    def words(low, high, *shape):
+        return torch.randint(low, high, shape, dtype=torch.int64, device="cuda:0", generator=gen)
+
+    N = ctx.N
+    assert 40 * N * batch * n_q > 256 << 20
+    pk, pt = words(0, min(ctx.q), 2, n_q, N), words(0, min(ctx.q), batch, n_q, N)
+    r, e0, e1 = words(-1, 2, batch, N), words(-40, 41, batch, N), words(-40, 41, batch, N)
+    out, one = words(0, 2, batch, 2, n_q, N), words(0, 2, 1, 2, n_q, N)
+    ws = words(0, 2, 3 * n_q * N * batch)
+    ctx.encrypt_device(pk, pt, r, e0, e1, n_q, batch, out, ws)
+    for i in range(0, batch, 13):
+        ctx.encrypt_device(pk, pt[i:i + 1], r[i:i + 1], e0[i:i + 1], e1[i:i + 1], n_q, 1, one, ws)
         assert torch.equal(out[i:i + 1], one)
     ctx.close()
