@@ -252,8 +252,10 @@ int ckksmi_rotate_hoisted_workspace_bytes(const ckksmi_ctx *ctx, int level, int 
 int ckksmi_conv2d_mac(ckksmi_ctx *ctx, const uint64_t *in, const int64_t *w, int C, int H, int W, int O, int kh, int kw, int stride, int pad, uint64_t *out, int level, void *ws, size_t ws_bytes, void *stream);
 /* Workspace for ckksmi_conv2d_mac / _rows / ckksmi_fc_mac (FC: C = F, kh = kw = 1) of this layer shape.  With at
  * least this much the multiply-accumulate runs on the matrix cores where the shape allows (ring degree >= 64, at
- * least 8 output channels, at most 16321 taps); with only ckksmi_workspace_bytes(CKKSMI_OP_CONV2D_MAC, ...) it runs
- * on the vector ALU.  Both produce the same words. */
+ * least 8 output channels, at most 16321 taps, kernels of at most 30 x 30, taps within 2^22 pixels of their window's
+ * origin in the strip of C channels); with only ckksmi_workspace_bytes(CKKSMI_OP_CONV2D_MAC, ...) it runs
+ * on the vector ALU.  With something in between, a layer of many taps and channels may run on the matrix cores by a
+ * slower method that needs less.  All produce the same words. */
 int ckksmi_conv2d_workspace_bytes(const ckksmi_ctx *ctx, int C, int O, int kh, int kw, int level, size_t *bytes);
 /* The same convolution restricted to output rows out_row0 .. out_row0+out_rows-1, for layers whose activations do
  * not fit in device memory at once: `in` holds only image rows in_row0 .. in_row0+in_rows-1 as [C][in_rows][W]

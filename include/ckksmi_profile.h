@@ -38,8 +38,8 @@ extern "C" {
 #define CKKSMI_K_ROWS_INNER 15      /* contiguous pass fused with the inner product */
 #define CKKSMI_K_ROWS_FINAL 16      /* contiguous pass fused with DivRound's last step */
 #define CKKSMI_K_CONV_COLS_RESCALE 17 /* the same with a single dropped prime (rescale) */
-#define CKKSMI_K_MAC_MFMA 18      /* conv / FC multiply-accumulate on the matrix cores */
-#define CKKSMI_K_MACPREP_MFMA 19  /* its weight digits and tap table */
+#define CKKSMI_K_MAC_MFMA 18      /* conv / FC multiply-accumulate on the matrix cores: digits streaming, or residues (conv_mac_rns_kernel) */
+#define CKKSMI_K_MACPREP_MFMA 19  /* its weight digits or residues (mac_prepare_rns_kernel) and tap table */
 #define CKKSMI_K_NTT_LDS 20       /* whole limb transform inside one workgroup's LDS */
 #define CKKSMI_K_TENSOR_ROWS 21   /* tensor product fused with the inverse contiguous pass of its third component */
 #define CKKSMI_K_AXPY_LIMB 22     /* one limb of every row += constant * another limb (merged division: P*d on the dropped q) */

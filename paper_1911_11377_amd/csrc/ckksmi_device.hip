@@ -112,9 +112,11 @@ LimbMap table_map(const int *index, int n_limbs, size_t src_stride, size_t dst_s
 // How much of a launch that moves `bytes` (operands of its own plus results) is streamed past the caches.  Results that leave for
 // good, or that the next kernel reads only after this one has written more than the L2s hold, do better without displacing what
 // is re-used (twiddles, keys, sources); once a launch moves more than the last-level cache holds (256 MB) its operands do too.
-// In between they are found there when the same buffers come back: plain transforms of 12 MB to 200 MB ran 1.1 - 1.2 x
-// slower with streamed operands, of 800 MB 1.05 x faster; products of one ciphertext lose 2 - 3 % with streamed results (12 MB).
-// 256 products at N = 2^14, 8 primes 2068 -> 1965 us, 64 at 2^16, 24 primes 7046 -> 6794, rescale of 16 ciphertexts at 2^15, 16 primes 102 -> 91.
+// In between they are found there when the same buffers come back: with streamed operands transforms of 100 and 200 MB take 1.18 - 1.2 x
+// the time at N = 2^16 (67 -> 79 us, 123 -> 147), 1.03 - 1.13 x at 2^12 and the same at 2^14; of 800 MB 0.92 x at 2^16 (623 -> 579), 0.97 - 1.01 x
+// at the others.  Results below 16 MB make no difference either way (one product at 2^16, 24 primes 231 and 232 us, four at 2^14 80.7 and 80.3).
+// Without streaming and with this rule: 256 products at N = 2^14, 8 primes 2170 -> 2108 us, 64 at 2^16, 24 primes 7340 -> 7210, one at 2^16
+// 240 -> 231, rescale of 16 ciphertexts at 2^15, 16 primes 96 -> 90.
 inline int stream_level(double bytes) { return bytes > 268435456.0 ? STREAM_ALL : bytes >= 16777216.0 ? STREAM_STORES : STREAM_NONE; }
 
 // transform `items` groups of map.per_item limbs; forward: coefficient -> evaluation

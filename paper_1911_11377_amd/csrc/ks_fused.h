@@ -213,7 +213,8 @@ __device__ __forceinline__ void modup_cols_target(const double (&yd)[NSRC][16], 
                                                   unsigned long long vpack, double Bm, bool stream, const double *ybl = nullptr) {
     typedef ColsGeom<Q> Geo;
     constexpr int NPROD = VARIANT == 2 ? NSRC - 1 : NSRC;
-    constexpr bool CHAIN = !P51 && NPROD >= 2 && !(VARIANT == 0 && NSRC == 4);  // four products and h could pass 2^53
+    // four products and h could pass 2^53 (without h, in ModUp from four sources, they could not: not measured there)
+    constexpr bool CHAIN = !P51 && NPROD >= 2 && !(VARIANT == 0 && NSRC == 4);
     // bounds, in units of p: the sum of products, and what enters the first stage (with h <= p, the reduced overshoot term, or, one
     // conversion for two divisions, a prepared product of the sum, y_B below 2p and h)
     constexpr double SUM = CHAIN ? chain_bound(NPROD) : 0.75 * NPROD;

@@ -20,7 +20,8 @@
 // 3136 taps, 256 channels, 2^18 words of 8 primes: 6.7 ms, 8.9 with the digits.  What bounds it, from timings with parts left out: the matrix
 // work alone takes 2.6 ms (1.3e15 products/s), with the A fragments 4.4 - 4.9 (96 GB from the L2s at 20 - 22 TB/s; 12 MB per prime, more than
 // an L2 holds), words and residues alone 3.9; vector and matrix instructions of a SIMD's two waves overlap by a quarter only
-// (8 matrix and 32 FP64 instructions take 103 ns, 58 and 74 apart).  Slower: 64 words x 64 channels (7.2: twice the residues per product),
+// (8 matrix and 32 FP64 instructions take 103 ns, 58 and 74 apart).  Counters: matrix pipe 0.22, vector ALU 0.39 and LDS 0.28 of the cycles busy (two
+// thirds of the LDS's in bank conflicts), 116 GB from the L2s with a hit rate of 0.89.  Slower: 64 words x 64 channels (7.2: twice the residues per product),
 // 64 words x 128 channels in two halves of the moduli (7.1: half the A fragments, but every word twice), 1024 threads of
 // half the tile each (7.2), 32x32x32 instructions (7.0), half of the waves with the residues first (7.3), A fragments half a step ahead (7.9).
 #pragma once

@@ -1,7 +1,7 @@
 // Whole limb transforms inside one workgroup for 2^12 <= N <= 2^14: the limb crosses HBM once.
 //
-// The transform is the same N1 x 256 decomposition as in ntt_v2.h, with the same butterflies, twiddles and lazy-range
-// schedule (so the same bits), but both passes run in one workgroup of N/16 threads and the intermediate between them
+// The transform is the same N1 x 256 decomposition as in ntt_v2.h, with the same butterflies and twiddles (the words are reduced at
+// other places in part; the residues that come out are the same), but both passes run in one workgroup of N/16 threads and the intermediate between them
 // lives in LDS instead of HBM: every thread keeps 16 words in registers, and the N1 x 256 matrix sits in LDS in the
 // padded row layout of the row pass (row r, column q at r*V2_GS + (q/16)*17 + q%16: 34 KiB at N = 2^12, 136 KiB at
 // N = 2^14).  Each 256-thread quarter of the workgroup does the column pass of one 4096-word column tile, exchanging
@@ -9,10 +9,11 @@
 // 16 lanes exactly as in ntt_v2_rows.  Twiddles are fetched per round (they are shared by every limb of the modulus and
 // stay in L2) instead of being held across items: a thread's registers hold one round's set at a time, which keeps the
 // 1024-thread size within its 128 registers (with both rounds' twiddles requested early 21 forward and 34 inverse registers
-// spilled).  Passes over 4096 limbs one after the other, forward / inverse: N = 2^12 56 / 59 us (two passes through HBM: 87 / 91), 2^13 139 /
-// 126 us (both rounds' twiddles early: 147 / 144), 2^14 300 / 297 us (324 / 308), which is 4.8 / 4.5, 3.9 / 4.3 and 3.6 / 3.6 TB/s (a device copy
-// moves 4.85); 4608 limbs of 2^14 words in bench.py's sweep 2.9 / 3.2 TB/s.  A few limbs of 2^13 words take as long as with early
-// twiddles forward (8 limbs 9.1 us) and 0.2 us longer inverse (9.1 and 9.3 us).
+// spilled).  Passes over 4096 limbs one after the other, forward / inverse: N = 2^12 57 / 60 us, 2^13 136 / 126, 2^14 278 / 303, which is 4.7 / 4.4,
+// 3.9 / 4.3 and 3.9 / 3.5 TB/s (a device copy moves 4.85); 4608 limbs of 2^14 words in bench.py's sweep 3.1 / 3.4 TB/s.  Before reductions were
+// thinned out: 56 / 59 us at 2^12 (two passes through HBM: 87 / 91), 139 / 126 at 2^13 (both rounds' twiddles early: 147 / 144), 300 / 297 at 2^14
+// (324 / 308).  8 limbs of 2^13 words: 8.9 / 9.0 us.  At N = 2^12 the row pass reduces four more of 16 words than elsewhere, because one round only
+// follows it (INV_ROW2_12): 4096 limbs inverse 60.4 us without them, 60.6 with.
 #pragma once
 #include "ntt_v2.h"
 
