@@ -207,10 +207,11 @@ __device__ __forceinline__ void inv_cols_in_regs(double (&x)[16], const double *
 //     value = (sum_a y_a*conv_a - hA) * P^-1 + y_B - hB     (the two conversion results the last pass would subtract,
 //                                                            brought to one: the transforms are linear)
 // SUB: h is subtracted (every mode but ModUp)
-template <bool P51, int NSRC, int Q, int VARIANT, bool SUB>
+// SRC0_LDS: the words of source 0 are in ybl instead of yd[0]
+template <bool P51, int NSRC, int Q, int VARIANT, bool SUB, bool SRC0_LDS>
 __device__ __forceinline__ void modup_cols_target(const double (&yd)[NSRC][16], WMul (&Wc)[NSRC], const double *twl, double *lds, u64d *dst,
-                                                  const ColsGeom<Q> &geo, double p, double pinv, double *twl_next, double tw_store, double hsub,
-                                                  unsigned long long vpack, double Bm, bool stream, const double *ybl = nullptr) {
+                                                  const ColsGeom<Q> &geo, double p, double pinv, double *twl_next, double tw_next, double hsub,
+                                                  unsigned long long vpack, double Bm, bool stream, const double *ybl) {
     typedef ColsGeom<Q> Geo;
     constexpr int NPROD = VARIANT == 2 ? NSRC - 1 : NSRC;
     // four products and h could pass 2^53 (without h, in ModUp from four sources, they could not: not measured there)
@@ -229,6 +230,11 @@ __device__ __forceinline__ void modup_cols_target(const double (&yd)[NSRC][16], 
     }
     const double M = CHAIN ? chain_origin(p) : 0.0;
     double x[16];
+    if (SRC0_LDS) {  // all of them requested at once
+#pragma unroll
+        for (int e = 0; e < 16; e++) x[e] = ybl[e * 256 + threadIdx.x];
+        SCHED_FENCE();
+    }
 #pragma unroll
     for (int e = 0; e < 16; e++) {
         double v = -hsub;
@@ -236,7 +242,7 @@ __device__ __forceinline__ void modup_cols_target(const double (&yd)[NSRC][16], 
         ProductChain c{0.0, 0.0};
 #pragma unroll
         for (int a = NSRC - NPROD; a < NSRC; a++) {
-            const double ya = (VARIANT == 0 && NSRC == 3 && a == 0 && ybl) ? ybl[e * 256 + threadIdx.x] : yd[a][e];
+            const double ya = (SRC0_LDS && a == 0) ? x[e] : yd[a][e];
             if (!CHAIN) v += mulmod_w(ya, Wc[a].w, Wc[a].wp, p);
             else if (a == NSRC - NPROD) c = chain_first(M, ya, Wc[a].w);
             else chain_add(c, ya, Wc[a].w);
@@ -255,7 +261,6 @@ __device__ __forceinline__ void modup_cols_target(const double (&yd)[NSRC][16], 
     }
 #pragma unroll
     for (int e = 0; e < 16; e++) lds[geo.l1(e)] = x[e];
-    twl_next[threadIdx.x] = tw_store;
     __syncthreads();
 #pragma unroll
     for (int i = 0; i < 16; i++) x[i] = lds[geo.l2(i)];
@@ -274,9 +279,10 @@ __device__ __forceinline__ void modup_cols_target(const double (&yd)[NSRC][16], 
             }
         fwd_stages<Geo::S0, Mk::F2>(x, tw2, p, pinv);
     }
+    twl_next[threadIdx.x] = tw_next;
     stream_if(stream, [&](auto nt) {
 #pragma unroll
-        for (int i = 0; i < 16; i++) stream_store<nt>(&dst[geo.g2(i)], mid_store(x[i]));
+        for (int i = 0; i < 16; i++) stream_store<nt>(scalar_base(dst + geo.c0 + Geo::d2(i)) + geo.t2(), mid_store(x[i]));
     });
 }
 
@@ -285,11 +291,15 @@ __device__ __forceinline__ void modup_cols_target(const double (&yd)[NSRC][16], 
 // addend, in the second exchange buffer and pays a second barrier per target (0.80 ms; all four in registers at one wave
 // per SIMD: 1.0 ms).  MODE 2 multiplies all four sources per target: it runs one wave per SIMD with all of them in
 // registers (0.97 ms; one of them in LDS at two waves: 1.21 ms; with spills at two: 1.4 ms).
+// One source tile leaves room for a third wave per SIMD, with one exchange buffer and two barriers per target (256 items of 8 primes at N = 2^14,
+// one prime per digit: 650 us with two waves and two buffers, 571 like this; with three source tiles the third wave spills, 2270 against 2240).
+template <int NSRC, int MODE>
+constexpr int modup_cols_waves() { return NSRC >= 4 && MODE == 2 ? 1 : NSRC == 1 && MODE <= 1 ? 3 : 2; }
 template <int Q, int NSRC, int MODE>
-__global__ __launch_bounds__(V2_THREADS, (NSRC >= 4 && MODE == 2) ? 1 : 2) void modup_cols_kernel(ModupColsArgs A) {
-    // one barrier per target: the exchange buffer alternates between two copies, the twiddles rotate through three
-    // (target k's set is written during target k-1, while slower waves may still read the set of target k-2... k-1)
-    __shared__ double lds[2][16 * V2_GS];
+__global__ __launch_bounds__(V2_THREADS, (modup_cols_waves<NSRC, MODE>())) void modup_cols_kernel(ModupColsArgs A) {
+    // the twiddles rotate through three sets; the second buffer alternates with the first, or holds a source (below)
+    constexpr bool WAVES3 = modup_cols_waves<NSRC, MODE>() == 3;
+    __shared__ double lds[WAVES3 ? 1 : 2][4096];
     __shared__ double twl[3][256];
     const unsigned N = 1u << A.logN;
     unsigned item = 0, j = 0;
@@ -378,7 +388,7 @@ __global__ __launch_bounds__(V2_THREADS, (NSRC >= 4 && MODE == 2) ? 1 : 2) void 
             const double sl = yd[0][e] - mulmod_w(v, Pinv.w, Pinv.wp, pl);  // (-0.75p, 1.75p)
             // y_B lives in the second exchange buffer from here on (this mode uses one buffer and two barriers per target):
             // four source tiles do not fit the registers of two waves per SIMD
-            lds[1][e * 256 + threadIdx.x] = canon(sl + A.hb2, pl, plinv);
+            lds[WAVES3 ? 0 : 1][e * 256 + threadIdx.x] = canon(sl + A.hb2, pl, plinv);
         }
     }
     // three source tiles: the first one lives in the second exchange buffer (one buffer, two barriers per target): without
@@ -386,7 +396,7 @@ __global__ __launch_bounds__(V2_THREADS, (NSRC >= 4 && MODE == 2) ? 1 : 2) void 
     constexpr bool SRC0_LDS = (MODE <= 1 && NSRC == 3);
     if (SRC0_LDS) {
 #pragma unroll
-        for (int e = 0; e < 16; e++) lds[1][e * 256 + threadIdx.x] = yd[0][e];
+        for (int e = 0; e < 16; e++) lds[WAVES3 ? 0 : 1][e * 256 + threadIdx.x] = yd[0][e];
     }
     const size_t crow = ((size_t)j * A.alpha + (nsrc - 1)) * A.alpha;
     // MODE 0: extended-basis index of target k (the digit's own limbs are skipped) and its modulus index;
@@ -394,14 +404,18 @@ __global__ __launch_bounds__(V2_THREADS, (NSRC >= 4 && MODE == 2) ? 1 : 2) void 
     auto ext_of = [&](int k) { return MODE == 0 ? (k < lo ? k : k + nsrc) : k; };
     auto mod_of = [&](int x) { return MODE == 0 ? (x < A.level ? x : A.n_q + x - A.level) : x; };
     twl[0][threadIdx.x] = A.tw[(size_t)mod_of(ext_of(k0)) * N + threadIdx.x];
-    double tw_next = k0 + 1 < k1 ? A.tw[(size_t)mod_of(ext_of(k0 + 1)) * N + threadIdx.x] : 0.0;
+    twl[1][threadIdx.x] = A.tw[(size_t)mod_of(ext_of(k0 + 1 < k1 ? k0 + 1 : k0)) * N + threadIdx.x];
     __syncthreads();
     for (int k = k0; k < k1; k++) {
         const int x = ext_of(k), t = mod_of(x);
         const double *tcur = twl[(k - k0) % 3];
-        double *tnext = twl[(k - k0 + 1) % 3];
-        const double tw_store = tw_next;  // twiddle of target k+1, written before this target's barrier
-        if (k + 2 < k1) tw_next = A.tw[(size_t)mod_of(ext_of(k + 2)) * N + threadIdx.x];
+        // The twiddles of target k + 2 are requested here and go to LDS just before this target's stores, into the set of target k - 1
+        // (everybody has passed this target's barrier by then).  Memory operations complete in order, so waiting for this word waits
+        // for the stores of target k - 1, which have had all of this target's arithmetic to drain; a request that is waited for behind
+        // stores makes the wave stand until they are written (ModUp of 64 items of 24 primes at N = 2^16 2180 us with such a request, 2070 like
+        // this, which includes all of a source's words fetched from LDS at once and stores with scalar bases).
+        const double tw_next = A.tw[(size_t)mod_of(ext_of(k + 2 < k1 ? k + 2 : k1 - 1)) * N + threadIdx.x];
+        double *tnext = twl[(k - k0 + 2) % 3];
         const double p = table_load(&A.modc[t].p, 0), pinv = table_load(&A.modc[t].pinv, 0);
         WMul Wc[NSRC];
         double hsub = 0.0, Bm = 0.0;
@@ -422,12 +436,13 @@ __global__ __launch_bounds__(V2_THREADS, (NSRC >= 4 && MODE == 2) ? 1 : 2) void 
             }
             dst = A.dst + ((size_t)blockIdx.y * A.nc + t) * N;
         }
-        constexpr bool ONE_BUF = MODE == 3 || SRC0_LDS;  // the second buffer holds y_B / the first source tile
-        double *xbuf = ONE_BUF ? lds[0] : lds[(k - k0) & 1];
+        constexpr bool ONE_BUF = MODE == 3 || SRC0_LDS || WAVES3;  // the second buffer holds y_B / the first source tile, or there is none
+        double *xbuf = ONE_BUF ? lds[0] : lds[(k - k0) & 1], *ybuf = lds[WAVES3 ? 0 : 1];
+        constexpr int VAR = MODE >= 2 ? MODE - 1 : 0;
         if (is_p51(A.p51, t))
-            modup_cols_target<true, NSRC, Q, (MODE >= 2 ? MODE - 1 : 0), MODE != 0>(yd, Wc, tcur, xbuf, dst, geo, p, pinv, tnext, tw_store, hsub, vpack, Bm, A.stream != STREAM_NONE, (MODE == 3 || SRC0_LDS) ? lds[1] : nullptr);
+            modup_cols_target<true, NSRC, Q, VAR, MODE != 0, SRC0_LDS>(yd, Wc, tcur, xbuf, dst, geo, p, pinv, tnext, tw_next, hsub, vpack, Bm, A.stream != STREAM_NONE, ybuf);
         else
-            modup_cols_target<false, NSRC, Q, (MODE >= 2 ? MODE - 1 : 0), MODE != 0>(yd, Wc, tcur, xbuf, dst, geo, p, pinv, tnext, tw_store, hsub, vpack, Bm, A.stream != STREAM_NONE, (MODE == 3 || SRC0_LDS) ? lds[1] : nullptr);
+            modup_cols_target<false, NSRC, Q, VAR, MODE != 0, SRC0_LDS>(yd, Wc, tcur, xbuf, dst, geo, p, pinv, tnext, tw_next, hsub, vpack, Bm, A.stream != STREAM_NONE, ybuf);
         if (ONE_BUF) __syncthreads();  // single exchange buffer: everybody has read it before the next target writes
     }
 }

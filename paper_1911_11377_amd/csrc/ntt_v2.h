@@ -332,6 +332,11 @@ struct ColsGeom {
     __device__ __forceinline__ ColsGeom(unsigned tid, unsigned tile) : r(tid / C), c(tid % C), a(tid >> 4), l16(tid & 15), c0(tile * C) {}
     __device__ __forceinline__ size_t g1(int e) const { return (size_t)(r + G * e) * 256 + c0 + c; }                       // global, round-1 register e
     __device__ __forceinline__ size_t g2(int i) const { return (size_t)(G * a + (i % G)) * 256 + c0 + l16 + 16 * (i / G); }  // global, round-2 register i
+    // the same in parts, g1(e) = c0 + d1(e) + t1() and g2(i) = c0 + d2(i) + t2(): uniform, constant, and the thread's own
+    static constexpr unsigned d1(int e) { return G * e * 256u; }
+    static constexpr unsigned d2(int i) { return (i % G) * 256u + 16u * (i / G); }
+    __device__ __forceinline__ unsigned t1() const { return r * 256u + c; }
+    __device__ __forceinline__ unsigned t2() const { return G * a * 256u + l16; }
     __device__ __forceinline__ unsigned l1(int e) const { return (r + G * e) * C + c; }                                    // LDS [N1][C]
     __device__ __forceinline__ unsigned l2(int i) const { return (G * a + (i % G)) * C + l16 + 16 * (i / G); }
 };
