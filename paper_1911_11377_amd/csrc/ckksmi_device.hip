@@ -326,8 +326,10 @@ void launch_rows_final(ckksmi_ctx *c, const u64 *tmpA, const u64 *x, size_t x_ro
         KL2(c, CKKSMI_K_ROWS_FINAL, (double)rows * nz, A.stream != STREAM_NONE, rows_final_scalar_kernel<true>, rows_final_scalar_kernel<false>, dim3(xch, tiles, nz), dim3(V2_THREADS), st, A, *stab);
     else if (gal)
         KL2(c, CKKSMI_K_ROWS_FINAL, (double)rows * nz, A.stream != STREAM_NONE, rows_final_gal_kernel<true>, rows_final_gal_kernel<false>, dim3(xch, tiles, nz), dim3(V2_THREADS), st, A, *gal);
+    else if (addend)
+        KL2(c, CKKSMI_K_ROWS_FINAL, (double)rows * nz, A.stream != STREAM_NONE, (rows_final_kernel<true, true>), (rows_final_kernel<false, true>), dim3(xch, tiles, nz), dim3(V2_THREADS), st, A);
     else
-        KL2(c, CKKSMI_K_ROWS_FINAL, (double)rows * nz, A.stream != STREAM_NONE, rows_final_kernel<true>, rows_final_kernel<false>, dim3(xch, tiles, nz), dim3(V2_THREADS), st, A);
+        KL2(c, CKKSMI_K_ROWS_FINAL, (double)rows * nz, A.stream != STREAM_NONE, (rows_final_kernel<true, false>), (rows_final_kernel<false, false>), dim3(xch, tiles, nz), dim3(V2_THREADS), st, A);
 }
 
 // Which divisions run as ONE kernel after the inverse transform of the dropped limb (ks_wg.h): one source (rescale, or ModDown with
@@ -533,6 +535,7 @@ void launch_tensor_rows(ckksmi_ctx *c, const u64 *a, const u64 *b, u64 *ymid, in
     A.terms = terms;
     A.a = (const u64d *)a; A.b = (const u64d *)b; A.ymid = (u64d *)ymid; A.modc = c->d_mod; A.tw_inv = c->d_tww_inv;
     A.logN = c->logN; A.level = level; A.p51 = c->p51mask; A.stream = stream_level(8.0 * c->N * items * level);
+    A.stream_src = stream_level(32.0 * c->N * items * level * terms) == STREAM_ALL;
     KL(c, CKKSMI_K_TENSOR_ROWS, (double)items * level, tensor_rows_kernel, dim3((unsigned)(c->N / 4096), level, items), dim3(V2_THREADS), st, A);
 }
 

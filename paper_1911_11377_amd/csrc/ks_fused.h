@@ -38,7 +38,8 @@ struct TensorRowsArgs {
     const double *tw_inv;
     int logN, level;
     int terms;
-    int stream;          // STREAM_*
+    int stream;          // STREAM_* of the result
+    int stream_src;      // the operands are streamed: 64 items of 24 primes at N = 2^16 386 us, 435 without
     P51Mask p51;
 };
 
@@ -58,11 +59,13 @@ __device__ __forceinline__ void tensor_rows_body(const TensorRowsArgs &A, double
     double *grp = lds + hi4 * V2_GS;
     // word pairs in the row-pair layout (every row stays with its 16 lanes: no workgroup barrier)
     ulonglong2 A1[8], B1[8];
+    stream_if(A.stream_src, [&](auto nt) {
 #pragma unroll
-    for (int s = 0; s < 8; s++) {
-        A1[s] = a1[row_pair_index(hi4, lo4, s)];
-        B1[s] = b1[row_pair_index(hi4, lo4, s)];
-    }
+        for (int s = 0; s < 8; s++) {
+            A1[s] = stream_load<nt>(a1 + row_pair_index(hi4, lo4, s));
+            B1[s] = stream_load<nt>(b1 + row_pair_index(hi4, lo4, s));
+        }
+    });
     SCHED_FENCE();
     double d2[16];
 #pragma unroll
@@ -475,7 +478,7 @@ __device__ __forceinline__ void rows_fwd_to_lds(const u64d *tile, double *lds, c
     double x[16];
     stream_if(stream, [&](auto nt) {
 #pragma unroll
-        for (int e = 0; e < 16; e++) x[e] = mid_load(stream_load<nt>(&tile[hi4 * 256 + lo4 + 16 * e]));
+        for (int e = 0; e < 16; e++) x[e] = mid_load(stream_load<nt>(scalar_base(tile) + (hi4 * 256 + lo4 + 16 * e)));
     });
     {
         // round-1 twiddles are the same for the 16 lanes of a row: kept in LDS, not in registers
@@ -837,7 +840,7 @@ struct RowsFinalArgs {
 // A.add_item_stride = words between the items' ciphertexts)
 struct RowsFinalGal { int R; unsigned g[CKKSMI_MAX_KEYS]; };
 
-template <bool P51, bool NTS, bool GAL = false>
+template <bool P51, bool NTS, bool ADD, bool GAL = false>
 __device__ __forceinline__ void rows_final_body(const RowsFinalArgs &A, double *lds, double *tw1_lds, int i, bool xm_val = false,
                                                 WMul xmv = WMul{0.0, 0.0}, const RowsFinalGal *gal = nullptr) {
     const unsigned N = 1u << A.logN, N1 = N >> 8;
@@ -848,26 +851,26 @@ __device__ __forceinline__ void rows_final_body(const RowsFinalArgs &A, double *
     load_row_twiddles(A.tw + (size_t)i * N, N1, tile, hi4, lo4, tw1_lds, tw2);
     const size_t tile0 = (size_t)tile * 4096;
     const WMul W = A.Binv[i];
-    const bool pre = A.pre != nullptr, xm = xm_val;
+    const bool pre = ADD && A.pre != nullptr, xm = xm_val;
     const WMul Pm = pre ? A.pre[i] : xmv;
     const unsigned r0 = blockIdx.x * (unsigned)A.rows_per_x;
     const unsigned r1 = (r0 + A.rows_per_x < (unsigned)A.rows) ? r0 + A.rows_per_x : (unsigned)A.rows;
     for (unsigned row = r0; row < r1; row++) {
         const u64d *xin = A.x + (size_t)row * A.x_row_stride + (size_t)i * N + tile0;
         u64d *out = A.out + (size_t)row * A.out_row_stride + (size_t)(i - A.out_limb0) * N + tile0;
-        const bool add = A.addend && (pre || xm || (row & 1u) == 0);
+        const bool add = ADD && A.addend && (pre || xm || (row & 1u) == 0);
         const u64d *ad = add ? A.addend + (size_t)(row / 2) * A.add_item_stride + (size_t)(row % 2) * A.add_comp_stride + (size_t)i * N + tile0 : xin;
         // operands of the last step are requested before the transform so that their latency overlaps it
         // pointwise part in the row-pair layout: 16 bytes per lane and memory instruction, no workgroup barrier
-        ulonglong2 xr[8], ar[8];
+        ulonglong2 xr[8], ar[ADD ? 8 : 1];
 #pragma unroll
         for (int s = 0; s < 8; s++) {
-            xr[s] = ((const ulonglong2 *)xin)[row_pair_index(hi4, lo4, s)];
+            xr[s] = pair_load<NTS>(xin, row_pair_index(hi4, lo4, s));
             if (GAL && add) {
                 const unsigned pair = row / 2u, item = pair / (unsigned)gal->R, r = pair % (unsigned)gal->R;
                 ar[s] = galois_pair_load(A.addend + (size_t)item * A.add_item_stride + (size_t)i * N,
                                          (unsigned)tile0 + hi4 * 256u + 32u * s + 2u * lo4, gal->g[r], A.logN);
-            } else {
+            } else if (ADD) {
                 ar[s] = ((const ulonglong2 *)ad)[row_pair_index(hi4, lo4, s)];
             }
         }
@@ -877,7 +880,7 @@ __device__ __forceinline__ void rows_final_body(const RowsFinalArgs &A, double *
         for (int s = 0; s < 8; s++) {
             const double *rr = lds + hi4 * V2_GS + row_pair_lds(lo4, s);
             double x0 = u2d(xr[s].x), x1 = u2d(xr[s].y);
-            if (pre) {  // |x + pre*addend - r| < p + 0.75p + ROWX: below 2^53
+            if (ADD && pre) {  // |x + pre*addend - r| < p + 0.75p + ROWX: below 2^53
                 x0 += mulmod_w(u2d(ar[s].x), Pm.w, Pm.wp, p);
                 x1 += mulmod_w(u2d(ar[s].y), Pm.w, Pm.wp, p);
             }
@@ -893,26 +896,29 @@ __device__ __forceinline__ void rows_final_body(const RowsFinalArgs &A, double *
                 v0 = mulmod_w(x0 - rr[0], W.w, W.wp, p);
                 v1 = mulmod_w(x1 - rr[1], W.w, W.wp, p);
             }
-            if (add && !pre) {
+            if (ADD && add && !pre) {
                 v0 += u2d(ar[s].x);
                 v1 += u2d(ar[s].y);
             }
-            stream_store<NTS>((ulonglong2 *)out + row_pair_index(hi4, lo4, s), make_ulonglong2(d2u(canon(v0, p, pinv)), d2u(canon(v1, p, pinv))));
+            pair_store<NTS>(out, row_pair_index(hi4, lo4, s), make_ulonglong2(d2u(canon(v0, p, pinv)), d2u(canon(v1, p, pinv))));
         }
         ROW_GROUP_SYNC();
     }
 }
 
-// grid: x = chunk of rows (item, component), y = row tile (N/4096), z = kept limb
-template <bool NTS>
-__global__ __launch_bounds__(V2_THREADS) void rows_final_kernel(RowsFinalArgs A) {
+// grid: x = chunk of rows (item, component), y = row tile (N/4096), z = kept limb.  ADD: with an addend; without one (a product's
+// tail, plain divisions) the words in flight leave room for a third wave per SIMD; with that and the kept limb's words streamed (with
+// two waves that made it slower) 128 rows of 23 kept limbs at N = 2^16 take 906 us against 931: 5.1 TB/s, where a copy of large
+// pieces moves 6.2
+template <bool NTS, bool ADD>
+__global__ __launch_bounds__(V2_THREADS, ADD ? 2 : 3) void rows_final_kernel(RowsFinalArgs A) {
     __shared__ double lds[16 * V2_GS];
     __shared__ double tw1_lds[16 * 16];
     const int i = A.limb0 + (int)blockIdx.z;
     if (is_p51(A.p51, i))
-        rows_final_body<true, NTS>(A, lds, tw1_lds, i);
+        rows_final_body<true, NTS, ADD>(A, lds, tw1_lds, i);
     else
-        rows_final_body<false, NTS>(A, lds, tw1_lds, i);
+        rows_final_body<false, NTS, ADD>(A, lds, tw1_lds, i);
 }
 
 // the same for rotations from a shared ModUp: the addend sigma_r(c0) is read through the automorphism
@@ -922,9 +928,9 @@ __global__ __launch_bounds__(V2_THREADS) void rows_final_gal_kernel(RowsFinalArg
     __shared__ double tw1_lds[16 * 16];
     const int i = A.limb0 + (int)blockIdx.z;
     if (is_p51(A.p51, i))
-        rows_final_body<true, NTS, true>(A, lds, tw1_lds, i, false, WMul{0.0, 0.0}, &G);
+        rows_final_body<true, NTS, true, true>(A, lds, tw1_lds, i, false, WMul{0.0, 0.0}, &G);
     else
-        rows_final_body<false, NTS, true>(A, lds, tw1_lds, i, false, WMul{0.0, 0.0}, &G);
+        rows_final_body<false, NTS, true, true>(A, lds, tw1_lds, i, false, WMul{0.0, 0.0}, &G);
 }
 
 // the same with the kept limb multiplied by a per-call scalar first: out = (c*x - r) * Binv (+ addend): rescale of c*x
@@ -935,7 +941,7 @@ __global__ __launch_bounds__(V2_THREADS) void rows_final_scalar_kernel(RowsFinal
     const int i = A.limb0 + (int)blockIdx.z;
     const WMul xmv = S.c[i];
     if (is_p51(A.p51, i))
-        rows_final_body<true, NTS>(A, lds, tw1_lds, i, true, xmv);
+        rows_final_body<true, NTS, true>(A, lds, tw1_lds, i, true, xmv);
     else
-        rows_final_body<false, NTS>(A, lds, tw1_lds, i, true, xmv);
+        rows_final_body<false, NTS, true>(A, lds, tw1_lds, i, true, xmv);
 }

@@ -121,6 +121,19 @@ template <bool NT, class P, class V> __device__ __forceinline__ void stream_stor
 }
 template <bool NT> __device__ __forceinline__ void stream_store(ulonglong2 *p, ulonglong2 v) { stream_store<NT>((u64pair *)p, u64pair{v.x, v.y}); }
 #endif
+// the i-th word pair from a workgroup-uniform address
+#ifdef CKKSMI_EMULATE
+template <bool NT> static inline ulonglong2 pair_load(const u64d *base, unsigned i) { return ((const ulonglong2 *)base)[i]; }
+template <bool NT> static inline void pair_store(u64d *base, unsigned i, ulonglong2 v) { ((ulonglong2 *)base)[i] = v; }
+#else
+template <bool NT> __device__ __forceinline__ ulonglong2 pair_load(const u64d *base, unsigned i) {
+    const u64pair v = stream_load<NT>(scalar_base((const u64pair *)base) + i);
+    return make_ulonglong2(v.x, v.y);
+}
+template <bool NT> __device__ __forceinline__ void pair_store(u64d *base, unsigned i, ulonglong2 v) {
+    stream_store<NT>(scalar_base((u64pair *)base) + i, u64pair{v.x, v.y});
+}
+#endif
 template <class F> __device__ __forceinline__ void stream_if(bool on, F f) {
     if (on) {
         STREAM_TAG("streamed");
