@@ -307,6 +307,7 @@ void launch_modup_cols(ckksmi_ctx *c, int mode, const u64 *y, size_t y_stride, u
 void launch_rows_final(ckksmi_ctx *c, const u64 *tmpA, const u64 *x, size_t x_row_stride, const u64 *addend, size_t add_item_stride,
                        size_t add_comp_stride, u64 *out, const WMul *Binv, int nc, int rows, hipStream_t st, int limb0 = 0,
                        int limb_count = -1, size_t out_row_stride = 0, const WMul *pre = nullptr, const ScalarTab *stab = nullptr, bool zsub = false, const RowsFinalGal *gal = nullptr) {
+    if (zsub && addend) { c->no_kernel = true; return; }  // the addend is in x already
     RowsFinalArgs A;
     A.zsub = zsub ? 1 : 0;
     A.pre = pre;

@@ -194,7 +194,7 @@ __device__ __forceinline__ void encrypt_rows_body(const EncryptRowsArgs &A, doub
         ulonglong2 mm[8];
 #pragma unroll
         for (int s = 0; s < 8; s++) mm[s] = ((const ulonglong2 *)(A.pt + ((size_t)it * A.level + i) * N + tile0))[row_pair_index(hi4, lo4, s)];
-        rows_fwd_to_lds<P51, false>(mid, lds, tw1_lds, tw2, p, pinv, hi4, lo4, A.stream == STREAM_ALL);
+        rows_fwd_to_lds<P51, ROW_REDUCED>(mid, lds, tw1_lds, tw2, p, pinv, hi4, lo4, A.stream == STREAM_ALL);
         double r[16];
 #pragma unroll
         for (int s = 0; s < 8; s++) {
@@ -203,7 +203,7 @@ __device__ __forceinline__ void encrypt_rows_body(const EncryptRowsArgs &A, doub
             r[2 * s + 1] = rr[1];
         }
         ROW_GROUP_SYNC();
-        rows_fwd_to_lds<P51, true>(mid + st, lds, tw1_lds, tw2, p, pinv, hi4, lo4, A.stream == STREAM_ALL);
+        rows_fwd_to_lds<P51, ROW_LAZY>(mid + st, lds, tw1_lds, tw2, p, pinv, hi4, lo4, A.stream == STREAM_ALL);
         u64d *c0 = A.ct + ((size_t)it * 2 * A.level + i) * N + tile0, *c1 = c0 + st;
 #pragma unroll
         for (int s = 0; s < 8; s++) {
@@ -214,7 +214,7 @@ __device__ __forceinline__ void encrypt_rows_body(const EncryptRowsArgs &A, doub
             stream_store<NTS>((ulonglong2 *)c0 + row_pair_index(hi4, lo4, s), make_ulonglong2(d2u(canon(v0, p, pinv)), d2u(canon(v1, p, pinv))));
         }
         ROW_GROUP_SYNC();
-        rows_fwd_to_lds<P51, true>(mid + 2 * st, lds, tw1_lds, tw2, p, pinv, hi4, lo4, A.stream == STREAM_ALL);
+        rows_fwd_to_lds<P51, ROW_LAZY>(mid + 2 * st, lds, tw1_lds, tw2, p, pinv, hi4, lo4, A.stream == STREAM_ALL);
 #pragma unroll
         for (int s = 0; s < 8; s++) {
             const double *ee = lds + hi4 * V2_GS + row_pair_lds(lo4, s);

@@ -201,7 +201,7 @@ __device__ __forceinline__ void inv_cols_in_regs(double (&x)[16], const double *
         inv_stages<0, INV_COL1, P51>(x, tw1, p, pinv, F.ninv, F.wlast);
     }
 #pragma unroll
-    for (int e = 0; e < 16; e++) x[e] = canon(x[e] + F.cadd, p, pinv);
+    for (int e = 0; e < 16; e++) x[e] = canon_near<P51>(x[e] + F.cadd, p, pinv);  // 1.5p and less than p
 }
 
 // VARIANT 1 (exact DivRound): vpack holds the overshoot of the thread's 16 coefficients, 3 bits each; Bm = Bbar mod p.
@@ -218,11 +218,13 @@ __device__ __forceinline__ void modup_cols_target(const double (&yd)[NSRC][16], 
     typedef ColsGeom<Q> Geo;
     constexpr int NPROD = VARIANT == 2 ? NSRC - 1 : NSRC;
     // four products and h could pass 2^53 (without h, in ModUp from four sources, they could not: not measured there)
+    // one source of a plain conversion: its constant is 1, the word itself (2 units of 2^50, conv_word in ks_wg.h, or one of 2^51) enters the transform
+    constexpr bool COPY = VARIANT == 0 && NSRC == 1;
     constexpr bool CHAIN = !P51 && NPROD >= 2 && !(VARIANT == 0 && NSRC == 4);
     // bounds, in units of p: the sum of products, and what enters the first stage (with h <= p, the reduced overshoot term, or, one
     // conversion for two divisions, a prepared product of the sum, y_B below 2p and h)
     constexpr double SUM = CHAIN ? chain_bound(NPROD) : 0.75 * NPROD;
-    constexpr double IN = VARIANT == 0 ? SUM + (SUB ? 1.0 : 0.0) : VARIANT == 1 ? SUM + LAZY_REDUCED : (P51 ? 0.64 : 0.5 + (SUM + 1.0) / 8.0) + 3.0;
+    constexpr double IN = COPY ? (P51 ? 1.0 : 2.0) : VARIANT == 0 ? SUM + (SUB ? 1.0 : 0.0) : VARIANT == 1 ? SUM + LAZY_REDUCED : (P51 ? 0.64 : 0.5 + (SUM + 1.0) / 8.0) + 3.0;
     constexpr int ENTRY = (int)(256.0 * IN + 0.999);
     static_assert(IN <= LazyRange<P51>::LIM, "the sum leaves the exact range");
     typedef ColsMasks<Q, P51, ENTRY> Mk;
@@ -246,7 +248,8 @@ __device__ __forceinline__ void modup_cols_target(const double (&yd)[NSRC][16], 
 #pragma unroll
         for (int a = NSRC - NPROD; a < NSRC; a++) {
             const double ya = (SRC0_LDS && a == 0) ? x[e] : yd[a][e];
-            if (!CHAIN) v += mulmod_w(ya, Wc[a].w, Wc[a].wp, p);
+            if (COPY) v = SUB ? ya - hsub : ya;
+            else if (!CHAIN) v += mulmod_w(ya, Wc[a].w, Wc[a].wp, p);
             else if (a == NSRC - NPROD) c = chain_first(M, ya, Wc[a].w);
             else chain_add(c, ya, Wc[a].w);
         }
@@ -467,13 +470,13 @@ __device__ __forceinline__ void load_row_twiddles(const double *tw, unsigned N1,
     __syncthreads();
 }
 
-// Finish the forward transform of one 16-row tile (column pass already done) and leave the results, balanced-reduced or (LAZY)
+// Finish the forward transform of one 16-row tile (column pass already done) and leave the results, balanced-reduced or (ROW_LAZY)
 // at most LazyRange::ROWX, in LDS in the padded layout: word (row g, position q) at g*V2_GS + (q/16)*17 + q%16.
 // Every row is handled by its own 16 lanes: ends with a row-group sync, and the caller puts one before the next call.
-template <bool P51, bool LAZY>
+template <bool P51, int X>
 __device__ __forceinline__ void rows_fwd_to_lds(const u64d *tile, double *lds, const double *tw1_lds, const double (&tw2)[15], double p,
                                                 double pinv, unsigned hi4, unsigned lo4, bool stream) {
-    typedef RowMasks<P51, LAZY> Mk;
+    typedef RowMasks<P51, X> Mk;
     double *grp = lds + hi4 * V2_GS;
     double x[16];
     stream_if(stream, [&](auto nt) {
@@ -494,7 +497,7 @@ __device__ __forceinline__ void rows_fwd_to_lds(const u64d *tile, double *lds, c
     for (int e = 0; e < 16; e++) x[e] = grp[lo4 * 17 + e];
     fwd_round<Mk::F2>(x, tw2, p, pinv);
 #pragma unroll
-    for (int e = 0; e < 16; e++) grp[lo4 * 17 + e] = LAZY ? x[e] : reduce_balanced(x[e], p, pinv);
+    for (int e = 0; e < 16; e++) grp[lo4 * 17 + e] = X == ROW_LAZY ? x[e] : reduce_balanced(x[e], p, pinv);
     ROW_GROUP_SYNC();
 }
 
@@ -526,16 +529,35 @@ struct RowsInnerArgs {
     const WMul *Pmod;    // [T] P mod q_i
 };
 
+// One word's terms of both accumulators: key words (canonical) times the transformed word v.
+// p < 2^51: |v| <= p/2 + 1 is the prepared factor (v/p computed once for both), a term is below 0.875p and four of them on a
+// reduced sum stay below 4p = 2^53.
+// p < 2^50: |v| <= LazyRange::FACTOR p: the quotient is taken from the product, which is off by less than 2 * 2.2 / 8, and what the
+// product drops is below 2.2p / 8: a term is below 1.33p, five of them on a reduced sum below 7.2p.
+template <bool P51> constexpr int KEY_TERMS = P51 ? 4 : 5;
+template <bool P51>
+__device__ __forceinline__ void key_term(u64d k0, u64d k1, double v, double p, double pinv, double &a0, double &a1) {
+    if (P51) {
+        const double vp = v * pinv;
+        a0 += mulmod_w(u2d(k0), v, vp, p);
+        a1 += mulmod_w(u2d(k1), v, vp, p);
+    } else {
+        a0 += mulmod(u2d(k0), v, p, pinv);
+        a1 += mulmod(u2d(k1), v, p, pinv);
+    }
+}
+
 // The term of the digit that contains limb x (its operand is the source polynomial itself, no transform) of a thread's 16
 // words: pairs row_pair_index(hi4, lo4, s) from word tile0 of the limb; accumulator 2*s + b belongs to word b of pair s.
 // In tensor mode also P * (d0, d1).  pending: terms in the accumulators since their last reduction.
-template <bool GAL>
+template <bool P51, bool GAL>
 __device__ __forceinline__ void inner_own_digit(const RowsInnerArgs &A, const u64d *key, unsigned item, int t, unsigned x, int j_own, bool tensor_mode,
                                                 size_t tile0, unsigned hi4, unsigned lo4, double p, double pinv, double (&a0)[16], double (&a1)[16],
                                                 int &pending, const GaloisTab *gal) {
     const unsigned N = 1u << A.logN;
     if (tensor_mode) {
-        // d0, d1, d2 of the thread's 16 words from the operands (summed over the terms, balanced-reduced)
+        // d0, d1, d2 of the thread's 16 words from the operands: one term and p < 2^50 as they come (0.875p, 1.75p, 0.875p), otherwise summed
+        // over the terms and balanced-reduced
         const size_t st = (size_t)A.level * N / 2;  // pairs between the two components of a ciphertext
         const ulonglong2 *pa = (const ulonglong2 *)(A.ta + ((size_t)item * A.terms * 2 * A.level + x) * N + tile0);
         const ulonglong2 *pb = (const ulonglong2 *)(A.tb + ((size_t)item * A.terms * 2 * A.level + x) * N + tile0);
@@ -569,6 +591,12 @@ __device__ __forceinline__ void inner_own_digit(const RowsInnerArgs &A, const u6
                         const double x0 = u2d(b ? A0[s].y : A0[s].x), x1 = u2d(b ? A1[s].y : A1[s].x);
                         const double y0 = u2d(b ? B0[s].y : B0[s].x), y1 = u2d(b ? B1[s].y : B1[s].x);
                         const double t0 = mulmod(x0, y0, p, pinv), t1 = mulmod(x0, y1, p, pinv) + mulmod(x1, y0, p, pinv), t2 = mulmod(x1, y1, p, pinv);
+                        if (!P51 && A.terms == 1) {
+                            l0[i] = t0;
+                            l1[i] = t1;
+                            l2[i] = t2;
+                            continue;
+                        }
                         // |t| <= 2.5p on top of a reduced sum: below 2^53
                         l0[i] = reduce_balanced((tm ? l0[i] : 0.0) + t0, p, pinv);
                         l1[i] = reduce_balanced((tm ? l1[i] : 0.0) + t1, p, pinv);
@@ -578,12 +606,13 @@ __device__ __forceinline__ void inner_own_digit(const RowsInnerArgs &A, const u6
             }
 #pragma unroll
             for (int s = 0; s < 4; s++) {
-                const double v0 = l2[2 * s], vp0 = v0 * pinv, v1 = l2[2 * s + 1], vp1 = v1 * pinv;
-                // two terms below 0.875p each: the own digit's product and P*d
-                a0[8 * h + 2 * s] = mulmod_w(u2d(kr0[s].x), v0, vp0, p) + mulmod_w(l0[2 * s], Pm.w, Pm.wp, p);
-                a1[8 * h + 2 * s] = mulmod_w(u2d(kr1[s].x), v0, vp0, p) + mulmod_w(l1[2 * s], Pm.w, Pm.wp, p);
-                a0[8 * h + 2 * s + 1] = mulmod_w(u2d(kr0[s].y), v1, vp1, p) + mulmod_w(l0[2 * s + 1], Pm.w, Pm.wp, p);
-                a1[8 * h + 2 * s + 1] = mulmod_w(u2d(kr1[s].y), v1, vp1, p) + mulmod_w(l1[2 * s + 1], Pm.w, Pm.wp, p);
+                // two terms of at most the bound of key_term each: P*d (0.72p) and the own digit's product
+                a0[8 * h + 2 * s] = mulmod_w(l0[2 * s], Pm.w, Pm.wp, p);
+                a1[8 * h + 2 * s] = mulmod_w(l1[2 * s], Pm.w, Pm.wp, p);
+                a0[8 * h + 2 * s + 1] = mulmod_w(l0[2 * s + 1], Pm.w, Pm.wp, p);
+                a1[8 * h + 2 * s + 1] = mulmod_w(l1[2 * s + 1], Pm.w, Pm.wp, p);
+                key_term<P51>(kr0[s].x, kr1[s].x, l2[2 * s], p, pinv, a0[8 * h + 2 * s], a1[8 * h + 2 * s]);
+                key_term<P51>(kr0[s].y, kr1[s].y, l2[2 * s + 1], p, pinv, a0[8 * h + 2 * s + 1], a1[8 * h + 2 * s + 1]);
             }
         }
         pending = 2;
@@ -602,32 +631,33 @@ __device__ __forceinline__ void inner_own_digit(const RowsInnerArgs &A, const u6
         SCHED_FENCE();
 #pragma unroll
         for (int s = 0; s < 8; s++) {
-            const double v0 = reduce_balanced(u2d(xo[s].x), p, pinv), vp0 = v0 * pinv;
-            const double v1 = reduce_balanced(u2d(xo[s].y), p, pinv), vp1 = v1 * pinv;
-            a0[2 * s] = mulmod_w(u2d(kr0[s].x), v0, vp0, p);
-            a1[2 * s] = mulmod_w(u2d(kr1[s].x), v0, vp0, p);
-            a0[2 * s + 1] = mulmod_w(u2d(kr0[s].y), v1, vp1, p);
-            a1[2 * s + 1] = mulmod_w(u2d(kr1[s].y), v1, vp1, p);
+            double v0 = u2d(xo[s].x), v1 = u2d(xo[s].y);
+            if (P51) {
+                v0 = reduce_balanced(v0, p, pinv);
+                v1 = reduce_balanced(v1, p, pinv);
+            }
+            key_term<P51>(kr0[s].x, kr1[s].x, v0, p, pinv, a0[2 * s], a1[2 * s]);
+            key_term<P51>(kr0[s].y, kr1[s].y, v1, p, pinv, a0[2 * s + 1], a1[2 * s + 1]);
         }
     }
 }
 
 // The accumulators leave as z (folded tail), as acc + P*d, or as they are
-template <bool GAL, bool NTS>
+template <bool P51, bool GAL, bool NTS>
 __device__ __forceinline__ void inner_store(const RowsInnerArgs &A, unsigned item, int t, unsigned x, bool tensor_mode, size_t tile0, unsigned hi4,
                                             unsigned lo4, double p, double pinv, const double (&a0)[16], const double (&a1)[16], const GaloisTab *gal) {
     const unsigned N = 1u << A.logN;
     u64d *o0 = A.acc + (((size_t)item * 2 + 0) * A.E + x) * N + tile0;
     u64d *o1 = A.acc + (((size_t)item * 2 + 1) * A.E + x) * N + tile0;
     if (tensor_mode && !A.keep_acc) {
-        // z = (acc + P*d) * P^-1; accumulators are below 2^53: the prepared product is exact for them as they are
+        // z = (acc + P*d) * P^-1; accumulators are below 2^53: the prepared product is exact for them as they are, and below 1.5p
         const WMul Pi = A.Pinv[t];
 #pragma unroll
         for (int s = 0; s < 8; s++) {
             const double z00 = mulmod_w(a0[2 * s], Pi.w, Pi.wp, p), z01 = mulmod_w(a0[2 * s + 1], Pi.w, Pi.wp, p);
             const double z10 = mulmod_w(a1[2 * s], Pi.w, Pi.wp, p), z11 = mulmod_w(a1[2 * s + 1], Pi.w, Pi.wp, p);
-            stream_store<NTS>((ulonglong2 *)o0 + row_pair_index(hi4, lo4, s), make_ulonglong2(d2u(canon(z00, p, pinv)), d2u(canon(z01, p, pinv))));
-            stream_store<NTS>((ulonglong2 *)o1 + row_pair_index(hi4, lo4, s), make_ulonglong2(d2u(canon(z10, p, pinv)), d2u(canon(z11, p, pinv))));
+            stream_store<NTS>((ulonglong2 *)o0 + row_pair_index(hi4, lo4, s), make_ulonglong2(d2u(canon_near<P51>(z00, p, pinv)), d2u(canon_near<P51>(z01, p, pinv))));
+            stream_store<NTS>((ulonglong2 *)o1 + row_pair_index(hi4, lo4, s), make_ulonglong2(d2u(canon_near<P51>(z10, p, pinv)), d2u(canon_near<P51>(z11, p, pinv))));
         }
         return;
     }
@@ -651,11 +681,11 @@ __device__ __forceinline__ void inner_store(const RowsInnerArgs &A, unsigned ite
         }
 #pragma unroll
         for (int s = 0; s < 8; s++) {
-            // accumulators are below 2^53: the prepared product is exact for them as they are
+            // the same plus a canonical word: below 2.5p
             const double z00 = mulmod_w(a0[2 * s], Pi.w, Pi.wp, p) + u2d(dw0[s].x), z01 = mulmod_w(a0[2 * s + 1], Pi.w, Pi.wp, p) + u2d(dw0[s].y);
             const double z10 = mulmod_w(a1[2 * s], Pi.w, Pi.wp, p) + has1 * u2d(dw1[s].x), z11 = mulmod_w(a1[2 * s + 1], Pi.w, Pi.wp, p) + has1 * u2d(dw1[s].y);
-            stream_store<NTS>((ulonglong2 *)o0 + row_pair_index(hi4, lo4, s), make_ulonglong2(d2u(canon(z00, p, pinv)), d2u(canon(z01, p, pinv))));
-            stream_store<NTS>((ulonglong2 *)o1 + row_pair_index(hi4, lo4, s), make_ulonglong2(d2u(canon(z10, p, pinv)), d2u(canon(z11, p, pinv))));
+            stream_store<NTS>((ulonglong2 *)o0 + row_pair_index(hi4, lo4, s), make_ulonglong2(d2u(canon_near<P51>(z00, p, pinv)), d2u(canon_near<P51>(z01, p, pinv))));
+            stream_store<NTS>((ulonglong2 *)o1 + row_pair_index(hi4, lo4, s), make_ulonglong2(d2u(canon_near<P51>(z10, p, pinv)), d2u(canon_near<P51>(z11, p, pinv))));
         }
         return;
     }
@@ -672,7 +702,7 @@ template <bool P51, bool GAL, bool NTS>
 __device__ __forceinline__ void rows_inner_body(const RowsInnerArgs &A, const KeyTab &K, double *lds, double *tw1_lds, double *tw2_lds, int t,
                                                 unsigned x, const GaloisTab *gal = nullptr) {
     BODY_TAG(P51);
-    typedef RowMasks<P51, false> Mk;
+    typedef RowMasks<P51, ROW_FACTOR> Mk;
     const unsigned N = 1u << A.logN, N1 = N >> 8;
     const double p = A.modc[t].p, pinv = A.modc[t].pinv;
     const unsigned tid = threadIdx.x, hi4 = tid >> 4, lo4 = tid & 15;
@@ -702,7 +732,7 @@ __device__ __forceinline__ void rows_inner_body(const RowsInnerArgs &A, const Ke
     const int j_own = (int)x < A.level ? (int)x / A.alpha : -1;
     const bool tensor_mode = !GAL && A.ta != nullptr && j_own >= 0;
     int pending = 1;  // terms in the accumulators since their last reduction (the own digit's term counts)
-    inner_own_digit<GAL>(A, key, item, t, x, j_own, tensor_mode, tile0, hi4, lo4, p, pinv, a0, a1, pending, gal);
+    inner_own_digit<P51, GAL>(A, key, item, t, x, j_own, tensor_mode, tile0, hi4, lo4, p, pinv, a0, a1, pending, gal);
     // The other digits, software-pipelined so that no memory latency sits in front of arithmetic: the limb words of a
     // digit are requested while the previous digit is multiplied, its key words while the limb goes through the row
     // pass.  xr holds the column-pass output of the converted limb in the register layout of the row pass.
@@ -747,7 +777,7 @@ __device__ __forceinline__ void rows_inner_body(const RowsInnerArgs &A, const Ke
                 fwd_round<Mk::F2>(xx, tw2, p, pinv);
             }
 #pragma unroll
-            for (int e = 0; e < 16; e++) grp[lo4 * 17 + e] = reduce_balanced(xx[e], p, pinv);
+            for (int e = 0; e < 16; e++) grp[lo4 * 17 + e] = P51 ? reduce_balanced(xx[e], p, pinv) : xx[e];
         }
         ROW_GROUP_SYNC();
         int jn = j + 1;
@@ -762,16 +792,11 @@ __device__ __forceinline__ void rows_inner_body(const RowsInnerArgs &A, const Ke
         SCHED_FENCE();
 #pragma unroll
         for (int s = 0; s < 8; s++) {
-            // the transformed word is the prepared factor (|v| <= p/2 + 1, v/p computed once for both components), the
-            // key word the other one: each term is below 0.875p and the sum is reduced only when it could pass 2^53
             const double *vrow = grp + row_pair_lds(lo4, s);
-            const double v0 = vrow[0], vp0 = v0 * pinv, v1 = vrow[1], vp1 = v1 * pinv;
-            a0[2 * s] += mulmod_w(u2d(kr0[s].x), v0, vp0, p);
-            a1[2 * s] += mulmod_w(u2d(kr1[s].x), v0, vp0, p);
-            a0[2 * s + 1] += mulmod_w(u2d(kr0[s].y), v1, vp1, p);
-            a1[2 * s + 1] += mulmod_w(u2d(kr1[s].y), v1, vp1, p);
+            key_term<P51>(kr0[s].x, kr1[s].x, vrow[0], p, pinv, a0[2 * s], a1[2 * s]);
+            key_term<P51>(kr0[s].y, kr1[s].y, vrow[1], p, pinv, a0[2 * s + 1], a1[2 * s + 1]);
         }
-        if (++pending == (P51 ? 4 : 8)) {  // p < 2^51: 0.5p + 4 * 0.875p = 4p < 2^53; p < 2^50: 0.5p + 8 * 0.875p < 8p <= 2^53
+        if (++pending == KEY_TERMS<P51>) {
 #pragma unroll
             for (int i = 0; i < 16; i++) {
                 a0[i] = reduce_balanced(a0[i], p, pinv);
@@ -782,7 +807,7 @@ __device__ __forceinline__ void rows_inner_body(const RowsInnerArgs &A, const Ke
         ROW_GROUP_SYNC();  // the row's lanes have read its words before the next digit overwrites them
         j = jn;
     }
-    inner_store<GAL, NTS>(A, item, t, x, tensor_mode, tile0, hi4, lo4, p, pinv, a0, a1, gal);
+    inner_store<P51, GAL, NTS>(A, item, t, x, tensor_mode, tile0, hi4, lo4, p, pinv, a0, a1, gal);
 }
 
 // grid: x = (row tile mod kt) + kt * item, y = row tile / kt, z = extended limb
@@ -875,7 +900,7 @@ __device__ __forceinline__ void rows_final_body(const RowsFinalArgs &A, double *
             }
         }
         SCHED_FENCE();
-        rows_fwd_to_lds<P51, true>(A.tmpA + ((size_t)row * A.nc + i) * N + tile0, lds, tw1_lds, tw2, p, pinv, hi4, lo4, A.stream == STREAM_ALL);
+        rows_fwd_to_lds<P51, ROW_LAZY>(A.tmpA + ((size_t)row * A.nc + i) * N + tile0, lds, tw1_lds, tw2, p, pinv, hi4, lo4, A.stream == STREAM_ALL);
 #pragma unroll
         for (int s = 0; s < 8; s++) {
             const double *rr = lds + hi4 * V2_GS + row_pair_lds(lo4, s);
@@ -900,7 +925,8 @@ __device__ __forceinline__ void rows_final_body(const RowsFinalArgs &A, double *
                 v0 += u2d(ar[s].x);
                 v1 += u2d(ar[s].y);
             }
-            pair_store<NTS>(out, row_pair_index(hi4, lo4, s), make_ulonglong2(d2u(canon(v0, p, pinv)), d2u(canon(v1, p, pinv))));
+            // a product below 1.5p and an addend, or (zsub: no addend) a word and a product of a word of at most ROWX: 2.5p
+            pair_store<NTS>(out, row_pair_index(hi4, lo4, s), make_ulonglong2(d2u(canon_near<P51>(v0, p, pinv)), d2u(canon_near<P51>(v1, p, pinv))));
         }
         ROW_GROUP_SYNC();
     }

@@ -28,12 +28,12 @@ struct InnerWgLds {
 
 // wg_fwd_block with the twiddles at hand: twc the column round's (a block of 2^12 words has one), the row rounds' in LDS.  One
 // barrier inside; the caller puts one between a digit's last use of the matrix and the next digit.
-template <int LOGM, bool P51, class F>
+template <int LOGM, bool P51, int ENTRY256, class F>
 __device__ __forceinline__ void inner_fwd_block(double (&x)[16], const double (&twc)[15], double *lds, double p, double pinv, F request) {
     static_assert(LOGM == 12, "one column round");
     typedef ColsGeom<0> Geo;
-    typedef ColsMasks<0, P51, 308> Mk;
-    typedef RowMasks<P51, false> Rm;
+    typedef ColsMasks<0, P51, ENTRY256> Mk;
+    typedef RowMasks<P51, ROW_FACTOR> Rm;
     typedef InnerWgLds<LOGM> Lay;
     const unsigned tid = threadIdx.x, row = tid >> 4, lo4 = tid & 15;
     const Geo geo(tid & 255u, tid >> 8);
@@ -63,7 +63,7 @@ __device__ __forceinline__ void inner_fwd_block(double (&x)[16], const double (&
         fwd_round<Rm::F2>(x, t2, p, pinv);
     }
 #pragma unroll
-    for (int e = 0; e < 16; e++) grp[lo4 * 17 + e] = reduce_balanced(x[e], p, pinv);
+    for (int e = 0; e < 16; e++) grp[lo4 * 17 + e] = P51 ? reduce_balanced(x[e], p, pinv) : x[e];
     ROW_GROUP_SYNC();
 }
 
@@ -86,7 +86,7 @@ __device__ __forceinline__ void inner_wg_body(const InnerWgArgs &A, const KeyTab
     const int j_own = (int)x < R.level ? (int)x / R.alpha : -1;
     const bool tensor_mode = !GAL && R.ta != nullptr && j_own >= 0;
     int pending = 1;
-    inner_own_digit<GAL>(R, key, item, t, x, j_own, tensor_mode, tile0, prow, lo4, p, pinv, a0, a1, pending, gal);
+    inner_own_digit<P51, GAL>(R, key, item, t, x, j_own, tensor_mode, tile0, prow, lo4, p, pinv, a0, a1, pending, gal);
     // twiddles of the first S stages on the way to this block, see conv_final_body
     double w[S + 1], wp[S + 1];
 #pragma unroll
@@ -155,7 +155,7 @@ __device__ __forceinline__ void inner_wg_body(const InnerWgArgs &A, const KeyTab
         const ulonglong2 *k1 = (const ulonglong2 *)(key + (((size_t)j * 2 + 1) * R.T + t) * N + tile0);
         ulonglong2 kr0[8], kr1[8];
         __syncthreads();  // everybody is done with the matrix (before the first digit: the twiddles are in place)
-        inner_fwd_block<LOGM, P51>(xx, twc, lds, p, pinv, [&]() {
+        inner_fwd_block<LOGM, P51, block_entry<P51, NSRC, false, S>()>(xx, twc, lds, p, pinv, [&]() {
 #pragma unroll
             for (int s = 0; s < 8; s++) {
                 kr0[s] = (k0 + 16 * s)[pr];
@@ -165,15 +165,11 @@ __device__ __forceinline__ void inner_wg_body(const InnerWgArgs &A, const KeyTab
         const double *grp = lds + prow * V2_GS;
 #pragma unroll
         for (int s = 0; s < 8; s++) {
-            // the transformed word is the prepared factor, each term is below 0.875p (as in rows_inner_body)
             const double *vrow = grp + row_pair_lds(lo4, s);
-            const double v0 = vrow[0], vp0 = v0 * pinv, v1 = vrow[1], vp1 = v1 * pinv;
-            a0[2 * s] += mulmod_w(u2d(kr0[s].x), v0, vp0, p);
-            a1[2 * s] += mulmod_w(u2d(kr1[s].x), v0, vp0, p);
-            a0[2 * s + 1] += mulmod_w(u2d(kr0[s].y), v1, vp1, p);
-            a1[2 * s + 1] += mulmod_w(u2d(kr1[s].y), v1, vp1, p);
+            key_term<P51>(kr0[s].x, kr1[s].x, vrow[0], p, pinv, a0[2 * s], a1[2 * s]);
+            key_term<P51>(kr0[s].y, kr1[s].y, vrow[1], p, pinv, a0[2 * s + 1], a1[2 * s + 1]);
         }
-        if (++pending == (P51 ? 4 : 8)) {
+        if (++pending == KEY_TERMS<P51>) {
 #pragma unroll
             for (int i = 0; i < 16; i++) {
                 a0[i] = reduce_balanced(a0[i], p, pinv);
@@ -182,7 +178,7 @@ __device__ __forceinline__ void inner_wg_body(const InnerWgArgs &A, const KeyTab
             pending = 0;
         }
     }
-    inner_store<GAL, false>(R, item, t, x, tensor_mode, tile0, prow, lo4, p, pinv, a0, a1, gal);
+    inner_store<P51, GAL, false>(R, item, t, x, tensor_mode, tile0, prow, lo4, p, pinv, a0, a1, gal);
 }
 
 // Consecutive workgroups go to the 8 XCDs in turn: an item's blocks sit on one XCD (they read the same sources), the items of an

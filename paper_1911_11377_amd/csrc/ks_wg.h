@@ -67,11 +67,24 @@ __device__ __forceinline__ double conv_sum(const double *y, const WMul *Wc, doub
     return chain_value(c, p, pinv) - hsub;
 }
 
-// One converted coefficient, balanced-reduced: sum_a y_a * conv_a - h.  A single source has conv = 1 (the empty product).
+// One converted coefficient: sum_a y_a * conv_a - h, balanced-reduced but for one source and p < 2^50: y - h lies between -2^50 and
+// 2^51 then, 2 units of 2^50 (in which the bounds of words modulo any p < 2^50 may be read).  A single source has conv = 1 (the empty product).
 template <int NSRC, bool P51>
 __device__ __forceinline__ double conv_word(const double (&y)[NSRC], const WMul (&Wc)[NSRC], double hsub, double p, double pinv) {
-    if (NSRC == 1) return reduce_balanced(y[0] - hsub, p, pinv);  // below 2^51 + p
+    if (NSRC == 1) return P51 ? reduce_balanced(y[0] - hsub, p, pinv) : y[0] - hsub;  // below 2^51 + p
     return reduce_balanced(conv_sum<NSRC, P51>(y, Wc, hsub, p, pinv), p, pinv);
+}
+// bound of a word after the first S stages that join 2^S words of at most b
+template <bool P51>
+constexpr double join_bound(double b, int S) {
+    for (int t = 0; t < S; t++) b += 0.5 + 1.5 * b / LazyRange<P51>::LIM;
+    return b;
+}
+// the same in 1/256 for a block of conv_word's or (TAIL) tail_word's; p < 2^51: reduced words, and reduced again after two stages
+template <bool P51, int NSRC, bool TAIL, int S>
+constexpr int block_entry() {
+    const double b = P51 || (NSRC > 1 && !TAIL) ? LAZY_REDUCED : TAIL ? 2.75 : 2.0;
+    return (int)(256.0 * (P51 && S >= 2 ? LAZY_REDUCED : join_bound<P51>(b, S)) + 0.999);
 }
 
 // The same for ModDown followed by rescale as one conversion (see modup_cols_kernel MODE 3): y[0] is the rescale's conversion
@@ -80,7 +93,10 @@ template <int NSRC, bool P51>
 __device__ __forceinline__ double tail_word(const double (&y)[NSRC], const WMul (&Wc)[NSRC], double hA, WMul Pinv, double hB, double p, double pinv) {
     // one special prime: its constant is 1; below 2^51 + p
     const double v = NSRC == 2 ? y[1] - hA : conv_sum<NSRC - 1, P51>(&y[1], &Wc[1], hA, p, pinv);
-    return reduce_balanced(mulmod_w(reduce_balanced(v, p, pinv), Pinv.w, Pinv.wp, p) + y[0] - hB, p, pinv);
+    if (P51) return reduce_balanced(mulmod_w(reduce_balanced(v, p, pinv), Pinv.w, Pinv.wp, p) + y[0] - hB, p, pinv);
+    // p < 2^50: y_B is below 2^51, and v (2 units of 2^50 with one special prime, below 2^53 with more, which are reduced) gives a
+    // product of at most 0.75p: 2.75
+    return mulmod_w(NSRC == 2 ? v : reduce_balanced(v, p, pinv), Pinv.w, Pinv.wp, p) + y[0] - hB;
 }
 
 // FIN 0: out = (x - r) * Binv;  1: out = x - r * Binv (x holds x * Binv + addend);  2: out = (x * xmv - r) * Binv (+ addend);
@@ -149,7 +165,7 @@ __device__ __forceinline__ void conv_final_body(const ConvFinalArgs &A, double *
     ulonglong2 *out = (ulonglong2 *)(F.out + (size_t)row * F.out_row_stride + off);
     const unsigned pr = row_pair_index(prow, lo4, 0);
     ulonglong2 xr[8];
-    wg_fwd_block<LOGM, P51, true>(x, tw, base, lds, p, pinv, [&]() {
+    wg_fwd_block<LOGM, P51, block_entry<P51, NSRC, FIN == 4, S>(), ROW_LAZY>(x, tw, base, lds, p, pinv, [&]() {
         stream_if(F.stream == STREAM_ALL, [&](auto nt) {
 #pragma unroll
             for (int s = 0; s < 8; s++) xr[s] = stream_load<nt>(xin + 16 * s + pr);
@@ -171,7 +187,8 @@ __device__ __forceinline__ void conv_final_body(const ConvFinalArgs &A, double *
             v0 += u2d(ar.x);
             v1 += u2d(ar.y);
         }
-        stream_store<NTS>(out + 16 * s + pr, make_ulonglong2(d2u(canon(v0, p, pinv)), d2u(canon(v1, p, pinv))));
+        // a product below 1.5p and an addend, or a word and a product of a word of at most ROWX: 2.5p
+        stream_store<NTS>(out + 16 * s + pr, make_ulonglong2(d2u(canon_near<P51>(v0, p, pinv)), d2u(canon_near<P51>(v1, p, pinv))));
     };
     if (FIN < 2 || FIN == 4 || !add) {
 #pragma unroll

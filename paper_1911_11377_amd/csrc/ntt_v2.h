@@ -192,6 +192,7 @@ struct LazyRange {
     static constexpr double LIM = P51 ? 4.0 : 8.0;    // 2^53 / p
     static constexpr double MIDF = P51 ? 2.5 : 3.5;   // forward, between column and row pass
     static constexpr double ROWX = P51 ? 2.0 : 6.2;   // forward, results that a pointwise step takes as they are
+    static constexpr double FACTOR = P51 ? 0.51 : 2.2;  // forward, results that are multiplied by words of a switching key
     static constexpr double INV0 = 1.25, INV1 = 2.0, MIDI = P51 ? 2.0 : 4.0;  // inverse: entry, between rounds, between row and column pass
 };
 #define LAZY_REDUCED 0.51  // |x| <= p/2 + 1
@@ -380,10 +381,16 @@ struct ColsMasks {
     static_assert(PLAN >= 0, "no reduction schedule");
     static constexpr int F1 = PLAN & 15, F2 = (PLAN >> 4) << (4 - Q);
 };
-// ... and of the row pass, from MIDF.  LAZY: the results serve a pointwise step as they are, else they are reduced or made canonical
-template <bool P51, bool LAZY>
+// ... and of the row pass, from MIDF.  What becomes of the results:
+//   ROW_REDUCED  they are reduced or made canonical whatever they are;
+//   ROW_LAZY     a pointwise step takes them as they are (ROWX);
+//   ROW_NEAR     p < 2^50: canon_near takes them;  ROW_FACTOR: a key word's product takes them (FACTOR).  Both cost one reduction of
+//                half of the words more than ROW_REDUCED and save that of all of them.  p < 2^51: as ROW_REDUCED.
+enum { ROW_REDUCED, ROW_LAZY, ROW_NEAR, ROW_FACTOR };
+template <bool P51, int X>
 struct RowMasks {
-    static constexpr int PLAN = fwd_plan(P51, LazyRange<P51>::MIDF, 8, LAZY ? LazyRange<P51>::ROWX : LazyRange<P51>::LIM);
+    typedef LazyRange<P51> R;
+    static constexpr int PLAN = fwd_plan(P51, R::MIDF, 8, X == ROW_LAZY ? R::ROWX : P51 || X == ROW_REDUCED ? R::LIM : X == ROW_NEAR ? 2.9 : R::FACTOR);
     static_assert(PLAN >= 0, "no reduction schedule");
     static constexpr int F1 = PLAN & 15, F2 = PLAN >> 4;
 };
@@ -450,7 +457,7 @@ __device__ __forceinline__ void ntt_v2_cols(const NttV2Args &A, double *lds, int
             inv_stages<0, INV_COL1, P51>(x, tw1, p, pinv, ninv, wlast);
 #pragma unroll
             for (int e = 0; e < 16; e++) {
-                const double v = canon(x[e] + cadd, p, pinv);
+                const double v = canon_near<P51>(x[e] + cadd, p, pinv);  // 1.5p and less than p
                 stream_store<NT>(&dst[geo.g1(e)], F64 ? (u64d)__double_as_longlong(v) : d2u(v));
             }
         }
@@ -471,7 +478,7 @@ __device__ __forceinline__ void ntt_v2_rows(const NttV2Args &A, double *lds, int
     load_twiddles(tw, N1 + blockIdx.x * 16 + hi4, lo4, tw1, tw2);
     const unsigned i0 = blockIdx.z * (unsigned)A.items_per_z;
     const unsigned i1 = (i0 + A.items_per_z < (unsigned)A.items) ? i0 + A.items_per_z : (unsigned)A.items;
-    typedef RowMasks<P51, false> Mk;
+    typedef RowMasks<P51, ROW_NEAR> Mk;
     const size_t tile0 = (size_t)blockIdx.x * 4096;
     double *grp = lds + hi4 * V2_GS;
     for (unsigned it = i0; it < i1; it++) {
@@ -489,7 +496,7 @@ __device__ __forceinline__ void ntt_v2_rows(const NttV2Args &A, double *lds, int
             for (int e = 0; e < 16; e++) x[e] = grp[lo4 * 17 + e];
             fwd_round<Mk::F2>(x, tw2, p, pinv);
 #pragma unroll
-            for (int e = 0; e < 16; e++) grp[lo4 * 17 + e] = canon(x[e], p, pinv);
+            for (int e = 0; e < 16; e++) grp[lo4 * 17 + e] = canon_near<P51>(x[e], p, pinv);
             ROW_GROUP_SYNC();
             // canonical words out in the row-pair layout: 16 bytes per lane and store
 #pragma unroll

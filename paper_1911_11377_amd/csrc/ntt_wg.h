@@ -20,15 +20,15 @@
 __device__ __forceinline__ unsigned wg_pad(unsigned row, unsigned col) { return row * V2_GS + (col >> 4) * 17u + (col & 15u); }
 
 // Forward transform of block `base - 2^S` of a ring of M * 2^S words (base = 1: the whole ring): x in the column layout (word
-// (geo.r + G*e, geo.c0 + geo.c)), at most 2.7p (p < 2^50) or 1.2p (p < 2^51) in magnitude; the results end in LDS, balanced-reduced or
-// (LAZY) at most LazyRange::ROWX, word (row g, position q) at wg_pad(g, q).  Every row is finished by its own 16 lanes (a row-group sync suffices to read it).
+// (geo.r + G*e, geo.c0 + geo.c)), at most ENTRY256 / 256 p in magnitude; the results end in LDS as X says (p < 2^51 and not ROW_LAZY:
+// balanced-reduced), word (row g, position q) at wg_pad(g, q).  Every row is finished by its own 16 lanes (a row-group sync suffices to read it).
 // `request` is called once the first row round is done: the place for memory requests whose latency the rest covers.
-template <int LOGM, bool P51, bool LAZY, class F>
+template <int LOGM, bool P51, int ENTRY256, int X, class F>
 __device__ __forceinline__ void wg_fwd_block(double (&x)[16], const double *tw, unsigned base, double *lds, double p, double pinv, F request) {
     constexpr int Q = LOGM - 12;
     typedef ColsGeom<Q> Geo;
-    typedef ColsMasks<Q, P51, P51 ? 308 : 692> Mk;
-    typedef RowMasks<P51, LAZY> Rm;
+    typedef ColsMasks<Q, P51, ENTRY256> Mk;
+    typedef RowMasks<P51, X> Rm;
     constexpr unsigned MR = (1u << LOGM) >> 8;
     const unsigned tid = threadIdx.x, row = tid >> 4, lo4 = tid & 15;
     const Geo geo(tid & 255u, tid >> 8);
@@ -87,7 +87,7 @@ __device__ __forceinline__ void wg_fwd_block(double (&x)[16], const double *tw, 
     for (int e = 0; e < 16; e++) x[e] = grp[lo4 * 17 + e];
     fwd_round<Rm::F2>(x, tw2, p, pinv);
 #pragma unroll
-    for (int e = 0; e < 16; e++) grp[lo4 * 17 + e] = LAZY ? x[e] : reduce_balanced(x[e], p, pinv);
+    for (int e = 0; e < 16; e++) grp[lo4 * 17 + e] = X == ROW_LAZY || (X != ROW_REDUCED && !P51) ? x[e] : reduce_balanced(x[e], p, pinv);
     ROW_GROUP_SYNC();
 }
 
@@ -254,18 +254,19 @@ __device__ __forceinline__ void ntt_wg_body(const NttV2Args &A, double *lds, int
             NTT_SCHED_FENCE();
 #pragma unroll
             for (int e = 0; e < 16; e++) x[e] = u2d(raw[e]);
-            wg_fwd_block<LOGN, P51, false>(x, tw, 1u, lds, p, pinv, []() {});
+            wg_fwd_block<LOGN, P51, 256, ROW_NEAR>(x, tw, 1u, lds, p, pinv, []() {});
             // canonical words out in word pairs: 16 bytes per lane, 256 contiguous bytes per row and store
 #pragma unroll
             for (int s = 0; s < 8; s++) {
                 const double *rr = grp + row_pair_lds(lo4, s);
-                stream_store<NT>((ulonglong2 *)dst + 16 * s + pr, make_ulonglong2(d2u(canon_small(rr[0], p)), d2u(canon_small(rr[1], p))));
+                const double v0 = P51 ? canon_small(rr[0], p) : canon_near<P51>(rr[0], p, pinv), v1 = P51 ? canon_small(rr[1], p) : canon_near<P51>(rr[1], p, pinv);
+                stream_store<NT>((ulonglong2 *)dst + 16 * s + pr, make_ulonglong2(d2u(v0), d2u(v1)));
             }
         } else {
             wg_inv_limb<LOGN, P51, SRC>(x, src, tw, lds, p, pinv, ninv, wlast, li, it, gal, ten);
 #pragma unroll
             for (int e = 0; e < 16; e++) {
-                const double v = canon(x[e] + cadd, p, pinv);
+                const double v = canon_near<P51>(x[e] + cadd, p, pinv);  // 1.5p and less than p
                 stream_store<NT>(scalar_base(dst + Geo::G * 256u * e) + voff, F64 ? (u64d)__double_as_longlong(v) : d2u(v));
             }
         }

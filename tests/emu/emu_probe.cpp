@@ -83,3 +83,13 @@ static double probe_inv_named(int round, int S0, double *x, const double *tw, do
 extern "C" double emu_probe_inv_round(int p51, int round, int S0, double *x, const double *tw, double ninv, double wlast, double p) {
     return p51 ? probe_inv_named<true>(round, S0, x, tw, ninv, wlast, p) : probe_inv_named<false>(round, S0, x, tw, ninv, wlast, p);
 }
+
+// canonical form of a word of at most 2.9p; one word's term of an inner product with a switching key, on top of a
+extern "C" double emu_probe_canon_near(int p51, double x, double p) { return p51 ? canon_near<true>(x, p, 1.0 / p) : canon_near<false>(x, p, 1.0 / p); }
+extern "C" double emu_probe_key_term(int p51, double k, double v, double a, double p) {
+    double a1 = 0.0;
+    if (p51) key_term<true>((u64d)k, (u64d)k, v, p, 1.0 / p, a, a1);
+    else key_term<false>((u64d)k, (u64d)k, v, p, 1.0 / p, a, a1);
+    return a;
+}
+extern "C" double emu_probe_key_factor(int p51) { return p51 ? LazyRange<true>::FACTOR : LazyRange<false>::FACTOR; }

@@ -484,3 +484,37 @@ def test_inverse_rounds_take_what_the_round_before_leaves(be, p51, chain):
                         want[lo], want[lo + span] = (u * tw[15], v * tw[16]) if last else (u, v * tw[(1 << s) - 1 + lo // (2 * span)])
                 assert all(v == int(v) and abs(v) <= bound * p for v in buf)
                 assert all((int(v) - w) % p == 0 for v, w in zip(buf, want))
+
+
+@pytest.mark.parametrize("bits,p51", [(20, 0), (40, 0), (50, 0), (51, 1)])
+def test_canonical_form_around_multiples_of_the_prime(be, bits, p51):
+    """words at and next to every multiple of p up to 2.9p, where the quotient's floor changes, and at the ends of the range"""
+    probe = be.lib.emu_probe_canon_near
+    probe.restype = ctypes.c_double
+    rng = np.random.default_rng(bits)
+    for p in (2**bits - 27, 2**bits - 2**14 + 1, 2 ** (bits - 1) + 9, 2 ** (bits - 1) + 2**14 + 1):
+        top = 29 * p // 10
+        words = [k * p + d for k in range(-3, 4) for d in range(-9, 10)] + [k * p // 2 + d for k in range(-5, 6, 2) for d in (-1, 0, 1)]
+        words += [top, -top] + [int(v) for v in rng.integers(-top, top + 1, 3000)]
+        for x in words:
+            if abs(x) <= top:
+                assert probe(p51, ctypes.c_double(x), ctypes.c_double(p)) == x % p
+
+
+@pytest.mark.parametrize("p51", [0, 1])
+def test_key_products_stay_exact_at_the_ends_of_their_range(be, p51):
+    """key words 0 .. p - 1 times words at the largest bound that a row pass leaves them at, on accumulators at what the terms before can sum to"""
+    probe = be.lib.emu_probe_key_term
+    probe.restype = be.lib.emu_probe_key_factor.restype = ctypes.c_double
+    factor, term, terms = be.lib.emu_probe_key_factor(p51), 0.875 if p51 else 1.33, 4 if p51 else 5
+    rng = np.random.default_rng(p51)
+    for p in (2 ** (50 + p51) - 27, 2 ** (49 + p51) + 9):
+        top = int(factor * p)
+        vs = [top, -top, top - 1, 1 - top, p // 2, -(p // 2), 0] + [int(v) for v in rng.integers(-top, top + 1, 40)]
+        ks = [p - 1, p - 2, p // 2, p // 2 + 1, 1, 0] + [int(v) for v in rng.integers(0, p, 40)]
+        base = int((0.5 + (terms - 1) * term) * p)
+        for k, v in itertools.product(ks, vs):
+            for a in (0, base, -base):
+                got = probe(p51, ctypes.c_double(k), ctypes.c_double(v), ctypes.c_double(a), ctypes.c_double(p))
+                assert got == int(got) and abs(got) < 2**53 and abs(int(got) - a) <= term * p
+                assert (int(got) - a - k * v) % p == 0
