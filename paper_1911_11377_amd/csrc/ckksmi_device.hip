@@ -879,6 +879,14 @@ int dev_upload_tables(ckksmi_ctx *c) {
         std::vector<WMul> p24(T);
         for (int t = 0; t < T; t++) p24[t] = make_wmul(((u64)1 << 24) % c->mod[t], c->mod[t]);
         c->d_pow24 = upload(c, p24.data(), p24.size(), ok);
+        std::vector<double> p32(3 * T);
+        for (int t = 0; t < T; t++) {
+            const u64 q = c->mod[t], b = ((u64)1 << 32) % q, b2 = hm::mulmod(b, b, q);
+            p32[3 * t] = make_wmul(b, q).w;
+            p32[3 * t + 1] = make_wmul(b2, q).w;
+            p32[3 * t + 2] = make_wmul(hm::mulmod(b2, b, q), q).w;
+        }
+        c->d_pow32 = upload(c, p32.data(), p32.size(), ok);
     }
     for (int t = 0; t < T; t++)
         if (c->mod[t] >= ((u64)1 << 50)) c->p51mask.w[t >> 6] |= 1ull << (t & 63);
@@ -1734,7 +1742,7 @@ extern "C" int ckksmi_conv2d_mac_rows(ckksmi_ctx *c, const uint64_t *in, const i
         char *wp = (char *)ws;  // every part is a multiple of 16 bytes
         const double units = (double)O * out_rows * Wo * 2 * level;
         MacMfmaArgs A;
-        A.in = (const u64d *)in; A.out = (u64d *)out; A.modc = c->d_mod; A.pow24 = c->d_pow24;
+        A.in = (const u64d *)in; A.out = (u64d *)out; A.modc = c->d_mod; A.pow24 = c->d_pow24; A.pow32 = c->d_pow32;
         A.logN = c->logN; A.level = level; A.C = C; A.H = H; A.W = W; A.O = O; A.kh = kh; A.kw = kw; A.stride = stride; A.pad = pad; A.Wo = Wo;
         A.in_row0 = in_row0; A.in_rows = in_rows; A.out_row0 = out_row0; A.out_rows = out_rows; A.Kb = ms.Kb; A.Mg = ms.Mg; A.quad = ms.quad;
         A.positions = positions; A.nrun = nrun; A.run = run; A.TY = ms.TY; A.TX = ms.TX; A.SR = ms.SR; A.SC = ms.SC; A.spr = spr; A.total_wgs = xdim; A.real_wgs = real;
@@ -1787,8 +1795,12 @@ extern "C" int ckksmi_conv2d_mac_rows(ckksmi_ctx *c, const uint64_t *in, const i
                 default: MAC_RES(4, true); break;
             }
 #undef MAC_RES
-        } else
-            KL(c, CKKSMI_K_MAC_MFMA, units, conv_mac_mfma_kernel, dim3((unsigned)xdim), dim3(256), S(stream), A);
+        } else {
+            // (a prime of 51 bits leaves no room for the wide groups of more than MM_RES_STEPS steps)
+            bool p51 = false;
+            for (int i = 0; i < level; i++) p51 = p51 || c->mod[i] >= ((u64)1 << 50);
+            KL2(c, CKKSMI_K_MAC_MFMA, units, ms.Kb <= MM_WIDE_STEPS && !p51, conv_mac_mfma_kernel<true>, conv_mac_mfma_kernel<false>, dim3((unsigned)xdim), dim3(256), S(stream), A);
+        }
         return g.rc();
     }
     if (ws_bytes < n_weights * level * sizeof(WMul)) return CKKSMI_EWORKSPACE;

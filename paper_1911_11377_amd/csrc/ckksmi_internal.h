@@ -94,6 +94,7 @@ struct ckksmi_ctx {
     // ---- device tables ----
     ModConst *d_mod = nullptr;   // [T]
     WMul *d_pow24 = nullptr;     // [T] 2^24 mod p (matrix-core MAC: recombination of the digit diagonals)
+    double *d_pow32 = nullptr;   // [T][3] 2^32, 2^64, 2^96 mod p, balanced (the same, four diagonals at a time)
     WMul *d_tw_fwd = nullptr;    // [T][N]  psi^brev(x), x in [1,N)
     WMul *d_tw_inv = nullptr;    // [T][N]  psi^-brev(x); entry 0 holds N^-1
     WMul *d_tw_inv_last = nullptr;  // [T]   psi^-brev(1) * N^-1  (last inverse stage)

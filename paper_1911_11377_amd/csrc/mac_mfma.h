@@ -53,6 +53,7 @@
 #define MM_BIAS 0x0080808080808080ull
 #define MM_FRAG (MM_MB * MM_DIG * 64)  // 16-byte A fragment chunks per step and channel group
 #define MM_RES_STEPS 4                 // steps whose A fragments the resident kernel keeps in LDS
+#define MM_WIDE_STEPS 8                // steps (512 taps) whose diagonals combine four at a time
 #define MM_STRIP_STEPS 2               // the same for the strip kernel
 #define MM_STRIP_POS 4                 // output positions (one per wave) that share a staged strip
 #define MM_STRIP_LINES 192             // 128-byte lines of a strip buffer (24 KB; two buffers)
@@ -71,12 +72,18 @@ static inline unsigned emu_perm_b32(unsigned hi, unsigned lo, unsigned sel) {
 #define MM_PERM(hi, lo, sel) emu_perm_b32(hi, lo, sel)
 #define MM_UNIFORM(v) (v)
 // matrix instructions that this wave leaves out and others of the block issue (the emulated exchange is a barrier)
+#define MM_LDS_LOAD16(src, base, lane) ((base)[lane] = *(const v4i *)(src))
+#define MM_LOADS_DONE() ((void)0)
 #define MM_MFMA_ABSENT(n) do { for (int a_ = 0; a_ < (n); a_++) (void)emu_mfma_i32_16x16x64_i8(v4i{}, v4i{}, v4i{}); } while (0)
 #else
 typedef int v4i __attribute__((ext_vector_type(4)));
 #define MM_MFMA(a, b, c) __builtin_amdgcn_mfma_i32_16x16x64_i8(a, b, c, 0, 0, 0)
 #define MM_PERM(hi, lo, sel) __builtin_amdgcn_perm(hi, lo, sel)
 #define MM_MFMA_ABSENT(n) (void)0
+// 16 bytes per active lane from memory to base[lane] in LDS (base: the same for the wave) without registers in between; complete after MM_LOADS_DONE
+#define MM_LDS_LOAD16(src, base, lane) \
+    __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(src), (__attribute__((address_space(3))) void *)(base), 16, 0, 0)
+#define MM_LOADS_DONE() __builtin_amdgcn_s_waitcnt(0x0f70)  // vmcnt(0)
 #define MM_UNIFORM(v) __builtin_amdgcn_readfirstlane(v)  // the same in every lane of the wave: keep it in a scalar register
 #endif
 
@@ -104,6 +111,7 @@ struct MacMfmaArgs {
     const unsigned *tapoff;  // [Kb*64] strip kernel: byte offset of the tap's line in the strip, ((c*SR + u)*SC + v)*128
     const ModConst *modc;
     const WMul *pow24;    // 2^24 mod p per modulus
+    const double *pow32;  // 2^32, 2^64, 2^96 mod p per modulus, balanced
     int logN, level;
     int C, H, W, O, kh, kw, stride, pad, Wo;
     int in_row0, in_rows, out_row0, out_rows;
@@ -307,13 +315,70 @@ __device__ __forceinline__ void mm_step(const v4i *a, unsigned lane, const v4i (
     }
 }
 
-// value = sum_d 256^d D_d + wsum: three diagonals combine exactly in a double (< 2^48), the groups by Horner in 2^24.
+// sum of four diagonals from d0 on, d0 + 2^8 d1 + 2^16 d2 + 2^24 d3 as a double: below 2^51, so that on top of the bits of 3 * 2^51 it is that
+// double's mantissa.  One v_mad_i64_i32 each (as fast as v_fma_f64 here) and one subtraction; four conversions and three products otherwise.
+// a prime's constants for the recombination, in scalar registers: fetched once, before the first results are stored
+struct MacConst {
+    double p, pinv, M, c1, c2, c3;  // WIDE
+    WMul P24;                       // otherwise
+};
+template <bool WIDE>
+__device__ __forceinline__ MacConst mac_const(const MacMfmaArgs &A, unsigned i) {
+    MacConst C;
+    C.p = table_load(&A.modc[i].p, 0);
+    C.pinv = table_load(&A.modc[i].pinv, 0);
+    C.M = 3377699720527872.0 * C.p;  // 3 * 2^50 p
+    C.c1 = WIDE ? table_load(A.pow32, 3 * i) : 0.0;
+    C.c2 = WIDE ? table_load(A.pow32, 3 * i + 1) : 0.0;
+    C.c3 = WIDE ? table_load(A.pow32, 3 * i + 2) : 0.0;
+    C.P24 = WIDE ? WMul{0.0, 0.0} : table_load(A.pow24 + i);
+    return C;
+}
+struct WideShifts { int k0, k8, k16, k24; };
+__device__ __forceinline__ WideShifts wide_shifts() {
+    WideShifts k{1, 1 << 8, 1 << 16, 1 << 24};
+#ifndef CKKSMI_EMULATE
+    asm("" : "+s"(k.k0), "+s"(k.k8), "+s"(k.k16), "+s"(k.k24));  // products, not shifts of 64 bits
+#endif
+    return k;
+}
+__device__ __forceinline__ double wide_group(int d0, int d1, int d2, int d3, const WideShifts &k) {
+    long long g = (long long)d0 * k.k0 + 0x4338000000000000ll;
+    g += (long long)d1 * k.k8;
+    g += (long long)d2 * k.k16;
+    g += (long long)d3 * k.k24;
+    return __longlong_as_double(g) - 6755399441055744.0;
+}
+
+// value = sum_d 256^d D_d + wsum.
+// WIDE (at most MM_WIDE_STEPS steps): |D_d| <= 7 * 2^14 * 512 < 2^25.9, four diagonals make an exact double below 2^50 and the groups join in ONE
+// accumulator (as in mr_recombine): it starts at 3 * 2^50 p and stays within half of it, so that a step drops less than p/2, exactly
+// kept in l, and the result is at most 2.6p.  42 instructions per word; 59 with the groups of three by Horner, which any number of steps
+// takes (three diagonals < 2^48 in a double, 2^24 between the groups).
 // Lane (g, column) holds rows 4g + r of each 16-channel block; outp points at channel 4g of the group, mstride = words
 // between output channels.  ALL: every channel of the group exists (no test per value: the eight chains stay one
 // straight-line block that the scheduler can interleave).
-template <bool ALL, int MB0 = 0, int MB1 = MM_MB>
-__device__ __forceinline__ void mm_recombine_store_impl(const v4i (&acc)[2 * MM_DIG - 1][MM_MB], const ModConst mc, const WMul P24,
+template <bool ALL, bool WIDE, int MB0 = 0, int MB1 = MM_MB>
+__device__ __forceinline__ void mm_recombine_store_impl(const v4i (&acc)[2 * MM_DIG - 1][MM_MB], const MacConst &C,
                                                         const double (&ws)[MM_MB][4], u64d *outp, size_t mstride, int m0, int O) {
+    if (WIDE) {
+        const WideShifts k = wide_shifts();
+#pragma unroll
+        for (int mb = MB0; mb < MB1; mb++)
+#pragma unroll
+            for (int r = 0; r < 4; r++) {
+                double g[3];
+#pragma unroll
+                for (int q = 0; q < 3; q++) g[q] = wide_group(acc[4 * q][mb][r], acc[4 * q + 1][mb][r], acc[4 * q + 2][mb][r], acc[4 * q + 3][mb][r], k);
+                ProductChain s = chain_first(C.M, g[1], C.c1);
+                chain_add(s, g[2], C.c2);
+                chain_add(s, (double)acc[12][mb][r], C.c3);
+                // 2.6p + 2^50 (p < 2^51: at most MM_RES_STEPS steps, 2^49) + p: below 2^53
+                const u64d val = d2u(canon(chain_value(s, C.p, C.pinv) + (g[0] + ws[mb][r]), C.p, C.pinv));
+                if (ALL || m0 + mb * 16 + r < O) outp[(size_t)(mb * 16 + r) * mstride] = val;
+            }
+        return;
+    }
 #pragma unroll
     for (int mb = MB0; mb < MB1; mb++)
 #pragma unroll
@@ -325,19 +390,20 @@ __device__ __forceinline__ void mm_recombine_store_impl(const v4i (&acc)[2 * MM_
             grp[4] = (double)acc[12][mb][r];
             double v = grp[4];
 #pragma unroll
-            for (int q = 3; q >= 0; q--) v = mulmod_w(v, P24.w, P24.wp, mc.p) + grp[q];
-            const u64d val = d2u(canon(v + ws[mb][r], mc.p, mc.pinv));
+            for (int q = 3; q >= 0; q--) v = mulmod_w(v, C.P24.w, C.P24.wp, C.p) + grp[q];
+            const u64d val = d2u(canon(v + ws[mb][r], C.p, C.pinv));
             if (ALL || m0 + mb * 16 + r < O) outp[(size_t)(mb * 16 + r) * mstride] = val;
         }
 }
 // mg: the channel group (the same for the whole workgroup)
-__device__ __forceinline__ void mm_recombine_store(const v4i (&acc)[2 * MM_DIG - 1][MM_MB], const ModConst mc, const WMul P24,
+template <bool WIDE>
+__device__ __forceinline__ void mm_recombine_store(const v4i (&acc)[2 * MM_DIG - 1][MM_MB], const MacConst &C,
                                                    const double (&ws)[MM_MB][4], u64d *outp, size_t mstride, unsigned mg, unsigned g, int O) {
     const int m0 = (int)(mg * MM_CH + 4 * g);
     if ((int)((mg + 1) * MM_CH) <= O)
-        mm_recombine_store_impl<true>(acc, mc, P24, ws, outp, mstride, m0, O);
+        mm_recombine_store_impl<true, WIDE>(acc, C, ws, outp, mstride, m0, O);
     else
-        mm_recombine_store_impl<false>(acc, mc, P24, ws, outp, mstride, m0, O);
+        mm_recombine_store_impl<false, WIDE>(acc, C, ws, outp, mstride, m0, O);
 }
 
 // Request the 16 words of one k-step (taps kb*64 + 16g + t of this lane's word) from their tap entries, and this
@@ -374,9 +440,10 @@ __device__ __forceinline__ unsigned mm_issue_loads(const MacMfmaArgs &A, const T
 // contiguous range of v, in which the channel group is the fastest index, then the output position, then the word
 // block, then the limb -- consecutive workgroups of one XCD read the same input words (other channels, overlapping
 // windows) and find them in its L2.
-template <bool INTERIOR>
+template <bool INTERIOR, bool WIDE>
 __device__ __forceinline__ void conv_mac_mfma_body(const MacMfmaArgs &A, v4i *a_lds, unsigned mg, unsigned pos, unsigned wb, unsigned lc);
 
+template <bool WIDE>
 __global__ __launch_bounds__(256, 2) void conv_mac_mfma_kernel(MacMfmaArgs A) {
     __shared__ v4i a_lds[MM_FRAG];
     const unsigned N = 1u << A.logN;
@@ -390,12 +457,12 @@ __global__ __launch_bounds__(256, 2) void conv_mac_mfma_kernel(MacMfmaArgs A) {
     const int oyl = (int)(pos / (unsigned)A.Wo), ox = (int)(pos % (unsigned)A.Wo);
     const int iy0 = (A.out_row0 + oyl) * A.stride - A.pad, ix0 = ox * A.stride - A.pad;
     if (iy0 >= 0 && iy0 + A.kh <= A.H && ix0 >= 0 && ix0 + A.kw <= A.W)
-        conv_mac_mfma_body<true>(A, a_lds, mg, pos, wb, lc);
+        conv_mac_mfma_body<true, WIDE>(A, a_lds, mg, pos, wb, lc);
     else
-        conv_mac_mfma_body<false>(A, a_lds, mg, pos, wb, lc);
+        conv_mac_mfma_body<false, WIDE>(A, a_lds, mg, pos, wb, lc);
 }
 
-template <bool INTERIOR>
+template <bool INTERIOR, bool WIDE>
 __device__ __forceinline__ void conv_mac_mfma_body(const MacMfmaArgs &A, v4i *a_lds, unsigned mg, unsigned pos, unsigned wb, unsigned lc) {
     const unsigned N = 1u << A.logN;
     const unsigned tid = threadIdx.x, lane = tid & 63, wave = MM_UNIFORM(tid >> 6);
@@ -403,6 +470,7 @@ __device__ __forceinline__ void conv_mac_mfma_body(const MacMfmaArgs &A, v4i *a_
     const int oyl = (int)(pos / (unsigned)A.Wo), ox = (int)(pos % (unsigned)A.Wo);
     const int iy0 = (A.out_row0 + oyl) * A.stride - A.pad, ix0 = ox * A.stride - A.pad;
     const int origin = (iy0 - A.in_row0) * A.W + ix0;
+    const MacConst C = mac_const<WIDE>(A, WG_UNIFORM(i));
     const size_t ctw = (size_t)2 * A.level * N;
     const unsigned n = wb * MM_WORDS + wave * 16 + (lane & 15);
     const unsigned g = lane >> 4;
@@ -457,7 +525,7 @@ __device__ __forceinline__ void conv_mac_mfma_body(const MacMfmaArgs &A, v4i *a_
     const int m0 = (int)(mg * MM_CH + 4 * g);
     const size_t mstride = (size_t)A.out_rows * A.Wo * ctw;
     u64d *outp = A.out + (size_t)m0 * mstride + ((size_t)oyl * A.Wo + ox) * ctw + (size_t)lc * N + n;
-    mm_recombine_store(acc, A.modc[i], A.pow24[i], ws, outp, mstride, mg, g, A.O);
+    mm_recombine_store<WIDE>(acc, C, ws, outp, mstride, mg, g, A.O);
 }
 
 // ---------------------------------------------------------------- layers of few taps: A fragments resident in LDS
@@ -515,6 +583,7 @@ __global__ __launch_bounds__(256, 2) void conv_mac_mfma_resident_kernel(MacMfmaA
     const unsigned lc = (unsigned)v;
     const unsigned tid = threadIdx.x, lane = tid & 63, wave = MM_UNIFORM(tid >> 6), g = lane >> 4;
     const unsigned i = lc % (unsigned)A.level;
+    const MacConst C = mac_const<true>(A, WG_UNIFORM(i));
     const size_t ctw = (size_t)2 * A.level * N;
     const unsigned n = wb * MM_WORDS + wave * 16 + (lane & 15);
     const u64d *inw = A.in + (size_t)lc * N + n;
@@ -577,7 +646,7 @@ __global__ __launch_bounds__(256, 2) void conv_mac_mfma_resident_kernel(MacMfmaA
             for (int mb = 0; mb < MM_MB; mb++)
 #pragma unroll
                 for (int r = 0; r < 4; r++) ws[mb][r] = ws_lds[mb * 16 + 4 * g + r];
-            mm_recombine_store(acc, A.modc[i], A.pow24[i], ws, outm + ((size_t)Pcur.oyl * A.Wo + Pcur.ox) * ctw, mstride, mg, g, A.O);
+            mm_recombine_store<true>(acc, C, ws, outm + ((size_t)Pcur.oyl * A.Wo + Pcur.ox) * ctw, mstride, mg, g, A.O);
             pos++;
         }
     }
@@ -588,14 +657,15 @@ __global__ __launch_bounds__(256, 2) void conv_mac_mfma_resident_kernel(MacMfmaA
 // v = ((limb * (N/16) + 16-word block) * nrun + c); workgroup c of a block takes tiles c*run ... c*run + run - 1.  Tile tau
 // covers output rows TY*(tau / spr) + wy and columns TX*(tau % spr) + wx, wave w = wy*TX + wx; a wave whose position lies
 // beyond the requested rows or the row's end computes on whatever the strip holds and stores nothing.  The strip of the
-// next tile is requested before the current tile's work and written to the other buffer after it: one barrier per tile.
+// next tile goes to the other buffer, straight from memory, during the current tile's matrix work: one barrier per tile.
 // Strip line (c*SR + r)*SC + col holds the block's 16 words of pixel (iy0 + r, ix0 + col) of channel c, zeros outside
 // the image.
 template <int KB, bool QUAD, int TY>
 __global__ __launch_bounds__(256, 2) void conv_mac_mfma_strip_kernel(MacMfmaArgs A) {
     constexpr int TX = MM_STRIP_POS / TY;
     __shared__ v4i a_lds[KB * MM_FRAG];
-    __shared__ v4i strip[2][MM_STRIP_LINES * 8];
+    __shared__ v4i strip0[MM_STRIP_LINES * 8];  // two objects: the loads into one are not waited for before words of the other are read
+    __shared__ v4i strip1[MM_STRIP_LINES * 8];
     __shared__ double ws_lds[MM_CH];
     __shared__ unsigned toff_lds[KB * 64];
     const unsigned N = 1u << A.logN;
@@ -608,6 +678,7 @@ __global__ __launch_bounds__(256, 2) void conv_mac_mfma_strip_kernel(MacMfmaArgs
     const unsigned tid = threadIdx.x, lane = tid & 63, wave = MM_UNIFORM(tid >> 6), g = lane >> 4;
     const unsigned wy = wave / (unsigned)TX, wx = wave % (unsigned)TX;
     const unsigned i = lc % (unsigned)A.level;
+    const MacConst C = mac_const<true>(A, WG_UNIFORM(i));
     const size_t ctw = (size_t)2 * A.level * N;
     const u64d *inw = A.in + (size_t)lc * N + wb * 16;  // the block's first word in ciphertext 0
     const size_t mstride = (size_t)A.out_rows * A.Wo * ctw;
@@ -616,7 +687,7 @@ __global__ __launch_bounds__(256, 2) void conv_mac_mfma_strip_kernel(MacMfmaArgs
     const unsigned tau0 = c * A.run, tau1 = tau0 + A.run < tiles ? tau0 + A.run : tiles;
     const unsigned lines = (unsigned)(A.C * A.SR * A.SC);
 
-    // staging: round r, this thread moves 16 bytes (part = tid % 8) of line r*32 + tid/8
+    // staging: round r, this thread moves 16 bytes of line r*32 + tid/8
     unsigned relc[MM_STRIP_ROUNDS];   // ciphertexts from the tile's origin pixel to this thread's line
     unsigned rcol[MM_STRIP_ROUNDS];   // strip row | strip column << 8 | line exists << 31
 #pragma unroll
@@ -632,8 +703,9 @@ __global__ __launch_bounds__(256, 2) void conv_mac_mfma_strip_kernel(MacMfmaArgs
     for (unsigned s = tid; s < (unsigned)KB * 64; s += 256) toff_lds[s] = A.tapoff[s];
     const u64d *inp = inw + (tid % 8u) * 2u;
 
-    // the 16-byte pieces of tile tau's strip, zeros outside the image (and outside the rows the caller handed over)
-    auto fetch = [&](unsigned tau, v4i (&sreg)[MM_STRIP_ROUNDS]) {
+    // the 16-byte pieces of tile tau's strip to `buf`, zeros outside the image (and outside the rows the caller handed over):
+    // piece r*256 + tid is part tid%8 of line r*32 + tid/8
+    auto fetch = [&](unsigned tau, v4i *buf) {
         const int ty = (int)(tau / (unsigned)A.spr), tx = (int)(tau % (unsigned)A.spr);
         const int iy0 = (A.out_row0 + ty * TY) * A.stride - A.pad, ix0 = tx * TX * A.stride - A.pad;
         const int origin = (iy0 - A.in_row0) * A.W + ix0;  // in ciphertexts; never negative for a pixel inside the strip
@@ -642,12 +714,9 @@ __global__ __launch_bounds__(256, 2) void conv_mac_mfma_strip_kernel(MacMfmaArgs
             const int iy = iy0 + (int)(rcol[r] & 0xffu), ix = ix0 + (int)((rcol[r] >> 8) & 0xffffu);
             const bool ok = (rcol[r] >> 31) && (unsigned)iy < (unsigned)A.H && (unsigned)ix < (unsigned)A.W &&
                             (unsigned)(iy - A.in_row0) < (unsigned)A.in_rows;
-            sreg[r] = ok ? *(const v4i *)(inp + (size_t)(unsigned)(origin + (int)relc[r]) * ctw) : v4i{0, 0, 0, 0};
+            if (ok) MM_LDS_LOAD16(inp + (size_t)(unsigned)(origin + (int)relc[r]) * ctw, buf + r * 256 + 64 * wave, lane);
+            else if (rcol[r] >> 31) buf[r * 256 + tid] = v4i{0, 0, 0, 0};
         }
-    };
-    auto stash = [&](int buf, const v4i (&sreg)[MM_STRIP_ROUNDS]) {
-#pragma unroll
-        for (int r = 0; r < MM_STRIP_ROUNDS; r++) strip[buf][r * 256 + tid] = sreg[r];  // line r*32 + tid/8, part tid%8
     };
 
     for (unsigned mg = 0; mg < (unsigned)A.Mg; mg++) {
@@ -658,18 +727,15 @@ __global__ __launch_bounds__(256, 2) void conv_mac_mfma_strip_kernel(MacMfmaArgs
             for (unsigned e = tid; e < MM_FRAG; e += 256) a_lds[kb * MM_FRAG + e] = asrc[e];
         }
         if (tid < MM_CH) ws_lds[tid] = A.wsum[((size_t)i * A.Mg + mg) * MM_CH + tid];
-        {
-            v4i sreg[MM_STRIP_ROUNDS];
-            fetch(tau0, sreg);
-            stash(0, sreg);
-        }
+        fetch(tau0, strip0);
+        MM_LOADS_DONE();
         __syncthreads();
         const int m0 = (int)(mg * MM_CH + 4 * g);
         u64d *outm = A.out + (size_t)m0 * mstride + (size_t)lc * N + wb * 16 + (lane & 15u);
 
-        for (unsigned tau = tau0; tau < tau1; tau++) {
-            const int buf = (int)((tau - tau0) & 1u);
-            const char *sb = (const char *)strip[buf];
+        auto tile = [&](unsigned tau, const v4i *cur, v4i *next) {
+            if (tau + 1 < tau1) fetch(tau + 1, next);
+            const char *sb = (const char *)cur;
             v4i acc[2 * MM_DIG - 1][MM_MB];
 #pragma unroll
             for (int kb = 0; kb < KB; kb++) {
@@ -686,10 +752,8 @@ __global__ __launch_bounds__(256, 2) void conv_mac_mfma_strip_kernel(MacMfmaArgs
                     if (quad) mm_step<false, true>(a, lane, bf, acc); else mm_step<false, false>(a, lane, bf, acc);
                 }
             }
-            // the next tile's strip is requested once the matrix work is issued: its registers are live only through the
-            // recombination, whose latency covers the loads
-            v4i sreg[MM_STRIP_ROUNDS];
-            if (tau + 1 < tau1) fetch(tau + 1, sreg);
+            // the loads have had the matrix work to arrive; here, so that nobody waits for this tile's stores
+            MM_LOADS_DONE();
             const int oyl = (int)(tau / (unsigned)A.spr) * TY + (int)wy, ox = (int)(tau % (unsigned)A.spr) * TX + (int)wx;
             const bool real = oyl < A.out_rows && ox < A.Wo;
             double ws[MM_MB][4];
@@ -698,9 +762,12 @@ __global__ __launch_bounds__(256, 2) void conv_mac_mfma_strip_kernel(MacMfmaArgs
 #pragma unroll
                 for (int r = 0; r < 4; r++) ws[mb][r] = ws_lds[mb * 16 + 4 * g + r];
             if (real)  // uniform for the wave: one without a position stores nothing
-                mm_recombine_store(acc, A.modc[i], A.pow24[i], ws, outm + ((size_t)oyl * A.Wo + ox) * ctw, mstride, mg, g, A.O);
-            if (tau + 1 < tau1) stash(buf ^ 1, sreg);
+                mm_recombine_store<true>(acc, C, ws, outm + ((size_t)oyl * A.Wo + ox) * ctw, mstride, mg, g, A.O);
             __syncthreads();
+        };
+        for (unsigned tau = tau0; tau < tau1; tau += 2) {
+            tile(tau, strip0, strip1);
+            if (tau + 1 < tau1) tile(tau + 1, strip1, strip0);
         }
     }
 }

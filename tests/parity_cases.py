@@ -1052,6 +1052,13 @@ PADDED_LAYERS += [(5, 28, 6, 8, 5, 2, 4, False, (0, 3), "conv_mac_mfma_resident_
 WIDE_LAYER = (1, 1, 144700, 8, 30, 50000, 29, False, (0, 1), "conv_mac_kernel")
 
 
+# (bits, input channels, kernel size, kernel): the largest sums that four diagonals combine (512 taps; with 51-bit primes 256), the first tap
+# counts beyond either, one and two steps with and without a short last one
+EXTREME_TAPS = [(50, 512, 1, "conv_mac_mfma_kernel"), (50, 513, 1, "conv_mac_mfma_kernel"), (51, 257, 1, "conv_mac_mfma_kernel"), (51, 512, 1, "conv_mac_mfma_kernel"),
+                (51, 256, 1, "conv_mac_mfma_resident_kernel"), (50, 208, 1, "conv_mac_mfma_resident_kernel"), (51, 5, 5, "conv_mac_mfma_strip_kernel"),
+                (50, 3, 5, "conv_mac_mfma_strip_kernel"), (40, 7, 3, "conv_mac_mfma_strip_kernel"), (20, 1, 4, "conv_mac_mfma_strip_kernel")]
+
+
 def case_padded_layer(be, layer, seed):
     cin, h, w, oc, kh, stride, pad, residues, rows, kernel = layer
     case_conv_channels(be, (6, 1, 50, 0, 51, 1), seed, cin, h, w, oc, kh, stride, pad, residues=residues, rows=rows, kernel=kernel)

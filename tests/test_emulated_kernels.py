@@ -518,3 +518,9 @@ def test_key_products_stay_exact_at_the_ends_of_their_range(be, p51):
                 got = probe(p51, ctypes.c_double(k), ctypes.c_double(v), ctypes.c_double(a), ctypes.c_double(p))
                 assert got == int(got) and abs(got) < 2**53 and abs(int(got) - a) <= term * p
                 assert (int(got) - a - k * v) % p == 0
+
+
+@pytest.mark.parametrize("bits,channels,size,kernel", pc.EXTREME_TAPS)
+def test_digit_diagonals_at_their_largest(be, bits, channels, size, kernel):
+    """every word p - 1, every weight +-(p - 1) / 2, output channels that end inside a channel group"""
+    pc.case_conv_channels(be, (6, 1, bits, 0, bits + 1, 1), 420 + channels, channels, size, size + 1, 35, size, 1, 0, residues=False, extreme=True, kernel=kernel)

@@ -871,3 +871,10 @@ def test_streamed_encryption_matches_cached_one(logN, n_q, batch):
         ctx.encrypt_device(pk, pt[i:i + 1], r[i:i + 1], e0[i:i + 1], e1[i:i + 1], n_q, 1, one, ws)
         assert torch.equal(out[i:i + 1], one)
     ctx.close()
+
+
+@pytest.mark.parametrize("bits,channels,size,kernel", pc.EXTREME_TAPS)
+def test_digit_diagonals_at_their_largest(be, bits, channels, size, kernel):
+    """every word p - 1, every weight +-(p - 1) / 2, output channels that end inside a channel group"""
+    announce("conv digits, %d bits, %d channels" % (bits, channels))
+    pc.case_conv_channels(be, (7, 2, bits, 0, bits + 1, 1), 420 + channels, channels, size, size + 1, 35, size, 1, 0, residues=False, extreme=True, kernel=kernel)
