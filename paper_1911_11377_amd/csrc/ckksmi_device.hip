@@ -659,8 +659,19 @@ void ks_core_fused(ckksmi_ctx *c, const u64 *d_eval, size_t d_stride, const KeyT
     RI.addend = (const u64d *)addend; RI.add_item_stride = add_item_stride; RI.add_comp_stride = add_comp_stride;
     RI.ta = (const u64d *)ta; RI.tb = (const u64d *)tb; RI.terms = terms; RI.keep_acc = merged ? 1 : 0; RI.Pmod = c->d_pmod;
     if (on_chip) launch_inner_wg(c, RI, K, ymid, items, st, gal);
-    else if (gal) KL2(c, CKKSMI_K_ROWS_INNER, (double)items * E, RI.stream != STREAM_NONE, rows_inner_gal_kernel<true>, rows_inner_gal_kernel<false>, dim3(RI.kt * items, tiles / RI.kt, E), dim3(V2_THREADS), st, RI, K, *gal);
-    else KL2(c, CKKSMI_K_ROWS_INNER, (double)items * E, RI.stream != STREAM_NONE, rows_inner_kernel<true>, rows_inner_kernel<false>, dim3(RI.kt * items, tiles / RI.kt, E), dim3(V2_THREADS), st, RI, K);
+    else {
+        const dim3 grid(RI.kt * items, tiles / RI.kt, E), block(V2_THREADS);
+        const double units = (double)items * E;
+#define ROWS_INNER_CASE(ST)                                                                                              \
+    case ST:                                                                                                             \
+        if (gal) KL(c, CKKSMI_K_ROWS_INNER, units, rows_inner_gal_kernel<ST>, grid, block, st, RI, K, *gal);             \
+        else KL(c, CKKSMI_K_ROWS_INNER, units, rows_inner_kernel<ST>, grid, block, st, RI, K);                           \
+        break;
+        switch (RI.stream) {
+            ROWS_INNER_CASE(STREAM_NONE) ROWS_INNER_CASE(STREAM_STORES) ROWS_INNER_CASE(STREAM_ALL)
+        }
+#undef ROWS_INNER_CASE
+    }
     if (merged) {
         merged_division(c, acc, ta ? nullptr : addend, add_item_stride, add_comp_stride, out, tmp, items, level, st);
         return;

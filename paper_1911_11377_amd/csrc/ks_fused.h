@@ -574,7 +574,7 @@ __device__ __forceinline__ void inner_own_digit(const RowsInnerArgs &A, const u6
                 kr1[s] = k1[row_pair_index(hi4, lo4, 4 * h + s)];
             }
             double l0[8], l1[8], l2[8];
-            for (int tm = 0; tm < A.terms; tm++) {
+            auto term = [&](int tm, auto add) {
                 const size_t to = (size_t)tm * 2 * st;
                 ulonglong2 A0[4], A1[4], B0[4], B1[4];
 #pragma unroll
@@ -591,19 +591,15 @@ __device__ __forceinline__ void inner_own_digit(const RowsInnerArgs &A, const u6
                         const double x0 = u2d(b ? A0[s].y : A0[s].x), x1 = u2d(b ? A1[s].y : A1[s].x);
                         const double y0 = u2d(b ? B0[s].y : B0[s].x), y1 = u2d(b ? B1[s].y : B1[s].x);
                         const double t0 = mulmod(x0, y0, p, pinv), t1 = mulmod(x0, y1, p, pinv) + mulmod(x1, y0, p, pinv), t2 = mulmod(x1, y1, p, pinv);
-                        if (!P51 && A.terms == 1) {
-                            l0[i] = t0;
-                            l1[i] = t1;
-                            l2[i] = t2;
-                            continue;
-                        }
-                        // |t| <= 2.5p on top of a reduced sum: below 2^53
-                        l0[i] = reduce_balanced((tm ? l0[i] : 0.0) + t0, p, pinv);
-                        l1[i] = reduce_balanced((tm ? l1[i] : 0.0) + t1, p, pinv);
-                        l2[i] = reduce_balanced((tm ? l2[i] : 0.0) + t2, p, pinv);
+                        // |t| <= 1.75p (2.5p for p < 2^51) on top of a reduced sum, or of one term as it comes: below 2^53
+                        l0[i] = add ? reduce_balanced(l0[i] + t0, p, pinv) : P51 ? reduce_balanced(t0, p, pinv) : t0;
+                        l1[i] = add ? reduce_balanced(l1[i] + t1, p, pinv) : P51 ? reduce_balanced(t1, p, pinv) : t1;
+                        l2[i] = add ? reduce_balanced(l2[i] + t2, p, pinv) : P51 ? reduce_balanced(t2, p, pinv) : t2;
                     }
                 }
-            }
+            };
+            term(0, StreamFlag<false>());
+            for (int tm = 1; tm < A.terms; tm++) term(tm, StreamFlag<true>());
 #pragma unroll
             for (int s = 0; s < 4; s++) {
                 // two terms of at most the bound of key_term each: P*d (0.72p) and the own digit's product
@@ -698,7 +694,7 @@ __device__ __forceinline__ void inner_store(const RowsInnerArgs &A, unsigned ite
 
 // GAL (a rotation): the source polynomial d_eval and the addend are read through the automorphism X -> X^g of their item
 // (gal->g[item]), so that no rotated copy of the ciphertext is ever written
-template <bool P51, bool GAL, bool NTS>
+template <bool P51, bool GAL, int STREAM>
 __device__ __forceinline__ void rows_inner_body(const RowsInnerArgs &A, const KeyTab &K, double *lds, double *tw1_lds, double *tw2_lds, int t,
                                                 unsigned x, const GaloisTab *gal = nullptr) {
     BODY_TAG(P51);
@@ -736,14 +732,15 @@ __device__ __forceinline__ void rows_inner_body(const RowsInnerArgs &A, const Ke
     // The other digits, software-pipelined so that no memory latency sits in front of arithmetic: the limb words of a
     // digit are requested while the previous digit is multiplied, its key words while the limb goes through the row
     // pass.  xr holds the column-pass output of the converted limb in the register layout of the row pass.
+    // (The requests stand in straight-line code, also past the last digit, where they re-read key words: behind a branch that may not be
+    // taken the compiler has to wait for all of them where it wants the key words, which exposes the latency of every digit's limb.)
     int j = (j_own == 0) ? 1 : 0;
+    const unsigned vr = hi4 * 256 + lo4, pr = row_pair_index(hi4, lo4, 0);
     u64d xr[16];
     if (j < A.beta) {
         const u64d *src = A.dtA + (((size_t)item * A.beta + j) * A.E + x) * N + tile0;
-        stream_if(A.stream == STREAM_ALL, [&](auto nt) {
 #pragma unroll
-            for (int i = 0; i < 16; i++) xr[i] = stream_load<nt>(&src[hi4 * 256 + lo4 + 16 * i]);
-        });
+        for (int i = 0; i < 16; i++) xr[i] = stream_load<STREAM == STREAM_ALL>(scalar_base(src) + (vr + 16 * i));
     }
     while (j < A.beta) {
         const u64d *k0 = key + (((size_t)j * 2 + 0) * A.T + t) * N + tile0;
@@ -751,8 +748,8 @@ __device__ __forceinline__ void rows_inner_body(const RowsInnerArgs &A, const Ke
         ulonglong2 kr0[8], kr1[8];
 #pragma unroll
         for (int s = 0; s < 8; s++) {
-            kr0[s] = ((const ulonglong2 *)k0)[row_pair_index(hi4, lo4, s)];
-            kr1[s] = ((const ulonglong2 *)k1)[row_pair_index(hi4, lo4, s)];
+            kr0[s] = pair_load<false>(k0, pr + 16 * s);
+            kr1[s] = pair_load<false>(k1, pr + 16 * s);
         }
         SCHED_FENCE();
         {
@@ -782,13 +779,9 @@ __device__ __forceinline__ void rows_inner_body(const RowsInnerArgs &A, const Ke
         ROW_GROUP_SYNC();
         int jn = j + 1;
         if (jn == j_own) jn++;
-        if (jn < A.beta) {
-            const u64d *src = A.dtA + (((size_t)item * A.beta + jn) * A.E + x) * N + tile0;
-            stream_if(A.stream == STREAM_ALL, [&](auto nt) {
+        const u64d *src = jn < A.beta ? A.dtA + (((size_t)item * A.beta + jn) * A.E + x) * N + tile0 : k0;
 #pragma unroll
-                for (int i = 0; i < 16; i++) xr[i] = stream_load<nt>(&src[hi4 * 256 + lo4 + 16 * i]);
-            });
-        }
+        for (int i = 0; i < 16; i++) xr[i] = stream_load<STREAM == STREAM_ALL>(scalar_base(src) + (vr + 16 * i));
         SCHED_FENCE();
 #pragma unroll
         for (int s = 0; s < 8; s++) {
@@ -807,11 +800,11 @@ __device__ __forceinline__ void rows_inner_body(const RowsInnerArgs &A, const Ke
         ROW_GROUP_SYNC();  // the row's lanes have read its words before the next digit overwrites them
         j = jn;
     }
-    inner_store<P51, GAL, NTS>(A, item, t, x, tensor_mode, tile0, hi4, lo4, p, pinv, a0, a1, gal);
+    inner_store<P51, GAL, STREAM != STREAM_NONE>(A, item, t, x, tensor_mode, tile0, hi4, lo4, p, pinv, a0, a1, gal);
 }
 
 // grid: x = (row tile mod kt) + kt * item, y = row tile / kt, z = extended limb
-template <bool NTS>
+template <int STREAM>
 __global__ __launch_bounds__(V2_THREADS, 2) void rows_inner_kernel(RowsInnerArgs A, KeyTab K) {
     __shared__ double lds[16 * V2_GS];
     __shared__ double tw1_lds[16 * 16];
@@ -819,13 +812,13 @@ __global__ __launch_bounds__(V2_THREADS, 2) void rows_inner_kernel(RowsInnerArgs
     const unsigned x = blockIdx.z;
     const int t = (int)x < A.level ? (int)x : A.n_q + (int)x - A.level;
     if (is_p51(A.p51, t))
-        rows_inner_body<true, false, NTS>(A, K, lds, tw1_lds, tw2_lds, t, x);
+        rows_inner_body<true, false, STREAM>(A, K, lds, tw1_lds, tw2_lds, t, x);
     else
-        rows_inner_body<false, false, NTS>(A, K, lds, tw1_lds, tw2_lds, t, x);
+        rows_inner_body<false, false, STREAM>(A, K, lds, tw1_lds, tw2_lds, t, x);
 }
 
 // the same for rotations: source polynomial and addend read through the items' automorphisms (no tensor mode here)
-template <bool NTS>
+template <int STREAM>
 __global__ __launch_bounds__(V2_THREADS, 2) void rows_inner_gal_kernel(RowsInnerArgs A, KeyTab K, GaloisTab G) {
     __shared__ double lds[16 * V2_GS];
     __shared__ double tw1_lds[16 * 16];
@@ -833,9 +826,9 @@ __global__ __launch_bounds__(V2_THREADS, 2) void rows_inner_gal_kernel(RowsInner
     const unsigned x = blockIdx.z;
     const int t = (int)x < A.level ? (int)x : A.n_q + (int)x - A.level;
     if (is_p51(A.p51, t))
-        rows_inner_body<true, true, NTS>(A, K, lds, tw1_lds, tw2_lds, t, x, &G);
+        rows_inner_body<true, true, STREAM>(A, K, lds, tw1_lds, tw2_lds, t, x, &G);
     else
-        rows_inner_body<false, true, NTS>(A, K, lds, tw1_lds, tw2_lds, t, x, &G);
+        rows_inner_body<false, true, STREAM>(A, K, lds, tw1_lds, tw2_lds, t, x, &G);
 }
 
 // ------------------------------------------------------------------ row pass + DivRound final step
