@@ -217,6 +217,35 @@ void launch_ntt(ckksmi_ctx *c, bool forward, const u64 *src, u64 *dst, const Lim
     }
 }
 
+unsigned zchunks_for(const ckksmi_ctx *c, unsigned wgs_per_item, size_t items, int &items_per_z);
+
+// Forward transform of encodings on the register-tiled sizes: the real parts of cbuf [items][N], scaled by factor and rounded, to pt [items][level][N].
+// *overflow is raised where one is too large.
+void launch_encode_ntt(ckksmi_ctx *c, const double2 *cbuf, double factor, int *overflow, u64 *pt, int level, size_t items, hipStream_t st) {
+    const size_t N = c->N;
+    int idx[CKKSMI_MAX_MODULI];
+    for (int i = 0; i < level; i++) idx[i] = i;
+    NttV2Args V;
+    memset(&V, 0, sizeof(V));
+    V.src = (const u64d *)cbuf; V.dst = (u64d *)pt; V.modc = c->d_mod; V.tw = c->d_tww_fwd; V.logN = c->logN; V.p51 = c->p51mask; V.items = (int)items;
+    V.map = table_map(idx, level, N, (size_t)level * N);
+    V.factor = factor; V.overflow = overflow;
+    const double units = (double)items * level;
+    const bool nt = stream_level(8.0 * N * items * level) != STREAM_NONE;
+    if (c->logN <= 13 || (c->logN == 14 && units >= 64)) {  // as in launch_ntt
+        const unsigned zc = zchunks_for(c, 4u * level, items, V.items_per_z);
+        const dim3 grid(level, zc), block((unsigned)(N / 16));
+        if (c->logN == 12) KL2(c, CKKSMI_K_ENCODE, units, nt, (ntt_wg_fwd_real_kernel<12, true>), (ntt_wg_fwd_real_kernel<12, false>), grid, block, st, V);
+        else if (c->logN == 13) KL2(c, CKKSMI_K_ENCODE, units, nt, (ntt_wg_fwd_real_kernel<13, true>), (ntt_wg_fwd_real_kernel<13, false>), grid, block, st, V);
+        else KL2(c, CKKSMI_K_ENCODE, units, nt, (ntt_wg_fwd_real_kernel<14, true>), (ntt_wg_fwd_real_kernel<14, false>), grid, block, st, V);
+        return;
+    }
+    const unsigned tiles = (unsigned)(N / 4096);
+    const unsigned zc = zchunks_for(c, tiles * level, items, V.items_per_z);
+    KL2(c, CKKSMI_K_ENCODE, units, nt, ntt_v2_fwd_cols_real_kernel<true>, ntt_v2_fwd_cols_real_kernel<false>, dim3(tiles, level, zc), dim3(V2_THREADS), st, V);
+    launch_ntt(c, true, pt, pt, table_map(idx, level, (size_t)level * N, (size_t)level * N), items, st, nullptr, 2);
+}
+
 inline unsigned ew_blocks(size_t total) { return (unsigned)((total + EW_THREADS - 1) / EW_THREADS); }
 
 ScalarTab scalar_tab(const ckksmi_ctx *c, int64_t v, int level) {
@@ -1502,12 +1531,16 @@ extern "C" int ckksmi_encode_device(ckksmi_ctx *c, const double *re, const doubl
     KL(c, CKKSMI_K_ENCODE, (double)batch, encode_scatter_kernel, dim3(ew_blocks(N / 2), batch), dim3(EW_THREADS), st, A);
     KL(c, CKKSMI_K_ENCODE, (double)batch, cfft_inv_kernel<false>, dim3(batch, (N1 + R - 1) / R), dim3(NTT_THREADS), st, A);
     if (A.LA) KL(c, CKKSMI_K_ENCODE, (double)batch, cfft_inv_kernel<true>, dim3(batch, N2 / NTT_TC), dim3(NTT_THREADS), st, A);
-    const size_t total = (size_t)batch * N;
-    KL(c, CKKSMI_K_ENCODE, (double)batch, encode_round_kernel, dim3(ew_blocks(total)), dim3(EW_THREADS), st, (const double2 *)ws, scale / (double)N,
-       (u64d *)pt, c->d_mod, c->logN, level, total, flag_word);
-    int idx[CKKSMI_MAX_MODULI];
-    for (int i = 0; i < level; i++) idx[i] = i;
-    launch_ntt(c, true, pt, pt, table_map(idx, level, (size_t)level * N, (size_t)level * N), batch, st);
+    if (c->fused) {
+        launch_encode_ntt(c, (const double2 *)ws, scale / (double)N, flag_word, pt, level, batch, st);
+    } else {
+        const size_t total = (size_t)batch * N;
+        KL(c, CKKSMI_K_ENCODE, (double)batch, encode_round_kernel, dim3(ew_blocks(total)), dim3(EW_THREADS), st, (const double2 *)ws, scale / (double)N,
+           (u64d *)pt, c->d_mod, c->logN, level, total, flag_word);
+        int idx[CKKSMI_MAX_MODULI];
+        for (int i = 0; i < level; i++) idx[i] = i;
+        launch_ntt(c, true, pt, pt, table_map(idx, level, (size_t)level * N, (size_t)level * N), batch, st);
+    }
     int flag = 0;
     if (hipMemcpyAsync(&flag, flag_word, sizeof(int), hipMemcpyDeviceToHost, st) != hipSuccess || hipStreamSynchronize(st) != hipSuccess)
         return CKKSMI_EDEVICE;

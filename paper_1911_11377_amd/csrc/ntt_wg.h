@@ -218,7 +218,7 @@ __device__ __forceinline__ void wg_inv_limb(double (&x)[16], const u64d *src, co
     }
 }
 
-// SRC (inverse only): see wg_inv_limb
+// SRC: inverse see wg_inv_limb, forward SRC_WORDS or SRC_REAL
 template <bool INV, int LOGN, bool P51, bool F64, bool NT, int SRC = 0>
 __device__ __forceinline__ void ntt_wg_body(const NttV2Args &A, double *lds, int t, unsigned li, const GaloisTab *gal = nullptr,
                                             const TensorSrc *ten = nullptr) {
@@ -249,11 +249,18 @@ __device__ __forceinline__ void ntt_wg_body(const NttV2Args &A, double *lds, int
         double x[16];
         if (!INV) {
             u64d raw[16];
+            if (SRC == SRC_REAL) {  // every other word: the real parts
+                const u64d *cw = A.src + 2 * (size_t)it * A.map.src_item_stride;
 #pragma unroll
-            for (int e = 0; e < 16; e++) raw[e] = stream_load<NT>(scalar_base(src + Geo::G * 256u * e) + voff);
+                for (int e = 0; e < 16; e++) raw[e] = *(scalar_base(cw + Geo::G * 512u * e) + 2u * voff);
+            } else {
+#pragma unroll
+                for (int e = 0; e < 16; e++) raw[e] = stream_load<NT>(scalar_base(src + Geo::G * 256u * e) + voff);
+            }
             NTT_SCHED_FENCE();
 #pragma unroll
-            for (int e = 0; e < 16; e++) x[e] = u2d(raw[e]);
+            for (int e = 0; e < 16; e++)
+                x[e] = SRC == SRC_REAL ? real_word(__longlong_as_double((long long)raw[e]), A.factor, p, pinv, li == 0 ? A.overflow : nullptr) : u2d(raw[e]);
             wg_fwd_block<LOGN, P51, 256, ROW_NEAR>(x, tw, 1u, lds, p, pinv, []() {});
             // canonical words out in word pairs: 16 bytes per lane, 256 contiguous bytes per row and store
 #pragma unroll
@@ -285,6 +292,17 @@ __global__ __launch_bounds__((1 << LOGN) / 16) void ntt_wg_kernel(NttV2Args A) {
         ntt_wg_body<INV, LOGN, true, F64, NT>(A, lds, t, li);
     else
         ntt_wg_body<INV, LOGN, false, F64, NT>(A, lds, t, li);
+}
+
+// an encoding's real coefficients, same grid
+template <int LOGN, bool NT>
+__global__ __launch_bounds__((1 << LOGN) / 16) void ntt_wg_fwd_real_kernel(NttV2Args A) {
+    __shared__ double lds[((1 << LOGN) >> 8) * V2_GS];
+    unsigned item_unused, li;
+    const int t = resolve_limb(A.map, blockIdx.x, item_unused, li);
+    if (t < 0) return;
+    if (is_p51(A.p51, t)) ntt_wg_body<false, LOGN, true, false, NT, SRC_REAL>(A, lds, t, li);
+    else ntt_wg_body<false, LOGN, false, false, NT, SRC_REAL>(A, lds, t, li);
 }
 
 // conversion inputs of a key switch (doubles), same grid: a rotation's polynomial, a product's third tensor component
