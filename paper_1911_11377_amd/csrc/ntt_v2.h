@@ -190,10 +190,11 @@ struct NttV2Args {
 };
 
 // Coefficient rint(v * factor) of an encoding as a residue: |m| < 2^62 is an integer that the double holds exactly, and p > 2N >= 2^13 keeps the
-// quotient below 2^49 and its error below 1/8 before rounding, so that the remainder (0.63p) is exact.
-__device__ __forceinline__ double real_word(double v, double factor, double p, double pinv, int *overflow) {
+// quotient below 2^49 and its error below 1/8 before rounding, so that the remainder (0.63p) is exact.  largest: of the magnitudes so far (a NaN stays out
+// of a maximum: it is turned into an infinity).
+__device__ __forceinline__ double real_word(double v, double factor, double p, double pinv, double &largest) {
     const double m = rint(v * factor);
-    if (overflow && !(fabs(m) < 4.0e18)) *overflow = 1;
+    largest = fmax(largest, m == m ? fabs(m) : HUGE_VAL);
     return reduce_balanced(m, p, pinv);
 }
 enum { SRC_WORDS, SRC_SMALL, SRC_REAL };  // sources of a forward transform
@@ -437,18 +438,28 @@ __device__ __forceinline__ void ntt_v2_cols(const NttV2Args &A, double *lds, int
         u64d *dst = A.dst + (size_t)it * A.map.dst_item_stride + (size_t)li * N;
         double x[16];
         if (!INV) {
+            u64d raw[16];
+#pragma unroll
+            for (int e = 0; e < 16; e++) {
+                if (SRC == SRC_REAL) raw[e] = ((const u64d *)A.src + 2 * (size_t)it * A.map.src_item_stride)[2 * geo.g1(e)];
+                else if (SRC == SRC_SMALL) raw[e] = (A.src + (size_t)it * A.map.src_item_stride)[geo.g1(e)];
+                else raw[e] = stream_load<NT>(&src[geo.g1(e)]);
+            }
+            NTT_SCHED_FENCE();  // all of them requested before the first is used
+            double largest = 0.0;
 #pragma unroll
             for (int e = 0; e < 16; e++) {
                 // SRC_SMALL, magnitudes below 2^51: shifted to a non-negative integer, which becomes a double without a conversion of 64 bits;
                 // the reduction brings it into the range of the first round
                 if (SRC == SRC_REAL) {
-                    x[e] = real_word(((const double2 *)A.src + (size_t)it * A.map.src_item_stride)[geo.g1(e)].x, A.factor, p, pinv, li == 0 ? A.overflow : nullptr);
+                    x[e] = real_word(__longlong_as_double((long long)raw[e]), A.factor, p, pinv, largest);
                 } else if (SRC == SRC_SMALL) {
-                    const long long v = ((const long long *)A.src + (size_t)it * A.map.src_item_stride)[geo.g1(e)];
+                    const long long v = (long long)raw[e];
                     x[e] = reduce_balanced(u2d((unsigned long long)(v + (1ll << 51))) - 2251799813685248.0, p, pinv);
                 }
-                else x[e] = u2d(stream_load<NT>(&src[geo.g1(e)]));
+                else x[e] = u2d(raw[e]);
             }
+            if (SRC == SRC_REAL && !(largest < 4.0e18)) *A.overflow = 1;
             fwd_round<Mk::F1>(x, tw1, p, pinv);
 #pragma unroll
             for (int e = 0; e < 16; e++) lds[geo.l1(e)] = x[e];
@@ -577,7 +588,7 @@ __global__ __launch_bounds__(V2_THREADS) void ntt_v2_fwd_cols_small_kernel(NttV2
 
 // forward column pass of an encoding's real coefficients (N >= 2^14, smaller rings: ntt_wg_fwd_real_kernel), same grid.  A kernel that rounds and writes
 // every limb's residues before the transform costs two more limb transfers (and 64-bit divisions): 64 encodings of 24 primes at N = 2^16
-// 862 -> 562 us for the rounding, the column and the row pass.
+// 862 -> 500 us for the rounding, the column and the row pass.
 template <bool NT>
 __global__ __launch_bounds__(V2_THREADS) void ntt_v2_fwd_cols_real_kernel(NttV2Args A) {
     __shared__ double lds[16 * V2_GS];

@@ -258,9 +258,10 @@ __device__ __forceinline__ void ntt_wg_body(const NttV2Args &A, double *lds, int
                 for (int e = 0; e < 16; e++) raw[e] = stream_load<NT>(scalar_base(src + Geo::G * 256u * e) + voff);
             }
             NTT_SCHED_FENCE();
+            double largest = 0.0;
 #pragma unroll
-            for (int e = 0; e < 16; e++)
-                x[e] = SRC == SRC_REAL ? real_word(__longlong_as_double((long long)raw[e]), A.factor, p, pinv, li == 0 ? A.overflow : nullptr) : u2d(raw[e]);
+            for (int e = 0; e < 16; e++) x[e] = SRC == SRC_REAL ? real_word(__longlong_as_double((long long)raw[e]), A.factor, p, pinv, largest) : u2d(raw[e]);
+            if (SRC == SRC_REAL && !(largest < 4.0e18)) *A.overflow = 1;
             wg_fwd_block<LOGN, P51, 256, ROW_NEAR>(x, tw, 1u, lds, p, pinv, []() {});
             // canonical words out in word pairs: 16 bytes per lane, 256 contiguous bytes per row and store
 #pragma unroll
