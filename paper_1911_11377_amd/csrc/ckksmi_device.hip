@@ -506,9 +506,17 @@ void launch_hoisted_inner(ckksmi_ctx *c, const HoistPlan &H, const u64 *dt, cons
         else if (need <= 4096) HOIST_TILE(4096, MB);  \
         else HOIST_TILE(HOIST_LDS_WORDS, MB);         \
     } while (0)
-        if (A.beta <= 4) HOIST_TILE_LW(4);
-        else if (A.beta <= 8) HOIST_TILE_LW(8);
-        else HOIST_TILE_LW(INNER_MAX_BETA);
+        switch (A.beta) {
+            case 1: HOIST_TILE_LW(1); break;
+            case 2: HOIST_TILE_LW(2); break;
+            case 3: HOIST_TILE_LW(3); break;
+            case 4: HOIST_TILE_LW(4); break;
+            case 5: HOIST_TILE_LW(5); break;
+            case 6: HOIST_TILE_LW(6); break;
+            case 7: HOIST_TILE_LW(7); break;
+            case 8: HOIST_TILE_LW(8); break;
+            default: HOIST_TILE_LW(INNER_MAX_BETA);
+        }
 #undef HOIST_TILE_LW
 #undef HOIST_TILE
         return;

@@ -524,3 +524,9 @@ def test_key_products_stay_exact_at_the_ends_of_their_range(be, p51):
 def test_digit_diagonals_at_their_largest(be, bits, channels, size, kernel):
     """every word p - 1, every weight +-(p - 1) / 2, output channels that end inside a channel group"""
     pc.case_conv_channels(be, (6, 1, bits, 0, bits + 1, 1), 420 + channels, channels, size, size + 1, 35, size, 1, 0, residues=False, extreme=True, kernel=kernel)
+
+
+@pytest.mark.parametrize("digits,batch", [(1, 13), (2, 5), (3, 11), (4, 1), (5, 7), (6, 6), (7, 3), (8, 9), (9, 2)])
+def test_shared_rotations_for_every_number_of_digits(be, digits, batch):
+    """items that end inside a group of four and inside a workgroup's share, one and several rotations"""
+    pc.case_rotate_hoisted(be, (8, digits, 40, 1, 41, 1), seed=440 + digits, rotations=[1, 5, 100], batch=batch)

@@ -878,3 +878,9 @@ def test_digit_diagonals_at_their_largest(be, bits, channels, size, kernel):
     """every word p - 1, every weight +-(p - 1) / 2, output channels that end inside a channel group"""
     announce("conv digits, %d bits, %d channels" % (bits, channels))
     pc.case_conv_channels(be, (7, 2, bits, 0, bits + 1, 1), 420 + channels, channels, size, size + 1, 35, size, 1, 0, residues=False, extreme=True, kernel=kernel)
+
+
+@pytest.mark.parametrize("digits,batch", [(1, 13), (2, 5), (3, 11), (4, 1), (5, 7), (6, 6), (7, 3), (8, 9), (9, 2)])
+def test_shared_rotations_for_every_number_of_digits(be, digits, batch):
+    announce("shared rotations, %d digits" % digits)
+    pc.case_rotate_hoisted(be, (9, digits, 50, 1, 51, 1), seed=440 + digits, rotations=[1, 5, 100], batch=batch)
