@@ -660,16 +660,15 @@ __device__ __forceinline__ void inner_store(const RowsInnerArgs &A, unsigned ite
     if (!tensor_mode && A.fold_tail && (int)x < A.level) {
         const WMul Pi = A.Pinv[t];
         const u64d *l0 = A.addend + (size_t)item * A.add_item_stride + (size_t)x * N, *d0 = l0 + tile0;
-        const bool both = A.fold_tail == 1;  // 2: only the first component has an addend (rotation)
+        const bool both = !GAL && A.fold_tail == 1;  // only the first component of a rotation has an addend
         const u64d *l1 = both ? l0 + A.add_comp_stride : l0, *d1 = l1 + tile0;
         const double has1 = both ? 1.0 : 0.0;
         ulonglong2 dw0[8], dw1[8];
 #pragma unroll
         for (int s = 0; s < 8; s++) {
-            if (GAL) {
-                const unsigned j = (unsigned)tile0 + hi4 * 256u + 32u * s + 2u * lo4;
-                dw0[s] = galois_pair_load(l0, j, gal->g[item], A.logN);
-                dw1[s] = both ? galois_pair_load(l1, j, gal->g[item], A.logN) : dw0[s];
+            if (GAL) {  // (a load that only some calls make had every one before it waited for: 131 rotations at N = 2^14, 8 primes 428 us, 417 like this)
+                dw0[s] = galois_pair_load(l0, (unsigned)tile0 + hi4 * 256u + 32u * s + 2u * lo4, gal->g[item], A.logN);
+                dw1[s] = make_ulonglong2(0ull, 0ull);
             } else {
                 dw0[s] = ((const ulonglong2 *)d0)[row_pair_index(hi4, lo4, s)];
                 dw1[s] = ((const ulonglong2 *)d1)[row_pair_index(hi4, lo4, s)];
@@ -884,13 +883,14 @@ __device__ __forceinline__ void rows_final_body(const RowsFinalArgs &A, double *
 #pragma unroll
         for (int s = 0; s < 8; s++) {
             xr[s] = pair_load<NTS>(xin, row_pair_index(hi4, lo4, s));
-            if (GAL && add) {
-                const unsigned pair = row / 2u, item = pair / (unsigned)gal->R, r = pair % (unsigned)gal->R;
+            if (ADD && !GAL) ar[s] = ((const ulonglong2 *)ad)[row_pair_index(hi4, lo4, s)];
+        }
+        if (GAL && add) {
+            const unsigned pair = row / 2u, item = pair / (unsigned)gal->R, r = pair % (unsigned)gal->R;
+#pragma unroll
+            for (int s = 0; s < 8; s++)
                 ar[s] = galois_pair_load(A.addend + (size_t)item * A.add_item_stride + (size_t)i * N,
                                          (unsigned)tile0 + hi4 * 256u + 32u * s + 2u * lo4, gal->g[r], A.logN);
-            } else if (ADD) {
-                ar[s] = ((const ulonglong2 *)ad)[row_pair_index(hi4, lo4, s)];
-            }
         }
         SCHED_FENCE();
         rows_fwd_to_lds<P51, ROW_LAZY>(A.tmpA + ((size_t)row * A.nc + i) * N + tile0, lds, tw1_lds, tw2, p, pinv, hi4, lo4, A.stream == STREAM_ALL);

@@ -291,8 +291,18 @@ __global__ __launch_bounds__((1 << LOGN) / 16) void tail_sources_kernel(TailSour
             for (int a = 0; a < A.k; a++) {  // this thread wrote these words itself
                 const WMul W = A.D.conv[(size_t)a * A.T + t];
                 const u64d *y = bl + (size_t)(a + 1) * N;
+                // words requested together, as many as the registers hold (one by one: 12.4 us for 32 rows at N = 2^12, 11.4 like this; eight at 2^14 spill,
+                // 512 rows 119 us, four 107, one by one 108)
+                constexpr int CH = LOGN == 14 ? 4 : 16;
 #pragma unroll
-                for (int e = 0; e < 16; e++) v[e] += mulmod_w(scalar_base((const double *)y + Geo::G * 256u * e)[voff], W.w, W.wp, p);  // <= p + 3 * 0.75p
+                for (int e0 = 0; e0 < 16; e0 += CH) {
+                    double yw[CH];
+#pragma unroll
+                    for (int e = 0; e < CH; e++) yw[e] = scalar_base((const double *)y + Geo::G * 256u * (e0 + e))[voff];
+                    SCHED_FENCE();
+#pragma unroll
+                    for (int e = 0; e < CH; e++) v[e0 + e] += mulmod_w(yw[e], W.w, W.wp, p);  // <= p + 3 * 0.75p
+                }
             }
 #pragma unroll
             for (int e = 0; e < 16; e++) {
