@@ -1,8 +1,8 @@
 // Modular arithmetic on the FP64 vector ALU.
 //
-// Why floating point: on CDNA the 32-bit integer multiplies a 64-bit Shoup/Barrett
-// product needs (about ten per modular multiply) issue at quarter rate, while
-// v_fma_f64 issues at full rate.  For moduli p < 2^51 a modular product can be made
+// Why floating point: a 64-bit Shoup/Barrett product needs about ten 32-bit integer
+// multiplies and their additions, and v_fma_f64 issues as fast as one of those (36 - 38 T
+// lane-instructions/s, both).  For moduli p < 2^51 a modular product can be made
 // EXACT with six FP64 instructions: the product is split error-free into
 // h = RN(a*b) and l = fma(a,b,-h); the quotient estimate q = rint(a * (b/p)) is
 // within one unit of the true quotient; fma(-q,p,h) + l then equals a*b - q*p
