@@ -10,7 +10,7 @@
 //
 // A ring larger than M is cut into 2^S blocks: the first S stages of the forward transform send block b of the result only
 // to linear combinations of the 2^S words n + q*M, so a workgroup forms its own block's word from 2^S source words with
-// 2^S - 1 products (the other blocks' workgroups repeat the conversion, which for one dropped prime is one reduction) and
+// 2^S - 1 products (the other blocks' workgroups repeat the conversion, which for one dropped prime is a subtraction, p < 2^50, or a reduction) and
 // transforms M words from there: stage s of the block uses the twiddles (2^S + b) * 2^s + i of the whole transform's table.
 //
 // Measured, whole rescales as two kernels after the inverse row pass and as this one: N = 2^14, 256 ciphertexts of 8 primes 476 and 323 us;
