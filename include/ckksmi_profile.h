@@ -68,7 +68,8 @@ const char *ckksmi_kernel_class_name(const ckksmi_ctx *ctx, int kernel_class);
 /* Launch-shape knobs (benchmarks and tests; the defaults suit a full GPU).
  * CKKSMI_TUNE_TARGET_WGS: number of workgroups a transform launch aims for before its workgroups start looping over
  * the items of the batch (default 8192; a small value makes even a small batch exercise the item loops).  The
- * matrix-core multiply-accumulate aims for half of it before a workgroup walks several output positions.  The numbers of limbs
+ * matrix-core multiply-accumulate aims for half of it before a workgroup walks several output positions, rotations from a shared ModUp for a quarter before it walks several
+ * rotations.  The numbers of limbs
  * and rows from which a sequence keeps its converted limbs on chip scale with it: a small value takes these kernels at small
  * batches.  Results never depend on it. */
 #define CKKSMI_TUNE_TARGET_WGS 0

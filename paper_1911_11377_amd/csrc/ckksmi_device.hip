@@ -476,6 +476,15 @@ struct HoistPlan {
 // the gather through LDS needs runs of 256 words and at most INNER_MAX_BETA digits; otherwise the plain gather kernel
 inline bool hoisted_tile_ok(const ckksmi_ctx *c, int beta) { return c->logN >= 8 && beta <= INNER_MAX_BETA && EW_THREADS == 256; }
 
+// the instance with the smallest LDS that holds `need` staged words (at least one item's: BETA rows of 256)
+template <int BETA, int LW>
+void launch_hoisted_tile(ckksmi_ctx *c, const HoistArgs &A, const dim3 &grid, int need, double work, hipStream_t st) {
+    if constexpr (LW > HOIST_LDS_WORDS) c->no_kernel = true;
+    else if constexpr (LW < 256 * BETA) launch_hoisted_tile<BETA, 2 * LW>(c, A, grid, need, work, st);
+    else if (need > LW) launch_hoisted_tile<BETA, 2 * LW>(c, A, grid, need, work, st);
+    else KL(c, CKKSMI_K_INNER_HOISTED, work, (inner_product_hoisted_tile_kernel<LW, BETA>), grid, dim3(EW_THREADS), st, A);
+}
+
 void launch_hoisted_inner(ckksmi_ctx *c, const HoistPlan &H, const u64 *dt, const u64 *d_eval, size_t d_stride, u64 *acc, int items, int level,
                           hipStream_t st) {
     HoistArgs A;
@@ -490,35 +499,21 @@ void launch_hoisted_inner(ckksmi_ctx *c, const HoistPlan &H, const u64 *dt, cons
         A.item_chunks = (items + A.items_per_wg - 1) / A.items_per_wg;
         // few items: the rotations are spread over workgroups as well, until the chip is filled (each rotation chunk stages
         // the source runs again)
-        const size_t base = (size_t)(c->N / 256) * A.E * A.item_chunks;
-        int rot_chunks = (int)std::min<size_t>((size_t)H.R, (2048 + base - 1) / base);
+        const size_t base = (size_t)(c->N / 256) * A.E * A.item_chunks, fill = (size_t)c->ntt_target_wgs / 4;  // 2048
+        int rot_chunks = std::max(1, (int)std::min<size_t>((size_t)H.R, (fill + base - 1) / base));
         A.rots_per_wg = (H.R + rot_chunks - 1) / rot_chunks;
         rot_chunks = (H.R + A.rots_per_wg - 1) / A.rots_per_wg;
         const unsigned z = (unsigned)(A.item_chunks * rot_chunks);
         const int need = A.items_per_wg * A.beta * 256;  // staged words
         const dim3 grid((unsigned)(c->N / 256), A.E, z);
         const double work = (double)items * H.R * A.E;
-#define HOIST_TILE(LW, MB) KL(c, CKKSMI_K_INNER_HOISTED, work, (inner_product_hoisted_tile_kernel<LW, MB>), grid, dim3(EW_THREADS), st, A)
-#define HOIST_TILE_LW(MB)                      \
-    do {                                       \
-        if (need <= 1024) HOIST_TILE(1024, MB);       \
-        else if (need <= 2048) HOIST_TILE(2048, MB);  \
-        else if (need <= 4096) HOIST_TILE(4096, MB);  \
-        else HOIST_TILE(HOIST_LDS_WORDS, MB);         \
-    } while (0)
+#define HOIST_TILE_CASE(BETA) case BETA: launch_hoisted_tile<BETA, 1024>(c, A, grid, need, work, st); break;
         switch (A.beta) {
-            case 1: HOIST_TILE_LW(1); break;
-            case 2: HOIST_TILE_LW(2); break;
-            case 3: HOIST_TILE_LW(3); break;
-            case 4: HOIST_TILE_LW(4); break;
-            case 5: HOIST_TILE_LW(5); break;
-            case 6: HOIST_TILE_LW(6); break;
-            case 7: HOIST_TILE_LW(7); break;
-            case 8: HOIST_TILE_LW(8); break;
-            default: HOIST_TILE_LW(INNER_MAX_BETA);
+            HOIST_TILE_CASE(1) HOIST_TILE_CASE(2) HOIST_TILE_CASE(3) HOIST_TILE_CASE(4) HOIST_TILE_CASE(5) HOIST_TILE_CASE(6) HOIST_TILE_CASE(7) HOIST_TILE_CASE(8)
+            HOIST_TILE_CASE(9) HOIST_TILE_CASE(10) HOIST_TILE_CASE(11) HOIST_TILE_CASE(12) HOIST_TILE_CASE(13) HOIST_TILE_CASE(14) HOIST_TILE_CASE(15) HOIST_TILE_CASE(16)
+            default: c->no_kernel = true;
         }
-#undef HOIST_TILE_LW
-#undef HOIST_TILE
+#undef HOIST_TILE_CASE
         return;
     }
     KL(c, CKKSMI_K_INNER_HOISTED, (double)items * H.R * A.E, inner_product_hoisted_kernel, dim3(ew_blocks(c->N), A.E, H.R), dim3(EW_THREADS), st, A);

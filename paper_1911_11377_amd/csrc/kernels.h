@@ -763,7 +763,6 @@ __global__ __launch_bounds__(EW_THREADS) void inner_product_hoisted_kernel(Hoist
 // galois_pair_load), so key words, staged words and results all move 16 bytes per lane.  The first 128 threads form the
 // first component's sums, the other 128 the second's (each key word is read once).
 #define HOIST_LDS_WORDS 8192  // 64 KiB: items_per_wg * beta * 256 words at most
-#define HOIST_EXACT_BETA 8
 #ifdef CKKSMI_EMULATE
 #define HOIST_UNIFORM(v) (v)
 #define HOIST_LOADS_DONE() ((void)0)
@@ -772,18 +771,21 @@ __global__ __launch_bounds__(EW_THREADS) void inner_product_hoisted_kernel(Hoist
 #define HOIST_LOADS_DONE() __builtin_amdgcn_s_waitcnt(0x0f70)  // vmcnt(0)
 #endif
 // LW: words of LDS, the smallest of 1024 .. HOIST_LDS_WORDS that holds the staged rows (few items: more workgroups per
-// compute unit, whose dependent key reads then overlap); MB: the number of digits up to HOIST_EXACT_BETA (INNER_MAX_BETA: a bound on it), which
-// sizes the registers that hold a rotation's key words.
+// compute unit, whose dependent key reads then overlap); BETA: the number of digits
 // What bounded it were loads one after the other: behind a condition each, of a row or a digit that may not exist, a workgroup's 16 staging loads
 // and every digit's LDS read were waited for singly.  Rows beyond the last are read from the last one now, the digit loops have no
 // conditions, and the next rotation's key words are waited for before this one's results are stored, so that nobody waits for the stores.
-// 256 rotations of 32 ciphertexts at N = 2^14, 8 primes: 532 -> 418 us; 7 of one ciphertext 34.2 -> 30.6.
+// 256 rotations of 32 ciphertexts at N = 2^14, 8 primes: 532 -> 418 us; 7 of one ciphertext 34.2 -> 30.6.  One instance for every number of digits: with one
+// for all above eight, whose loops have conditions, and pairs of items where three fit, 9 digits of 32 ciphertexts took 730 us, 630 before that, 495 now
+// (10: 870, 760, 645; 12: 1370, 1350, 1345; 16 at N = 2^13, 9 ciphertexts: 356, 338, 329).
 // grid: x = source run (N/256), y = extended limb, z = (chunk of items_per_wg items, chunk of rots_per_wg rotations)
-template <int LW, int MB>
+template <int LW, int BETA>
 __global__ __launch_bounds__(EW_THREADS) void inner_product_hoisted_tile_kernel(HoistArgs A) {
     __shared__ double tile[LW];
-    constexpr bool EXACT = MB <= HOIST_EXACT_BETA;
-    const int beta = EXACT ? MB : A.beta;
+    // items together, whose LDS reads are in flight at once: as many as divide the number that fits (two items of 15 or 16 digits: more than
+    // 256 registers)
+    constexpr int FIT = LW / 256 / BETA, G = FIT % 4 == 0 ? 4 : FIT % 5 == 0 ? 5 : FIT % 3 == 0 ? 3 : FIT % 2 == 0 && BETA <= 14 ? 2 : 1;
+    static_assert(FIT >= 1, "one item's rows");
     const unsigned N = 1u << A.logN;
     const unsigned tid = threadIdx.x, pr = tid & 127u, comp = HOIST_UNIFORM(tid >> 7), src0 = blockIdx.x * 256u, x = blockIdx.y;
     const int t = (int)x < A.level ? (int)x : A.n_q + (int)x - A.level;
@@ -793,26 +795,25 @@ __global__ __launch_bounds__(EW_THREADS) void inner_product_hoisted_tile_kernel(
     const int r_begin = (int)(blockIdx.z / (unsigned)A.item_chunks) * A.rots_per_wg;
     const int r_end = r_begin + A.rots_per_wg < A.R ? r_begin + A.rots_per_wg : A.R;
     const int n_items = (item0 + A.items_per_wg < A.items ? item0 + A.items_per_wg : A.items) - item0;
-    ulonglong2 kn[MB];
+    ulonglong2 kn[BETA];
     unsigned m_next = 0;
     auto request = [&](int r) {  // a rotation's key words at this run's image
         m_next = (automorphism_source(src0, A.ginv[r], A.logN) & ~255u) + 2u * pr;
         const u64d *key = A.key[r] + ((size_t)comp * A.T + t) * N;
 #pragma unroll
-        for (int j = 0; j < MB; j++)
-            if (EXACT || j < beta) kn[j] = *(const ulonglong2 *)(key + (size_t)j * 2 * A.T * N + m_next);
+        for (int j = 0; j < BETA; j++) kn[j] = *(const ulonglong2 *)(key + (size_t)j * 2 * A.T * N + m_next);
     };
     {
         // the staged rows (item, digit), at most LW / 256 of them: the two halves of the workgroup take
         // them in turn, all of a half's rows requested together
-        const int n_rows = n_items * beta;
+        const int n_rows = n_items * BETA;
         ulonglong2 raw[LW / 512];
 #pragma unroll
         for (int k = 0; k < LW / 512; k++) {
             const int q = 2 * k + (int)comp, qq = q < n_rows ? q : n_rows - 1;
-            const size_t item = (size_t)(item0 + qq / beta);
-            const int j = qq % beta;
-            const u64d *row = j == j_own ? A.d_eval + item * A.d_eval_item_stride + (size_t)x * N : A.dt + ((item * beta + j) * A.E + x) * N;
+            const size_t item = (size_t)(item0 + qq / BETA);
+            const int j = qq % BETA;
+            const u64d *row = j == j_own ? A.d_eval + item * A.d_eval_item_stride + (size_t)x * N : A.dt + ((item * BETA + j) * A.E + x) * N;
             raw[k] = ((const ulonglong2 *)(row + src0))[pr];
         }
         request(r_begin);
@@ -828,14 +829,13 @@ __global__ __launch_bounds__(EW_THREADS) void inner_product_hoisted_tile_kernel(
         const unsigned m = m_next;
         const unsigned s = automorphism_source(m, A.g[r], A.logN) - src0;  // below 256; the word after m comes from s ^ 1
         const bool swap = s & 1u;
-        double k0[MB], k1[MB];
+        double k0[BETA], k1[BETA];
 #pragma unroll
-        for (int j = 0; j < MB; j++) {
+        for (int j = 0; j < BETA; j++) {
             k0[j] = u2d(kn[j].x);
             k1[j] = u2d(kn[j].y);
         }
         if (r + 1 < r_end) request(r + 1);
-        constexpr int FIT = LW / 256 / MB, G = FIT >= 4 ? 4 : FIT >= 2 ? 2 : 1;  // items together: their LDS reads are in flight at once
         for (int i0 = 0; i0 < n_items; i0 += G) {
             double a0[G], a1[G];  // the sums of the words m and m + 1
 #pragma unroll
@@ -843,19 +843,18 @@ __global__ __launch_bounds__(EW_THREADS) void inner_product_hoisted_tile_kernel(
                 const int ii = i0 + g < n_items ? i0 + g : n_items - 1;
                 a0[g] = a1[g] = 0.0;
 #pragma unroll
-                for (int j = 0; j < MB; j++)
-                    if (EXACT || j < beta) {
-                        const double2 vv = *(const double2 *)(tile + (ii * beta + j) * 256 + (s & ~1u));
-                        const double v0 = swap ? vv.y : vv.x, v1 = swap ? vv.x : vv.y;
-                        // a reduced sum (p/2 + 1) and two products (1.25p each) stay below 3p + 1 < 2^53
-                        a0[g] += mulmod(v0, k0[j], mc.p, mc.pinv);
-                        a1[g] += mulmod(v1, k1[j], mc.p, mc.pinv);
-                        if (j & 1) {
-                            a0[g] = reduce_balanced(a0[g], mc.p, mc.pinv);
-                            a1[g] = reduce_balanced(a1[g], mc.p, mc.pinv);
-                        }
+                for (int j = 0; j < BETA; j++) {
+                    const double2 vv = *(const double2 *)(tile + (ii * BETA + j) * 256 + (s & ~1u));
+                    const double v0 = swap ? vv.y : vv.x, v1 = swap ? vv.x : vv.y;
+                    // a reduced sum (p/2 + 1) and two products (1.25p each) stay below 3p + 1 < 2^53
+                    a0[g] += mulmod(v0, k0[j], mc.p, mc.pinv);
+                    a1[g] += mulmod(v1, k1[j], mc.p, mc.pinv);
+                    if (j & 1) {
+                        a0[g] = reduce_balanced(a0[g], mc.p, mc.pinv);
+                        a1[g] = reduce_balanced(a1[g], mc.p, mc.pinv);
                     }
-                if (beta & 1) {
+                }
+                if (BETA & 1) {
                     a0[g] = reduce_balanced(a0[g], mc.p, mc.pinv);
                     a1[g] = reduce_balanced(a1[g], mc.p, mc.pinv);
                 }

@@ -520,6 +520,17 @@ def case_rotate_hoisted(be, shape, seed, rotations, batch=3, level=None, small_w
     ctx.close()
 
 
+# (digits, items): for every number of digits of the gathered inner product, several groups of items or an odd end of one
+GATHERED_DIGITS = [(1, 9), (2, 6), (3, 11), (4, 5), (5, 7), (6, 6), (7, 5), (8, 5), (9, 4), (10, 5), (11, 3), (12, 5), (13, 3), (14, 5), (15, 3), (16, 5)]
+
+
+def case_several_rotations_per_workgroup(be, logN, bits, digits, batch):
+    """three rotations in two shares: a workgroup walks two of them, another one"""
+    shares = (1 << logN) // 256 * (digits + 1) * -(-batch // min(batch, 32 // digits))  # workgroups of one share
+    with be.tuned(4 * (shares + 1)):
+        case_rotate_hoisted(be, (logN, digits, bits, 1, bits + 1, 1), seed=470 + digits, rotations=[1, 5, 100], batch=batch)
+
+
 def case_packed_layer(be, shape, seed, M_float, level=None, max_rotations=None):
     """a rotation-packed layer (matrix through hoisted rotations, plaintext diagonals, tree of adds, rescale) against the
     oracle's schedule, word for word; the encoded diagonals are inputs of both sides"""

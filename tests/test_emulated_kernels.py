@@ -530,3 +530,9 @@ def test_digit_diagonals_at_their_largest(be, bits, channels, size, kernel):
 def test_shared_rotations_for_every_number_of_digits(be, digits, batch):
     """items that end inside a group of four and inside a workgroup's share, one and several rotations"""
     pc.case_rotate_hoisted(be, (8, digits, 40, 1, 41, 1), seed=440 + digits, rotations=[1, 5, 100], batch=batch)
+
+
+@pytest.mark.parametrize("digits,batch", [c for c in pc.GATHERED_DIGITS if c[0] in (1, 3, 5, 6, 8, 9, 12, 16)])
+def test_shared_rotations_several_per_workgroup(be, digits, batch):
+    """the next rotation's key words are requested while this one's sums run, over several groups of items"""
+    pc.case_several_rotations_per_workgroup(be, 8, 40, digits, batch)

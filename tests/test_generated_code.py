@@ -1,5 +1,5 @@
-"""What the compiler makes of the kernels that address memory through scalar_base (csrc/ntt_v2.h): the assembly for gfx950 of
-one instance of each, compiled here without a GPU."""
+"""What the compiler makes of some of the kernels: the assembly for gfx950 of instances of them, compiled here without a
+GPU.  Kernels that address memory through scalar_base (csrc/ntt_v2.h), and what a kernel's time was seen to hang on."""
 import os
 import re
 import subprocess
@@ -14,29 +14,47 @@ KERNELS = ["ntt_wg_kernel<false, 13>(NttV2Args)", "ntt_wg_kernel<true, 14>(NttV2
            # the streamed instances
            "ntt_wg_kernel<false, 13, true>(NttV2Args)", "ntt_wg_kernel<true, 14, true>(NttV2Args)", "conv_final_kernel<14, 1, 1, 0, true>(ConvFinalArgs)",
            "conv_final_gal_kernel<14, 2, 1, true>(ConvFinalArgs, RowsFinalGal)"]
+HEADS = ["ckksmi_internal.h", "kernels.h", "ntt_v2.h", "ks_fused.h", "ntt_wg.h", "ks_wg.h", "ks_inner_wg.h"]
+
+pytestmark = pytest.mark.skipif(not os.path.exists(lib_build.HIPCC), reason="no hipcc")
 
 
-@pytest.mark.skipif(not os.path.exists(lib_build.HIPCC), reason="no hipcc")
-def test_scalar_bases_give_global_accesses(tmp_path):
-    """no flat memory access (64-bit vector address each, waited for with the LDS) in any of these kernels"""
-    src = tmp_path / "instances.hip"
-    heads = ["ckksmi_internal.h", "kernels.h", "ntt_v2.h", "ks_fused.h", "ntt_wg.h", "ks_wg.h", "ks_inner_wg.h"]
-    src.write_text("#include <hip/hip_runtime.h>\n" + "".join('#include "%s"\n' % h for h in heads)
-                   + "".join("template __global__ void %s;\n" % k for k in KERNELS))
-    out = tmp_path / "instances.s"
+def _assembly(tmp_path, kernels):
+    """{mangled name: lines} of the instances, the compiler's own figures behind a kernel's end among them"""
+    src, out = tmp_path / "instances.hip", tmp_path / "instances.s"
+    src.write_text("#include <hip/hip_runtime.h>\n" + "".join('#include "%s"\n' % h for h in HEADS)
+                   + "".join("template __global__ void %s;\n" % k for k in kernels))
     flags = [f for f in lib_build.FLAGS if f not in ("-shared", "-fPIC", "-Wall")]
     subprocess.check_call([lib_build.HIPCC] + flags + ["--cuda-device-only", "-S", "-I", lib_build.CSRC, str(src), "-o", str(out)], stderr=subprocess.DEVNULL)
-    kernel, flat, glob = None, {}, {}
+    kernel, lines = None, {}
     for line in out.read_text().splitlines():
-        m = re.match(r"(_Z\d+(?:ntt_wg|conv_final|tail_sources|inner_wg)\w*):", line)
+        m = re.match(r"(_Z\w+):", line)
         if m:
             kernel = m.group(1)
-            flat[kernel] = glob[kernel] = 0
-        elif re.match(r"_Z\w+:", line):
-            kernel = None
-        elif kernel:
-            flat[kernel] += bool(re.match(r"\s+flat_(load|store)", line))
-            glob[kernel] += bool(re.match(r"\s+global_(load|store)", line))
-    assert len(flat) == len(KERNELS), sorted(flat)
+        if kernel:
+            lines.setdefault(kernel, []).append(line)
+    wanted = {k: v for k, v in lines.items() if any(re.match(r"_Z\d+%sI" % k2.split("<")[0], k) for k2 in kernels)}
+    assert len(wanted) == len(kernels), sorted(lines)
+    return wanted
+
+
+def _count(lines, pattern):
+    return sum(bool(re.match(pattern, line)) for line in lines)
+
+
+def test_scalar_bases_give_global_accesses(tmp_path):
+    """no flat memory access (64-bit vector address each, waited for with the LDS) in any of these kernels"""
+    code = _assembly(tmp_path, KERNELS)
+    flat = {k: _count(v, r"\s+flat_(load|store)") for k, v in code.items()}
+    glob = {k: _count(v, r"\s+global_(load|store)") for k, v in code.items()}
     assert not any(flat.values()), flat
     assert all(n >= 16 for n in glob.values()), glob
+
+
+@pytest.mark.parametrize("digits", [9, 16])
+def test_gathered_inner_product_has_no_conditions_on_digits(tmp_path, digits):
+    """a rotation's key words and an item's staged words are read in straight-line code, whatever the number of digits (with a condition for
+    every digit: 137 branches)"""
+    (lines,) = _assembly(tmp_path, ["inner_product_hoisted_tile_kernel<8192, %d>(HoistArgs)" % digits]).values()
+    assert _count(lines, r"\s+global_load_dwordx4") >= 16 + 2 * digits
+    assert _count(lines, r"\s+s_cbranch") <= 48 and _count(lines, r"\s+scratch_") == 0

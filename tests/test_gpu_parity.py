@@ -884,3 +884,9 @@ def test_digit_diagonals_at_their_largest(be, bits, channels, size, kernel):
 def test_shared_rotations_for_every_number_of_digits(be, digits, batch):
     announce("shared rotations, %d digits" % digits)
     pc.case_rotate_hoisted(be, (9, digits, 50, 1, 51, 1), seed=440 + digits, rotations=[1, 5, 100], batch=batch)
+
+
+@pytest.mark.parametrize("logN,digits,batch", [(9, d, b) for d, b in pc.GATHERED_DIGITS] + [(12, 10, 4)])
+def test_shared_rotations_several_per_workgroup(be, logN, digits, batch):
+    announce("several shared rotations per workgroup, N=2^%d, %d digits" % (logN, digits))
+    pc.case_several_rotations_per_workgroup(be, logN, 50, digits, batch)
