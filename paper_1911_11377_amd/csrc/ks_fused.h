@@ -860,6 +860,11 @@ struct RowsFinalGal { int R; unsigned g[CKKSMI_MAX_KEYS]; };
 template <bool P51, bool NTS, bool ADD, bool GAL = false>
 __device__ __forceinline__ void rows_final_body(const RowsFinalArgs &A, double *lds, double *tw1_lds, int i, bool xm_val = false,
                                                 WMul xmv = WMul{0.0, 0.0}, const RowsFinalGal *gal = nullptr) {
+    // The kept limb's words are streamed with the results, from 16 MB on, without an addend (three waves per SIMD: a product's tail at N = 2^16, 24 primes,
+    // 4 ciphertexts 68.5 -> 62 us, 64.2 with streaming from 256 MB on only; 48: 692 -> 681, even) and for rotations from a shared ModUp (128 rotations of 11
+    // primes at N = 2^14 257 -> 228, 246 without).  Scalar multiples are slower with it: at N = 2^16 4 rows of
+    // 17 kept limbs 28.2 -> 31.4, 80 of 1 29.4 -> 32.6, 400 of 1 122 -> 128.
+    constexpr bool KEPT_NT = NTS && (!ADD || GAL);
     const unsigned N = 1u << A.logN, N1 = N >> 8;
     const double p = A.modc[i].p, pinv = A.modc[i].pinv;
     const unsigned tid = threadIdx.x, hi4 = tid >> 4, lo4 = tid & 15;
@@ -882,7 +887,7 @@ __device__ __forceinline__ void rows_final_body(const RowsFinalArgs &A, double *
         ulonglong2 xr[8], ar[ADD ? 8 : 1];
 #pragma unroll
         for (int s = 0; s < 8; s++) {
-            xr[s] = pair_load<NTS>(xin, row_pair_index(hi4, lo4, s));
+            xr[s] = pair_load<KEPT_NT>(xin, row_pair_index(hi4, lo4, s));
             if (ADD && !GAL) ar[s] = ((const ulonglong2 *)ad)[row_pair_index(hi4, lo4, s)];
         }
         if (GAL && add) {
@@ -926,9 +931,8 @@ __device__ __forceinline__ void rows_final_body(const RowsFinalArgs &A, double *
 }
 
 // grid: x = chunk of rows (item, component), y = row tile (N/4096), z = kept limb.  ADD: with an addend; without one (a product's
-// tail, plain divisions) the words in flight leave room for a third wave per SIMD; with that and the kept limb's words streamed (with
-// two waves that made it slower) 128 rows of 23 kept limbs at N = 2^16 take 906 us against 931: 5.1 TB/s, where a copy of large
-// pieces moves 6.2
+// tail, plain divisions) the words in flight leave room for a third wave per SIMD; with that and the kept limb's words streamed
+// 128 rows of 23 kept limbs at N = 2^16 take 906 us against 931: 5.1 TB/s, where a copy of large pieces moves 6.2
 template <bool NTS, bool ADD>
 __global__ __launch_bounds__(V2_THREADS, ADD ? 2 : 3) void rows_final_kernel(RowsFinalArgs A) {
     __shared__ double lds[16 * V2_GS];

@@ -58,3 +58,10 @@ def test_gathered_inner_product_has_no_conditions_on_digits(tmp_path, digits):
     (lines,) = _assembly(tmp_path, ["inner_product_hoisted_tile_kernel<8192, %d>(HoistArgs)" % digits]).values()
     assert _count(lines, r"\s+global_load_dwordx4") >= 16 + 2 * digits
     assert _count(lines, r"\s+s_cbranch") <= 48 and _count(lines, r"\s+scratch_") == 0
+
+
+def test_kept_limbs_are_streamed_where_that_was_faster(tmp_path):
+    """word pairs are requested past the caches by the last pass without an addend, not by the one for scalar multiples"""
+    code = _assembly(tmp_path, ["rows_final_kernel<true, false>(RowsFinalArgs)", "rows_final_scalar_kernel<true>(RowsFinalArgs, ScalarTab)"])
+    streamed = {("scalar" if "scalar" in k else "plain"): _count(v, r"\s+global_load_dwordx4 .* nt") for k, v in code.items()}
+    assert streamed == {"scalar": 0, "plain": 16}, streamed  # 8 each for p < 2^50 and p < 2^51
