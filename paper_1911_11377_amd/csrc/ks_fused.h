@@ -481,7 +481,7 @@ __device__ __forceinline__ void rows_fwd_to_lds(const u64d *tile, double *lds, c
     double x[16];
     stream_if(stream, [&](auto nt) {
 #pragma unroll
-        for (int e = 0; e < 16; e++) x[e] = mid_load(stream_load<nt>(scalar_base(tile) + (hi4 * 256 + lo4 + 16 * e)));
+        for (int e = 0; e < 16; e++) x[e] = mid_load(stream_load<nt>(&tile[hi4 * 256 + lo4 + 16 * e]));
     });
     {
         // round-1 twiddles are the same for the 16 lanes of a row: kept in LDS, not in registers
