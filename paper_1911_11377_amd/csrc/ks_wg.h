@@ -291,9 +291,10 @@ __global__ __launch_bounds__((1 << LOGN) / 16) void tail_sources_kernel(TailSour
             for (int a = 0; a < A.k; a++) {  // this thread wrote these words itself
                 const WMul W = A.D.conv[(size_t)a * A.T + t];
                 const u64d *y = bl + (size_t)(a + 1) * N;
-                // words requested together, as many as the registers hold (one by one: 12.4 us for 32 rows at N = 2^12, 11.4 like this; eight at 2^14 spill,
-                // 512 rows 119 us, four 107, one by one 108)
-                constexpr int CH = LOGN == 14 ? 4 : 16;
+                // Words requested together, as many as the registers hold beside the waves that were there: all of them at N = 2^12 (one by one: 12.4 us for 32 rows,
+                // 11.4 like this; 27.1 and 24.8 for 1024), four above (eight at 2^14 spill, 512 rows 119 us, four 107, one by one 108; 16 at
+                // 2^13 are one workgroup per compute unit instead of two, 512 rows 46.3 -> 49.5, four 43.6).
+                constexpr int CH = LOGN == 12 ? 16 : 4;
 #pragma unroll
                 for (int e0 = 0; e0 < 16; e0 += CH) {
                     double yw[CH];

@@ -65,3 +65,10 @@ def test_kept_limbs_are_streamed_where_that_was_faster(tmp_path):
     code = _assembly(tmp_path, ["rows_final_kernel<true, false>(RowsFinalArgs)", "rows_final_scalar_kernel<true>(RowsFinalArgs, ScalarTab)"])
     streamed = {("scalar" if "scalar" in k else "plain"): _count(v, r"\s+global_load_dwordx4 .* nt") for k, v in code.items()}
     assert streamed == {"scalar": 0, "plain": 16}, streamed  # 8 each for p < 2^50 and p < 2^51
+
+
+def test_tail_sources_leave_room_for_two_workgroups(tmp_path):
+    """N = 2^13: the words in flight do not take the registers of the compute unit's second workgroup (512 threads each: four waves per SIMD)"""
+    (lines,) = _assembly(tmp_path, ["tail_sources_kernel<13>(TailSourcesArgs)"]).values()
+    occupancy = [int(m.group(1)) for m in (re.match(r"; Occupancy: (\d+)", line) for line in lines) if m]
+    assert occupancy == [4], occupancy
