@@ -1014,9 +1014,50 @@ def case_conv(be, shape, seed, Cin, H, W, Oc, kh, stride, pad, level=None, rows_
     ctx.close()
 
 
-def case_conv_channels(be, shape, seed, Cin, H, W, Oc, kh, stride, pad, residues, rows=None, extreme=False, kernel="conv_mac_mfma_kernel"):
+def _balanced_digits(w, n=7):
+    """w = sum of d_j 256^j with digits -128 .. 127 (the last one takes the rest)"""
+    out = []
+    for _ in range(n - 1):
+        d = (w + 128) % 256 - 128
+        out.append(d)
+        w = (w - d) // 256
+    return out + [w]
+
+
+def digit_extremes(q):
+    """words and weights whose seven digits (a word's byte minus 128, a weight's balanced digit) are at their ends, as far as primes q let them:
+    words of bytes 0, of bytes 255 and alternating, weights of digits -128, of 127 and alternating, each also next to the bound of all q"""
+    n = (min(q).bit_length() - 1) // 8  # digits that are free
+    top = min(q) >> (8 * n)             # what is left for the one above
+    words = [0, 256**n - 1 + ((top - 1) << (8 * n) if top > 1 else 0), sum(255 << (8 * i) for i in range(0, n, 2)), sum(255 << (8 * i) for i in range(1, n, 2)), min(q) - 1]
+    half = (min(q) - 1) // 2
+    weights = []
+    for pattern in ([-128] * n, [127] * n, [-128, 127] * n, [127, -128] * n):
+        w = sum(d * 256**j for j, d in enumerate(pattern[:n]))
+        while abs(w) > half:  # the last digit moves towards zero
+            w -= 256 ** (n - 1) * (1 if w > 0 else -1)
+        weights += [w] + [w + s * 256**n for s in (-1, 1) if abs(w + s * 256**n) <= half]
+    assert all(0 <= x < min(q) for x in words) and all(abs(w) <= half for w in weights)
+    return words, weights + [half, -half]
+
+
+def largest_diagonals(words, weights, taps):
+    """the largest |D_d|, sums of digit products on a diagonal, and |D_d + 2^8 D_d+1 + 2^16 D_d+2 + 2^24 D_d+3|, d = 0, 4, 8, when all taps agree"""
+    largest, group = 0, 0
+    for x in words:
+        xd = [(x >> (8 * i) & 255) - 128 for i in range(7)]
+        for w in weights:
+            wd = _balanced_digits(w)
+            D = [taps * sum(xd[i] * wd[d - i] for i in range(7) if 0 <= d - i < 7) for d in range(13)]
+            largest = max(largest, max(map(abs, D)))
+            group = max(group, max(abs(sum(D[d + k] << (8 * k) for k in range(4))) for d in (0, 4, 8)))
+    return largest, group
+
+
+def case_conv_channels(be, shape, seed, Cin, H, W, Oc, kh, stride, pad, residues, rows=None, extreme=False, kernel="conv_mac_mfma_kernel", digits=False):
     """one layer: residues or digits, told apart by the digit kernels' sums of weights, or neither (conv_mac_kernel); `rows`: one strip of output rows;
-    `extreme`: every word p - 1 and every weight (p - 1) / 2, the largest sum that the residues have to tell apart"""
+    `extreme`: every word p - 1 and every weight (p - 1) / 2, the largest sum that the residues have to tell apart; `digits`: words and weights of
+    digit_extremes, all taps of an output alike, which makes the largest sums that the digit diagonals have to hold"""
     M = make_material(shape, seed)
     O = M.O
     ctx = be.context(*shape)
@@ -1029,6 +1070,13 @@ def case_conv_channels(be, shape, seed, Cin, H, W, Oc, kh, stride, pad, residues
             x[..., i, :] = O.q[i] - 1
         wi[...] = (O.q[0] - 1) // 2
         wi[1] *= -1
+    if digits:
+        words, weights = digit_extremes(O.q[:level])
+        x[...] = np.asarray(words, dtype=np.uint64)[np.arange(O.N) % len(words)]
+        wi[...] = np.asarray(weights, dtype=np.int64)[np.arange(Oc) % len(weights)].reshape(Oc, 1, 1, 1)
+        D, group = largest_diagonals(words, weights, Cin * kh * kh)
+        if min(O.q[:level]).bit_length() >= 50:  # the bounds that the kernels state: seven products of 2^14 a tap, 2^24 of the largest in a group
+            assert D >= 6 * 2**14 * Cin * kh * kh and group >= 5 * 2**14 * Cin * kh * kh << 24
     Ho, Wo = (H + 2 * pad - kh) // stride + 1, (W + 2 * pad - kh) // stride + 1
     want = O.conv2d_mac(x, wi, stride, pad, level)
     r0, r1 = rows or (0, Ho)
@@ -1063,7 +1111,7 @@ PADDED_LAYERS += [(5, 28, 6, 8, 5, 2, 4, False, (0, 3), "conv_mac_mfma_resident_
 WIDE_LAYER = (1, 1, 144700, 8, 30, 50000, 29, False, (0, 1), "conv_mac_kernel")
 
 
-# (bits, input channels, kernel size, kernel): the largest sums that four diagonals combine (512 taps; with 51-bit primes 256), the first tap
+# (bits, input channels, kernel size, kernel): the most taps whose diagonals combine four at a time (512; with 51-bit primes 256), the first
 # counts beyond either, one and two steps with and without a short last one
 EXTREME_TAPS = [(50, 512, 1, "conv_mac_mfma_kernel"), (50, 513, 1, "conv_mac_mfma_kernel"), (51, 257, 1, "conv_mac_mfma_kernel"), (51, 512, 1, "conv_mac_mfma_kernel"),
                 (51, 256, 1, "conv_mac_mfma_resident_kernel"), (50, 208, 1, "conv_mac_mfma_resident_kernel"), (51, 5, 5, "conv_mac_mfma_strip_kernel"),
