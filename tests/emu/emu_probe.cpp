@@ -93,3 +93,6 @@ extern "C" double emu_probe_key_term(int p51, double k, double v, double a, doub
     return a;
 }
 extern "C" double emu_probe_key_factor(int p51) { return p51 ? LazyRange<true>::FACTOR : LazyRange<false>::FACTOR; }
+
+// an encoding's coefficient as a residue; the magnitude that it reports
+extern "C" double emu_probe_real_word(double v, double factor, double p, double *largest) { return real_word(v, factor, p, 1.0 / p, *largest); }

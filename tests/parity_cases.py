@@ -699,6 +699,49 @@ def case_sample_device(be, shape, seed, rows=3, sigma=3.2, first_index=(1 << 33)
     ctx.close()
 
 
+def case_encode_refusals(be, shape, batch=2):
+    """a slot that is too large, infinite or not a number, in the first or the last item, is reported; the call after it is not"""
+    ctx = be.context(*shape)
+    half, L = 1 << shape[0] - 1, shape[1]
+    z = np.stack([wl.slots_real(half, 700, ("refuse", i)).real for i in range(batch)]).astype(np.float64)
+    pt, ws = be.empty(batch, L, 2 * half), be.ws(batch * 2 * half * 16)
+    encode = lambda v, scale: ctx.encode_device(be.to_dev(v, np.float64), None, scale, L, batch, pt, ws, stream=be.stream)
+    encode(z, 2.0**30)
+    want = be.to_host(pt)
+    for item, slot, value in ((0, 0, 2.0**80), (batch - 1, half - 1, 2.0**80), (batch - 1, 5, np.inf), (0, half // 2, -np.inf), (batch - 1, half - 1, np.nan)):
+        bad = z.copy()
+        bad[item, slot] = value
+        try:
+            encode(bad, 2.0**30)
+            raise AssertionError("%r in slot %d of item %d accepted" % (value, slot, item))
+        except ckksmi.CkksmiError as e:
+            assert e.code == ckksmi.EINVAL
+        encode(z, 2.0**30)
+        assert np.array_equal(be.to_host(pt), want)
+    # every slot v: the constant coefficient is v * scale, 2^61 and 3.9e18 are accepted, 4.1e18 is refused
+    for value, ok in ((2.0**61, True), (-3.9e18, True), (4.1e18, False)):
+        try:
+            encode(np.full((batch, half), value / 2.0**30), 2.0**30)
+            assert ok, "%g accepted" % value
+        except ckksmi.CkksmiError as e:
+            assert e.code == ckksmi.EINVAL and not ok, "%g refused" % value
+    ctx.close()
+
+
+def case_encode_batch_against_singles(be, shape, batch, log_scale=40):
+    """a batch large enough for whole limbs in a workgroup, word for word the same as its items one by one"""
+    ctx = be.context(*shape)
+    half, L = 1 << shape[0] - 1, shape[1]
+    z = np.stack([wl.slots_real(half, 701, ("singles", i)).real for i in range(batch)]).astype(np.float64)
+    pt, one, ws = be.empty(batch, L, 2 * half), be.empty(1, L, 2 * half), be.ws(batch * 2 * half * 16)
+    ctx.encode_device(be.to_dev(z, np.float64), None, 2.0**log_scale, L, batch, pt, ws, stream=be.stream)
+    got = be.to_host(pt).reshape(batch, L, -1)
+    for i in sorted({0, 1, batch // 2, batch - 1}):
+        ctx.encode_device(be.to_dev(z[i:i + 1], np.float64), None, 2.0**log_scale, L, 1, one, ws, stream=be.stream)
+        assert np.array_equal(be.to_host(one).reshape(L, -1), got[i]), "item %d" % i
+    ctx.close()
+
+
 def case_variant_errors(be, shape=(6, 3, 30, 1, 31, 1)):
     """argument checks of the variant entry points: every refusal happens on the host, before anything is enqueued"""
     ctx = be.context(*shape)

@@ -536,3 +536,33 @@ def test_shared_rotations_for_every_number_of_digits(be, digits, batch):
 def test_shared_rotations_several_per_workgroup(be, digits, batch):
     """the next rotation's key words are requested while this one's sums run, over several groups of items"""
     pc.case_several_rotations_per_workgroup(be, 8, 40, digits, batch)
+
+
+def test_coefficients_become_residues_exactly(be):
+    """the remainder of one floating-point reduction for coefficients up to 4e18, where the quotient by the smallest primes has 49 bits: at and next to
+    multiples of p and of p / 2, as far as a double can be there"""
+    probe = be.lib.emu_probe_real_word
+    probe.restype = ctypes.c_double
+    rng = np.random.default_rng(70)
+    for p in (2**13 + 1, 12289, 40961, 2**20 + 7, 2**40 - 87, 2**50 - 27, 2**50 + 31, 2**51 - 129):
+        near = [k * p // 2 + d for k in [1, 2, 3] + [int(x) for x in rng.integers(1, 8 * 10**18 // p, 1500)] for d in (-1, 0, 1)]
+        for m in near + [int(x) for x in rng.integers(0, 4 * 10**18, 1500)] + [0, 4 * 10**18 - 512]:
+            for v in (float(m), -float(m)):
+                if abs(v) < 4e18:
+                    largest = ctypes.c_double(0.0)
+                    r = probe(ctypes.c_double(v), ctypes.c_double(1.0), ctypes.c_double(p), ctypes.byref(largest))
+                    assert r == int(r) and abs(r) <= 0.63 * p and (int(r) - int(v)) % p == 0 and largest.value == abs(v)
+    for v in (4e18, -5e18, float("inf"), float("-inf"), float("nan")):
+        largest = ctypes.c_double(1.0)
+        probe(ctypes.c_double(v), ctypes.c_double(1.0), ctypes.c_double(40961.0), ctypes.byref(largest))
+        assert not largest.value < 4e18
+
+
+@pytest.mark.parametrize("shape,batch", [((12, 2, 40, 0, 41, 1), 2), ((14, 1, 50, 0, 51, 1), 2), ((15, 1, 51, 0, 52, 1), 1)])
+def test_encodings_that_are_too_large_are_refused(be, shape, batch):
+    pc.case_encode_refusals(be, shape, batch)
+
+
+def test_encodings_in_batches_and_one_by_one(be):
+    """N = 2^14: 64 limbs take the whole-limb kernel, one item the two passes"""
+    pc.case_encode_batch_against_singles(be, (14, 2, 50, 0, 51, 1), 32)

@@ -890,3 +890,22 @@ def test_shared_rotations_for_every_number_of_digits(be, digits, batch):
 def test_shared_rotations_several_per_workgroup(be, logN, digits, batch):
     announce("several shared rotations per workgroup, N=2^%d, %d digits" % (logN, digits))
     pc.case_several_rotations_per_workgroup(be, logN, 50, digits, batch)
+
+
+@pytest.mark.parametrize("shape,batch", [((12, 2, 40, 0, 41, 1), 3), ((13, 2, 40, 0, 41, 1), 2), ((14, 1, 50, 0, 51, 1), 2), ((14, 8, 50, 0, 51, 1), 9),
+                                         ((15, 2, 51, 0, 52, 1), 2), ((16, 3, 50, 0, 51, 1), 2)])
+def test_encodings_that_are_too_large_are_refused(be, shape, batch):
+    announce("encodings refused, %r" % (shape,))
+    pc.case_encode_refusals(be, shape, batch)
+
+
+@pytest.mark.parametrize("shape,batch", [((14, 8, 50, 0, 51, 1), 9), ((14, 3, 51, 0, 52, 1), 70)])
+def test_encodings_in_batches_and_one_by_one(be, shape, batch):
+    announce("encodings in batches, %r" % (shape,))
+    pc.case_encode_batch_against_singles(be, shape, batch)
+
+
+@pytest.mark.parametrize("logN", [13, 14, 15, 16])
+def test_encodings_at_every_ring_size(be, logN):
+    announce("encoding at N=2^%d" % logN)
+    pc.case_encode_encrypt_device(be, (logN, 2, 50, 1, 51, 1), seed=365, batch=1, log_scale=40)
