@@ -228,6 +228,9 @@ __device__ __forceinline__ void modup_cols_target(const double (&yd)[NSRC][16], 
     constexpr int ENTRY = (int)(256.0 * IN + 0.999);
     static_assert(IN <= LazyRange<P51>::LIM, "the sum leaves the exact range");
     typedef ColsMasks<Q, P51, ENTRY> Mk;
+    // A copied word is bounded in units of 2^50 and p may be far smaller.  After a stage that reduces, all words are bounded in p itself, as the
+    // canonical form behind the row pass (ROW_NEAR) needs it.
+    static_assert(!COPY || P51 || Mk::PLAN != 0, "a copied word that no stage reduces");
     BODY_TAG(P51);
     if (VARIANT == 2) {  // the products by these constants would be moved above the branch all the same: 350 registers spilled
 #pragma unroll

@@ -397,8 +397,9 @@ struct ColsMasks {
 // ... and of the row pass, from MIDF.  What becomes of the results:
 //   ROW_REDUCED  they are reduced or made canonical whatever they are;
 //   ROW_LAZY     a pointwise step takes them as they are (ROWX);
-//   ROW_NEAR     p < 2^50: canon_near takes them;  ROW_FACTOR: a key word's product takes them (FACTOR).  Both cost one reduction of
-//                half of the words more than ROW_REDUCED and save that of all of them.  p < 2^51: as ROW_REDUCED.
+//   ROW_NEAR     p < 2^50: canon_near takes them (the words that enter have to be bounded in p itself);  ROW_FACTOR: a key word's product takes
+//                them (FACTOR).  Both cost one reduction of half of the words more than ROW_REDUCED and save that of all of them.  p < 2^51: as
+//                ROW_REDUCED.
 enum { ROW_REDUCED, ROW_LAZY, ROW_NEAR, ROW_FACTOR };
 template <bool P51, int X>
 struct RowMasks {

@@ -9,8 +9,8 @@ from paper_1911_11377_amd import workloads as wl
 class Material:
     """Oracle-side parameter set + keys for one seeded instance."""
 
-    def __init__(self, logN, n_q, q_bits, k, special_bits, alpha, seed, rotations=()):
-        self.O = orc.Oracle(logN, n_q, q_bits, k, special_bits, alpha)
+    def __init__(self, logN, n_q, q_bits, k, special_bits, alpha, seed, rotations=(), moduli=None):
+        self.O = orc.Oracle(logN, n_q, q_bits, k, special_bits, alpha, moduli=moduli)
         O = self.O
         self.seed = seed
         self.logN, self.N = logN, 1 << logN

@@ -41,8 +41,8 @@ class GpuBackend(_Tunable):
         assert torch.cuda.is_available(), "GPU tests need a GPU"
         self.lib_path = None
 
-    def context(self, logN, n_q, q_bits, k, special_bits, alpha):
-        return self._tune(ckksmi.Context(logN, n_q, q_bits, k, special_bits, alpha, device=0))
+    def context(self, logN, n_q, q_bits, k, special_bits, alpha, moduli=None):
+        return self._tune(ckksmi.Context(logN, n_q, q_bits, k, special_bits, alpha, device=0, moduli=moduli))
 
     def to_dev(self, arr, dtype=np.uint64):
         a = np.ascontiguousarray(arr, dtype=dtype)
@@ -71,8 +71,8 @@ class EmuBackend(_Tunable):
         self.lib_path = emu_support.emu_lib_path()
         self.lib = ckksmi.load(self.lib_path)
 
-    def context(self, logN, n_q, q_bits, k, special_bits, alpha):
-        return self._tune(ckksmi.Context(logN, n_q, q_bits, k, special_bits, alpha, device=0, lib=self.lib_path))
+    def context(self, logN, n_q, q_bits, k, special_bits, alpha, moduli=None):
+        return self._tune(ckksmi.Context(logN, n_q, q_bits, k, special_bits, alpha, device=0, lib=self.lib_path, moduli=moduli))
 
     def to_dev(self, arr, dtype=np.uint64):
         return self.es.to_emu(self.lib, arr, dtype)
@@ -92,8 +92,16 @@ class EmuBackend(_Tunable):
 
 
 def make_material(shape, seed, rotations=()):
-    logN, n_q, q_bits, k, special_bits, alpha = shape
-    return Material(logN, n_q, q_bits, k, special_bits, alpha, seed=seed, rotations=rotations)
+    logN, n_q, q_bits, k, special_bits, alpha, moduli = tuple(shape) + (None,) * (7 - len(shape))
+    return Material(logN, n_q, q_bits, k, special_bits, alpha, seed=seed, rotations=rotations, moduli=moduli)
+
+
+def mixed_shape(logN, q_bits, special_bits, alpha):
+    """a shape whose primes have these widths, in this order"""
+    moduli = []
+    for bits in q_bits + special_bits:
+        moduli += orc.find_primes(bits, logN, 1, exclude=moduli)
+    return logN, len(q_bits), max(q_bits), len(special_bits), max(special_bits), alpha, tuple(moduli)
 
 
 def random_cts(M, level, batch, seed, tag, comps=2):
@@ -1261,3 +1269,20 @@ def case_pool(be, shape, seed, Cin, H, W, k, level=None, pad=0):
         assert e.code == ckksmi.EINVAL
     ctx.close()
 
+
+
+# (widths of the primes, of the special ones, primes per digit): words of wide primes enter transforms modulo narrow ones as they are, and the other way round
+MIXED_WIDTHS = [((51, 20, 50, 24, 40), (51,), 1), ((20, 51, 22, 50), (50,), 1), ((50, 24, 49, 51, 22, 40), (51, 30), 2), ((22, 50, 24, 51, 50), (50, 51, 24), 3)]
+
+
+def case_mixed_widths(be, logN, widths, seed):
+    """every key switch and division of a chain of wide and narrow primes, on and off chip"""
+    shape = mixed_shape(logN, *widths)
+    assert [m.bit_length() for m in shape[6]] == [b for b in widths[0] + widths[1]]
+    L = shape[1]
+    case_rescale(be, shape, seed=seed)
+    case_relin_and_composite(be, shape, seed=seed + 1, batch=2, levels=[L, L - 1])
+    case_rotate(be, shape, seed=seed + 2, rotations=[1, 77], batch=3, level=L)
+    case_rotate_hoisted(be, shape, seed=seed + 3, rotations=[1, 5], batch=2, level=L)
+    if logN == 12:
+        case_edge_values(be, shape, seed=seed + 4, conv=False)

@@ -566,3 +566,11 @@ def test_encodings_that_are_too_large_are_refused(be, shape, batch):
 def test_encodings_in_batches_and_one_by_one(be):
     """N = 2^14: 64 limbs take the whole-limb kernel, one item the two passes"""
     pc.case_encode_batch_against_singles(be, (14, 2, 50, 0, 51, 1), 32)
+
+
+@pytest.mark.parametrize("logN,widths", [(12, w) for w in pc.MIXED_WIDTHS] + [(13, pc.MIXED_WIDTHS[0]), (14, pc.MIXED_WIDTHS[0])])
+def test_chains_of_wide_and_narrow_primes(be, logN, widths):
+    pc.case_mixed_widths(be, logN, widths, seed=480)
+    if logN == 12:
+        with be.tuned(8):  # converted limbs on chip
+            pc.case_relin_and_composite(be, pc.mixed_shape(logN, *widths), seed=485, batch=2, levels=[len(widths[0])])

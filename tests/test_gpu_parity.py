@@ -909,3 +909,11 @@ def test_encodings_in_batches_and_one_by_one(be, shape, batch):
 def test_encodings_at_every_ring_size(be, logN):
     announce("encoding at N=2^%d" % logN)
     pc.case_encode_encrypt_device(be, (logN, 2, 50, 1, 51, 1), seed=365, batch=1, log_scale=40)
+
+
+@pytest.mark.parametrize("logN,widths", [(n, w) for w in pc.MIXED_WIDTHS for n in (12, 14)] + [(13, pc.MIXED_WIDTHS[0]), (15, pc.MIXED_WIDTHS[1]), (16, pc.MIXED_WIDTHS[0])])
+def test_chains_of_wide_and_narrow_primes(be, logN, widths):
+    announce("mixed primes %r at N=2^%d" % (widths, logN))
+    pc.case_mixed_widths(be, logN, widths, seed=480)
+    with be.tuned(64):  # few items fill the chip: converted limbs on chip
+        pc.case_relin_and_composite(be, pc.mixed_shape(logN, *widths), seed=485, batch=2, levels=[len(widths[0])])
