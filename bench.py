@@ -102,14 +102,14 @@ def bytes_per_unit(name, N, level, k, alpha, batch):
 
 def laneops_per_unit(name, N, level, k, alpha):
     """FP64 vector instructions per unit of work (counted from the kernel source, per word: conversions u64<->f64 2 each,
-    twiddle product 6, butterfly add/sub 2, reduction 3, canonical form 7) for the kernels where the ALU can bind"""
+    twiddle product 6, butterfly add/sub 2, reduction 3, canonical form 7, of a word below 2.9p 3) for the kernels where the ALU can bind"""
     beta = -(-level // alpha)
     # one pass of a transform between the lazily reduced intermediate formats: 8 stages at 4 per word (twiddle product
     # 6 + add + sub per butterfly) and half of the 3 instructions of lazy reductions per word of a whole transform
     xform_pass = 8 * 4 + 1.5
 
-    def products(n):  # a conversion's sum of n products: one reduction for two or three of them
-        return 4 * n + 3 if n in (2, 3) else 7 * n
+    def products(n):  # a conversion's sum of n products: one reduction for two or three of them; one source is copied
+        return 0 if n == 1 else 4 * n + 3 if n in (2, 3) else 7 * n
 
     table = {
         # source words converted to doubles once per workgroup, not once per target
@@ -119,12 +119,13 @@ def laneops_per_unit(name, N, level, k, alpha):
         "modup_cols_kernel<4, 1, 1>": N * (products(1) + 1 + xform_pass),
         "modup_cols_kernel<4, %d, 3>" % (k + 1): N * (products(k) + 1 + 6 + 2 + xform_pass),
         "modup_cols_kernel<4, %d, 2>" % (k + 1): N * (products(k + 1) + 1 + 6 + xform_pass),
-        # per word: a row pass for every digit except the limb's own one (level of the E limbs have one), two
-        # multiply-accumulates per digit (key word conversion 2 + exact product 5 + add 1, the prepared quotient and the
-        # lazy reductions shared: about 2 more per digit), canonical form of the two results
-        "rows_inner_kernel": N * ((beta - float(level) / (level + k)) * (xform_pass + 3) + beta * (2 * 8 + 2) + 2 * 7
-                                  + 2 * (5 + 3) * float(level) / (level + k)),
-        "rows_final_kernel": N * (xform_pass + 2 + 1 + 5 + 3 + 7 + 2),   # (+5 when the kept limb is scaled before the subtraction)
+        # per word: a row pass for every digit except the limb's own one (level of the E limbs have one; half of the words
+        # reduced once more), two multiply-accumulates per digit (key word conversion 2 + exact product 6 + add 1, a reduction
+        # every five terms), and at the end, for a ciphertext limb, the tensor (eight conversions, four products, an addition, two
+        # products with P), products with P^-1 and the canonical form of the two results
+        "rows_inner_kernel": N * ((beta - float(level) / (level + k)) * (xform_pass + 1.5) + beta * 2 * (9 + 3 / 5.0)
+                                  + (8 + 4 * 6 + 1 + 2 * 5 + 2 * (5 + 3 + 2)) * float(level) / (level + k) + 2 * (7 + 2) * float(k) / (level + k)),
+        "rows_final_kernel": N * (xform_pass + 2 + 1 + 5 + 3 + 2),   # (+5 when the kept limb is scaled before the subtraction)
     }
     return table.get(name)
 

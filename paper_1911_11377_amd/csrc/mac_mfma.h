@@ -315,8 +315,6 @@ __device__ __forceinline__ void mm_step(const v4i *a, unsigned lane, const v4i (
     }
 }
 
-// sum of four diagonals from d0 on, d0 + 2^8 d1 + 2^16 d2 + 2^24 d3 as a double: below 2^51, so that on top of the bits of 3 * 2^51 it is that
-// double's mantissa.  One v_mad_i64_i32 each (as fast as v_fma_f64 here) and one subtraction; four conversions and three products otherwise.
 // a prime's constants for the recombination, in scalar registers: fetched once, before the first results are stored
 struct MacConst {
     double p, pinv, M, c1, c2, c3;  // WIDE
@@ -334,6 +332,8 @@ __device__ __forceinline__ MacConst mac_const(const MacMfmaArgs &A, unsigned i) 
     C.P24 = WIDE ? WMul{0.0, 0.0} : table_load(A.pow24 + i);
     return C;
 }
+// sum of four diagonals from d0 on, d0 + 2^8 d1 + 2^16 d2 + 2^24 d3 as a double: below 2^51, so that on top of the bits of 3 * 2^51 it is that
+// double's mantissa.  One v_mad_i64_i32 each (as fast as v_fma_f64 here) and one subtraction; four conversions and three products otherwise.
 struct WideShifts { int k0, k8, k16, k24; };
 __device__ __forceinline__ WideShifts wide_shifts() {
     WideShifts k{1, 1 << 8, 1 << 16, 1 << 24};
