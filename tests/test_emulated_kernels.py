@@ -522,8 +522,8 @@ def test_key_products_stay_exact_at_the_ends_of_their_range(be, p51):
 
 @pytest.mark.parametrize("bits,channels,size,kernel", pc.EXTREME_TAPS)
 def test_digit_diagonals_at_their_largest(be, bits, channels, size, kernel):
-    """words and weights of extreme digits, all taps alike; output channels that end inside a channel group"""
-    pc.case_conv_channels(be, (6, 1, bits, 0, bits + 1, 1), 420 + channels, channels, size, size + 1, 35, size, 1, 0, residues=False, digits=True, kernel=kernel)
+    """every word p - 1, every weight +-(p - 1) / 2, output channels that end inside a channel group"""
+    pc.case_conv_channels(be, (6, 1, bits, 0, bits + 1, 1), 420 + channels, channels, size, size + 1, 35, size, 1, 0, residues=False, extreme=True, kernel=kernel)
 
 
 @pytest.mark.parametrize("digits,batch", [(1, 13), (2, 5), (3, 11), (4, 1), (5, 7), (6, 6), (7, 3), (8, 9), (9, 2)])
@@ -574,3 +574,9 @@ def test_chains_of_wide_and_narrow_primes(be, logN, widths):
     if logN == 12:
         with be.tuned(8):  # converted limbs on chip
             pc.case_relin_and_composite(be, pc.mixed_shape(logN, *widths), seed=485, batch=2, levels=[len(widths[0])])
+
+
+@pytest.mark.parametrize("bits,channels,size,kernel", pc.EXTREME_TAPS)
+def test_digit_diagonals_at_extreme_digits(be, bits, channels, size, kernel):
+    """words and weights of extreme digits, all taps alike; output channels that end inside a channel group"""
+    pc.case_conv_channels(be, (6, 1, bits, 0, bits + 1, 1), 420 + channels, channels, size, size + 1, 35, size, 1, 0, residues=False, digits=True, kernel=kernel)

@@ -1,5 +1,5 @@
-"""What the compiler makes of some of the kernels: the assembly for gfx950 of instances of them, compiled here without a
-GPU.  Kernels that address memory through scalar_base (csrc/ntt_v2.h), and what a kernel's time was seen to hang on."""
+"""What the compiler makes of the kernels that address memory through scalar_base (csrc/ntt_v2.h): the assembly for gfx950 of
+one instance of each, compiled here without a GPU."""
 import os
 import re
 import subprocess
@@ -14,9 +14,36 @@ KERNELS = ["ntt_wg_kernel<false, 13>(NttV2Args)", "ntt_wg_kernel<true, 14>(NttV2
            # the streamed instances
            "ntt_wg_kernel<false, 13, true>(NttV2Args)", "ntt_wg_kernel<true, 14, true>(NttV2Args)", "conv_final_kernel<14, 1, 1, 0, true>(ConvFinalArgs)",
            "conv_final_gal_kernel<14, 2, 1, true>(ConvFinalArgs, RowsFinalGal)"]
-HEADS = ["ckksmi_internal.h", "kernels.h", "ntt_v2.h", "ks_fused.h", "ntt_wg.h", "ks_wg.h", "ks_inner_wg.h"]
 
-pytestmark = pytest.mark.skipif(not os.path.exists(lib_build.HIPCC), reason="no hipcc")
+
+@pytest.mark.skipif(not os.path.exists(lib_build.HIPCC), reason="no hipcc")
+def test_scalar_bases_give_global_accesses(tmp_path):
+    """no flat memory access (64-bit vector address each, waited for with the LDS) in any of these kernels"""
+    src = tmp_path / "instances.hip"
+    heads = ["ckksmi_internal.h", "kernels.h", "ntt_v2.h", "ks_fused.h", "ntt_wg.h", "ks_wg.h", "ks_inner_wg.h"]
+    src.write_text("#include <hip/hip_runtime.h>\n" + "".join('#include "%s"\n' % h for h in heads)
+                   + "".join("template __global__ void %s;\n" % k for k in KERNELS))
+    out = tmp_path / "instances.s"
+    flags = [f for f in lib_build.FLAGS if f not in ("-shared", "-fPIC", "-Wall")]
+    subprocess.check_call([lib_build.HIPCC] + flags + ["--cuda-device-only", "-S", "-I", lib_build.CSRC, str(src), "-o", str(out)], stderr=subprocess.DEVNULL)
+    kernel, flat, glob = None, {}, {}
+    for line in out.read_text().splitlines():
+        m = re.match(r"(_Z\d+(?:ntt_wg|conv_final|tail_sources|inner_wg)\w*):", line)
+        if m:
+            kernel = m.group(1)
+            flat[kernel] = glob[kernel] = 0
+        elif re.match(r"_Z\w+:", line):
+            kernel = None
+        elif kernel:
+            flat[kernel] += bool(re.match(r"\s+flat_(load|store)", line))
+            glob[kernel] += bool(re.match(r"\s+global_(load|store)", line))
+    assert len(flat) == len(KERNELS), sorted(flat)
+    assert not any(flat.values()), flat
+    assert all(n >= 16 for n in glob.values()), glob
+
+
+HEADS = ["ckksmi_internal.h", "kernels.h", "ntt_v2.h", "ks_fused.h", "ntt_wg.h", "ks_wg.h"]
+needs_hipcc = pytest.mark.skipif(not os.path.exists(lib_build.HIPCC), reason="no hipcc")
 
 
 def _assembly(tmp_path, kernels):
@@ -42,15 +69,7 @@ def _count(lines, pattern):
     return sum(bool(re.match(pattern, line)) for line in lines)
 
 
-def test_scalar_bases_give_global_accesses(tmp_path):
-    """no flat memory access (64-bit vector address each, waited for with the LDS) in any of these kernels"""
-    code = _assembly(tmp_path, KERNELS)
-    flat = {k: _count(v, r"\s+flat_(load|store)") for k, v in code.items()}
-    glob = {k: _count(v, r"\s+global_(load|store)") for k, v in code.items()}
-    assert not any(flat.values()), flat
-    assert all(n >= 16 for n in glob.values()), glob
-
-
+@needs_hipcc
 @pytest.mark.parametrize("digits", [9, 16])
 def test_gathered_inner_product_has_no_conditions_on_digits(tmp_path, digits):
     """a rotation's key words and an item's staged words are read in straight-line code, whatever the number of digits (with a condition for
@@ -60,6 +79,7 @@ def test_gathered_inner_product_has_no_conditions_on_digits(tmp_path, digits):
     assert _count(lines, r"\s+s_cbranch") <= 48 and _count(lines, r"\s+scratch_") == 0
 
 
+@needs_hipcc
 def test_kept_limbs_are_streamed_where_that_was_faster(tmp_path):
     """word pairs are requested past the caches by the last pass without an addend, not by the one for scalar multiples"""
     code = _assembly(tmp_path, ["rows_final_kernel<true, false>(RowsFinalArgs)", "rows_final_scalar_kernel<true>(RowsFinalArgs, ScalarTab)"])
@@ -67,6 +87,7 @@ def test_kept_limbs_are_streamed_where_that_was_faster(tmp_path):
     assert streamed == {"scalar": 0, "plain": 16}, streamed  # 8 each for p < 2^50 and p < 2^51
 
 
+@needs_hipcc
 def test_tail_sources_leave_room_for_two_workgroups(tmp_path):
     """N = 2^13: the words in flight do not take the registers of the compute unit's second workgroup (512 threads each: four waves per SIMD)"""
     (lines,) = _assembly(tmp_path, ["tail_sources_kernel<13>(TailSourcesArgs)"]).values()

@@ -875,9 +875,9 @@ def test_streamed_encryption_matches_cached_one(logN, n_q, batch):
 
 @pytest.mark.parametrize("bits,channels,size,kernel", pc.EXTREME_TAPS)
 def test_digit_diagonals_at_their_largest(be, bits, channels, size, kernel):
-    """words and weights of extreme digits, all taps alike; output channels that end inside a channel group"""
+    """every word p - 1, every weight +-(p - 1) / 2, output channels that end inside a channel group"""
     announce("conv digits, %d bits, %d channels" % (bits, channels))
-    pc.case_conv_channels(be, (7, 2, bits, 0, bits + 1, 1), 420 + channels, channels, size, size + 1, 35, size, 1, 0, residues=False, digits=True, kernel=kernel)
+    pc.case_conv_channels(be, (7, 2, bits, 0, bits + 1, 1), 420 + channels, channels, size, size + 1, 35, size, 1, 0, residues=False, extreme=True, kernel=kernel)
 
 
 @pytest.mark.parametrize("digits,batch", [(1, 13), (2, 5), (3, 11), (4, 1), (5, 7), (6, 6), (7, 3), (8, 9), (9, 2)])
@@ -917,3 +917,10 @@ def test_chains_of_wide_and_narrow_primes(be, logN, widths):
     pc.case_mixed_widths(be, logN, widths, seed=480)
     with be.tuned(64):  # few items fill the chip: converted limbs on chip
         pc.case_relin_and_composite(be, pc.mixed_shape(logN, *widths), seed=485, batch=2, levels=[len(widths[0])])
+
+
+@pytest.mark.parametrize("bits,channels,size,kernel", pc.EXTREME_TAPS)
+def test_digit_diagonals_at_extreme_digits(be, bits, channels, size, kernel):
+    """words and weights of extreme digits, all taps alike; output channels that end inside a channel group"""
+    announce("conv extreme digits, %d bits, %d channels" % (bits, channels))
+    pc.case_conv_channels(be, (7, 2, bits, 0, bits + 1, 1), 420 + channels, channels, size, size + 1, 35, size, 1, 0, residues=False, digits=True, kernel=kernel)
