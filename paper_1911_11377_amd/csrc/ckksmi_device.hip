@@ -332,10 +332,11 @@ void launch_modup_cols(ckksmi_ctx *c, int mode, const u64 *y, size_t y_stride, u
 }
 
 // limb_count < 0: every limb, out laid out [rows][nc][N]; otherwise only limbs limb0 .. limb0+limb_count-1, written to
-// out + row*out_row_stride + (limb - limb0)*N
+// out + row*out_row_stride + (limb - limb0)*N.  callers_words: the kept limbs are an argument of the call, not written by it
 void launch_rows_final(ckksmi_ctx *c, const u64 *tmpA, const u64 *x, size_t x_row_stride, const u64 *addend, size_t add_item_stride,
                        size_t add_comp_stride, u64 *out, const WMul *Binv, int nc, int rows, hipStream_t st, int limb0 = 0,
-                       int limb_count = -1, size_t out_row_stride = 0, const WMul *pre = nullptr, const ScalarTab *stab = nullptr, bool zsub = false, const RowsFinalGal *gal = nullptr) {
+                       int limb_count = -1, size_t out_row_stride = 0, const WMul *pre = nullptr, const ScalarTab *stab = nullptr, bool zsub = false, const RowsFinalGal *gal = nullptr,
+                       bool callers_words = false) {
     if (zsub && addend) { c->no_kernel = true; return; }  // the addend is in x already
     RowsFinalArgs A;
     A.zsub = zsub ? 1 : 0;
@@ -357,9 +358,11 @@ void launch_rows_final(ckksmi_ctx *c, const u64 *tmpA, const u64 *x, size_t x_ro
     else if (gal)
         KL2(c, CKKSMI_K_ROWS_FINAL, (double)rows * nz, A.stream != STREAM_NONE, rows_final_gal_kernel<true>, rows_final_gal_kernel<false>, dim3(xch, tiles, nz), dim3(V2_THREADS), st, A, *gal);
     else if (addend)
-        KL2(c, CKKSMI_K_ROWS_FINAL, (double)rows * nz, A.stream != STREAM_NONE, (rows_final_kernel<true, true>), (rows_final_kernel<false, true>), dim3(xch, tiles, nz), dim3(V2_THREADS), st, A);
+        KL2(c, CKKSMI_K_ROWS_FINAL, (double)rows * nz, A.stream != STREAM_NONE, (rows_final_kernel<true, true, false>), (rows_final_kernel<false, true, false>), dim3(xch, tiles, nz), dim3(V2_THREADS), st, A);
+    else if (callers_words)
+        KL2(c, CKKSMI_K_ROWS_FINAL, (double)rows * nz, A.stream != STREAM_NONE, (rows_final_kernel<true, false, false>), (rows_final_kernel<false, false, false>), dim3(xch, tiles, nz), dim3(V2_THREADS), st, A);
     else
-        KL2(c, CKKSMI_K_ROWS_FINAL, (double)rows * nz, A.stream != STREAM_NONE, (rows_final_kernel<true, false>), (rows_final_kernel<false, false>), dim3(xch, tiles, nz), dim3(V2_THREADS), st, A);
+        KL2(c, CKKSMI_K_ROWS_FINAL, (double)rows * nz, A.stream != STREAM_NONE, (rows_final_kernel<true, false, true>), (rows_final_kernel<false, false, false>), dim3(xch, tiles, nz), dim3(V2_THREADS), st, A);
 }
 
 // Which divisions run as ONE kernel after the inverse transform of the dropped limb (ks_wg.h): one source (rescale, or ModDown with
@@ -448,10 +451,10 @@ void launch_conv_final(ckksmi_ctx *c, int fin_kind, const u64 *y, size_t y_strid
 // DivRound of `rows` rows on the register-tiled kernels: dropped limbs (evaluation form) at b_limbs + r*b_stride (nb limbs;
 // b_scratch == b_limbs works in place), kept limbs at x + r*x_stride; out[r][i] = (x_i - NTT(r_i - h)) * Bbar^-1.
 // gal (rotations from a shared ModUp): c0 of the input items, read through the automorphisms, joins every even row.
-// zsub: the kept limbs already hold x * Bbar^-1 + addend, out = x - NTT(r - h) * Bbar^-1.
+// zsub: the kept limbs already hold x * Bbar^-1 + addend, out = x - NTT(r - h) * Bbar^-1.  callers_words: see launch_rows_final.
 void divround_rows(ckksmi_ctx *c, const DivRoundDev &D, const FinConst *fin, const int *bidx, const u64 *b_limbs, size_t b_stride,
                    u64 *b_scratch, size_t bs_stride, const u64 *x, size_t x_stride, u64 *tmp, int nc, int rows, u64 *out, hipStream_t st,
-                   bool zsub = false, const RowsFinalGal *gal = nullptr, const u64 *c0 = nullptr, size_t c0_stride = 0) {
+                   bool zsub = false, const RowsFinalGal *gal = nullptr, const u64 *c0 = nullptr, size_t c0_stride = 0, bool callers_words = false) {
     if (conv_final_ok(c, D.nb, rows, nc)) {
         launch_ntt(c, false, b_limbs, b_scratch, table_map(bidx, D.nb, b_stride, bs_stride), rows, st, fin, 3, nullptr, true);
         launch_conv_final(c, zsub ? 1 : (gal ? 3 : 0), b_scratch, bs_stride, D, x, x_stride, c0, c0_stride, 0, out, nc, rows, st, gal);
@@ -460,7 +463,7 @@ void divround_rows(ckksmi_ctx *c, const DivRoundDev &D, const FinConst *fin, con
     // inverse row pass of the dropped limbs; the conversion kernel runs their inverse column pass itself
     launch_ntt(c, false, b_limbs, b_scratch, table_map(bidx, D.nb, b_stride, bs_stride), rows, st, fin, 2);
     launch_modup_cols(c, 1, b_scratch, bs_stride, tmp, rows, 0, nc, &D, (double)rows * nc, st, fin);
-    launch_rows_final(c, tmp, x, x_stride, c0, c0_stride, 0, out, D.Binv, nc, rows, st, 0, -1, 0, nullptr, nullptr, zsub, gal);
+    launch_rows_final(c, tmp, x, x_stride, c0, c0_stride, 0, out, D.Binv, nc, rows, st, 0, -1, 0, nullptr, nullptr, zsub, gal, callers_words);
 }
 
 // Rotations with a shared ModUp: R rotations of every item of a key-switch sweep (see inner_product_hoisted_kernel)
@@ -742,7 +745,7 @@ void rescale_core_fused(ckksmi_ctx *c, const u64 *a, u64 *out, int items, int le
     u64 *tmp = last + (size_t)items * 2 * N;
     int lidx[1] = {level - 1};
     divround_rows(c, c->divround[1 + (level - 1)], c->d_fin_rescale + (level - 1), lidx, a + (size_t)(level - 1) * N, (size_t)level * N, last,
-                  N, a, (size_t)level * N, tmp, level - 1, items * 2, out, st);
+                  N, a, (size_t)level * N, tmp, level - 1, items * 2, out, st, false, nullptr, nullptr, 0, true);
 }
 
 // out = DivRound_{q_{level-1}}(v * a) without materialising v*a: the dropped limb's inverse transform multiplies by v in its

@@ -860,14 +860,14 @@ struct RowsFinalArgs {
 // A.add_item_stride = words between the items' ciphertexts)
 struct RowsFinalGal { int R; unsigned g[CKKSMI_MAX_KEYS]; };
 
-template <bool P51, bool NTS, bool ADD, bool GAL = false>
+template <bool P51, bool NTS, bool ADD, bool KEPT_NT, bool GAL = false>
 __device__ __forceinline__ void rows_final_body(const RowsFinalArgs &A, double *lds, double *tw1_lds, int i, bool xm_val = false,
                                                 WMul xmv = WMul{0.0, 0.0}, const RowsFinalGal *gal = nullptr) {
-    // The kept limb's words are streamed with the results, from 16 MB on, without an addend (three waves per SIMD: a product's tail at N = 2^16, 24 primes,
-    // 4 ciphertexts 68.5 -> 62 us, 64.2 with streaming from 256 MB on only; 48: 692 -> 681, even) and for rotations from a shared ModUp (128 rotations of 11
-    // primes at N = 2^14 257 -> 228, 246 without).  Scalar multiples are slower with it: at N = 2^16 4 rows of
-    // 17 kept limbs 28.2 -> 31.4, 80 of 1 29.4 -> 32.6, 400 of 1 122 -> 128.
-    constexpr bool KEPT_NT = NTS && (!ADD || GAL);
+    // KEPT_NT: the kept limb's words are streamed with the results, from 16 MB on, where the call's own kernels wrote them: without an addend (three waves per
+    // SIMD: a product's tail at N = 2^16, 24 primes, 4 ciphertexts 69.2 -> 62.0 us, 63.6 without; 150 of 9 at N = 2^14 184 -> 173, 182 without) and for
+    // rotations from a shared ModUp (128 rotations of 11 primes at N = 2^14 257 -> 228, 246 without).  Words of the caller may be in the caches: rescales of
+    // 30 kept limbs at N = 2^16 31.8 us, 34.5 streamed, of 72 39.9 and 42.2 (other buffers each time 34.5 both and 42.4, 42.3).  So may those of
+    // scalar multiples, at two waves besides: 4 rows of 17 kept limbs 28.2 -> 31.4, 80 of 1 29.4 -> 32.6, 400 of 1 122 -> 128.
     const unsigned N = 1u << A.logN, N1 = N >> 8;
     const double p = A.modc[i].p, pinv = A.modc[i].pinv;
     const unsigned tid = threadIdx.x, hi4 = tid >> 4, lo4 = tid & 15;
@@ -936,15 +936,15 @@ __device__ __forceinline__ void rows_final_body(const RowsFinalArgs &A, double *
 // grid: x = chunk of rows (item, component), y = row tile (N/4096), z = kept limb.  ADD: with an addend; without one (a product's
 // tail, plain divisions) the words in flight leave room for a third wave per SIMD; with that and the kept limb's words streamed
 // 128 rows of 23 kept limbs at N = 2^16 take 906 us against 931: 5.1 TB/s, where a copy of large pieces moves 6.2
-template <bool NTS, bool ADD>
+template <bool NTS, bool ADD, bool KEPT_NT>
 __global__ __launch_bounds__(V2_THREADS, ADD ? 2 : 3) void rows_final_kernel(RowsFinalArgs A) {
     __shared__ double lds[16 * V2_GS];
     __shared__ double tw1_lds[16 * 16];
     const int i = A.limb0 + (int)blockIdx.z;
     if (is_p51(A.p51, i))
-        rows_final_body<true, NTS, ADD>(A, lds, tw1_lds, i);
+        rows_final_body<true, NTS, ADD, KEPT_NT>(A, lds, tw1_lds, i);
     else
-        rows_final_body<false, NTS, ADD>(A, lds, tw1_lds, i);
+        rows_final_body<false, NTS, ADD, KEPT_NT>(A, lds, tw1_lds, i);
 }
 
 // the same for rotations from a shared ModUp: the addend sigma_r(c0) is read through the automorphism
@@ -954,9 +954,9 @@ __global__ __launch_bounds__(V2_THREADS) void rows_final_gal_kernel(RowsFinalArg
     __shared__ double tw1_lds[16 * 16];
     const int i = A.limb0 + (int)blockIdx.z;
     if (is_p51(A.p51, i))
-        rows_final_body<true, NTS, true, true>(A, lds, tw1_lds, i, false, WMul{0.0, 0.0}, &G);
+        rows_final_body<true, NTS, true, NTS, true>(A, lds, tw1_lds, i, false, WMul{0.0, 0.0}, &G);
     else
-        rows_final_body<false, NTS, true, true>(A, lds, tw1_lds, i, false, WMul{0.0, 0.0}, &G);
+        rows_final_body<false, NTS, true, NTS, true>(A, lds, tw1_lds, i, false, WMul{0.0, 0.0}, &G);
 }
 
 // the same with the kept limb multiplied by a per-call scalar first: out = (c*x - r) * Binv (+ addend): rescale of c*x
@@ -967,7 +967,7 @@ __global__ __launch_bounds__(V2_THREADS) void rows_final_scalar_kernel(RowsFinal
     const int i = A.limb0 + (int)blockIdx.z;
     const WMul xmv = S.c[i];
     if (is_p51(A.p51, i))
-        rows_final_body<true, NTS, true>(A, lds, tw1_lds, i, true, xmv);
+        rows_final_body<true, NTS, true, false>(A, lds, tw1_lds, i, true, xmv);
     else
-        rows_final_body<false, NTS, true>(A, lds, tw1_lds, i, true, xmv);
+        rows_final_body<false, NTS, true, false>(A, lds, tw1_lds, i, true, xmv);
 }
