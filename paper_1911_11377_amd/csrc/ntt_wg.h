@@ -262,12 +262,16 @@ __device__ __forceinline__ void ntt_wg_body(const NttV2Args &A, double *lds, int
 #pragma unroll
             for (int e = 0; e < 16; e++) x[e] = SRC == SRC_REAL ? real_word(__longlong_as_double((long long)raw[e]), A.factor, p, pinv, largest) : u2d(raw[e]);
             if (SRC == SRC_REAL && !(largest < 4.0e18)) *A.overflow = 1;
-            wg_fwd_block<LOGN, P51, 256, ROW_NEAR>(x, tw, 1u, lds, p, pinv, []() {});
+            // Limbs of N >= 2^13 that stay in the caches (streamed from 256 MB on) lose by the shorter plan with canon_near: 200 items of 9 limbs at
+            // N = 2^14 123.2 us reduced, 125.4 near, at 2^13 69.8 and 70.6, 400 120.5 and 123.0; streamed or smaller ones gain (1000 at 2^14 650.7 and 647.5, 400 at
+            // 2^12 48.0 and 47.3).  Reduced with a plan for 1p as well (these words are canonical) N = 2^14 spills: 128.9.
+            constexpr bool NEAR = NT || LOGN == 12 || SRC == SRC_REAL;
+            wg_fwd_block<LOGN, P51, NEAR ? 256 : P51 ? 308 : 692, NEAR ? ROW_NEAR : ROW_REDUCED>(x, tw, 1u, lds, p, pinv, []() {});
             // canonical words out in word pairs: 16 bytes per lane, 256 contiguous bytes per row and store
 #pragma unroll
             for (int s = 0; s < 8; s++) {
                 const double *rr = grp + row_pair_lds(lo4, s);
-                const double v0 = P51 ? canon_small(rr[0], p) : canon_near<P51>(rr[0], p, pinv), v1 = P51 ? canon_small(rr[1], p) : canon_near<P51>(rr[1], p, pinv);
+                const double v0 = P51 || !NEAR ? canon_small(rr[0], p) : canon_near<P51>(rr[0], p, pinv), v1 = P51 || !NEAR ? canon_small(rr[1], p) : canon_near<P51>(rr[1], p, pinv);
                 stream_store<NT>((ulonglong2 *)dst + 16 * s + pr, make_ulonglong2(d2u(v0), d2u(v1)));
             }
         } else {

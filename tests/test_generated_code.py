@@ -94,3 +94,13 @@ def test_tail_sources_leave_room_for_two_workgroups(tmp_path):
     (lines,) = _assembly(tmp_path, ["tail_sources_kernel<13>(TailSourcesArgs)"]).values()
     occupancy = [int(m.group(1)) for m in (re.match(r"; Occupancy: (\d+)", line) for line in lines) if m]
     assert occupancy == [4], occupancy
+
+
+@needs_hipcc
+def test_forward_transforms_end_as_was_faster(tmp_path):
+    """whole limbs from N = 2^13 on: the results are reduced before the exchange, in streamed transforms made canonical behind it (a floor each, for p < 2^50);
+    neither spills"""
+    code = _assembly(tmp_path, ["ntt_wg_kernel<false, %d, %s>(NttV2Args)" % (n, nt) for n in (12, 13, 14) for nt in ("false", "true")])
+    floors = {re.search(r"Li(1\d)ELb([01])", k).groups(): _count(v, r"\s+v_floor_f64") for k, v in code.items()}
+    assert floors == {("12", "0"): 16, ("12", "1"): 16, ("13", "0"): 0, ("13", "1"): 16, ("14", "0"): 0, ("14", "1"): 16}, floors
+    assert not any(_count(v, r"\s+scratch_") for v in code.values())
