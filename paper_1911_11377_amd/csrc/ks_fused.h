@@ -476,7 +476,9 @@ __device__ __forceinline__ void load_row_twiddles(const double *tw, unsigned N1,
 // Finish the forward transform of one 16-row tile (column pass already done) and leave the results, balanced-reduced or (ROW_LAZY)
 // at most LazyRange::ROWX, in LDS in the padded layout: word (row g, position q) at g*V2_GS + (q/16)*17 + q%16.
 // Every row is handled by its own 16 lanes: ends with a row-group sync, and the caller puts one before the next call.
-template <bool P51, int X>
+// SBASE: the words are requested from a scalar base.  The last pass without an addend is faster with it (14 products of 5 primes at N = 2^14 13.7 -> 13.1 us, 2 of 8 at
+// 2^16 15.5 -> 14.9), the one for scalar multiples and the row pass of an encryption are slower (29.6 -> 30.5, 20.8 -> 21.2).
+template <bool P51, int X, bool SBASE = false>
 __device__ __forceinline__ void rows_fwd_to_lds(const u64d *tile, double *lds, const double *tw1_lds, const double (&tw2)[15], double p,
                                                 double pinv, unsigned hi4, unsigned lo4, bool stream) {
     typedef RowMasks<P51, X> Mk;
@@ -484,7 +486,10 @@ __device__ __forceinline__ void rows_fwd_to_lds(const u64d *tile, double *lds, c
     double x[16];
     stream_if(stream, [&](auto nt) {
 #pragma unroll
-        for (int e = 0; e < 16; e++) x[e] = mid_load(stream_load<nt>(&tile[hi4 * 256 + lo4 + 16 * e]));
+        for (int e = 0; e < 16; e++) {
+            if constexpr (SBASE) x[e] = mid_load(stream_load<nt>(scalar_base(tile) + (hi4 * 256 + lo4 + 16 * e)));
+            else x[e] = mid_load(stream_load<nt>(&tile[hi4 * 256 + lo4 + 16 * e]));
+        }
     });
     {
         // round-1 twiddles are the same for the 16 lanes of a row: kept in LDS, not in registers
@@ -782,8 +787,9 @@ __device__ __forceinline__ void rows_inner_body(const RowsInnerArgs &A, const Ke
         int jn = j + 1;
         if (jn == j_own) jn++;
         const u64d *src = jn < A.beta ? A.dtA + (((size_t)item * A.beta + jn) * A.E + x) * N + tile0 : k0;
+        const unsigned vn = jn < A.beta ? vr : 0u;  // (past the last digit all lanes re-read the same few words: two digits 21.9 -> 21.5 us)
 #pragma unroll
-        for (int i = 0; i < 16; i++) xr[i] = stream_load<STREAM == STREAM_ALL>(scalar_base(src) + (vr + 16 * i));
+        for (int i = 0; i < 16; i++) xr[i] = stream_load<STREAM == STREAM_ALL>(scalar_base(src) + (vn + 16 * i));
         SCHED_FENCE();
 #pragma unroll
         for (int s = 0; s < 8; s++) {
@@ -901,7 +907,7 @@ __device__ __forceinline__ void rows_final_body(const RowsFinalArgs &A, double *
                                          (unsigned)tile0 + hi4 * 256u + 32u * s + 2u * lo4, gal->g[r], A.logN);
         }
         SCHED_FENCE();
-        rows_fwd_to_lds<P51, ROW_LAZY>(A.tmpA + ((size_t)row * A.nc + i) * N + tile0, lds, tw1_lds, tw2, p, pinv, hi4, lo4, A.stream == STREAM_ALL);
+        rows_fwd_to_lds<P51, ROW_LAZY, !ADD>(A.tmpA + ((size_t)row * A.nc + i) * N + tile0, lds, tw1_lds, tw2, p, pinv, hi4, lo4, A.stream == STREAM_ALL);
 #pragma unroll
         for (int s = 0; s < 8; s++) {
             const double *rr = lds + hi4 * V2_GS + row_pair_lds(lo4, s);

@@ -104,3 +104,11 @@ def test_forward_transforms_end_as_was_faster(tmp_path):
     floors = {re.search(r"Li(1\d)ELb([01])", k).groups(): _count(v, r"\s+v_floor_f64") for k, v in code.items()}
     assert floors == {("12", "0"): 16, ("12", "1"): 16, ("13", "0"): 0, ("13", "1"): 16, ("14", "0"): 0, ("14", "1"): 16}, floors
     assert not any(_count(v, r"\s+scratch_") for v in code.values())
+
+
+@needs_hipcc
+def test_last_passes_address_their_words_as_was_faster(tmp_path):
+    """the transformed words of a division without an addend come from scalar bases, those of scalar multiples by addresses of their own"""
+    code = _assembly(tmp_path, ["rows_final_kernel<false, false, false>(RowsFinalArgs)", "rows_final_scalar_kernel<false>(RowsFinalArgs, ScalarTab)"])
+    scalar = {("scalar" if "scalar" in k else "plain"): _count(v, r"\s+global_load_dwordx2 v\S+ v\d+, s\[") for k, v in code.items()}
+    assert scalar["plain"] - scalar["scalar"] >= 32, scalar  # 16 each for p < 2^50 and p < 2^51
